@@ -37,9 +37,9 @@ constexpr int64_t bytes_per_particle()
     b += 4 * 8;                // s: predictor arrays
     b += 6 * 8;                // s: viscosity switches (alpha, predictor, rate, div v of
                                //    the last step, div v, |curl v|)
-    b += 3 * 4;                // s: fp32 offsets
+    b += (int64_t)sizeof(Off4);       // s: fp32 offsets (fp64 positions lie in the records' copies)
     b += 16 * 8 + 4;           // t: re-sort buffers
-    b += 2 * 4;                // leaf starts, leaf of each particle
+    b += 4;                    // leaf starts
     b += 4 + 2 * 8 + 5 * 8 + 3 * 4;   // s: block time-steps (level, step ticks, half-step v, u,
                                       //    alpha, active flag, limiter level and mark)
     b += 8 * 8 + 4 + 2 * 8;    // t: block re-sort (a, du, rho, Omega, dt, vsig, level, ticks)
@@ -125,7 +125,6 @@ void free_all(sph_ctx *c)
     c->skeys = nullptr;
     c->scratch_u32 = nullptr;
     c->lstart = nullptr;
-    c->leaf_id = nullptr;
     c->tree_n = -1;
     c->bytes = 4096;   // fixed buffers (status, scalars, box, partials, tree info)
     c->built = false;
@@ -205,8 +204,8 @@ sph_status lay_out(sph_ctx *c, int64_t cap, Take take)
     A_(S.frec32, cap);
     A_(S.nngb, cap); A_(S.nforce, cap);
     A_(S.id, cap); A_(T.id, cap);
-    A_(S.fx, cap); A_(S.fy, cap); A_(S.fz, cap);
-    A_(c->lstart, cap + 1); A_(c->leaf_id, cap);
+    A_(S.off, cap);
+    A_(c->lstart, cap + 1);
     double **bd[] = {&S.vhx, &S.vhy, &S.vhz, &S.uh, &S.alh, &T.ax, &T.ay, &T.az, &T.du, &T.rho,
                      &T.omega, &T.dt, &T.vsig};
     for (double **pp : bd) A_(*pp, cap);
@@ -676,7 +675,7 @@ struct SavedBuffers {
     uint32_t *perm;
     Node *nodes;
     int64_t node_cap;
-    uint32_t *lstart, *leaf_id;
+    uint32_t *lstart;
     double *cache;
     int64_t cache_size;
     uint64_t *skeys;
@@ -688,7 +687,7 @@ struct SavedBuffers {
 SavedBuffers save_buffers(const sph_ctx *c)
 {
     return SavedBuffers{{c->keys[0], c->keys[1]}, {c->vals[0], c->vals[1]}, c->hist, c->hist_cap,
-                        c->perm, c->nodes, c->node_cap, c->lstart, c->leaf_id, c->cache,
+                        c->perm, c->nodes, c->node_cap, c->lstart, c->cache,
                         c->cache_size, c->skeys, c->scratch_u32, c->tree_n, c->ncap, c->s, c->t};
 }
 
@@ -699,7 +698,7 @@ void restore_buffers(sph_ctx *c, const SavedBuffers &b)
     c->hist = b.hist; c->hist_cap = b.hist_cap;
     c->perm = b.perm;
     c->nodes = b.nodes; c->node_cap = b.node_cap;
-    c->lstart = b.lstart; c->leaf_id = b.leaf_id;
+    c->lstart = b.lstart;
     c->cache = b.cache; c->cache_size = b.cache_size;
     c->skeys = b.skeys; c->scratch_u32 = b.scratch_u32;
     c->tree_n = b.tree_n; c->ncap = b.ncap;

@@ -457,10 +457,9 @@ __global__ __launch_bounds__(kScanThreads) void k_seg_apply(int64_t n, int G,
     if (threadIdx.x == kScanThreads - 1) tcnt[blockIdx.x] = tot;
 }
 
-// per tile: leaf index of every particle and the first particle of every leaf
-__global__ __launch_bounds__(kScanThreads) void k_leaf_ids(int64_t n, const uint32_t *__restrict__ flag,
+// per tile: the first particle of every leaf
+__global__ __launch_bounds__(kScanThreads) void k_leaf_starts(int64_t n, const uint32_t *__restrict__ flag,
                                                            const uint32_t *__restrict__ toff,
-                                                           uint32_t *__restrict__ leaf_id,
                                                            uint32_t *__restrict__ lstart)
 {
     __shared__ uint32_t sh[kScanThreads];
@@ -479,7 +478,6 @@ __global__ __launch_bounds__(kScanThreads) void k_leaf_ids(int64_t n, const uint
             lstart[run] = (uint32_t)k;
             run++;
         }
-        leaf_id[k] = run - 1;
         if (k == n - 1) lstart[run] = (uint32_t)n;
     }
 }
@@ -522,6 +520,7 @@ __device__ inline Node merge_children(const Node *__restrict__ child, int64_t c0
 
 // Leaf boxes and largest h: 16 lanes per leaf read its (consecutive)
 // particles together, then reduce with shuffles inside their 16-lane group.
+// The same pass writes the candidate positions of the pair loops.
 constexpr int kLeafLanes = 16;
 
 __global__ __launch_bounds__(256) void k_leaves(const TreeInfo *__restrict__ T,
@@ -530,7 +529,8 @@ __global__ __launch_bounds__(256) void k_leaves(const TreeInfo *__restrict__ T,
                                                 const double *__restrict__ y,
                                                 const double *__restrict__ z,
                                                 const double *__restrict__ h,
-                                                Node *__restrict__ nodes)
+                                                Node *__restrict__ nodes,
+                                                Pos4 *__restrict__ pos, Off4 *__restrict__ off)
 {
     const int64_t L = T->cnt[0];
     const int q = threadIdx.x % kLeafLanes;
@@ -543,6 +543,7 @@ __global__ __launch_bounds__(256) void k_leaves(const TreeInfo *__restrict__ T,
             const double v[3] = {x[k], y[k], z[k]};
             for (int a = 0; a < 3; a++) { lo[a] = fmin(lo[a], v[a]); hi[a] = fmax(hi[a], v[a]); }
             hm = fmax(hm, h[k]);
+            if (pos) pos[k] = Pos4{v[0], v[1], v[2], 0.0};
         }
         for (int o = kLeafLanes / 2; o > 0; o >>= 1) {
             for (int a = 0; a < 3; a++) {
@@ -558,6 +559,11 @@ __global__ __launch_bounds__(256) void k_leaves(const TreeInfo *__restrict__ T,
             nd.pad = 0.0;
             nodes[l] = nd;
         }
+        // FP32-pair mode: single-precision offsets from the centre of the box
+        if (off)
+            for (int64_t k = lstart[l] + q; k < (int64_t)lstart[l + 1]; k += kLeafLanes)
+                off[k] = Off4{(float)(x[k] - 0.5 * (lo[0] + hi[0])), (float)(y[k] - 0.5 * (lo[1] + hi[1])),
+                              (float)(z[k] - 0.5 * (lo[2] + hi[2])), 0.0f};
     }
 }
 
@@ -613,24 +619,6 @@ __global__ __launch_bounds__(1024) void k_tree_level_small(const TreeInfo *__res
         }
         __syncthreads();
     }
-}
-
-// FP32-pair mode: single-precision offsets of each particle from the centre of
-// its leaf box.
-__global__ __launch_bounds__(256) void k_offsets(int64_t n, const uint32_t *__restrict__ leaf_id,
-                                                 const double *__restrict__ x,
-                                                 const double *__restrict__ y,
-                                                 const double *__restrict__ z,
-                                                 const Node *__restrict__ leaves,
-                                                 float *__restrict__ fx, float *__restrict__ fy,
-                                                 float *__restrict__ fz)
-{
-    int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const Node &nd = leaves[leaf_id[k]];
-    fx[k] = (float)(x[k] - 0.5 * (nd.lo[0] + nd.hi[0]));
-    fy[k] = (float)(y[k] - 0.5 * (nd.lo[1] + nd.hi[1]));
-    fz[k] = (float)(z[k] - 0.5 * (nd.lo[2] + nd.hi[2]));
 }
 
 // Force record of particle k: A_k = P_k / (Omega_k rho_k^2),
@@ -782,7 +770,8 @@ sph_status build_tree(sph_ctx *c, int64_t n)
     c->tree_n = -1;
     if (n == 0) return SPH_OK;
     const int G = c->p.leaf_size;
-    if (!c->skeys || !c->scratch_u32 || !c->lstart || !c->leaf_id || !c->d_tree || !c->nodes)
+    const bool f32 = c->p.precision == SPH_FP32_PAIR;
+    if (!c->skeys || !c->scratch_u32 || !c->lstart || !c->d_tree || !c->nodes)
         return fail(c, SPH_ESTATE, "build_tree: order not built");
     const int64_t ntile = ceil_div(n, kScanTile);
     if (2 * ntile > c->hist_cap) return fail(c, SPH_ENOMEM, "scan tile capacity");
@@ -801,14 +790,12 @@ sph_status build_tree(sph_ctx *c, int64_t n)
                        tmax);
     hipLaunchKernelGGL(k_tree_info, dim3(1), dim3(64), 0, c->stream, n, G, tcnt, tmax, ntile,
                        c->d_tree);
-    hipLaunchKernelGGL(k_leaf_ids, dim3((unsigned)ntile), dim3(kScanThreads), 0, c->stream, n,
-                       flag, tcnt, c->leaf_id, c->lstart);
+    hipLaunchKernelGGL(k_leaf_starts, dim3((unsigned)ntile), dim3(kScanThreads), 0, c->stream, n,
+                       flag, tcnt, c->lstart);
     hipLaunchKernelGGL(k_leaves, dim3(grid_for(n, 256)), dim3(256), 0, c->stream, c->d_tree,
-                       c->lstart, c->s.x, c->s.y, c->s.z, c->s.h, c->nodes);
+                       c->lstart, c->s.x, c->s.y, c->s.z, c->s.h, c->nodes,
+                       f32 ? nullptr : c->s.pos(), f32 ? c->s.off : nullptr);
     upper_levels(c, n);
-    if (c->p.precision == SPH_FP32_PAIR)
-        hipLaunchKernelGGL(k_offsets, dim3(grid_for(n, 256)), dim3(256), 0, c->stream, n,
-                           c->leaf_id, c->s.x, c->s.y, c->s.z, c->nodes, c->s.fx, c->s.fy, c->s.fz);
     sph_status st = hip_check(c, hipGetLastError(), "build_tree");
     if (st == SPH_OK) c->tree_n = n;
     return st;

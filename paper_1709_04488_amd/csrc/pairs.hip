@@ -75,7 +75,8 @@ sph_status density_prepare(sph_ctx *c, int64_t n)
     DensArgs a{};
     fill_common(c, n, a);
     a.x = c->s.x; a.y = c->s.y; a.z = c->s.z; a.m = c->s.m;
-    a.fx = c->s.fx; a.fy = c->s.fy; a.fz = c->s.fz;
+    a.pos = c->s.pos();
+    a.off = c->s.off;
     a.h = c->s.h; a.rho = c->s.rho; a.omega = c->s.omega; a.nngb = c->s.nngb;
     a.status = c->d_status;
     a.counts = c->d_counts;
@@ -96,8 +97,7 @@ sph_status density_prepare(sph_ctx *c, int64_t n)
                          a.counts, a.tree, a.lstart, a.work, c->d_dargs};
     for (const void *q : req)
         if (!q) return fail(c, SPH_EINVAL, "density: internal buffer not allocated");
-    if (c->p.precision == SPH_FP32_PAIR && (!a.fx || !a.fy || !a.fz))
-        return fail(c, SPH_EINVAL, "density: offsets not allocated");
+    if (!a.pos || !a.off) return fail(c, SPH_EINVAL, "density: positions not allocated");
     if (c->tree_n != n || n <= 0) return fail(c, SPH_ESTATE, "density: tree not built");
     TRY_(reduce_mass_range(c, n));
     hipLaunchKernelGGL(k_prologue<DensArgs>, dim3(1), dim3(64), 0, c->stream, a,
@@ -114,7 +114,8 @@ sph_status forces_prepare(sph_ctx *c, int64_t n)
     a.h = c->s.h;
     a.rec = c->s.frec;
     a.rec32 = c->p.precision == SPH_FP32_PAIR ? c->s.frec32 : nullptr;
-    a.fx = c->s.fx; a.fy = c->s.fy; a.fz = c->s.fz;
+    a.pos = c->s.pos();
+    a.off = c->s.off;
     a.ax = c->s.ax; a.ay = c->s.ay; a.az = c->s.az; a.du = c->s.du;
     a.vsig = c->s.vsig; a.dt = c->s.dt; a.nforce = c->s.nforce;
     a.status = c->d_status;
@@ -144,8 +145,9 @@ sph_status forces_prepare(sph_ctx *c, int64_t n)
                          c->d_fargs};
     for (const void *q : req)
         if (!q) return fail(c, SPH_EINVAL, "forces: internal buffer not allocated");
-    if (c->p.precision == SPH_FP32_PAIR && (!a.fx || !a.fy || !a.fz || !a.rec32))
-        return fail(c, SPH_EINVAL, "forces: offsets not allocated");
+    if (!a.pos || !a.off) return fail(c, SPH_EINVAL, "forces: positions not allocated");
+    if (c->p.precision == SPH_FP32_PAIR && !a.rec32)
+        return fail(c, SPH_EINVAL, "forces: records not allocated");
     if (c->tree_n != n || n <= 0) return fail(c, SPH_ESTATE, "forces: tree not built");
     hipLaunchKernelGGL(k_prologue<ForceArgs>, dim3(1), dim3(64), 0, c->stream, a,
                        (ForceArgs *)c->d_fargs, c->d_counts, (int)kCntForceFirst,

@@ -152,6 +152,19 @@ __device__ inline int64_t wave_sum_int(int v)
            (int64_t)__builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48);
 }
 
+// Wave-wide sum in a fixed order, wave-uniform.
+__device__ inline double wave_sum(double v)
+{
+    v = group_sum<16>(v);
+    auto row = [&](int l) {
+        const uint64_t b = __builtin_bit_cast(uint64_t, v);
+        const uint32_t lo = __builtin_amdgcn_readlane((int)(uint32_t)b, l);
+        const uint32_t hi = __builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
+        return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+    };
+    return (row(0) + row(16)) + (row(32) + row(48));
+}
+
 __device__ inline int wave_max_int(int v)
 {
     int w = xlane<1>(v);
@@ -507,205 +520,57 @@ __device__ inline Shift leaf_shift(const Node &home, const Node &cand, const Box
 }
 
 // ---------------------------------------------------------------------------
-// Staging and the compacted candidate tests shared by the pair loops
+// Candidate groups and the tests shared by the pair loops
 // ---------------------------------------------------------------------------
-// A wave holds the G home particles of one leaf, LPP = 64 / G lanes each.
-// Candidate leaves are staged NL = 128 / G at a time (128 candidate slots).
-// For every (home particle, staged leaf) combination the wave first measures
-// the distance from the particle to the leaf's box; only combinations that can
-// hold a pair are expanded, four candidate tests per lane, dealt out densely
-// over the 64 lanes.  Hits are bits of a per-particle mask over the 128 slots
-// (set with an LDS atomic OR, so the result does not depend on lane timing);
-// the flush walks each particle's mask in ascending slot order, its set bits
-// shared round-robin by the particle's own lanes.
+// A wave holds the G home particles of one leaf, LPP = 64 / G lanes each when
+// it evaluates pair terms.  To find the pairs it turns round: a lane holds a
+// candidate, the home particle is the same for all lanes.
+//
+// Candidate leaves come in groups of at most 64, one per lane, which set up a
+// table in LDS (first particle, particle count, periodic shift) and measure,
+// for every home particle, the distance to the leaf's box: a 64-bit ballot
+// per home particle says which leaves of the group can hold neighbours of it.
+// The candidates are then loaded into registers, kRows rows of 64 slots at a
+// time (slot s = particle s % G of leaf s / G), and tested against each home
+// particle in turn, skipping rows none of whose leaves passed.  A test is a
+// handful of instructions for 64 candidates, its result a ballot in scalar
+// registers, and the hits' ranks are bit counts of that ballot: no hit masks
+// in LDS, no bit-by-bit walk over them, every lane at work.
+//
+// What bounds it: instruction issue.  Testing (particle, leaf) combinations
+// dealt out over the lanes from LDS, with hit masks by LDS atomics and a flush
+// that popped mask bits, spent about 16,600 vector instructions per home leaf
+// on C1-like sets (2.1M particles, G = 16, 92 candidate leaves per home leaf).
+constexpr int kGroup = kWave;       // candidate leaves per group
+constexpr int kRows = 4;            // rows of 64 candidates held in registers
 
-constexpr int kSlots = 2 * kWave;   // candidate slots per staged group
-constexpr int kTestsPerLane = 4;    // candidate tests per lane per combination
+// How the separations of a group see the periodic box: no shift at all, one
+// shift per leaf, or the minimum image pair by pair (boxes so small that a
+// leaf's shift is ambiguous).  A pair closer than the reach has the same
+// image under the last two.
+enum : int { kImgNone = 0, kImgShift = 1, kImgPair = 2 };
 
-// Per-slot candidate data: FP64 positions, or in FP32-pair mode the
-// single-precision offsets from the leaf centres; w is the mass (density; not
-// staged when all masses are equal) or the squared gather reach (R h)^2
-// (forces).
-struct SlotsFP64 {
-    double x[kSlots], y[kSlots], z[kSlots], w[kSlots];
-};
-struct SlotsFP32 {
-    double w[kSlots];
-    float fx[kSlots], fy[kSlots], fz[kSlots];
-};
-static_assert(sizeof(SlotsFP32) >= kFront * sizeof(uint32_t) &&
-                  sizeof(SlotsFP64) >= kFront * sizeof(uint32_t),
-              "the staging slots double as the walk's spare frontier buffer");
+// Home particles as the tests read them (one broadcast read each): position
+// and the threshold on r^2 (< 0: takes no part); FP32-pair tests read the
+// offsets from the leaf centre instead.
+struct alignas(32) HomeRow { double x, y, z, thr; };
+struct alignas(16) HomeRowF { float x, y, z, thr; };
 
 template <int G, int PREC>
-struct Stage {
-    static constexpr int NL = kSlots / G;
-    union {
-        std::conditional_t<PREC == SPH_FP64, SlotsFP64, SlotsFP32> c;
-        uint32_t walk_spare[kFront];   // lent to walks, which run between groups
-    };
-    uint32_t j[kSlots];
-    // per staged leaf
-    double lo[NL][3], hi[NL][3];
-    double sx[NL], sy[NL], sz[NL];   // shift added to x_i - x_j (per-leaf periodic image)
-    double hmax[NL];
-    float ox[NL], oy[NL], oz[NL];    // FP32-pair: leaf-centre offset (with the shift)
-    int32_t jn[NL];
-    int32_t per_pair[NL];            // minimum image pair by pair instead of a shift
-    // per home particle
-    double hx[G], hy[G], hz[G];
-    float hfx[G], hfy[G], hfz[G];
-    double thr[G];                   // record threshold on r^2 (< 0: particle takes no part)
-    uint64_t mask[G][2];             // hits over the 128 slots
-    uint8_t combo[kSlots];           // compacted (particle, leaf) combinations
+struct HomeTab {
+    HomeRow d[G];
+    HomeRowF f[PREC == SPH_FP32_PAIR ? G : 1];
 };
 
-// Stage `count` (<= NL) candidate leaves; lane l fills slots l and l + 64,
-// slot s holding particle s % G of staged leaf s / G.  REACH2: w holds h and
-// the slot keeps the squared gather reach (R h)^2 of kernel K instead.
-template <int G, int PREC, int K, bool REACH2 = false, bool MAYBE_NO_W = false>
-__device__ inline void stage_group(Stage<G, PREC> &S, const uint32_t *leaves, int count,
-                                   const uint32_t *__restrict__ lstart, const Node *__restrict__ nodes,
-                                   const Node &home, const Box &bx, double hcov,
-                                   const double *__restrict__ x, const double *__restrict__ y,
-                                   const double *__restrict__ z, const double *__restrict__ w,
-                                   const float *__restrict__ fx, const float *__restrict__ fy,
-                                   const float *__restrict__ fz)
-{
-    constexpr int NL = Stage<G, PREC>::NL;
-    const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-    for (int half = 0; half < 2; half++) {
-        const int s = lane + half * kWave;
-        const int k = s / G, slot = s % G;
-        if (k < count) {
-            const uint32_t c = leaves[k];
-            const int64_t j0 = as_global(lstart)[c];
-            const int jn = (int)(as_global(lstart)[c + 1] - j0);
-            if (slot < jn) {
-                const int64_t j = j0 + slot;
-                if (!MAYBE_NO_W || w) {   // MAYBE_NO_W: w == nullptr, the caller reads no w
-                    const double wv = as_global(w)[j];
-                    S.c.w[s] = REACH2 ? (Kern<K>::R * wv) * (Kern<K>::R * wv) : wv;
-                }
-                if constexpr (PREC == SPH_FP64) {
-                    S.c.x[s] = as_global(x)[j];
-                    S.c.y[s] = as_global(y)[j];
-                    S.c.z[s] = as_global(z)[j];
-                } else {
-                    S.c.fx[s] = as_global(fx)[j];
-                    S.c.fy[s] = as_global(fy)[j];
-                    S.c.fz[s] = as_global(fz)[j];
-                }
-                S.j[s] = (uint32_t)j;
-            }
-            if (slot == 0) {
-                const Node cand = load_global(nodes + c);
-                // hcov < 0: symmetric force criterion, reach R max(h over both leaves)
-                const Shift sh = leaf_shift(
-                    home, cand, bx, Kern<K>::R * (hcov < 0.0 ? fmax(home.hmax, cand.hmax) : hcov));
-                for (int a = 0; a < 3; a++) {
-                    S.lo[k][a] = cand.lo[a];
-                    S.hi[k][a] = cand.hi[a];
-                }
-                S.hmax[k] = cand.hmax;
-                S.sx[k] = sh.s[0];
-                S.sy[k] = sh.s[1];
-                S.sz[k] = sh.s[2];
-                S.per_pair[k] = sh.per_pair ? 1 : 0;
-                S.jn[k] = jn;
-                if (PREC == SPH_FP32_PAIR) {
-                    S.ox[k] = (float)((0.5 * (home.lo[0] + home.hi[0]) - 0.5 * (cand.lo[0] + cand.hi[0])) +
-                                      (sh.per_pair ? 0.0 : sh.s[0]));
-                    S.oy[k] = (float)((0.5 * (home.lo[1] + home.hi[1]) - 0.5 * (cand.lo[1] + cand.hi[1])) +
-                                      (sh.per_pair ? 0.0 : sh.s[1]));
-                    S.oz[k] = (float)((0.5 * (home.lo[2] + home.hi[2]) - 0.5 * (cand.lo[2] + cand.hi[2])) +
-                                      (sh.per_pair ? 0.0 : sh.s[2]));
-                }
-            }
-        } else if (slot == 0 && k < NL) {
-            S.jn[k] = 0;
-        }
-    }
-    wave_lds_sync();
-}
-
-// Separation x_i - x_j of a home particle (given by value) and staged slot s;
-// the same expression serves every test and flush, so they see identical bits.
-// PP = false: no staged leaf needs the pair-by-pair minimum image (the
-// caller has checked), which drops that branch.
-template <int G, int PREC, bool PP = true>
-__device__ inline void separation(const Stage<G, PREC> &S, const Box &bx, double hx, double hy,
-                                  double hz, float hfx, float hfy, float hfz, int s, double &dx,
-                                  double &dy, double &dz, double &r2)
-{
-    const int k = s / G;
-    if constexpr (PREC == SPH_FP64) {
-        dx = hx - S.c.x[s];
-        dy = hy - S.c.y[s];
-        dz = hz - S.c.z[s];
-        if (PP && S.per_pair[k]) {
-            dx = min_image(dx, bx.len[0], bx.half[0]);
-            dy = min_image(dy, bx.len[1], bx.half[1]);
-            dz = min_image(dz, bx.len[2], bx.half[2]);
-        } else {
-            dx += S.sx[k];
-            dy += S.sy[k];
-            dz += S.sz[k];
-        }
-        r2 = exact_r2(dx, dy, dz);
-    } else {
-        float fdx = (hfx - S.c.fx[s]) + S.ox[k];
-        float fdy = (hfy - S.c.fy[s]) + S.oy[k];
-        float fdz = (hfz - S.c.fz[s]) + S.oz[k];
-        if (PP && S.per_pair[k]) {
-            fdx = min_image_f(fdx, (float)bx.len[0], (float)bx.half[0]);
-            fdy = min_image_f(fdy, (float)bx.len[1], (float)bx.half[1]);
-            fdz = min_image_f(fdz, (float)bx.len[2], (float)bx.half[2]);
-        }
-        dx = fdx;
-        dy = fdy;
-        dz = fdz;
-        r2 = (double)(fdx * fdx + fdy * fdy + fdz * fdz);
-    }
-}
-
-// r_ij^2 for a superset filter (the caller's threshold carries a relative
-// slack far above rounding): in FP64 without pair-by-pair images the leaf's
-// shift joins the home position first, which the compiler shares between the
-// tests of one (particle, leaf) combination; otherwise the exact separation.
-template <int G, int PREC, bool PP>
-__device__ inline double filter_r2(const Stage<G, PREC> &S, const Box &bx, int p, int s)
-{
-    if constexpr (PREC == SPH_FP64 && !PP) {
-        const int k = s / G;
-        const double dx = (S.hx[p] + S.sx[k]) - S.c.x[s];
-        const double dy = (S.hy[p] + S.sy[k]) - S.c.y[s];
-        const double dz = (S.hz[p] + S.sz[k]) - S.c.z[s];
-        return dx * dx + dy * dy + dz * dz;
-    } else {
-        double dx, dy, dz, r2;
-        separation<G, PREC, PP>(S, bx, S.hx[p], S.hy[p], S.hz[p], S.hfx[p], S.hfy[p], S.hfz[p], s,
-                                dx, dy, dz, r2);
-        return r2;
-    }
-}
-
-// Squared distance from home particle p to staged leaf k's box in the frame of
-// the separation; 0 for a per-pair leaf (every candidate is then tested).
-template <int G, int PREC>
-__device__ inline double box_dist2(const Stage<G, PREC> &S, int p, int k)
-{
-    const double c[3] = {S.hx[p] + S.sx[k], S.hy[p] + S.sy[k], S.hz[p] + S.sz[k]};
-    double d2 = 0.0;
-#pragma unroll
-    for (int a = 0; a < 3; a++) {
-        // the gap below lo or above hi, 0 inside (at most one is positive)
-        const double d = fmax(fmax(S.lo[k][a] - c[a], c[a] - S.hi[k][a]), 0.0);
-        d2 += d * d;
-    }
-    return S.per_pair[k] ? 0.0 : d2;
-}
+// Per leaf of the group: first particle and particle count (jm), the shift
+// added to x_i - x_j (FP64), or the distance of the leaf centres with the
+// shift (FP32-pair).
+template <int PREC>
+struct LeafTab {
+    using T = std::conditional_t<PREC == SPH_FP64, double, float>;
+    uint2 jm[kGroup];
+    T ox[kGroup], oy[kGroup], oz[kGroup];
+};
 
 // The relative slack of the box test: it must accept every combination whose
 // candidates the record test can accept (rounding of the two differently
@@ -713,128 +578,292 @@ __device__ inline double box_dist2(const Stage<G, PREC> &S, int p, int k)
 template <int PREC>
 __device__ constexpr double box_slack() { return PREC == SPH_FP64 ? 1.0 + 1e-6 : 1.0 + 1e-4; }
 
-// Hit masks of one staged group: bit s of S.mask[p] set iff rec(p, s, pp), with
-// rec evaluated only where relevant(p, k) holds for the slot's leaf k; pp is
-// std::true_type when some staged leaf needs the pair-by-pair minimum image,
-// std::false_type otherwise (for separation's PP parameter).
-template <int G, int PREC, class Relevant, class Record>
-__device__ inline bool group_tests(Stage<G, PREC> &S, int count, Relevant relevant, Record rec,
-                                   bool diag, int64_t &boxes, int64_t &tests)
+// The next group of at most `depth` candidate leaves of a walk's result
+// (0: none left): a slice of the list, or after a truncated walk the passing
+// ones of the next 64 leaves under the listed nodes (written to wb.tmp).
+template <class Test>
+__device__ inline int next_group(const TreeInfo &T, const Node *nodes, const WalkResult &wr,
+                                 Test test, WalkBuf &wb, int depth, int64_t &pos,
+                                 const uint32_t *&leaves)
 {
-    constexpr int NL = Stage<G, PREC>::NL;
-    constexpr int LPC = G / kTestsPerLane;   // lanes per combination
-    constexpr int CPR = kWave / LPC;         // combinations per round
-    static_assert(G * NL == kSlots && LPC * kTestsPerLane == G, "combination layout");
+    if (wr.lev == 0) {
+        const int left = wr.n - (int)pos;
+        if (left <= 0) return 0;
+        leaves = wr.list + pos;
+        const int n = left < depth ? left : depth;
+        pos += n;
+        return n;
+    }
     const int lane = threadIdx.x & (kWave - 1);
-    const uint64_t lt = __lanemask_lt();
-    // combination c = p * NL + k; this lane judges c = lane and c = lane + 64
-    bool r0, r1;
-    {
-        const int p = lane / NL, k = lane % NL;
-        r0 = k < count && relevant(p, k);
+    const int sh = 3 * wr.lev;
+    const int64_t L = T.cnt[0], total = (int64_t)wr.n << sh;
+    while (pos < total) {
+        const int64_t t = pos + lane;
+        const int64_t c = t < total ? ((int64_t)wr.list[t >> sh] << sh) + (t & ((1ll << sh) - 1)) : L;
+        const bool pass = c < L && test(load_global(nodes + c));
+        const uint64_t mask = __ballot(pass);
+        pos += kWave;
+        if (mask) {
+            wave_lds_sync();   // the last group's readers of wb.tmp
+            if (pass) wb.tmp[__popcll(mask & __lanemask_lt())] = (uint32_t)c;
+            wave_lds_sync();
+            leaves = wb.tmp;
+            return (int)__popcll(mask);
+        }
     }
-    {
-        const int c = lane + kWave;
-        const int p = c / NL, k = c % NL;
-        r1 = k < count && relevant(p, k);
+    return 0;
+}
+
+// Leaves per group of a list of n: groups of equal size (whole rows), at most
+// `most`.
+template <int G>
+__device__ inline int group_depth(int n, int most)
+{
+    constexpr int LPR = kWave / G;
+    const int groups = (n + most - 1) / most;
+    const int d = groups > 0 ? (n + groups - 1) / groups : most;
+    const int r = (d + LPR - 1) / LPR * LPR;
+    return r < most ? r : most;
+}
+
+// Set up a group (lane l: leaf leaves[l]): the table, and in `lmask` (lane p
+// for home particle p) the leaves whose box is near enough to home particle p
+// to hold a pair.  hcov < 0: symmetric force criterion (reach R max(h) over
+// both leaves).  Returns how separations see the box.
+template <int G, int PREC, int K>
+__device__ inline int open_group(const uint32_t *leaves, int count, const uint32_t *__restrict__ lstart,
+                                 const Node *__restrict__ nodes, const Node &home, const Box &bx,
+                                 double hcov, const HomeTab<G, PREC> &H, uint64_t takes_part,
+                                 LeafTab<PREC> &tab, uint64_t &lmask)
+{
+    constexpr double RK = Kern<K>::R;
+    const int lane = threadIdx.x & (kWave - 1);
+    const bool valid = lane < count;
+    double cx = 0.0, cy = 0.0, cz = 0.0, ex = 0.0, ey = 0.0, ez = 0.0, reach2 = -1.0;
+    bool per_pair = false, shifted = false;
+    uint2 jm{0u, 0u};
+    if (valid) {
+        const uint32_t c = leaves[lane];
+        const uint32_t j0 = as_global(lstart)[c];
+        jm.x = j0;
+        jm.y = as_global(lstart)[c + 1] - j0;
+        const Node cand = load_global(nodes + c);
+        const Shift sh = leaf_shift(home, cand, bx, RK * (hcov < 0.0 ? fmax(home.hmax, cand.hmax) : hcov));
+        per_pair = sh.per_pair;
+        shifted = sh.s[0] != 0.0 || sh.s[1] != 0.0 || sh.s[2] != 0.0;
+        const double mx = 0.5 * (cand.lo[0] + cand.hi[0]), my = 0.5 * (cand.lo[1] + cand.hi[1]);
+        const double mz = 0.5 * (cand.lo[2] + cand.hi[2]);
+        // the box seen from the home particles, half extents rounded outwards
+        // by taking the larger side
+        ex = fmax(cand.hi[0] - mx, mx - cand.lo[0]);
+        ey = fmax(cand.hi[1] - my, my - cand.lo[1]);
+        ez = fmax(cand.hi[2] - mz, mz - cand.lo[2]);
+        cx = mx - sh.s[0];
+        cy = my - sh.s[1];
+        cz = mz - sh.s[2];
+        if (hcov < 0.0) {
+            const double hk = RK * cand.hmax;
+            reach2 = hk * hk;
+        }
+        if constexpr (PREC == SPH_FP64) {
+            tab.ox[lane] = sh.s[0];
+            tab.oy[lane] = sh.s[1];
+            tab.oz[lane] = sh.s[2];
+        } else {
+            tab.ox[lane] = (float)((0.5 * (home.lo[0] + home.hi[0]) - mx) + (per_pair ? 0.0 : sh.s[0]));
+            tab.oy[lane] = (float)((0.5 * (home.lo[1] + home.hi[1]) - my) + (per_pair ? 0.0 : sh.s[1]));
+            tab.oz[lane] = (float)((0.5 * (home.lo[2] + home.hi[2]) - mz) + (per_pair ? 0.0 : sh.s[2]));
+        }
     }
-    const uint64_t m0 = __ballot(r0), m1 = __ballot(r1);
-    const int n0 = (int)__popcll(m0);
-    if (r0) S.combo[__popcll(m0 & lt)] = (uint8_t)lane;
-    if (r1) S.combo[n0 + (int)__popcll(m1 & lt)] = (uint8_t)(lane + kWave);
-    const int C = n0 + (int)__popcll(m1);
-    // diagnostics (when asked for), wave-uniform: every judged combination is
-    // a box test, and a passing one tests each particle of its leaf (7-bit
-    // count per lane)
-    if (diag) {
-        boxes += (int64_t)count * G;
-        const int mine = (r0 ? S.jn[lane % NL] : 0) + (r1 ? S.jn[(lane + kWave) % NL] : 0);
-        for (int b = 0; b < 7; b++) tests += (int64_t)__popcll(__ballot((mine >> b) & 1)) << b;
+    tab.jm[lane] = jm;
+    const int img = __ballot(per_pair) ? kImgPair : (__ballot(shifted) ? kImgShift : kImgNone);
+    lmask = 0;
+    for (int p = 0; p < G; p++) {
+        if (!((takes_part >> p) & 1)) continue;
+        const HomeRow h = H.d[p];
+        const double dx = fmax(fabs(h.x - cx) - ex, 0.0);
+        const double dy = fmax(fabs(h.y - cy) - ey, 0.0);
+        const double dz = fmax(fabs(h.z - cz) - ez, 0.0);
+        const double d2 = (dx * dx + dy * dy) + dz * dz;
+        const double lim = hcov < 0.0 ? fmax(h.thr, reach2) : h.thr;
+        const uint64_t m = __ballot(valid && (per_pair || d2 <= lim * box_slack<PREC>()));
+        lmask = lane == p ? m : lmask;
     }
     wave_lds_sync();
-    const int u = lane % LPC;
-    // combinations of one round start their tests at different slots, which
-    // spreads their LDS reads over the banks
-    const int rot = lane / LPC;
-    // every test runs (slots past the leaf's end read stale but in-bounds
-    // LDS) and its slot predicate masks the result: no branch per test
-    auto rounds = [&](auto pp_possible) {
-        for (int b = 0; b < C; b += CPR) {
-            const int idx = b + lane / LPC;
-            if (idx < C) {
-                const int c = S.combo[idx];
-                const int p = c / NL, k = c % NL;
-                const int jn = S.jn[k];
-                uint64_t bits = 0;
+    return img;
+}
+
+// One row of candidates in this lane's registers.
+template <int PREC>
+struct Cand {
+    using T = std::conditional_t<PREC == SPH_FP64, double, float>;
+    T x, y, z;      // position, or the offset from its leaf's centre
+    T ox, oy, oz;   // shift (FP64, kImgShift) or leaf-centre distance (FP32-pair)
+    bool ok;        // the slot holds a particle
+};
+
+// x_i - x_j and r^2 of one home particle and one candidate: the expression
+// every test and evaluation uses, so all see the same bits (r^2 in FP64 as
+// exact_r2 forms it).
+template <int PREC, int IMG, class T>
+__device__ inline T separation(const Box &bx, T hx, T hy, T hz, T x, T y, T z, T ox, T oy, T oz,
+                               T &dx, T &dy, T &dz)
+{
+    if constexpr (PREC == SPH_FP64) {
+        dx = hx - x;
+        dy = hy - y;
+        dz = hz - z;
+        if constexpr (IMG == kImgPair) {
+            dx = min_image(dx, bx.len[0], bx.half[0]);
+            dy = min_image(dy, bx.len[1], bx.half[1]);
+            dz = min_image(dz, bx.len[2], bx.half[2]);
+        } else if constexpr (IMG == kImgShift) {
+            dx += ox;
+            dy += oy;
+            dz += oz;
+        }
+        return exact_r2(dx, dy, dz);
+    } else {
+        dx = (hx - x) + ox;
+        dy = (hy - y) + oy;
+        dz = (hz - z) + oz;
+        if constexpr (IMG == kImgPair) {
+            dx = min_image_f(dx, (float)bx.len[0], (float)bx.half[0]);
+            dy = min_image_f(dy, (float)bx.len[1], (float)bx.half[1]);
+            dz = min_image_f(dz, (float)bx.len[2], (float)bx.half[2]);
+        }
+        return dx * dx + dy * dy + dz * dz;
+    }
+}
+
+template <int G, int PREC, int IMG>
+__device__ inline uint32_t load_cand(const LeafTab<PREC> &tab, int row, const Pos4 *__restrict__ pos,
+                                     const Off4 *__restrict__ off, Cand<PREC> &c)
+{
+    const int s = row * kWave + (int)(threadIdx.x & (kWave - 1));
+    const int k = s / G, slot = s % G;
+    const uint2 jm = tab.jm[k];
+    c.ok = slot < (int)jm.y;
+    const uint32_t j = jm.x + (c.ok ? slot : 0);   // (a missing leaf's entry is particle 0)
+    if constexpr (PREC == SPH_FP64) {
+        const auto *q = as_global((const double *)(pos + j));
+        c.x = q[0];
+        c.y = q[1];
+        c.z = q[2];
+        if constexpr (IMG == kImgShift) {
+            c.ox = tab.ox[k];
+            c.oy = tab.oy[k];
+            c.oz = tab.oz[k];
+        }
+    } else {
+        const auto *q = as_global((const float *)(off + j));
+        c.x = q[0];
+        c.y = q[1];
+        c.z = q[2];
+        c.ox = tab.ox[k];
+        c.oy = tab.oy[k];
+        c.oz = tab.oz[k];
+    }
+    return j;
+}
+
+__device__ inline uint64_t readlane64(uint64_t v, int l)
+{
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
+    return ((uint64_t)hi << 32) | lo;
+}
+__device__ inline double readlane_d(double v, int l)
+{
+    return __builtin_bit_cast(double, readlane64(__builtin_bit_cast(uint64_t, v), l));
+}
+
+// Number of set bits of a ballot below this lane.
+__device__ inline uint32_t rank_of(uint64_t m)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// The open group's candidates against the home particles.  hit(c, w, p, h, r2)
+// decides a test (w: the extra value load(r, j, ok) gave for this candidate),
+// room(p, n, have) says whether n more hits of p fit after the `have` it
+// holds, and put(p, at, c-row, slot, r2) takes a hit at place `at`.  cnt (lane
+// p) counts the hits held.  Returns the home particle whose hit list is full:
+// the caller empties that list (or all of them), sets cnt to match and calls
+// again to go on (lmask then holds what is left of the group); -1 when the
+// group is done.
+template <int G, int PREC, int IMG, int NR, class Load, class Hit, class Room, class Put>
+__device__ inline int test_rows(const LeafTab<PREC> &tab, const HomeTab<G, PREC> &H, int count,
+                                 const Box &bx, const Pos4 *__restrict__ pos,
+                                 const Off4 *__restrict__ off, uint64_t &lmask, int &cnt,
+                                 bool diag, int64_t &tests, Load load, Hit hit, Room room, Put put)
+{
+    constexpr int LPR = kWave / G;                      // leaves per row
+    constexpr uint64_t RM = (1ull << LPR) - 1;          // one row's leaves
+    constexpr uint64_t BM = NR * LPR >= 64 ? ~0ull : (1ull << (NR * LPR)) - 1;
+    using T = typename Cand<PREC>::T;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int nrows = (count + LPR - 1) / LPR;
+    for (int r0 = 0; r0 < nrows; r0 += NR) {
+        // home particles with a near leaf among these rows
+        uint64_t todo = __ballot(lane < G && ((lmask >> (r0 * LPR)) & BM) != 0);
+        if (todo == 0) continue;
+        Cand<PREC> c[NR];
+        T w[NR];
+        __builtin_amdgcn_s_setprio(2);
 #pragma unroll
-                for (int t = 0; t < kTestsPerLane; t++) {
-                    const int slot = u + LPC * ((t + rot) % kTestsPerLane);
-                    const int s = k * G + slot;
-                    const bool hit = (slot < jn) & rec(p, s, pp_possible);
-                    bits |= (uint64_t)hit << (s & 63);
+        for (int r = 0; r < NR; r++) {
+            const uint32_t j = load_cand<G, PREC, IMG>(tab, r0 + r, pos, off, c[r]);
+            w[r] = load(j);
+        }
+        __builtin_amdgcn_s_setprio(0);
+        while (todo) {
+            const int p = (int)__builtin_ctzll(todo);
+            todo &= todo - 1;
+            const uint64_t bits = readlane64(lmask, p) >> (r0 * LPR);
+            int have = __builtin_amdgcn_readlane(cnt, p);
+            T hx, hy, hz, thr;
+            if constexpr (PREC == SPH_FP64) {
+                const HomeRow h = H.d[p];
+                hx = h.x; hy = h.y; hz = h.z; thr = h.thr;
+            } else {
+                const HomeRowF h = H.f[p];
+                hx = h.x; hy = h.y; hz = h.z; thr = h.thr;
+            }
+            int full = -1;
+#pragma unroll
+            for (int r = 0; r < NR; r++) {
+                if (full < 0 && ((bits >> (r * LPR)) & RM) != 0) {
+                    T dx, dy, dz;
+                    const T r2 = separation<PREC, IMG>(bx, hx, hy, hz, c[r].x, c[r].y, c[r].z, c[r].ox,
+                                                       c[r].oy, c[r].oz, dx, dy, dz);
+                    const bool h = c[r].ok && hit(r2, thr, w[r]);
+                    const uint64_t m = __ballot(h);
+                    if (diag) tests += (int64_t)__popcll(__ballot(c[r].ok));
+                    if (m) {
+                        const int n = (int)__popcll(m);
+                        if (!room(have, n)) {
+                            full = r;
+                        } else {
+                            if (h) put(p, have + (int)rank_of(m), (r0 + r) * kWave + lane, r2, w[r]);
+                            have += n;
+                        }
+                    }
                 }
-                if (bits)
-                    atomicOr((unsigned long long *)&S.mask[p][(k * G) >> 6], (unsigned long long)bits);
+            }
+            cnt = lane == p ? have : cnt;
+            if (full >= 0) {
+                // what is done leaves the masks: these rows of the particles
+                // before p, and of p the rows before the full one
+                const uint64_t mine = lane < p ? BM : (lane == p ? (1ull << (full * LPR)) - 1 : 0ull);
+                lmask &= ~(mine << (r0 * LPR));
+                return p;
             }
         }
-    };
-    const bool any_pp = __ballot(lane < count && S.per_pair[lane < NL ? lane : 0]) != 0ull;
-    if (any_pp)
-        rounds(std::true_type{});
-    else
-        rounds(std::false_type{});
-    wave_lds_sync();
-    return any_pp;
-}
-
-// As for_my_bits, but this lane's bits two at a time: fn(sa, sb) with sb < 0
-// when sa is its last, so the caller can issue both pairs' loads before
-// using either.
-// Clear the lowest set bit of the 128-bit mask (w0, w1), without a branch.
-__device__ inline void pop_low(uint64_t &w0, uint64_t &w1)
-{
-    const bool lo = w0 != 0;
-    const uint64_t a = w0 & (w0 - 1), b = w1 & (w1 - 1);
-    w0 = lo ? a : w0;
-    w1 = lo ? w1 : b;
-}
-
-template <int LPP, class Fn>
-__device__ inline int for_my_bit_pairs(uint64_t w0, uint64_t w1, int e0, Fn fn)
-{
-    const int n = (int)__popcll(w0) + (int)__popcll(w1);
-    auto pop = [&]() { pop_low(w0, w1); };
-    auto low = [&]() { return w0 ? (int)__builtin_ctzll(w0) : 64 + (int)__builtin_ctzll(w1); };
-    for (int t = 0; t < e0; t++) pop();
-    for (int e = e0; e < n; e += 2 * LPP) {
-        const int sa = low();
-        for (int t = 0; t < LPP; t++) pop();
-        int sb = -1;
-        if (e + LPP < n) {
-            sb = low();
-            for (int t = 0; t < LPP; t++) pop();
-        }
-        fn(sa, sb);
+        // these rows are done for every home particle
+        lmask &= ~(BM << (r0 * LPR));
     }
-    return n;
-}
-
-// The set bits of a 128-bit mask in ascending order, shared round-robin by
-// the LPP lanes of a particle: this lane takes the bits of rank e = e0,
-// e0 + LPP, ... (0 <= e0 < LPP) and calls fn(slot, e).  Returns the number of
-// set bits.
-template <int LPP, class Fn>
-__device__ inline int for_my_bits(uint64_t w0, uint64_t w1, int e0, Fn fn)
-{
-    const int n = (int)__popcll(w0) + (int)__popcll(w1);
-    for (int t = 0; t < e0; t++) pop_low(w0, w1);
-    for (int e = e0; e < n; e += LPP) {
-        const int s = w0 ? (int)__builtin_ctzll(w0) : 64 + (int)__builtin_ctzll(w1);
-        fn(s, e);
-#pragma unroll
-        for (int t = 0; t < LPP; t++) pop_low(w0, w1);
-    }
-    return n;
+    return -1;
 }
 
 // ---------------------------------------------------------------------------
@@ -884,50 +913,125 @@ __device__ inline int find_req(const uint32_t *pre, int nreq, int64_t g)
 // Density loop + h solve
 // ---------------------------------------------------------------------------
 
+// FP64 evaluations keep, instead of the sums of m f and m q f' alone, what
+// gives the kernel sum at any nearby h without another pass over the
+// neighbours.  With q' = q / (1 + x) for h' = h (1 + x), a' = (R - q')_+ is
+// (a + R x) / (1 + x) while no neighbour enters or leaves the support of one
+// of the kernel's pieces, so
+//   sum m f(q') = (1 + x)^-N (D0 + x D1 + x^2 D2 + x^3 D3 ...),
+// N = 3 (M4: exact with D0..D3) or 5 (quintic: D4 and D5 left out, an error of
+// order x^4), and the h-rho relation sum m f = eta^3 m_i / sigma is a
+// polynomial in x.
+template <int K>
+struct Sums {
+    double d0 = 0.0, d1 = 0.0, d2 = 0.0;
+    double wn = 0.0;                       // D3 of unequal masses, quintic's D3
+    double edge = 1e300;                   // smallest |q - knot| met
+    int n = 0, n1 = 0;                     // entries inside R h, inside h
+    static constexpr int N = K == SPH_KERNEL_QUINTIC ? 5 : 3;
+};
+
+template <int K, bool EQ>
+__device__ inline void add_entry(Sums<K> &s, double r2, double m, double hinv, double h2)
+{
+    // r = r^2 / sqrt(r^2) without a branch (r^2 = 0 gives 0 * finite = 0; the
+    // 1e-300 leaves any r^2 above 1e-284 unchanged); one refinement of the
+    // hardware estimate
+    const double q = (r2 * rsqrt_nr1(r2 + 1e-300)) * hinv;
+    const bool in = r2 < h2;
+    s.n += in ? 1 : 0;
+    if constexpr (K == SPH_KERNEL_QUINTIC) {
+        const double t3 = 3.0 - q;
+        const double a = fmax(t3, 0.0), b = fmax(2.0 - q, 0.0), c = fmax(1.0 - q, 0.0);
+        s.edge = fmin(s.edge, fabs(t3));
+        const double a2 = a * a, b2 = b * b, c2 = c * c;
+        const double a3 = a2 * a, b3 = b2 * b, c3 = c2 * c;
+        const double a4 = a2 * a2, b4 = b2 * b2, c4 = c2 * c2;
+        const double e0 = a4 * a - 6.0 * (b4 * b) + 15.0 * (c4 * c);
+        const double e1 = 15.0 * a4 - 60.0 * b4 + 75.0 * c4;
+        const double e2 = 90.0 * a3 - 240.0 * b3 + 150.0 * c3;
+        const double e3 = 270.0 * a2 - 480.0 * b2 + 150.0 * c2;
+        if constexpr (EQ) {
+            s.d0 += e0;
+            s.d1 += e1;
+            s.d2 += e2;
+            s.wn += e3;
+        } else {
+            s.d0 += m * e0;
+            s.d1 += m * e1;
+            s.d2 += m * e2;
+            s.wn += m * e3;
+        }
+    } else {
+        const double t2 = 2.0 - q, t1 = 1.0 - q;
+        const double a = fmax(t2, 0.0), b = fmax(t1, 0.0);
+        s.edge = fmin(fmin(s.edge, fabs(t2)), fabs(t1));
+        const double a2 = a * a, b2 = b * b;
+        const double e0 = (0.25 * a2) * a - b2 * b;
+        const double e1 = 0.5 * a2 - b2;     // x 3
+        const double e2 = a - b;             // x 3
+        const bool in1 = t1 > 0.0;
+        if constexpr (EQ) {
+            s.d0 += e0;
+            s.d1 += e1;
+            s.d2 += e2;
+            s.n1 += in1 ? 1 : 0;
+        } else {
+            s.d0 += m * e0;
+            s.d1 += m * e1;
+            s.d2 += m * e2;
+            s.wn += m * ((in ? 2.0 : 0.0) - (in1 ? 1.0 : 0.0));
+        }
+    }
+}
+
+template <int KK>
+__device__ inline double group_min(double v)
+{
+    if constexpr (KK >= 2) v = fmin(v, xlane<1>(v));
+    if constexpr (KK >= 4) v = fmin(v, xlane<2>(v));
+    if constexpr (KK >= 8) v = fmin(v, xlane<4>(v));
+    if constexpr (KK >= 16) v = fmin(v, xlane<8>(v));
+    return v;
+}
+
+// A tight tolerance: the result then does not depend on how the root was
+// approached, and the polynomial above may stand in for a pass.  With a loose
+// one (the paper's 1 %) the solve stops at whatever h meets it, so it keeps to
+// the plain Newton path.
+constexpr double kTightTol = 1e-9;
+
 template <int G, int PREC, int K>
 __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(Batch<DensArgs> B)
 {
     constexpr int LPP = kWave / G;   // lanes per home particle
-    constexpr int NL = kSlots / G;   // candidate leaves staged per group
     constexpr int KP = Kern<K>::list;
     constexpr double RK = Kern<K>::R, SIG = Kern<K>::sigma;
-    constexpr int ROWS = KP / LPP;   // cache rows of 64 entries
+    constexpr bool F64 = PREC == SPH_FP64;
+    // list entries that the lanes of a particle read per step: 4 each
+    constexpr int CHUNK = 4 * LPP;
+    static_assert(KP % CHUNK == 0, "lists hold whole steps");
     __shared__ WalkBuf wb;
     __shared__ TreeInfo T;
-    __shared__ Stage<G, PREC> S;
+    __shared__ union {
+        LeafTab<PREC> tab;
+        uint32_t walk_spare[kFront];   // lent to walks, which run between sweeps
+    } S;
+    __shared__ HomeTab<G, PREC> H;
     __shared__ uint32_t pre[kMaxBatch + 1];
-    // Per home particle, the Newton iteration's bracket and the results of its
-    // latest evaluation.  Every lane of a particle computes the same values;
-    // kept in registers they were spilled to scratch and reloaded at every
-    // step (the loop is register-bound at 4 waves per SIMD), so they live in
-    // LDS where the per-wave budget (10 KB at 16 waves per CU) has room: FP64
-    // up to G = 16 and FP32-pair.  Each lane of the particle writes the same
-    // value and reads its own wave's writes (LDS operations of a wave are
-    // performed in order).
-    constexpr bool NR_LDS = PREC == SPH_FP32_PAIR || G <= 16;
-    __shared__ double nr_mem[NR_LDS ? 5 * G : 1];
     batch_prefix(B, pre);
     const int lane = threadIdx.x;
     const int p = lane / LPP, q = lane % LPP;
-    double *const nr_lo = nr_mem + (NR_LDS ? 0 * G + p : 0);
-    double *const nr_hi = nr_mem + (NR_LDS ? 1 * G + p : 0);
-    double *const nr_h = nr_mem + (NR_LDS ? 2 * G + p : 0);
-    double *const nr_rho = nr_mem + (NR_LDS ? 3 * G + p : 0);
-    double *const nr_om = nr_mem + (NR_LDS ? 4 * G + p : 0);
     // Candidate lists of this block: for every home particle up to KP entries
     // (r^2, and m unless all masses are equal) of the candidates within R Rc
-    // of it, in the order a sweep meets them.  Entry e of particle p sits in
-    // row e / LPP, column p LPP + e % LPP, and lane (p, q) owns the entries
-    // e = q (mod LPP) both when a sweep writes them and when later Newton
-    // steps read them back, summing them in the same order: a step from the
-    // list gives the bits of a sweep.  The particle itself is marked (mass or,
-    // with equal masses, r^2 = 0 stored negated) to keep it out of the count.
+    // of it, in the order a sweep meets them, one particle after the other.
     // FP32-pair forms every r^2 in single precision, so its list holds them
     // as floats (half the bytes, the same values); FP64 lists hold doubles.
-    using ListR2 = std::conditional_t<PREC == SPH_FP64, double, float>;
-    double *const cslice = B.cache + (size_t)blockIdx.x * (2 * ROWS * kWave);
+    // A particle's lanes read 64 consecutive bytes of its list per load.
+    using ListR2 = std::conditional_t<F64, double, float>;
+    double *const cslice = B.cache + (size_t)blockIdx.x * (2 * KP * G);
     ListR2 *const cr2 = reinterpret_cast<ListR2 *>(cslice);
-    double *const cm = cslice + ROWS * kWave;
+    double *const cm = cslice + KP * G;
     int64_t evals = 0, walks = 0, visits = 0, overflows = 0, nr_total = 0, tests = 0, boxes = 0;
     int64_t list_over = 0;
     int iter_max = 0;
@@ -971,38 +1075,26 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
         const int64_t i = first + p;
         const bool active = p < nhome && (!A.active || as_global(A.active)[i] != 0);
         const int64_t ii = active ? i : first;
-        const double hx = as_global(A.x)[ii], hy = as_global(A.y)[ii], hz = as_global(A.z)[ii];
-        float hfx = 0.f, hfy = 0.f, hfz = 0.f;
-        if (PREC == SPH_FP32_PAIR) {
-            hfx = as_global(A.fx)[ii];
-            hfy = as_global(A.fy)[ii];
-            hfz = as_global(A.fz)[ii];
-        }
         const double mi = as_global(A.m)[ii];
         const double mu = as_const(A.mrange)[0];
         const bool equal_m = mu == as_const(A.mrange)[1];
+        const bool tight = F64 && A.h_rtol <= kTightTol;
         const Node home = load_const(A.nodes + leaf);
         double h = as_global((const double *)A.h)[ii];
-        double lo_b = 0.0, hi_b = INFINITY;          // registers unless NR_LDS
+        double lo_b = 0.0, hi_b = INFINITY;
         bool conv = !active;
         double h_out = h, rho_out = 0.0, om_out = 1.0;
-        if constexpr (NR_LDS) {
-            *nr_lo = 0.0;
-            *nr_hi = INFINITY;
-            *nr_h = h;
-            *nr_rho = 0.0;
-            *nr_om = 1.0;
-        }
         int n_out = 0;
         if (q == 0) {
-            S.hx[p] = hx;
-            S.hy[p] = hy;
-            S.hz[p] = hz;
-            S.hfx[p] = hfx;
-            S.hfy[p] = hfy;
-            S.hfz[p] = hfz;
-            S.mask[p][0] = 0;
-            S.mask[p][1] = 0;
+            H.d[p].x = as_global(A.x)[ii];
+            H.d[p].y = as_global(A.y)[ii];
+            H.d[p].z = as_global(A.z)[ii];
+            if constexpr (!F64) {
+                const auto *o = as_global((const float *)(A.off + ii));
+                H.f[p].x = o[0];
+                H.f[p].y = o[1];
+                H.f[p].z = o[2];
+            }
         }
 
         double hcov = A.walk_margin * wave_max(active ? h : 0.0);
@@ -1011,9 +1103,10 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
             const double R2 = R * R;
             return [&bx, &home, R2](const Node &nd) { return box_gap2(home.lo, home.hi, nd, bx) < R2; };
         };
-        // the walk and the staging are chains of dependent loads: the wave
-        // issues them at raised priority, ahead of waves in their arithmetic
-        // (measured: the force loop 1 % faster, the density loop unchanged)
+        // the walk and the candidate loads are chains of dependent loads: the
+        // wave issues them at raised priority, ahead of waves in their
+        // arithmetic (measured: the force loop 1 % faster, the density loop
+        // unchanged)
         __builtin_amdgcn_s_setprio(2);
         WalkResult wr = walk(T, A.nodes, make_test(hcov), wb, S.walk_spare);
         __builtin_amdgcn_s_setprio(0);
@@ -1022,191 +1115,297 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
         int iter = 0;
         int evals_leaf = 0;   // this lane's density pairs evaluated for this leaf
         // list state of this particle: `cached` = the list holds every
-        // candidate within R Rc (count <= KP); valid while h <= Rc
+        // candidate within R Rc; valid while h <= Rc.  count: its entries.
         bool cached = false;
         double Rc = 0.0;
         int count = 0;
         for (;;) {
-            double s0 = 0.0, s2 = 0.0;
-            int cnt = 0;
             const double hinv = 1.0 / h;
             const double h2x4 = (RK * h) * (RK * h);
-            const float h2x4f = (float)h2x4;
-            // pair terms of one list entry (r^2, and the mass when masses differ).
-            // Branch-free: an entry outside R h adds 0 * f (+0 or -0, which leave
-            // the sums' bits unchanged) and no count; the lanes of a wave almost
-            // never agree on skipping, so a branch would save no work.  The
-            // particle itself is an entry (r^2 = 0) and is counted here; the
-            // count drops it after the reduction.
-            auto accumulate = [&](double r2, double mw) {
-                const bool in = PREC == SPH_FP64 ? r2 < h2x4 : (float)r2 < h2x4f;
-                const double mj = in ? (equal_m ? mu : mw) : 0.0;
-                if (PREC == SPH_FP64) {
-                    double f, df;
-                    // r = r^2 / sqrt(r^2) without a branch (r^2 = 0 gives
-                    // 0 * finite = 0; the 1e-300 leaves any r^2 above 1e-284
-                    // unchanged); one refinement of the hardware estimate
-                    const double qq = (r2 * rsqrt_nr1(r2 + 1e-300)) * hinv;
-                    kern<K>(qq, f, df);
-                    s0 += mj * f;
-                    s2 += mj * (qq * df);
+            Sums<K> sm;
+            double s0 = 0.0, s2 = 0.0;   // FP32-pair sums
+            const float h2x4f = (float)h2x4, hinvf = (float)hinv;
+            // the pair terms of this particle's list entries [0, n), its lanes
+            // sharing them four at a time; entries past n up to a whole step
+            // are far away and add nothing
+            auto eval_list = [&](int n) {
+                const ListR2 *l = cr2 + p * KP;
+                const double *lm = cm + p * KP;
+                if constexpr (F64) {
+                    using D2 = double __attribute__((ext_vector_type(2)));
+                    auto sums = [&](auto eq) {
+                        constexpr bool EQ = decltype(eq)::value;
+                        for (int e = 2 * q; e < n; e += CHUNK) {
+                            const D2 u = *(const __attribute__((address_space(1))) D2 *)(l + e);
+                            const D2 v = *(const __attribute__((address_space(1))) D2 *)(l + e + 2 * LPP);
+                            D2 mu2{}, mv2{};
+                            if constexpr (!EQ) {
+                                mu2 = *(const __attribute__((address_space(1))) D2 *)(lm + e);
+                                mv2 = *(const __attribute__((address_space(1))) D2 *)(lm + e + 2 * LPP);
+                            }
+                            add_entry<K, EQ>(sm, u.x, mu2.x, hinv, h2x4);
+                            add_entry<K, EQ>(sm, u.y, mu2.y, hinv, h2x4);
+                            add_entry<K, EQ>(sm, v.x, mv2.x, hinv, h2x4);
+                            add_entry<K, EQ>(sm, v.y, mv2.y, hinv, h2x4);
+                        }
+                    };
+                    if (equal_m) sums(std::true_type{});
+                    else sums(std::false_type{});
                 } else {
-                    float f, df;
-                    const float qq = sqrtf((float)r2) * (float)hinv;
-                    kern<K>(qq, f, df);
-                    s0 += mj * (double)f;
-                    s2 += mj * (double)(qq * df);
+                    using F4 = float __attribute__((ext_vector_type(4)));
+                    using D4 = double __attribute__((ext_vector_type(4)));
+                    for (int e = 4 * q; e < n; e += CHUNK) {
+                        const F4 u = *(const __attribute__((address_space(1))) F4 *)(l + e);
+                        D4 mw{mu, mu, mu, mu};
+                        if (!equal_m) mw = *(const __attribute__((address_space(1))) D4 *)(lm + e);
+#pragma unroll
+                        for (int k = 0; k < 4; k++) {
+                            // branch-free: an entry outside R h adds 0 * f
+                            const bool in = u[k] < h2x4f;
+                            const double mj = in ? mw[k] : 0.0;
+                            float f, df;
+                            const float qq = sqrtf(u[k]) * hinvf;
+                            kern<K>(qq, f, df);
+                            s0 += mj * (double)f;
+                            s2 += mj * (double)(qq * df);
+                            sm.n += in ? 1 : 0;
+                        }
+                    }
                 }
-                cnt += in ? 1 : 0;
+            };
+            // the n entries of home particle pp's list, which is full, added to
+            // its sums (on its first lane) by the whole wave; the list starts
+            // afresh.  n and the order depend on the particle and the rows
+            // alone
+            auto empty_list = [&](int pp, int n) {
+                Sums<K> t;
+                double t0 = 0.0, t2 = 0.0;
+                const double hv = readlane_d(hinv, pp * LPP), hh = readlane_d(h2x4, pp * LPP);
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                for (int e = lane; e < n; e += kWave) {
+                    const ListR2 r2 = as_global(cr2)[pp * KP + e];
+                    const double mw = equal_m ? mu : as_global(cm)[pp * KP + e];
+                    if constexpr (F64) {
+                        if (equal_m) add_entry<K, true>(t, r2, mw, hv, hh);
+                        else add_entry<K, false>(t, r2, mw, hv, hh);
+                    } else {
+                        const bool in = r2 < (float)hh;
+                        const double mj = in ? mw : 0.0;
+                        float f, df;
+                        const float qq = sqrtf(r2) * (float)hv;
+                        kern<K>(qq, f, df);
+                        t0 += mj * (double)f;
+                        t2 += mj * (double)(qq * df);
+                        t.n += in ? 1 : 0;
+                    }
+                }
+                const int n0 = (int)wave_sum_int(t.n), n1 = (int)wave_sum_int(t.n1);
+                const bool own = lane == pp * LPP;
+                sm.n += own ? n0 : 0;
+                if constexpr (F64) {
+                    sm.n1 += own ? n1 : 0;
+                    const double d0 = wave_sum(t.d0), d1 = wave_sum(t.d1), d2 = wave_sum(t.d2);
+                    const double wn = wave_sum(t.wn);
+                    sm.d0 += own ? d0 : 0.0;
+                    sm.d1 += own ? d1 : 0.0;
+                    sm.d2 += own ? d2 : 0.0;
+                    sm.wn += own ? wn : 0.0;
+                } else {
+                    t0 = wave_sum(t0);
+                    t2 = wave_sum(t2);
+                    s0 += own ? t0 : 0.0;
+                    s2 += own ? t2 : 0.0;
+                }
+            };
+            // entries [n, whole step) of this particle's list: far away
+            auto pad_list = [&](int n) {
+                const int end = (n + CHUNK - 1) / CHUNK * CHUNK;
+                for (int e = n + q; e < end; e += LPP) {
+                    cr2[p * KP + e] = F64 ? (ListR2)1e300 : (ListR2)1e30f;
+                    if (!equal_m) cm[p * KP + e] = 0.0;
+                }
+                // the lanes read what other lanes of the wave stored
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
             };
             if (__ballot(!conv && !cached) != 0ull) {
-                // sweep: every particle still iterating takes its pair terms from
-                // the candidates directly and rebuilds its list around its
-                // current h (the first KP entries; a longer list is not kept)
+                // sweep: every particle still iterating rebuilds its list
+                // around its current h.  A list that fills up is added to the
+                // sums and started afresh; it cannot serve later steps then
                 double rc2 = -1.0;
                 if (!conv) {
                     Rc = fmin(kCacheGrow * h, hcov);
                     rc2 = (RK * Rc) * (RK * Rc) * (1.0 + 1e-6);
                 }
-                if (q == 0) S.thr[p] = rc2;
                 wave_lds_sync();
-                int base = 0;
-                auto group = [&](const uint32_t *leaves, int ng) {
-                    // FP32-pair stages no mass when all masses are equal (measured
-                    // faster; the FP64 loop is faster staging it anyway)
-                    constexpr bool skip_m = PREC == SPH_FP32_PAIR;
-                    __builtin_amdgcn_s_setprio(2);
-                    stage_group<G, PREC, K, false, skip_m>(S, leaves, ng, A.lstart, A.nodes, home, bx,
-                                                        hcov, A.x, A.y, A.z,
-                                                        skip_m && equal_m ? nullptr : A.m, A.fx,
-                                                        A.fy, A.fz);
-                    __builtin_amdgcn_s_setprio(0);
-                    const bool any_pp = group_tests<G, PREC>(
-                        S, ng,
-                        [&](int pp, int k) {
-                            const double thr = S.thr[pp];
-                            return thr >= 0.0 && box_dist2(S, pp, k) <= thr * box_slack<PREC>();
-                        },
-                        [&](int pp, int sl, auto ppc) {
-                            return filter_r2<G, PREC, decltype(ppc)::value>(S, bx, pp, sl) < S.thr[pp];
-                        },
-                        A.count_tests != 0, boxes, tests);
-                    const uint64_t w0 = S.mask[p][0], w1 = S.mask[p][1];
-                    // list position base + e belongs to lane (base + e) % LPP
-                    const int e0 = (q - base % LPP + LPP) % LPP;
-                    auto flush = [&](auto ppc) {
-                        return for_my_bits<LPP>(w0, w1, e0, [&](int sl, int e) {
-                            const int pos = base + e;
-                            double dx, dy, dz, r2;
-                            // FP64: the home position from LDS (fewer long-lived
-                            // registers; measured faster), FP32-pair: the offsets
-                            // held in registers (measured faster there)
-                            separation<G, PREC, decltype(ppc)::value>(
-                                S, bx, PREC == SPH_FP64 ? S.hx[p] : hx, PREC == SPH_FP64 ? S.hy[p] : hy,
-                                PREC == SPH_FP64 ? S.hz[p] : hz, hfx, hfy, hfz, sl, dx, dy, dz, r2);
-                            // (with equal masses mw is not used, and FP32-pair
-                            // does not stage it)
-                            double mw = 0.0;
-                            if (PREC == SPH_FP64 || !equal_m) mw = S.c.w[sl];
-                            if (pos < KP) {
-                                const int at = (pos / LPP) * kWave + lane;
-                                cr2[at] = (ListR2)r2;
-                                if (!equal_m) cm[at] = mw;
-                            }
-                            accumulate(r2, mw);
-                        });
-                    };
-                    const int n = any_pp ? flush(std::true_type{}) : flush(std::false_type{});
-                    base += n;
-                    if (q == 0) {
-                        S.mask[p][0] = 0;
-                        S.mask[p][1] = 0;
-                    }
-                    wave_lds_sync();
-                };
-                visits += for_each_leaf_group<NL>(T, A.nodes, wr, make_test(hcov), wb, group,
-                                                  B.stage);
-                count = base;
-                cached = !conv && count <= KP;
-                list_over += (int64_t)__popcll(__ballot(!conv && q == 0 && count > KP));
-            } else {
-                // every particle still iterating has a complete list and h <= Rc:
-                // the entries inside R h, in list order, are the hits of a sweep
-                // (rows <= ROWS: a cached list has at most KP entries.)  Rows past
-                // this lane's entries pass r^2 = (R h)^2, which adds nothing
-                // Rows are read kRowBatch at a time, every load issued before the
-                // first sum (ROWS is a multiple of kRowBatch, so the rows read past
-                // `rows` stay inside the block's slice; they count as not mine)
-                constexpr int kRowBatch = 4;
-                static_assert(ROWS % kRowBatch == 0, "list rows come in whole batches");
-                const int rows = wave_max_int(conv ? 0 : (count + LPP - 1) / LPP);
-                const ListR2 *__restrict__ lr2 = cr2 + lane;
-                const double *__restrict__ lm = cm + lane;
-                const int lim = conv ? 0 : count;   // entries of this particle still iterating
-                for (int r0 = 0; r0 < rows; r0 += kRowBatch) {
-                    double r2b[kRowBatch], mwb[kRowBatch];
-#pragma unroll
-                    for (int b = 0; b < kRowBatch; b++) {
-                        r2b[b] = (double)lr2[(r0 + b) * kWave];
-                        mwb[b] = equal_m ? 0.0 : lm[(r0 + b) * kWave];
-                    }
-#pragma unroll
-                    for (int b = 0; b < kRowBatch; b++) {
-                        const bool mine = (r0 + b) * LPP + q < lim;
-                        accumulate(mine ? r2b[b] : h2x4, mwb[b]);
-                    }
+                if (q == 0) {
+                    H.d[p].thr = rc2;
+                    if constexpr (!F64) H.f[p].thr = (float)rc2;
                 }
+                wave_lds_sync();
+                const uint64_t lanes_in = __ballot(!conv);
+                uint64_t takes_part = 0;   // bit p: home particle p
+#pragma unroll
+                for (int k = 0; k < G; k++)
+                    takes_part |= ((lanes_in >> (k * LPP)) & 1ull) << k;
+                const int depth = group_depth<G>(wr.n, B.stage > 0 ? B.stage * G / 2 : kGroup);
+                uint64_t emptied = 0;      // bit p: the list of home particle p is not complete
+                int held = 0;              // lane p: entries in the list of home particle p
+                int64_t at = 0;
+                const uint32_t *leaves = nullptr;
+                auto test = make_test(hcov);
+                for (;;) {
+                    const int ng = next_group(T, A.nodes, wr, test, wb, depth, at, leaves);
+                    if (ng == 0) break;
+                    uint64_t lmask;
+                    const int img = open_group<G, PREC, K>(leaves, ng, A.lstart, A.nodes, home, bx, hcov,
+                                                           H, takes_part, S.tab, lmask);
+                    visits += ng;
+                    if (A.count_tests) boxes += (int64_t)ng * (int)__popcll(takes_part);
+                    auto load = [&](uint32_t j) { return equal_m ? mu : as_global(A.m)[j]; };
+                    auto hit = [&](auto r2, auto thr, double) { return r2 < thr; };
+                    auto room = [&](int have, int n) { return have + n <= KP; };
+                    auto put = [&](int pp, int e, int, auto r2, double mw) {
+                        cr2[pp * KP + e] = r2;
+                        if (!equal_m) cm[pp * KP + e] = mw;
+                    };
+                    for (;;) {
+                        int full;
+                        if (img == kImgNone)
+                            full = test_rows<G, PREC, kImgNone, kRows>(
+                                S.tab, H, ng, bx, A.pos, A.off, lmask, held, A.count_tests != 0, tests,
+                                load, hit, room, put);
+                        else if (img == kImgShift && F64)
+                            full = test_rows<G, PREC, kImgShift, kRows / 2>(
+                                S.tab, H, ng, bx, A.pos, A.off, lmask, held, A.count_tests != 0, tests,
+                                load, hit, room, put);
+                        else if (img == kImgShift)
+                            full = test_rows<G, PREC, kImgNone, kRows>(
+                                S.tab, H, ng, bx, A.pos, A.off, lmask, held, A.count_tests != 0, tests,
+                                load, hit, room, put);
+                        else
+                            full = test_rows<G, PREC, kImgPair, kRows / 2>(
+                                S.tab, H, ng, bx, A.pos, A.off, lmask, held, A.count_tests != 0, tests,
+                                load, hit, room, put);
+                        if (full < 0) break;
+                        empty_list(full, __builtin_amdgcn_readlane(held, full));
+                        held = lane == full ? 0 : held;
+                        list_over += (emptied >> full) & 1 ? 0 : 1;
+                        emptied |= 1ull << full;
+                    }
+                    wave_lds_sync();   // the next group rewrites the table
+                }
+                const int mine = __shfl(held, p);   // every lane takes part
+                count = conv ? 0 : mine;
+                cached = !conv && !((emptied >> p) & 1);
+                pad_list(count);
             }
+            eval_list(conv ? 0 : count);
             // one evaluation for every particle still iterating (uniform)
             nr_total += (int64_t)__popcll(__ballot(!conv && q == 0));
-            s0 = group_sum<LPP>(s0);
-            s2 = group_sum<LPP>(s2);
-            cnt = group_sum<LPP>(cnt) - 1;   // without the particle itself
+            const int cnt = group_sum<LPP>(sm.n) - 1;   // without the particle itself
+            // x: relative change of h to the root (the polynomial's, where it
+            // could be solved), b1: the polynomial's derivative there
+            double x = 0.0, b1 = 0.0, edge = 0.0;
+            bool poly = false;
+            if constexpr (F64) {
+                const double sc = equal_m ? mu : 1.0;
+                const double f3 = K == SPH_KERNEL_QUINTIC ? 1.0 : 3.0;
+                const double D0 = sc * group_sum<LPP>(sm.d0);
+                const double D1 = sc * (f3 * group_sum<LPP>(sm.d1));
+                const double D2 = sc * (f3 * group_sum<LPP>(sm.d2));
+                double D3 = group_sum<LPP>(sm.wn);
+                if constexpr (K != SPH_KERNEL_QUINTIC) {
+                    const int n1 = group_sum<LPP>(sm.n1);
+                    if (equal_m) D3 = (double)(2 * (cnt + 1) - n1);
+                }
+                D3 *= sc;
+                edge = group_min<LPP>(sm.edge);
+                constexpr double N = Sums<K>::N;
+                s0 = D0;
+                s2 = N * D0 - D1;
+                if (tight) {
+                    // (1 + x)^N eta^3 m / sigma against D0 + x D1 + ..., through x^3
+                    const double kt = A.eta3 * mi / SIG;
+                    const double e0 = D0 - kt, e1 = D1 - N * kt;
+                    const double e2 = D2 - (N * (N - 1.0) / 2.0) * kt;
+                    const double e3 = D3 - (N * (N - 1.0) * (N - 2.0) / 6.0) * kt;
+                    double st = 0.0;
+                    for (int k = 0; k < 8; k++) {
+                        const double f = ((e3 * x + e2) * x + e1) * x + e0;
+                        const double g1 = (3.0 * e3 * x + 2.0 * e2) * x + e1;
+                        st = f / g1;
+                        x -= st;
+                        // (a lane whose solve runs away ends as not solved)
+                        if (__ballot(!conv && fabs(st) > 1e-16 + 1e-15 * fabs(x) && fabs(x) < 1.0) == 0ull)
+                            break;
+                    }
+                    poly = fabs(x) < 0.5 && fabs(st) <= 1e-15 + 1e-12 * fabs(x);
+                    b1 = (3.0 * D3 * x + 2.0 * D2) * x + D1;
+                }
+            } else {
+                s0 = group_sum<LPP>(s0);
+                s2 = group_sum<LPP>(s2);
+            }
             if (!conv && q == 0) evals_leaf += cnt;
             if (!conv) {
                 // the root of g(h) = h^3 rho(h) - eta^3 m = sigma sum m f - eta^3 m
-                // (non-decreasing in h) is the h of the h-rho relation.  Newton runs
-                // on the equivalent F(h) = h - eta (m / rho(h))^(1/3), which is
-                // exactly linear where rho does not vary over the kernel and so
-                // converges in fewer steps than Newton on the cubic g; F has the
-                // sign of g, and F'(h) = 1 - (h*/h)(1 - Omega) with h* = h - F
+                // (non-decreasing in h) is the h of the h-rho relation
                 const double g = SIG * s0 - A.eta3 * mi;
-                const double hs = h * cbrt(A.eta3 * mi / (SIG * s0));
                 const double om = -s2 / (3.0 * s0);
-                const double fp = 1.0 - (hs * hinv) * (1.0 - om);
-                if constexpr (NR_LDS) {
-                    *nr_h = h;
-                    *nr_rho = SIG * s0 * hinv * hinv * hinv;
-                    *nr_om = om;
+                double step, fp = 1.0;
+                if (poly) {
+                    step = -h * x;
                 } else {
-                    h_out = h;
-                    rho_out = SIG * s0 * hinv * hinv * hinv;
-                    om_out = om;
+                    // Newton on the equivalent F(h) = h - eta (m / rho(h))^(1/3),
+                    // which is exactly linear where rho does not vary over the
+                    // kernel and so converges in fewer steps than Newton on the
+                    // cubic g; F has the sign of g, and F'(h) = 1 - (h*/h)(1 -
+                    // Omega) with h* = h - F
+                    const double hs = h * cbrt(A.eta3 * mi / (SIG * s0));
+                    fp = 1.0 - (hs * hinv) * (1.0 - om);
+                    step = fp > 0.0 ? (h - hs) / fp : INFINITY;
                 }
+                h_out = h;
+                rho_out = SIG * s0 * hinv * hinv * hinv;
+                om_out = om;
                 n_out = cnt;
-                // the Newton step decides convergence before any safeguard: h and rho
+                // the step decides convergence before any safeguard: h and rho
                 // are final once the step would change h by at most h_rtol h and rho
                 // (d ln rho / d ln h = 3 (Omega - 1)) by at most h_rtol rho, down to
                 // a zero step at the root
-                const double step = fp > 0.0 ? (h - hs) / fp : INFINITY;
                 const double sens = fmax(1.0, 3.0 * fabs(om - 1.0));
                 if (g == 0.0 || fabs(step) * sens <= A.h_rtol * h) {
                     conv = true;
                 } else {
-                    double lo = NR_LDS ? *nr_lo : lo_b, hi = NR_LDS ? *nr_hi : hi_b;
-                    if (g < 0.0) lo = fmax(lo, h); else hi = fmin(hi, h);
+                    if (g < 0.0) lo_b = fmax(lo_b, h); else hi_b = fmin(hi_b, h);
                     double hn = fp > 0.0 ? h - step : (g < 0.0 ? 2.0 * h : 0.5 * h);
                     hn = fmin(fmax(hn, 0.5 * h), 2.0 * h);
                     // outside the bracket of known signs: bisect it
-                    if (!(hn > lo && hn < hi)) hn = hi < INFINITY ? 0.5 * (lo + hi) : 2.0 * h;
-                    if (!(hn == hn)) conv = true;
-                    else h = hn;
-                    if constexpr (NR_LDS) {
-                        *nr_lo = lo;
-                        *nr_hi = hi;
+                    const bool inside = hn > lo_b && hn < hi_b;
+                    if (!inside) hn = hi_b < INFINITY ? 0.5 * (lo_b + hi_b) : 2.0 * h;
+                    // the polynomial is the kernel sum at hn itself if no
+                    // neighbour crosses a knot on the way (the 1e-13 covers the
+                    // rounding of q) and the list holds every neighbour there:
+                    // the solve is done without another pass
+                    const bool exact = poly && inside && cached && hn <= Rc &&
+                                       edge > RK * fabs(x) * (1.0 + 1e-9) + 1e-13 &&
+                                       (K != SPH_KERNEL_QUINTIC || fabs(x) <= 1e-5);
+                    if (!(hn == hn)) {
+                        conv = true;
+                    } else if (exact) {
+                        conv = true;
+                        constexpr double N = Sums<K>::N;
+                        const double kt = A.eta3 * mi / SIG, y = 1.0 + x;
+                        const double yn = K == SPH_KERNEL_QUINTIC ? (y * y) * (y * y) : y * y;
+                        h_out = hn;
+                        rho_out = A.eta3 * mi / (hn * hn * hn);
+                        om_out = -(N * kt - b1 / yn) / (3.0 * kt);
                     } else {
-                        lo_b = lo;
-                        hi_b = hi;
+                        h = hn;
                     }
                 }
             }
@@ -1224,11 +1423,6 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
             }
         }
         bool bad = false, slow = false, wide = false;
-        if constexpr (NR_LDS) {
-            h_out = *nr_h;
-            rho_out = *nr_rho;
-            om_out = *nr_om;
-        }
         if (active && q == 0) {
             A.h[i] = h_out;
             A.rho[i] = rho_out;
@@ -1255,6 +1449,12 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
 // Force loop
 // ---------------------------------------------------------------------------
 
+// Hits held per home particle between two flushes (16-bit ids, 4 KB of LDS:
+// with the walk buffer and the tables a wave stays within 10 KB up to G = 16).
+// At least the 64 hits that one row can give.
+template <int G>
+constexpr int force_list() { return 2048 / G; }
+
 // AC: the launch carries artificial conductivity (some set of the batch has
 // alpha_AC > 0; a set with alpha_AC = 0 then adds exact zeros).
 // SW: the launch carries per-particle alpha or the velocity divergence and
@@ -1264,10 +1464,16 @@ template <int G, int PREC, bool AC, bool SW, int K>
 __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(Batch<ForceArgs> B)
 {
     constexpr int LPP = kWave / G;
-    constexpr int NL = kSlots / G;
+    constexpr int CAP = force_list<G>();
+    constexpr bool F64 = PREC == SPH_FP64;
     __shared__ WalkBuf wb;
     __shared__ TreeInfo T;
-    __shared__ Stage<G, PREC> S;
+    __shared__ LeafTab<PREC> tab;
+    __shared__ union {
+        uint16_t id[G * CAP];          // hits of each home particle: slots of the open group
+        uint32_t walk_spare[kFront];   // lent to walks, which run between groups
+    } S;
+    __shared__ HomeTab<G, PREC> H;
     __shared__ uint32_t pre[kMaxBatch + 1];
     batch_prefix(B, pre);
     const int lane = threadIdx.x;
@@ -1312,10 +1518,11 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
         const int64_t ii = p < nhome ? i : first;
         const double hx = as_global(F.x)[ii], hy = as_global(F.y)[ii], hz = as_global(F.z)[ii];
         float hfx = 0.f, hfy = 0.f, hfz = 0.f;
-        if (PREC == SPH_FP32_PAIR) {
-            hfx = as_global(F.fx)[ii];
-            hfy = as_global(F.fy)[ii];
-            hfz = as_global(F.fz)[ii];
+        if constexpr (!F64) {
+            const auto *o = as_global((const float *)(F.off + ii));
+            hfx = o[0];
+            hfy = o[1];
+            hfz = o[2];
         }
         const ForceRec ri = load_global(F.rec + ii);
         const double vxi = ri.vx, vyi = ri.vy, vzi = ri.vz;
@@ -1332,23 +1539,20 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
         const float Aif = (float)Ai, cif = (float)ci, rhoif = (float)rhoi;
         const Node home = load_const(F.nodes + leaf);
         if (q == 0) {
-            S.hx[p] = hx;
-            S.hy[p] = hy;
-            S.hz[p] = hz;
-            S.hfx[p] = hfx;
-            S.hfy[p] = hfy;
-            S.hfz[p] = hfz;
-            S.thr[p] = active ? hi2x4 : -1.0;
-            S.mask[p][0] = 0;
-            S.mask[p][1] = 0;
+            H.d[p] = HomeRow{hx, hy, hz, active ? hi2x4 : -1.0};
+            if constexpr (!F64) H.f[p] = HomeRowF{hfx, hfy, hfz, active ? (float)hi2x4 : -1.f};
         }
+        const uint64_t lanes_in = __ballot(active);
+        uint64_t takes_part = 0;   // bit p: home particle p
+#pragma unroll
+        for (int k = 0; k < G; k++) takes_part |= ((lanes_in >> (k * LPP)) & 1ull) << k;
         // symmetric criterion: a node can hold force neighbours of the home leaf
         // if its box is closer than 2 max(h over home, h over node)
         auto test = [&bx, &home](const Node &nd) {
             const double R = RK * fmax(home.hmax, nd.hmax) * (1.0 + 1e-10);
             return box_gap2(home.lo, home.hi, nd, bx) < R * R;
         };
-        // walk and staging at raised priority, as in the density loop
+        // walk and candidate loads at raised priority, as in the density loop
         __builtin_amdgcn_s_setprio(2);
         const WalkResult wr = walk(T, F.nodes, test, wb, S.walk_spare);
         __builtin_amdgcn_s_setprio(0);
@@ -1359,188 +1563,211 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
         int cnt = 0, selfs = 0;
         int lmx_l = 0;                                       // block time-steps
         const int lev_i = F.lev ? as_global(F.lev)[ii] : 0;
-        auto group = [&](const uint32_t *leaves, int ng) {
-            __builtin_amdgcn_s_setprio(2);
-            stage_group<G, PREC, K, true>(S, leaves, ng, F.lstart, F.nodes, home, bx, -1.0, F.x, F.y, F.z,
-                                       F.h, F.fx, F.fy, F.fz);
-            __builtin_amdgcn_s_setprio(0);
-            group_tests<G, PREC>(
-                S, ng,
-                [&](int pp, int k) {
-                    const double thr = S.thr[pp];
-                    const double hk = RK * S.hmax[k];
-                    return thr >= 0.0 && box_dist2(S, pp, k) <= fmax(thr, hk * hk) * box_slack<PREC>();
-                },
-                [&](int pp, int sl, auto ppc) {
-                    double dx, dy, dz, r2;
-                    separation<G, PREC, decltype(ppc)::value>(S, bx, S.hx[pp], S.hy[pp], S.hz[pp],
-                                                              S.hfx[pp], S.hfy[pp], S.hfz[pp], sl, dx,
-                                                              dy, dz, r2);
-                    // the particle itself passes too; the flush drops it
-                    const double thr = S.thr[pp];
-                    const double hj2x4 = S.c.w[sl];
-                    if (PREC == SPH_FP64) return r2 < thr || r2 < hj2x4;
-                    return (float)r2 < (float)thr || (float)r2 < (float)hj2x4;
-                },
-                F.count_tests != 0, boxes, tests);
-            const uint64_t w0 = S.mask[p][0], w1 = S.mask[p][1];
-            // the record of a neighbour that the pair terms read (one line)
-            // FP32-pair: the neighbours' single-precision records (32 bytes)
-            using JData = std::conditional_t<PREC == SPH_FP64, ForceRec, ForceRec32>;
-            auto load_j = [&](int sl) {
-                if constexpr (PREC == SPH_FP64) return load_global(F.rec + S.j[sl]);
-                else return load_global(F.rec32 + S.j[sl]);
-            };
-            auto pair_terms = [&](int sl, const JData &d) {
-                double dx, dy, dz, r2;
-                // FP64: home position from LDS, as in the density flush
-                separation<G, PREC>(S, bx, PREC == SPH_FP64 ? S.hx[p] : hx,
-                                    PREC == SPH_FP64 ? S.hy[p] : hy, PREC == SPH_FP64 ? S.hz[p] : hz,
-                                    hfx, hfy, hfz, sl, dx, dy, dz, r2);
-                const double cj = d.c;
-                if (r2 == 0.0) {
-                    vs_max = fmax(vs_max, PREC == SPH_FP64 ? ci + cj : (double)(cif + (float)cj));
-                    return;
+        // FP32-pair: the neighbours' single-precision records (32 bytes)
+        using JData = std::conditional_t<F64, ForceRec, ForceRec32>;
+        using Real = std::conditional_t<F64, double, float>;
+        auto pair_terms = [&](uint32_t j, const JData &d, Real sdx, Real sdy, Real sdz, Real sr2) {
+            const double dx = sdx, dy = sdy, dz = sdz, r2 = sr2;
+            const double cj = d.c;
+            if (r2 == 0.0) {
+                vs_max = fmax(vs_max, PREC == SPH_FP64 ? ci + cj : (double)(cif + (float)cj));
+                return;
+            }
+            // the pair's viscosity strength: (alpha_i + alpha_j)/2 with
+            // per-particle values, alpha_AV otherwise
+            const double aij = (SW && alpha_p) ? 0.5 * (alpha_i + as_global(alpha_p)[j])
+                                               : alpha;
+            if constexpr (PREC == SPH_FP64) {
+                const double rinv = rsqrt_nr(r2);
+                const double rr = r2 * rinv;
+                const double ex = dx * rinv, ey = dy * rinv, ez = dz * rinv;
+                const double hinvj = d.hinv;
+                const double gfj = SIG * (hinvj * hinvj) * (hinvj * hinvj);
+                double fi, dfi, fj, dfj;
+                kern<K>(rr * hinvi, fi, dfi);
+                kern<K>(rr * hinvj, fj, dfj);
+                double gi, gj, gsum;
+                sym_grads(gfi, dfi, gfj, dfj, gi, gj, gsum);
+                const double w = ((vxi - d.vx) * ex + (vyi - d.vy) * ey) + (vzi - d.vz) * ez;
+                const double mj = d.m;
+                double cvec = -mj * sym_dot2(Ai, gi, d.A, gj);
+                double cdu = Ai * mj * gi * w;
+                const double wneg = fmin(w, 0.0);
+                const double vs = (ci + cj) - beta * wneg;
+                vs_max = fmax(vs_max, vs);
+                const double rbinv = rcp_nr(0.5 * (rhoi + d.rho));
+                const double visc = (mj * rbinv) * aij * vs * wneg;
+                const double gbar = 0.5 * gsum;
+                cvec += visc * gbar;
+                cdu -= visc * 0.5 * wneg * gbar;
+                if constexpr (AC) {
+                    // u and P of both particles from their sound speeds
+                    const double c2i = ci * ci, c2j = cj * cj;
+                    const double vc = ac_price
+                        ? sqrt(fabs(rhoi * c2i - d.rho * c2j) * inv_gamma * rbinv)
+                        : fabs(w);
+                    cdu += (mj * rbinv) * alpha_ac * vc * ((c2i - c2j) * u_per_c2) * gbar;
                 }
-                // the pair's viscosity strength: (alpha_i + alpha_j)/2 with
-                // per-particle values, alpha_AV otherwise
-                const double aij = (SW && alpha_p) ? 0.5 * (alpha_i + as_global(alpha_p)[S.j[sl]])
-                                                   : alpha;
-                if constexpr (PREC == SPH_FP64) {
-                    const double rinv = rsqrt_nr(r2);
-                    const double rr = r2 * rinv;
-                    const double ex = dx * rinv, ey = dy * rinv, ez = dz * rinv;
-                    const double hinvj = d.hinv;
-                    const double gfj = SIG * (hinvj * hinvj) * (hinvj * hinvj);
-                    double fi, dfi, fj, dfj;
-                    kern<K>(rr * hinvi, fi, dfi);
-                    kern<K>(rr * hinvj, fj, dfj);
-                    double gi, gj, gsum;
-                    sym_grads(gfi, dfi, gfj, dfj, gi, gj, gsum);
-                    const double w = ((vxi - d.vx) * ex + (vyi - d.vy) * ey) + (vzi - d.vz) * ez;
-                    const double mj = d.m;
-                    double cvec = -mj * sym_dot2(Ai, gi, d.A, gj);
-                    double cdu = Ai * mj * gi * w;
-                    const double wneg = fmin(w, 0.0);
-                    const double vs = (ci + cj) - beta * wneg;
-                    vs_max = fmax(vs_max, vs);
-                    const double rbinv = rcp_nr(0.5 * (rhoi + d.rho));
-                    const double visc = (mj * rbinv) * aij * vs * wneg;
-                    const double gbar = 0.5 * gsum;
-                    cvec += visc * gbar;
-                    cdu -= visc * 0.5 * wneg * gbar;
-                    if constexpr (AC) {
-                        // u and P of both particles from their sound speeds
-                        const double c2i = ci * ci, c2j = cj * cj;
-                        const double vc = ac_price
-                            ? sqrt(fabs(rhoi * c2i - d.rho * c2j) * inv_gamma * rbinv)
-                            : fabs(w);
-                        cdu += (mj * rbinv) * alpha_ac * vc * ((c2i - c2j) * u_per_c2) * gbar;
-                    }
-                    axi += cvec * ex;
-                    ayi += cvec * ey;
-                    azi += cvec * ez;
-                    dui += cdu;
-                    if constexpr (SW) {
-                        // v_ij . G_i = w gi and v_ij x G_i = gi (v_ij x rhat)
-                        const double vxij = vxi - d.vx, vyij = vyi - d.vy, vzij = vzi - d.vz;
-                        dvs += mj * w * gi;
-                        cxs += mj * gi * (vyij * ez - vzij * ey);
-                        cys += mj * gi * (vzij * ex - vxij * ez);
-                        czs += mj * gi * (vxij * ey - vyij * ex);
-                    }
-                } else {
-                    const float fdx = (float)dx, fdy = (float)dy, fdz = (float)dz;
-                    // hardware reciprocal square root and reciprocal (1 ulp each),
-                    // functions of symmetric operands, so (j, i) sees the same values
-                    const float rinv = __builtin_amdgcn_rsqf((float)r2);
-                    const float rr = (float)r2 * rinv;
-                    const float ex = fdx * rinv, ey = fdy * rinv, ez = fdz * rinv;
-                    const float hinvj = d.hinv;
-                    // own and other kernel factors formed by the same float
-                    // expression, so the (j, i) pair sees exactly the values of
-                    // the (i, j) pair
-                    const float gfjf = (float)SIG * (hinvj * hinvj) * (hinvj * hinvj);
-                    float fi, dfi, fj, dfj;
-                    kern<K>(rr * hinvif, fi, dfi);
-                    kern<K>(rr * hinvj, fj, dfj);
-                    float gi, gj, gsum;
-                    sym_grads(gfif, dfi, gfjf, dfj, gi, gj, gsum);
-                    const float w = ((vxif - d.vx) * ex + (vyif - d.vy) * ey) + (vzif - d.vz) * ez;
-                    const float mj = d.m;
-                    const float cjf = d.c;
-                    float cvec = -mj * sym_dot2(Aif, gi, d.A, gj);
-                    float cdu = Aif * mj * gi * w;
-                    const float wneg = fminf(w, 0.0f);
-                    const float vs = (cif + cjf) - (float)beta * wneg;
-                    vs_max = fmax(vs_max, (double)vs);
-                    const float rbinv = __builtin_amdgcn_rcpf(0.5f * (rhoif + d.rho));
-                    const float visc = (mj * rbinv) * (float)aij * vs * wneg;
-                    const float gbar = 0.5f * gsum;
-                    cvec += visc * gbar;
-                    cdu -= visc * 0.5f * wneg * gbar;
-                    if constexpr (AC) {
-                        // differences of u and P formed in double precision from
-                        // the single-precision values both sides of the pair see
-                        const double c2i = (double)cif * cif, c2j = (double)cjf * cjf;
-                        const float du_ij = (float)((c2i - c2j) * u_per_c2);
-                        const float vc =
-                            ac_price
-                                ? sqrtf((float)(fabs((double)rhoif * c2i - (double)d.rho * c2j) *
-                                                inv_gamma) * rbinv)
-                                : fabsf(w);
-                        cdu += (mj * rbinv) * (float)alpha_ac * vc * du_ij * gbar;
-                    }
-                    axi += (double)(cvec * ex);
-                    ayi += (double)(cvec * ey);
-                    azi += (double)(cvec * ez);
-                    dui += (double)cdu;
-                    if constexpr (SW) {
-                        const float vxij = vxif - d.vx, vyij = vyif - d.vy, vzij = vzif - d.vz;
-                        dvs += (double)(mj * w * gi);
-                        cxs += (double)(mj * gi * (vyij * ez - vzij * ey));
-                        cys += (double)(mj * gi * (vzij * ex - vxij * ez));
-                        czs += (double)(mj * gi * (vxij * ey - vyij * ex));
-                    }
+                axi += cvec * ex;
+                ayi += cvec * ey;
+                azi += cvec * ez;
+                dui += cdu;
+                if constexpr (SW) {
+                    // v_ij . G_i = w gi and v_ij x G_i = gi (v_ij x rhat)
+                    const double vxij = vxi - d.vx, vyij = vyi - d.vy, vzij = vzi - d.vz;
+                    dvs += mj * w * gi;
+                    cxs += mj * gi * (vyij * ez - vzij * ey);
+                    cys += mj * gi * (vzij * ex - vxij * ez);
+                    czs += mj * gi * (vxij * ey - vyij * ex);
                 }
-            };
-            // the particle's hits of this group (same count on all its lanes).
-            // FP32-pair: two at a time, both neighbours' records requested
-            // before either is used (measured faster; at the FP64 register
-            // budget the second record costs more than it hides)
-            // the particle itself is among the hits of its own leaf: it takes
-            // no pair terms and is not counted
-            const uint32_t self = (uint32_t)i;
-            // block time-steps: the deepest neighbour level, and inactive
-            // neighbours more than lim levels shallower marked to wake up
-            auto limiter = [&](uint32_t j) {
-                if (!F.lev) return;
-                const int lj = as_global(F.lev)[j];
-                lmx_l = lj > lmx_l ? lj : lmx_l;
-                if (lj < lev_i - F.lim && as_global(F.active)[j] == 0) atomicMax(&F.mark[j], lev_i);
-            };
-            if (PREC == SPH_FP32_PAIR) {
-                cnt += for_my_bit_pairs<LPP>(w0, w1, q, [&](int sa, int sb) {
-                    const JData da = load_j(sa);
-                    JData db = da;
-                    if (sb >= 0) db = load_j(sb);
-                    if (S.j[sa] != self) { limiter(S.j[sa]); pair_terms(sa, da); } else selfs++;
-                    if (sb >= 0) {
-                        if (S.j[sb] != self) { limiter(S.j[sb]); pair_terms(sb, db); } else selfs++;
-                    }
-                });
             } else {
-                cnt += for_my_bits<LPP>(w0, w1, q, [&](int sl, int) {
-                    if (S.j[sl] != self) { limiter(S.j[sl]); pair_terms(sl, load_j(sl)); } else selfs++;
-                });
+                const float fdx = (float)dx, fdy = (float)dy, fdz = (float)dz;
+                // hardware reciprocal square root and reciprocal (1 ulp each),
+                // functions of symmetric operands, so (j, i) sees the same values
+                const float rinv = __builtin_amdgcn_rsqf((float)r2);
+                const float rr = (float)r2 * rinv;
+                const float ex = fdx * rinv, ey = fdy * rinv, ez = fdz * rinv;
+                const float hinvj = d.hinv;
+                // own and other kernel factors formed by the same float
+                // expression, so the (j, i) pair sees exactly the values of
+                // the (i, j) pair
+                const float gfjf = (float)SIG * (hinvj * hinvj) * (hinvj * hinvj);
+                float fi, dfi, fj, dfj;
+                kern<K>(rr * hinvif, fi, dfi);
+                kern<K>(rr * hinvj, fj, dfj);
+                float gi, gj, gsum;
+                sym_grads(gfif, dfi, gfjf, dfj, gi, gj, gsum);
+                const float w = ((vxif - d.vx) * ex + (vyif - d.vy) * ey) + (vzif - d.vz) * ez;
+                const float mj = d.m;
+                const float cjf = d.c;
+                float cvec = -mj * sym_dot2(Aif, gi, d.A, gj);
+                float cdu = Aif * mj * gi * w;
+                const float wneg = fminf(w, 0.0f);
+                const float vs = (cif + cjf) - (float)beta * wneg;
+                vs_max = fmax(vs_max, (double)vs);
+                const float rbinv = __builtin_amdgcn_rcpf(0.5f * (rhoif + d.rho));
+                const float visc = (mj * rbinv) * (float)aij * vs * wneg;
+                const float gbar = 0.5f * gsum;
+                cvec += visc * gbar;
+                cdu -= visc * 0.5f * wneg * gbar;
+                if constexpr (AC) {
+                    // differences of u and P formed in double precision from
+                    // the single-precision values both sides of the pair see
+                    const double c2i = (double)cif * cif, c2j = (double)cjf * cjf;
+                    const float du_ij = (float)((c2i - c2j) * u_per_c2);
+                    const float vc =
+                        ac_price
+                            ? sqrtf((float)(fabs((double)rhoif * c2i - (double)d.rho * c2j) *
+                                            inv_gamma) * rbinv)
+                            : fabsf(w);
+                    cdu += (mj * rbinv) * (float)alpha_ac * vc * du_ij * gbar;
+                }
+                axi += (double)(cvec * ex);
+                ayi += (double)(cvec * ey);
+                azi += (double)(cvec * ez);
+                dui += (double)cdu;
+                if constexpr (SW) {
+                    const float vxij = vxif - d.vx, vyij = vyif - d.vy, vzij = vzif - d.vz;
+                    dvs += (double)(mj * w * gi);
+                    cxs += (double)(mj * gi * (vyij * ez - vzij * ey));
+                    cys += (double)(mj * gi * (vzij * ex - vxij * ez));
+                    czs += (double)(mj * gi * (vxij * ey - vyij * ex));
+                }
             }
-            if (q == 0) {
-                S.mask[p][0] = 0;
-                S.mask[p][1] = 0;
-            }
-            wave_lds_sync();
         };
-        for_each_leaf_group<NL>(T, F.nodes, wr, test, wb, group, B.stage);
+        // block time-steps: the deepest neighbour level, and inactive
+        // neighbours more than lim levels shallower marked to wake up
+        auto limiter = [&](uint32_t j) {
+            if (!F.lev) return;
+            const int lj = as_global(F.lev)[j];
+            lmx_l = lj > lmx_l ? lj : lmx_l;
+            if (lj < lev_i - F.lim && as_global(F.active)[j] == 0) atomicMax(&F.mark[j], lev_i);
+        };
+        // the hits this particle holds, its lanes sharing them round-robin.
+        // The particle itself is among the hits of its own leaf: it takes no
+        // pair terms and is not counted
+        auto flush = [&](int n, int img) {
+            const uint32_t self = (uint32_t)i;
+            for (int e = q; e < n; e += LPP) {
+                const int s = S.id[p * CAP + e];
+                const int k = s / G;
+                const uint32_t j = tab.jm[k].x + (uint32_t)(s % G);
+                Real dx, dy, dz, r2;
+                JData d;
+                if constexpr (F64) {
+                    d = load_global(F.rec + j);
+                    const auto *o = as_global((const double *)(F.pos + j));
+                    const double x = o[0], y = o[1], z = o[2];
+                    if (img == kImgNone)
+                        r2 = separation<PREC, kImgNone, double>(bx, hx, hy, hz, x, y, z, 0.0, 0.0, 0.0,
+                                                                dx, dy, dz);
+                    else if (img == kImgShift)
+                        r2 = separation<PREC, kImgShift, double>(bx, hx, hy, hz, x, y, z, tab.ox[k],
+                                                                 tab.oy[k], tab.oz[k], dx, dy, dz);
+                    else
+                        r2 = separation<PREC, kImgPair, double>(bx, hx, hy, hz, x, y, z, 0.0, 0.0, 0.0,
+                                                                dx, dy, dz);
+                } else {
+                    d = load_global(F.rec32 + j);
+                    const auto *o = as_global((const float *)(F.off + j));
+                    const float x = o[0], y = o[1], z = o[2];
+                    if (img != kImgPair)
+                        r2 = separation<PREC, kImgNone, float>(bx, hfx, hfy, hfz, x, y, z, tab.ox[k],
+                                                               tab.oy[k], tab.oz[k], dx, dy, dz);
+                    else
+                        r2 = separation<PREC, kImgPair, float>(bx, hfx, hfy, hfz, x, y, z, tab.ox[k],
+                                                               tab.oy[k], tab.oz[k], dx, dy, dz);
+                }
+                if (j != self) {
+                    limiter(j);
+                    pair_terms(j, d, dx, dy, dz, r2);
+                } else {
+                    selfs++;
+                }
+            }
+        };
+        const int depth = group_depth<G>(wr.n, B.stage > 0 ? B.stage * G / 2 : kGroup);
+        int64_t at = 0;
+        const uint32_t *leaves = nullptr;
+        for (;;) {
+            const int ng = next_group(T, F.nodes, wr, test, wb, depth, at, leaves);
+            if (ng == 0) break;
+            uint64_t lmask;
+            const int img = open_group<G, PREC, K>(leaves, ng, F.lstart, F.nodes, home, bx, -1.0, H,
+                                                   takes_part, tab, lmask);
+            if (F.count_tests) boxes += (int64_t)ng * (int)__popcll(takes_part);
+            // a candidate's own squared gather reach (R h)^2
+            auto load = [&](uint32_t j) {
+                const double hj = as_global(F.h)[j];
+                return (Real)((RK * hj) * (RK * hj));
+            };
+            // the particle itself passes too; the flush drops it
+            auto hit = [&](Real r2, Real thr, Real w) { return r2 < thr || r2 < w; };
+            auto room = [&](int have, int n) { return have + n <= CAP; };
+            auto put = [&](int pp, int e, int s, Real, Real) { S.id[pp * CAP + e] = (uint16_t)s; };
+            int held = 0;              // lane p: hits held of home particle p
+            for (;;) {
+                int full;
+                if (img == kImgNone || (img == kImgShift && !F64))
+                    full = test_rows<G, PREC, kImgNone, kRows>(tab, H, ng, bx, F.pos, F.off, lmask, held,
+                                                               F.count_tests != 0, tests, load, hit, room, put);
+                else if (img == kImgShift)
+                    full = test_rows<G, PREC, F64 ? kImgShift : kImgNone, kRows / 2>(
+                        tab, H, ng, bx, F.pos, F.off, lmask, held, F.count_tests != 0, tests, load, hit, room,
+                        put);
+                else
+                    full = test_rows<G, PREC, kImgPair, kRows / 2>(tab, H, ng, bx, F.pos, F.off, lmask, held,
+                                                                   F.count_tests != 0, tests, load, hit, room,
+                                                                   put);
+                wave_lds_sync();
+                const int n = __shfl(held, p);
+                cnt += n;
+                flush(n, img);
+                held = 0;
+                wave_lds_sync();
+                if (full < 0) break;
+            }
+        }
         axi = group_sum<LPP>(axi);
         ayi = group_sum<LPP>(ayi);
         azi = group_sum<LPP>(azi);

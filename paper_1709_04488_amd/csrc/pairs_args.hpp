@@ -28,7 +28,8 @@ struct DensArgs {
     Box box;
     const Node *nodes;
     const double *x, *y, *z, *m;
-    const float *fx, *fy, *fz;
+    const Pos4 *pos;        // FP64: positions, one record per particle
+    const Off4 *off;        // FP32-pair: offsets from the leaf centre
     double *h, *rho, *omega;
     int32_t *nngb;
     int32_t *status;
@@ -56,7 +57,8 @@ struct ForceArgs {
     const double *x, *y, *z, *h;
     const ForceRec *rec;
     const ForceRec32 *rec32;   // FP32-pair: the single-precision records
-    const float *fx, *fy, *fz;
+    const Pos4 *pos;           // FP64: positions, one record per particle
+    const Off4 *off;           // FP32-pair: offsets from the leaf centre
     double *ax, *ay, *az, *du, *vsig, *dt;
     int32_t *nforce;
     int32_t *status;

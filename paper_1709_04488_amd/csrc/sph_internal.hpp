@@ -174,8 +174,18 @@ struct alignas(32) ForceRec32 {
     float c, hinv, vx, vy, vz, m, A, rho;
 };
 
-// Arrays in sorted (Morton) order.  FP32-pair mode adds float offsets from the
-// centre of each particle's leaf.
+// A particle's position as the pair loops' candidate loads read it: FP64, or
+// in FP32-pair mode the single-precision offset from the centre of its leaf.
+// One record per particle: a row of 64 candidates takes two or one wide loads.
+struct alignas(32) Pos4 {
+    double x, y, z, pad;
+};
+struct alignas(16) Off4 {
+    float x, y, z, pad;
+};
+static_assert(sizeof(Pos4) == sizeof(ForceRec32), "they share memory");
+
+// Arrays in sorted (Morton) order.
 struct Sorted {
     double *x = nullptr, *y = nullptr, *z = nullptr;
     double *vx = nullptr, *vy = nullptr, *vz = nullptr;
@@ -200,8 +210,11 @@ struct Sorted {
     int64_t *ts = nullptr, *te = nullptr;
     double *vhx = nullptr, *vhy = nullptr, *vhz = nullptr, *uh = nullptr, *alh = nullptr;
     int32_t *act = nullptr, *lmx = nullptr, *mark = nullptr;
-    // FP32-pair mode
-    float *fx = nullptr, *fy = nullptr, *fz = nullptr;
+    // candidate positions of the pair loops, written by the tree build:
+    // FP32-pair offsets, or FP64 positions, which share the memory of the
+    // single-precision records (only FP32-pair mode has those)
+    Off4 *off = nullptr;
+    Pos4 *pos() const { return (Pos4 *)frec32; }
 };
 
 // Device clock of the block time-steps (one level-0 step = 2^lmax ticks).
@@ -255,7 +268,6 @@ struct sph_ctx {
     int64_t node_cap = 0;
     sph::TreeInfo *d_tree = nullptr;    // device-resident tree description
     uint32_t *lstart = nullptr;         // leaf -> first sorted particle, [L+1]
-    uint32_t *leaf_id = nullptr;        // sorted particle -> leaf
     uint32_t *d_work = nullptr;         // per-XCD claim counters of the pair kernels
     double *cache = nullptr;            // density-loop candidate lists, a slice per pair-kernel block
     int64_t cache_size = 0;             // its bytes (cache_bytes(G, 1) per block at leaf size G)
