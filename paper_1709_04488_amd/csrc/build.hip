@@ -507,14 +507,18 @@ __global__ void k_tree_info(int64_t n, int G, const uint32_t *__restrict__ toff,
 __device__ inline Node merge_children(const Node *__restrict__ child, int64_t c0, int64_t c1)
 {
     Node nd;
-    for (int a = 0; a < 3; a++) { nd.lo[a] = INFINITY; nd.hi[a] = -INFINITY; }
+    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
     nd.hmax = 0.0;
     nd.pad = 0.0;
     for (int64_t c = c0; c < c1; c++) {
         const Node &ch = child[c];
-        for (int a = 0; a < 3; a++) { nd.lo[a] = fmin(nd.lo[a], ch.lo[a]); nd.hi[a] = fmax(nd.hi[a], ch.hi[a]); }
+        for (int a = 0; a < 3; a++) {
+            lo[a] = fmin(lo[a], ch.c[a] - ch.e[a]);
+            hi[a] = fmax(hi[a], ch.c[a] + ch.e[a]);
+        }
         nd.hmax = fmax(nd.hmax, ch.hmax);
     }
+    set_box(nd, lo, hi);
     return nd;
 }
 
@@ -554,7 +558,7 @@ __global__ __launch_bounds__(256) void k_leaves(const TreeInfo *__restrict__ T,
         }
         if (q == 0) {
             Node nd;
-            for (int a = 0; a < 3; a++) { nd.lo[a] = lo[a]; nd.hi[a] = hi[a]; }
+            set_box(nd, lo, hi);
             nd.hmax = hm;
             nd.pad = 0.0;
             nodes[l] = nd;

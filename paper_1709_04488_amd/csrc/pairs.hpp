@@ -71,6 +71,16 @@ __device__ inline T load_global(const T *p)
     return v;
 }
 
+// The same pointer, but the compiler cannot tell: what is loaded through it
+// again is loaded again (a scalar load) instead of staying in scalar registers
+// from the first load on, which spilled them by the hundred.
+template <class T>
+__device__ inline T *reload(T *p)
+{
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
 __device__ inline void wave_lds_sync()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -252,20 +262,17 @@ __device__ inline void load_tree(const TreeInfo *__restrict__ src, TreeInfo &dst
     __syncthreads();
 }
 
-// Squared gap between box [lo, hi] and node box (0 if they overlap), with the
-// periodic images of the node when the box is periodic.
-__device__ inline double box_gap2(const double lo[3], const double hi[3], const Node &nd,
-                                  const Box &bx)
+// Squared gap between two nodes' boxes (0 if they overlap), with the periodic
+// images when the box is periodic: along an axis the nearest image of two
+// intervals is that of their centres.
+__device__ inline double box_gap2(const Node &a, const Node &b, const Box &bx)
 {
     double s = 0.0;
-    for (int a = 0; a < 3; a++) {
-        double g = fmax(fmax(nd.lo[a] - hi[a], lo[a] - nd.hi[a]), 0.0);
-        if (bx.periodic) {
-            double L = bx.len[a];
-            double g1 = fmax(fmax(nd.lo[a] + L - hi[a], lo[a] - (nd.hi[a] + L)), 0.0);
-            double g2 = fmax(fmax(nd.lo[a] - L - hi[a], lo[a] - (nd.hi[a] - L)), 0.0);
-            g = fmin(g, fmin(g1, g2));
-        }
+#pragma unroll
+    for (int k = 0; k < 3; k++) {
+        double d = fabs(a.c[k] - b.c[k]);
+        if (bx.periodic) d = fmin(d, fabs(bx.len[k] - d));
+        const double g = fmax(d - (a.e[k] + b.e[k]), 0.0);
         s += g * g;
     }
     return s;
@@ -511,9 +518,9 @@ __device__ inline Shift leaf_shift(const Node &home, const Node &cand, const Box
     Shift sh{{0.0, 0.0, 0.0}, false};
     if (!bx.periodic) return sh;
     for (int a = 0; a < 3; a++) {
-        double dc = 0.5 * (home.lo[a] + home.hi[a]) - 0.5 * (cand.lo[a] + cand.hi[a]);
+        const double dc = home.c[a] - cand.c[a];
         sh.s[a] = dc > bx.half[a] ? -bx.len[a] : (dc < -bx.half[a] ? bx.len[a] : 0.0);
-        double span = reach + 0.5 * ((home.hi[a] - home.lo[a]) + (cand.hi[a] - cand.lo[a]));
+        const double span = reach + (home.e[a] + cand.e[a]);
         if (!(span < 0.49 * bx.len[a])) sh.per_pair = true;
     }
     return sh;
@@ -564,19 +571,22 @@ struct HomeTab {
 
 // Per leaf of the group: first particle and particle count (jm), the shift
 // added to x_i - x_j (FP64), or the distance of the leaf centres with the
-// shift (FP32-pair).
-template <int PREC>
+// shift (FP32-pair).  lm: per home particle, the leaves near enough to hold a
+// pair.
+template <int G, int PREC>
 struct LeafTab {
     using T = std::conditional_t<PREC == SPH_FP64, double, float>;
     uint2 jm[kGroup];
     T ox[kGroup], oy[kGroup], oz[kGroup];
+    uint64_t lm[G];
 };
 
 // The relative slack of the box test: it must accept every combination whose
 // candidates the record test can accept (rounding of the two differently
-// formed distances; FP32-pair separations carry single-precision error).
+// formed distances; FP32-pair separations carry single-precision error).  The
+// leaf's half extents grow by this part of the reach.
 template <int PREC>
-__device__ constexpr double box_slack() { return PREC == SPH_FP64 ? 1.0 + 1e-6 : 1.0 + 1e-4; }
+__device__ constexpr double box_slack() { return PREC == SPH_FP64 ? 1e-6 : 1e-4; }
 
 // The next group of at most `depth` candidate leaves of a walk's result
 // (0: none left): a slice of the list, or after a truncated walk the passing
@@ -634,33 +644,34 @@ template <int G, int PREC, int K>
 __device__ inline int open_group(const uint32_t *leaves, int count, const uint32_t *__restrict__ lstart,
                                  const Node *__restrict__ nodes, const Node &home, const Box &bx,
                                  double hcov, const HomeTab<G, PREC> &H, uint64_t takes_part,
-                                 LeafTab<PREC> &tab, uint64_t &lmask)
+                                 LeafTab<G, PREC> &tab, uint64_t &lmask)
 {
     constexpr double RK = Kern<K>::R;
     const int lane = threadIdx.x & (kWave - 1);
-    const bool valid = lane < count;
-    double cx = 0.0, cy = 0.0, cz = 0.0, ex = 0.0, ey = 0.0, ez = 0.0, reach2 = -1.0;
+    // (a missing leaf is far away)
+    double cx = 1e150, cy = 0.0, cz = 0.0, ex = 0.0, ey = 0.0, ez = 0.0, reach2 = -1.0;
     bool per_pair = false, shifted = false;
     uint2 jm{0u, 0u};
-    if (valid) {
+    if (lane < G) tab.lm[lane] = 0;
+    if (lane < count) {
         const uint32_t c = leaves[lane];
         const uint32_t j0 = as_global(lstart)[c];
         jm.x = j0;
         jm.y = as_global(lstart)[c + 1] - j0;
         const Node cand = load_global(nodes + c);
-        const Shift sh = leaf_shift(home, cand, bx, RK * (hcov < 0.0 ? fmax(home.hmax, cand.hmax) : hcov));
+        const double reach = RK * (hcov < 0.0 ? fmax(home.hmax, cand.hmax) : hcov);
+        const Shift sh = leaf_shift(home, cand, bx, reach);
         per_pair = sh.per_pair;
         shifted = sh.s[0] != 0.0 || sh.s[1] != 0.0 || sh.s[2] != 0.0;
-        const double mx = 0.5 * (cand.lo[0] + cand.hi[0]), my = 0.5 * (cand.lo[1] + cand.hi[1]);
-        const double mz = 0.5 * (cand.lo[2] + cand.hi[2]);
-        // the box seen from the home particles, half extents rounded outwards
-        // by taking the larger side
-        ex = fmax(cand.hi[0] - mx, mx - cand.lo[0]);
-        ey = fmax(cand.hi[1] - my, my - cand.lo[1]);
-        ez = fmax(cand.hi[2] - mz, mz - cand.lo[2]);
-        cx = mx - sh.s[0];
-        cy = my - sh.s[1];
-        cz = mz - sh.s[2];
+        // the box as the home particles see it; a leaf with pair-by-pair
+        // images is near to all of them
+        cx = cand.c[0] - sh.s[0];
+        cy = cand.c[1] - sh.s[1];
+        cz = cand.c[2] - sh.s[2];
+        const double slack = per_pair ? INFINITY : box_slack<PREC>() * reach;
+        ex = cand.e[0] + slack;
+        ey = cand.e[1] + slack;
+        ez = cand.e[2] + slack;
         if (hcov < 0.0) {
             const double hk = RK * cand.hmax;
             reach2 = hk * hk;
@@ -670,14 +681,14 @@ __device__ inline int open_group(const uint32_t *leaves, int count, const uint32
             tab.oy[lane] = sh.s[1];
             tab.oz[lane] = sh.s[2];
         } else {
-            tab.ox[lane] = (float)((0.5 * (home.lo[0] + home.hi[0]) - mx) + (per_pair ? 0.0 : sh.s[0]));
-            tab.oy[lane] = (float)((0.5 * (home.lo[1] + home.hi[1]) - my) + (per_pair ? 0.0 : sh.s[1]));
-            tab.oz[lane] = (float)((0.5 * (home.lo[2] + home.hi[2]) - mz) + (per_pair ? 0.0 : sh.s[2]));
+            tab.ox[lane] = (float)((home.c[0] - cand.c[0]) + (per_pair ? 0.0 : sh.s[0]));
+            tab.oy[lane] = (float)((home.c[1] - cand.c[1]) + (per_pair ? 0.0 : sh.s[1]));
+            tab.oz[lane] = (float)((home.c[2] - cand.c[2]) + (per_pair ? 0.0 : sh.s[2]));
         }
     }
     tab.jm[lane] = jm;
     const int img = __ballot(per_pair) ? kImgPair : (__ballot(shifted) ? kImgShift : kImgNone);
-    lmask = 0;
+#pragma unroll
     for (int p = 0; p < G; p++) {
         if (!((takes_part >> p) & 1)) continue;
         const HomeRow h = H.d[p];
@@ -685,11 +696,12 @@ __device__ inline int open_group(const uint32_t *leaves, int count, const uint32
         const double dy = fmax(fabs(h.y - cy) - ey, 0.0);
         const double dz = fmax(fabs(h.z - cz) - ez, 0.0);
         const double d2 = (dx * dx + dy * dy) + dz * dz;
-        const double lim = hcov < 0.0 ? fmax(h.thr, reach2) : h.thr;
-        const uint64_t m = __ballot(valid && (per_pair || d2 <= lim * box_slack<PREC>()));
-        lmask = lane == p ? m : lmask;
+        // (every lane stores the same value)
+        tab.lm[p] = __ballot(d2 <= fmax(h.thr, reach2));
     }
     wave_lds_sync();
+    lmask = tab.lm[lane < G ? lane : 0];
+    if (lane >= G) lmask = 0;
     return img;
 }
 
@@ -699,7 +711,6 @@ struct Cand {
     using T = std::conditional_t<PREC == SPH_FP64, double, float>;
     T x, y, z;      // position, or the offset from its leaf's centre
     T ox, oy, oz;   // shift (FP64, kImgShift) or leaf-centre distance (FP32-pair)
-    bool ok;        // the slot holds a particle
 };
 
 // x_i - x_j and r^2 of one home particle and one candidate: the expression
@@ -736,34 +747,35 @@ __device__ inline T separation(const Box &bx, T hx, T hy, T hz, T x, T y, T z, T
     }
 }
 
+// Candidate of this lane in row `row` of the open group; an empty slot's is far
+// away (its tests fail).  Returns its index (a valid one in any case).
 template <int G, int PREC, int IMG>
-__device__ inline uint32_t load_cand(const LeafTab<PREC> &tab, int row, const Pos4 *__restrict__ pos,
+__device__ inline uint32_t load_cand(const LeafTab<G, PREC> &tab, int row, const Pos4 *__restrict__ pos,
                                      const Off4 *__restrict__ off, Cand<PREC> &c)
 {
+    using T = typename Cand<PREC>::T;
     const int s = row * kWave + (int)(threadIdx.x & (kWave - 1));
     const int k = s / G, slot = s % G;
     const uint2 jm = tab.jm[k];
-    c.ok = slot < (int)jm.y;
-    const uint32_t j = jm.x + (c.ok ? slot : 0);   // (a missing leaf's entry is particle 0)
+    const bool ok = slot < (int)jm.y;
+    const uint32_t j = jm.x + (ok ? slot : 0);   // (a missing leaf's entry is particle 0)
     if constexpr (PREC == SPH_FP64) {
         const auto *q = as_global((const double *)(pos + j));
         c.x = q[0];
         c.y = q[1];
         c.z = q[2];
-        if constexpr (IMG == kImgShift) {
-            c.ox = tab.ox[k];
-            c.oy = tab.oy[k];
-            c.oz = tab.oz[k];
-        }
     } else {
         const auto *q = as_global((const float *)(off + j));
         c.x = q[0];
         c.y = q[1];
         c.z = q[2];
+    }
+    if constexpr (PREC != SPH_FP64 || IMG == kImgShift) {
         c.ox = tab.ox[k];
         c.oy = tab.oy[k];
         c.oz = tab.oz[k];
     }
+    c.x = ok ? c.x : (PREC == SPH_FP64 ? (T)1e150 : (T)1e18f);
     return j;
 }
 
@@ -784,44 +796,45 @@ __device__ inline uint32_t rank_of(uint64_t m)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// The open group's candidates against the home particles.  hit(c, w, p, h, r2)
-// decides a test (w: the extra value load(r, j, ok) gave for this candidate),
-// room(p, n, have) says whether n more hits of p fit after the `have` it
-// holds, and put(p, at, c-row, slot, r2) takes a hit at place `at`.  cnt (lane
-// p) counts the hits held.  Returns the home particle whose hit list is full:
-// the caller empties that list (or all of them), sets cnt to match and calls
-// again to go on (lmask then holds what is left of the group); -1 when the
-// group is done.
-template <int G, int PREC, int IMG, int NR, class Load, class Hit, class Room, class Put>
-__device__ inline int test_rows(const LeafTab<PREC> &tab, const HomeTab<G, PREC> &H, int count,
-                                 const Box &bx, const Pos4 *__restrict__ pos,
-                                 const Off4 *__restrict__ off, uint64_t &lmask, int &cnt,
-                                 bool diag, int64_t &tests, Load load, Hit hit, Room room, Put put)
+// The open group's candidates against the home particles.  hit(r2, thr, w) is
+// the ballot of a row's test (w: the value load(j) gave for the candidate), and
+// put(at, rank, slot, r2, w) takes a hit at place at + rank of the lists (`cap`
+// >= 64 places for each home particle, one after the other).  cnt (lane p)
+// counts the hits held.  Returns the home
+// particle whose hit list is full: the caller empties that list (or all of
+// them), sets cnt to match and calls again to go on (lmask then holds what is
+// left of the group); -1 when the group is done.  Which hits a list holds when
+// it is full depends on the particle and the rows alone.
+template <int G, int PREC, int IMG, int NR, class Load, class Hit, class Put>
+__device__ inline int test_rows(const LeafTab<G, PREC> &tab, const HomeTab<G, PREC> &H, int count,
+                                const Box &bx, const Pos4 *__restrict__ pos,
+                                const Off4 *__restrict__ off, uint64_t &lmask, int &cnt, int cap,
+                                bool diag, int &tested, Load load, Hit hit, Put put)
 {
     constexpr int LPR = kWave / G;                      // leaves per row
-    constexpr uint64_t RM = (1ull << LPR) - 1;          // one row's leaves
-    constexpr uint64_t BM = NR * LPR >= 64 ? ~0ull : (1ull << (NR * LPR)) - 1;
+    constexpr uint32_t RM = (1u << LPR) - 1;            // one row's leaves
+    constexpr uint32_t BM = NR * LPR >= 32 ? ~0u : (1u << (NR * LPR)) - 1;
+    static_assert(NR * LPR <= 32, "a block's leaves fit 32 bits");
     using T = typename Cand<PREC>::T;
     const int lane = threadIdx.x & (kWave - 1);
     const int nrows = (count + LPR - 1) / LPR;
     for (int r0 = 0; r0 < nrows; r0 += NR) {
         // home particles with a near leaf among these rows
-        uint64_t todo = __ballot(lane < G && ((lmask >> (r0 * LPR)) & BM) != 0);
+        const uint32_t near = (uint32_t)(lmask >> (r0 * LPR)) & BM;
+        uint64_t todo = __ballot(near != 0);
         if (todo == 0) continue;
+        if (diag)
+            for (int r = 0; r < NR; r++)
+                tested += (int)__popcll(__ballot(((near >> (r * LPR)) & RM) != 0));
         Cand<PREC> c[NR];
-        T w[NR];
+        decltype(load(0u)) w[NR];
         __builtin_amdgcn_s_setprio(2);
 #pragma unroll
-        for (int r = 0; r < NR; r++) {
-            const uint32_t j = load_cand<G, PREC, IMG>(tab, r0 + r, pos, off, c[r]);
-            w[r] = load(j);
-        }
+        for (int r = 0; r < NR; r++) w[r] = load(load_cand<G, PREC, IMG>(tab, r0 + r, pos, off, c[r]));
         __builtin_amdgcn_s_setprio(0);
-        while (todo) {
+        do {
             const int p = (int)__builtin_ctzll(todo);
             todo &= todo - 1;
-            const uint64_t bits = readlane64(lmask, p) >> (r0 * LPR);
-            int have = __builtin_amdgcn_readlane(cnt, p);
             T hx, hy, hz, thr;
             if constexpr (PREC == SPH_FP64) {
                 const HomeRow h = H.d[p];
@@ -830,38 +843,37 @@ __device__ inline int test_rows(const LeafTab<PREC> &tab, const HomeTab<G, PREC>
                 const HomeRowF h = H.f[p];
                 hx = h.x; hy = h.y; hz = h.z; thr = h.thr;
             }
+            const uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)near, p);
+            int have = __builtin_amdgcn_readlane(cnt, p);
             int full = -1;
 #pragma unroll
             for (int r = 0; r < NR; r++) {
-                if (full < 0 && ((bits >> (r * LPR)) & RM) != 0) {
-                    T dx, dy, dz;
-                    const T r2 = separation<PREC, IMG>(bx, hx, hy, hz, c[r].x, c[r].y, c[r].z, c[r].ox,
-                                                       c[r].oy, c[r].oz, dx, dy, dz);
-                    const bool h = c[r].ok && hit(r2, thr, w[r]);
-                    const uint64_t m = __ballot(h);
-                    if (diag) tests += (int64_t)__popcll(__ballot(c[r].ok));
-                    if (m) {
-                        const int n = (int)__popcll(m);
-                        if (!room(have, n)) {
-                            full = r;
-                        } else {
-                            if (h) put(p, have + (int)rank_of(m), (r0 + r) * kWave + lane, r2, w[r]);
-                            have += n;
-                        }
-                    }
+                if (!((bits >> (r * LPR)) & RM)) continue;
+                T dx, dy, dz;
+                const T r2 = separation<PREC, IMG>(bx, hx, hy, hz, c[r].x, c[r].y, c[r].z, c[r].ox,
+                                                   c[r].oy, c[r].oz, dx, dy, dz);
+                const uint64_t m = hit(r2, thr, w[r]);
+                const int to = have + (int)__popcll(m);
+                if (to > cap) {
+                    full = r;
+                    goto filled;
                 }
+                if (__builtin_amdgcn_inverse_ballot_w64(m))
+                    put((uint32_t)(p * cap + have), rank_of(m), (r0 + r) * kWave + lane, r2, w[r]);
+                have = to;
             }
+        filled:
             cnt = lane == p ? have : cnt;
             if (full >= 0) {
                 // what is done leaves the masks: these rows of the particles
                 // before p, and of p the rows before the full one
-                const uint64_t mine = lane < p ? BM : (lane == p ? (1ull << (full * LPR)) - 1 : 0ull);
-                lmask &= ~(mine << (r0 * LPR));
+                const uint32_t mine = lane < p ? BM : (lane == p ? (1u << (full * LPR)) - 1u : 0u);
+                lmask &= ~((uint64_t)mine << (r0 * LPR));
                 return p;
             }
-        }
+        } while (todo);
         // these rows are done for every home particle
-        lmask &= ~(BM << (r0 * LPR));
+        lmask &= ~((uint64_t)BM << (r0 * LPR));
     }
     return -1;
 }
@@ -1014,7 +1026,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
     __shared__ WalkBuf wb;
     __shared__ TreeInfo T;
     __shared__ union {
-        LeafTab<PREC> tab;
+        LeafTab<G, PREC> tab;
         uint32_t walk_spare[kFront];   // lent to walks, which run between sweeps
     } S;
     __shared__ HomeTab<G, PREC> H;
@@ -1032,29 +1044,19 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
     double *const cslice = B.cache + (size_t)blockIdx.x * (2 * KP * G);
     ListR2 *const cr2 = reinterpret_cast<ListR2 *>(cslice);
     double *const cm = cslice + KP * G;
-    int64_t evals = 0, walks = 0, visits = 0, overflows = 0, nr_total = 0, tests = 0, boxes = 0;
-    int64_t list_over = 0;
-    int iter_max = 0;
+    // the request's counters, lane k for counts[k] (no scalar registers)
+    int64_t tally = 0;
+    auto count_up = [&](int k, int v) { tally += lane == k ? v : 0; };
     int cur = -1;
     const __attribute__((address_space(4))) DensArgs *Ap = nullptr;
-    // per-request diagnostics, flushed when the wave moves to another request
+    // flushed when the wave moves to another request
     auto flush_counts = [&]() {
-        if (lane == 0 && cur >= 0) {
-            auto add = [&](int k, int64_t v) {
-                if (v) atomicAdd((unsigned long long *)&Ap->counts[k], (unsigned long long)v);
-            };
-            add(kCntDensEvals, evals);
-            atomicMax((unsigned long long *)&Ap->counts[kCntNrMax], (unsigned long long)iter_max);
-            add(kCntDensOverflows, overflows);
-            add(kCntDensVisits, visits);
-            add(kCntDensWalks, walks);
-            add(kCntNrTotal, nr_total);
-            add(kCntDensTests, tests);
-            add(kCntDensBoxes, boxes);
-            add(kCntDensListOverflows, list_over);
+        if (cur >= 0 && tally != 0) {
+            unsigned long long *to = (unsigned long long *)&Ap->counts[lane];
+            if (lane == kCntNrMax) atomicMax(to, (unsigned long long)tally);
+            else atomicAdd(to, (unsigned long long)tally);
         }
-        evals = walks = visits = overflows = nr_total = tests = boxes = list_over = 0;
-        iter_max = 0;
+        tally = 0;
     };
     for_each_home_leaf(pre[B.nreq], B.work, B.claim, [&](int64_t gleaf) {
         // the request and its argument block are wave-uniform (scalar registers)
@@ -1069,7 +1071,6 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
         const int64_t li = gleaf - (int64_t)__builtin_amdgcn_readfirstlane(pre[r]);
         const int64_t leaf = A.leaf_list ? (int64_t)as_const(A.leaf_list)[li] : li;
         if (A.leaf_act && as_const(A.leaf_act)[leaf] == 0) return;   // no active particle
-        const Box bx = load_const(&B.req[r]->box);
         const int64_t first = as_const(A.lstart)[leaf];
         const int nhome = (int)(as_const(A.lstart)[leaf + 1] - first);
         const int64_t i = first + p;
@@ -1079,7 +1080,6 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
         const double mu = as_const(A.mrange)[0];
         const bool equal_m = mu == as_const(A.mrange)[1];
         const bool tight = F64 && A.h_rtol <= kTightTol;
-        const Node home = load_const(A.nodes + leaf);
         double h = as_global((const double *)A.h)[ii];
         double lo_b = 0.0, hi_b = INFINITY;
         bool conv = !active;
@@ -1098,20 +1098,26 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
         }
 
         double hcov = A.walk_margin * wave_max(active ? h : 0.0);
-        auto make_test = [&](double hc) {
-            const double R = RK * hc * (1.0 + 1e-10);
+        auto near_home = [&](const Node &home, const Box &bx) {
+            const double R = RK * hcov * (1.0 + 1e-10);
             const double R2 = R * R;
-            return [&bx, &home, R2](const Node &nd) { return box_gap2(home.lo, home.hi, nd, bx) < R2; };
+            return [&bx, &home, R2](const Node &nd) { return box_gap2(home, nd, bx) < R2; };
+        };
+        auto walk_home = [&]() {
+            const Node home = load_const(reload(A.nodes) + leaf);
+            const Box bx = load_const(&reload(B.req[r])->box);
+            const WalkResult w = walk(T, A.nodes, near_home(home, bx), wb, S.walk_spare);
+            count_up(kCntDensWalks, 1);
+            if (w.lev) count_up(kCntDensOverflows, 1);
+            return w;
         };
         // the walk and the candidate loads are chains of dependent loads: the
         // wave issues them at raised priority, ahead of waves in their
         // arithmetic (measured: the force loop 1 % faster, the density loop
         // unchanged)
         __builtin_amdgcn_s_setprio(2);
-        WalkResult wr = walk(T, A.nodes, make_test(hcov), wb, S.walk_spare);
+        WalkResult wr = walk_home();
         __builtin_amdgcn_s_setprio(0);
-        walks++;
-        if (wr.lev) overflows++;
         int iter = 0;
         int evals_leaf = 0;   // this lane's density pairs evaluated for this leaf
         // list state of this particle: `cached` = the list holds every
@@ -1238,7 +1244,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                 double rc2 = -1.0;
                 if (!conv) {
                     Rc = fmin(kCacheGrow * h, hcov);
-                    rc2 = (RK * Rc) * (RK * Rc) * (1.0 + 1e-6);
+                    rc2 = (RK * Rc) * (RK * Rc) * (1.0 + 1e-6);   // far above rounding
                 }
                 wave_lds_sync();
                 if (q == 0) {
@@ -1256,45 +1262,50 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                 int held = 0;              // lane p: entries in the list of home particle p
                 int64_t at = 0;
                 const uint32_t *leaves = nullptr;
-                auto test = make_test(hcov);
+                const auto &Q = *reload(Ap);
+                const Node home = load_const(reload(A.nodes) + leaf);
+                const Box bx = load_const(&reload(B.req[r])->box);
+                auto test = near_home(home, bx);
                 for (;;) {
-                    const int ng = next_group(T, A.nodes, wr, test, wb, depth, at, leaves);
+                    const int ng = next_group(T, Q.nodes, wr, test, wb, depth, at, leaves);
                     if (ng == 0) break;
                     uint64_t lmask;
-                    const int img = open_group<G, PREC, K>(leaves, ng, A.lstart, A.nodes, home, bx, hcov,
+                    const int img = open_group<G, PREC, K>(leaves, ng, Q.lstart, Q.nodes, home, bx, hcov,
                                                            H, takes_part, S.tab, lmask);
-                    visits += ng;
-                    if (A.count_tests) boxes += (int64_t)ng * (int)__popcll(takes_part);
-                    auto load = [&](uint32_t j) { return equal_m ? mu : as_global(A.m)[j]; };
-                    auto hit = [&](auto r2, auto thr, double) { return r2 < thr; };
-                    auto room = [&](int have, int n) { return have + n <= KP; };
-                    auto put = [&](int pp, int e, int, auto r2, double mw) {
-                        cr2[pp * KP + e] = r2;
-                        if (!equal_m) cm[pp * KP + e] = mw;
+                    count_up(kCntDensVisits, ng);
+                    int tested = 0;
+                    const bool diag = Q.count_tests != 0;
+                    auto load = [&](uint32_t j) { return equal_m ? mu : as_global(Q.m)[j]; };
+                    auto hit = [&](auto r2, auto thr, double) { return __ballot(r2 < thr); };
+                    auto put = [&](uint32_t at, uint32_t rank, int, auto r2, double mw) {
+                        // (fixed uniform base, 32-bit lane offset)
+                        auto *to = (__attribute__((address_space(1))) char *)cr2;
+                        *(__attribute__((address_space(1))) ListR2 *)(to + (at + rank) * (uint32_t)sizeof(ListR2)) = r2;
+                        if (!equal_m) {
+                            auto *tm = (__attribute__((address_space(1))) char *)cm;
+                            *(__attribute__((address_space(1))) double *)(tm + (at + rank) * 8u) = mw;
+                        }
                     };
                     for (;;) {
                         int full;
-                        if (img == kImgNone)
-                            full = test_rows<G, PREC, kImgNone, kRows>(
-                                S.tab, H, ng, bx, A.pos, A.off, lmask, held, A.count_tests != 0, tests,
-                                load, hit, room, put);
-                        else if (img == kImgShift && F64)
-                            full = test_rows<G, PREC, kImgShift, kRows / 2>(
-                                S.tab, H, ng, bx, A.pos, A.off, lmask, held, A.count_tests != 0, tests,
-                                load, hit, room, put);
+                        if (img == kImgNone || (img == kImgShift && !F64))
+                            full = test_rows<G, PREC, kImgNone, kRows>(S.tab, H, ng, bx, Q.pos, Q.off, lmask,
+                                                                       held, KP, diag, tested, load, hit, put);
                         else if (img == kImgShift)
-                            full = test_rows<G, PREC, kImgNone, kRows>(
-                                S.tab, H, ng, bx, A.pos, A.off, lmask, held, A.count_tests != 0, tests,
-                                load, hit, room, put);
+                            full = test_rows<G, PREC, F64 ? kImgShift : kImgNone, kRows / 2>(
+                                S.tab, H, ng, bx, Q.pos, Q.off, lmask, held, KP, diag, tested, load, hit, put);
                         else
                             full = test_rows<G, PREC, kImgPair, kRows / 2>(
-                                S.tab, H, ng, bx, A.pos, A.off, lmask, held, A.count_tests != 0, tests,
-                                load, hit, room, put);
+                                S.tab, H, ng, bx, Q.pos, Q.off, lmask, held, KP, diag, tested, load, hit, put);
                         if (full < 0) break;
                         empty_list(full, __builtin_amdgcn_readlane(held, full));
                         held = lane == full ? 0 : held;
-                        list_over += (emptied >> full) & 1 ? 0 : 1;
+                        count_up(kCntDensListOverflows, (emptied >> full) & 1 ? 0 : 1);
                         emptied |= 1ull << full;
+                    }
+                    if (diag) {
+                        count_up(kCntDensBoxes, ng * (int)__popcll(takes_part));
+                        count_up(kCntDensTests, tested * kWave);
                     }
                     wave_lds_sync();   // the next group rewrites the table
                 }
@@ -1305,7 +1316,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
             }
             eval_list(conv ? 0 : count);
             // one evaluation for every particle still iterating (uniform)
-            nr_total += (int64_t)__popcll(__ballot(!conv && q == 0));
+            count_up(kCntNrTotal, (int)__popcll(__ballot(!conv && q == 0)));
             const int cnt = group_sum<LPP>(sm.n) - 1;   // without the particle itself
             // x: relative change of h to the root (the polynomial's, where it
             // could be solved), b1: the polynomial's derivative there
@@ -1416,10 +1427,8 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
             if (hmx > hcov) {
                 hcov = A.walk_margin * hmx;
                 __builtin_amdgcn_s_setprio(2);
-                wr = walk(T, A.nodes, make_test(hcov), wb, S.walk_spare);
+                wr = walk_home();
                 __builtin_amdgcn_s_setprio(0);
-                walks++;
-                if (wr.lev) overflows++;
             }
         }
         bool bad = false, slow = false, wide = false;
@@ -1430,6 +1439,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
             A.nngb[i] = n_out;
             bad = !isfinite(h_out) || !isfinite(rho_out) || !isfinite(om_out) || !(rho_out > 0.0);
             slow = !bad && !conv;
+            const auto &bx = reload(Ap)->box;
             if (bx.periodic) {
                 const double Lmin = fmin(fmin(bx.len[0], bx.len[1]), bx.len[2]);
                 wide = !(2.0 * RK * h_out < Lmin);
@@ -1438,8 +1448,8 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
         report(A.status, bad, kFlagNonFinite, 2);
         report(A.status, slow, kFlagNotConverged, 1);
         report(A.status, wide, kFlagStencil, 3);
-        iter_max = iter > iter_max ? iter : iter_max;
-        evals += wave_sum_int(evals_leaf);
+        tally = lane == kCntNrMax && iter > tally ? iter : tally;
+        count_up(kCntDensEvals, (int)wave_sum_int(evals_leaf));
         wave_lds_sync();   // the home table is rewritten for the next leaf
     });
     flush_counts();
@@ -1468,7 +1478,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
     constexpr bool F64 = PREC == SPH_FP64;
     __shared__ WalkBuf wb;
     __shared__ TreeInfo T;
-    __shared__ LeafTab<PREC> tab;
+    __shared__ LeafTab<G, PREC> tab;
     __shared__ union {
         uint16_t id[G * CAP];          // hits of each home particle: slots of the open group
         uint32_t walk_spare[kFront];   // lent to walks, which run between groups
@@ -1478,20 +1488,15 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
     batch_prefix(B, pre);
     const int lane = threadIdx.x;
     const int p = lane / LPP, q = lane % LPP;
-    int64_t pairs_total = 0, overflows = 0, tests = 0, boxes = 0;
+    // the request's counters, lane k for counts[k] (no scalar registers)
+    int64_t tally = 0;
+    auto count_up = [&](int k, int v) { tally += lane == k ? v : 0; };
     int cur = -1;
     const __attribute__((address_space(4))) ForceArgs *Fp = nullptr;
     auto flush_counts = [&]() {
-        if (lane == 0 && cur >= 0) {
-            auto add = [&](int k, int64_t v) {
-                if (v) atomicAdd((unsigned long long *)&Fp->counts[k], (unsigned long long)v);
-            };
-            add(kCntForceEvals, pairs_total);
-            add(kCntForceOverflows, overflows);
-            add(kCntForceTests, tests);
-            add(kCntForceBoxes, boxes);
-        }
-        pairs_total = overflows = tests = boxes = 0;
+        if (cur >= 0 && tally != 0)
+            atomicAdd((unsigned long long *)&Fp->counts[lane], (unsigned long long)tally);
+        tally = 0;
     };
     for_each_home_leaf(pre[B.nreq], B.work, B.claim, [&](int64_t gleaf) {
         const int r = __builtin_amdgcn_readfirstlane(find_req(pre, B.nreq, gleaf));
@@ -1550,13 +1555,13 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
         // if its box is closer than 2 max(h over home, h over node)
         auto test = [&bx, &home](const Node &nd) {
             const double R = RK * fmax(home.hmax, nd.hmax) * (1.0 + 1e-10);
-            return box_gap2(home.lo, home.hi, nd, bx) < R * R;
+            return box_gap2(home, nd, bx) < R * R;
         };
         // walk and candidate loads at raised priority, as in the density loop
         __builtin_amdgcn_s_setprio(2);
         const WalkResult wr = walk(T, F.nodes, test, wb, S.walk_spare);
         __builtin_amdgcn_s_setprio(0);
-        if (wr.lev) overflows++;
+        if (wr.lev) count_up(kCntForceOverflows, 1);
 
         double axi = 0.0, ayi = 0.0, azi = 0.0, dui = 0.0, vs_max = -INFINITY;
         double dvs = 0.0, cxs = 0.0, cys = 0.0, czs = 0.0;   // div v, curl v sums (SW)
@@ -1735,30 +1740,28 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
             uint64_t lmask;
             const int img = open_group<G, PREC, K>(leaves, ng, F.lstart, F.nodes, home, bx, -1.0, H,
                                                    takes_part, tab, lmask);
-            if (F.count_tests) boxes += (int64_t)ng * (int)__popcll(takes_part);
+            int tested = 0;
+            const bool diag = F.count_tests != 0;
             // a candidate's own squared gather reach (R h)^2
             auto load = [&](uint32_t j) {
                 const double hj = as_global(F.h)[j];
                 return (Real)((RK * hj) * (RK * hj));
             };
             // the particle itself passes too; the flush drops it
-            auto hit = [&](Real r2, Real thr, Real w) { return r2 < thr || r2 < w; };
-            auto room = [&](int have, int n) { return have + n <= CAP; };
-            auto put = [&](int pp, int e, int s, Real, Real) { S.id[pp * CAP + e] = (uint16_t)s; };
+            auto hit = [&](Real r2, Real thr, Real w) { return __ballot(r2 < thr) | __ballot(r2 < w); };
+            auto put = [&](uint32_t at, uint32_t rank, int s, Real, Real) { S.id[at + rank] = (uint16_t)s; };
             int held = 0;              // lane p: hits held of home particle p
             for (;;) {
                 int full;
                 if (img == kImgNone || (img == kImgShift && !F64))
-                    full = test_rows<G, PREC, kImgNone, kRows>(tab, H, ng, bx, F.pos, F.off, lmask, held,
-                                                               F.count_tests != 0, tests, load, hit, room, put);
+                    full = test_rows<G, PREC, kImgNone, kRows>(tab, H, ng, bx, F.pos, F.off, lmask, held, CAP,
+                                                               diag, tested, load, hit, put);
                 else if (img == kImgShift)
                     full = test_rows<G, PREC, F64 ? kImgShift : kImgNone, kRows / 2>(
-                        tab, H, ng, bx, F.pos, F.off, lmask, held, F.count_tests != 0, tests, load, hit, room,
-                        put);
+                        tab, H, ng, bx, F.pos, F.off, lmask, held, CAP, diag, tested, load, hit, put);
                 else
                     full = test_rows<G, PREC, kImgPair, kRows / 2>(tab, H, ng, bx, F.pos, F.off, lmask, held,
-                                                                   F.count_tests != 0, tests, load, hit, room,
-                                                                   put);
+                                                                   CAP, diag, tested, load, hit, put);
                 wave_lds_sync();
                 const int n = __shfl(held, p);
                 cnt += n;
@@ -1766,6 +1769,10 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
                 held = 0;
                 wave_lds_sync();
                 if (full < 0) break;
+            }
+            if (diag) {
+                count_up(kCntForceBoxes, ng * (int)__popcll(takes_part));
+                count_up(kCntForceTests, tested * kWave);
             }
         }
         axi = group_sum<LPP>(axi);
@@ -1802,7 +1809,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
                   !isfinite(vsig);
         }
         report(F.status, bad, kFlagNonFinite, 2);
-        pairs_total += wave_sum_int((q == 0 && active) ? cnt : 0);
+        count_up(kCntForceEvals, (int)wave_sum_int((q == 0 && active) ? cnt : 0));
         wave_lds_sync();   // the home table is rewritten for the next leaf
     });
     flush_counts();
@@ -1839,7 +1846,7 @@ __global__ __launch_bounds__(kWave) void k_neighbours(NgbArgs N, int pass)
         auto test = [&bx, &home, mode](const Node &nd) {
             const double hh = mode == 0 ? home.hmax : fmax(home.hmax, nd.hmax);
             const double R = RK * hh * (1.0 + 1e-10);
-            return box_gap2(home.lo, home.hi, nd, bx) < R * R;
+            return box_gap2(home, nd, bx) < R * R;
         };
         const WalkResult wr = walk(T, N.nodes, test, wb, spare);
         if (wr.lev) overflows++;
@@ -1965,7 +1972,7 @@ __global__ __launch_bounds__(kWave, 4) void k_mfv(MfvArgs M)
         const Node home = M.nodes[leaf];
         auto test = [&bx, &home](const Node &nd) {
             const double R = RK * home.hmax * (1.0 + 1e-10);
-            return box_gap2(home.lo, home.hi, nd, bx) < R * R;
+            return box_gap2(home, nd, bx) < R * R;
         };
         const WalkResult wr = walk(T, M.nodes, test, wb, spare);
         if (wr.lev) overflows++;

@@ -95,14 +95,33 @@ inline int64_t cache_bytes(int G, int kernel, int64_t blocks)
     return blocks * 2 * (int64_t)kern_list(kernel) * G * (int64_t)sizeof(double);
 }
 
-// Tree node: bounding box of the particles below it and their largest h.
-// 64 bytes, so one node is half a 128-byte cache line.
+// Tree node: bounding box of the particles below it, as centre and half
+// extents (what the distance tests take; the half extents are rounded up so
+// that the box holds its particles), and their largest h.  64 bytes, so one
+// node is half a 128-byte cache line.
 struct alignas(64) Node {
-    double lo[3];
+    double c[3];
     double hmax;
-    double hi[3];
+    double e[3];
     double pad;
 };
+
+// The node of the box [lo, hi]: half extents to the farther side, with a few
+// units in the last place of the coordinates on top.
+__device__ inline void set_box(Node &nd, const double lo[3], const double hi[3])
+{
+    for (int a = 0; a < 3; a++) {
+        nd.c[a] = 0.5 * (lo[a] + hi[a]);
+        const double e = fmax(hi[a] - nd.c[a], nd.c[a] - lo[a]);
+        nd.e[a] = e + 1e-15 * (fabs(nd.c[a]) + e);
+        // a box of nothing (no finite position): infinitely far from anything,
+        // and without effect on the box of its parent
+        if (!(hi[a] >= lo[a])) {
+            nd.c[a] = 0.0;
+            nd.e[a] = -INFINITY;
+        }
+    }
+}
 
 // Tree description, written on the device by the build (the leaf count is
 // data dependent) and read by every pair kernel.
