@@ -689,7 +689,7 @@ __global__ __launch_bounds__(1024) void k_tree_level_small(const TreeInfo *__res
 
 // Force record of particle k: A_k = P_k / (Omega_k rho_k^2),
 // c_k = sqrt(gamma P_k / rho_k), 1/h_k, v_k, m_k, rho_k with
-// P_k = (gamma - 1) rho_k u_k.
+// P_k = (gamma - 1) rho_k u_k.  Also (R h_k)^2 into the position records.
 __global__ __launch_bounds__(256) void k_force_prep(int64_t n, double gamma,
                                                     const double *__restrict__ rho,
                                                     const double *__restrict__ omega,
@@ -700,7 +700,8 @@ __global__ __launch_bounds__(256) void k_force_prep(int64_t n, double gamma,
                                                     const double *__restrict__ vy,
                                                     const double *__restrict__ vz,
                                                     ForceRec *__restrict__ rec,
-                                                    ForceRec32 *__restrict__ rec32)
+                                                    ForceRec32 *__restrict__ rec32, double support,
+                                                    Pos4 *__restrict__ pos, Off4 *__restrict__ off)
 {
     int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (k >= n) return;
@@ -716,7 +717,10 @@ __global__ __launch_bounds__(256) void k_force_prep(int64_t n, double gamma,
     f.A = P / (omega[k] * r * r);
     f.rho = r;
     rec[k] = f;
+    const double reach = support * h[k];
+    if (pos) pos[k].reach2 = reach * reach;
     if (rec32) {
+        off[k].reach2 = (float)(reach * reach);
         ForceRec32 g;
         g.c = (float)f.c;
         g.hinv = (float)f.hinv;
@@ -881,9 +885,11 @@ sph_status force_prep(sph_ctx *c, int64_t n, const double *u_sorted, const doubl
                       const double *vy, const double *vz)
 {
     if (n == 0) return SPH_OK;
+    const bool f32 = c->p.precision == SPH_FP32_PAIR;
     hipLaunchKernelGGL(k_force_prep, dim3(grid_for(n, 256)), dim3(256), 0, c->stream, n,
                        c->p.gamma, c->s.rho, c->s.omega, u_sorted, c->s.h, c->s.m, vx, vy, vz,
-                       c->s.frec, c->p.precision == SPH_FP32_PAIR ? c->s.frec32 : nullptr);
+                       c->s.frec, f32 ? c->s.frec32 : nullptr, kern_support(c->p.kernel),
+                       f32 ? nullptr : c->s.pos(), f32 ? c->s.off : nullptr);
     return hip_check(c, hipGetLastError(), "force_prep");
 }
 

@@ -47,6 +47,11 @@ __device__ inline const __attribute__((address_space(1))) T *as_global(const T *
 {
     return (const __attribute__((address_space(1))) T *)p;
 }
+template <class T>
+__device__ inline __attribute__((address_space(1))) T *as_global_out(T *p)
+{
+    return (__attribute__((address_space(1))) T *)p;
+}
 // A whole read-only record, word by word through one of those views.
 template <class T>
 __device__ inline T load_const(const T *p)
@@ -86,6 +91,14 @@ __device__ inline void wave_lds_sync()
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Lanes may then read what other lanes of the wave stored to global memory.
+__device__ inline void wave_mem_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
 }
 
 // Cross-lane moves inside a 16-lane DPP row, for butterfly reductions: the
@@ -530,32 +543,36 @@ __device__ inline Shift leaf_shift(const Node &home, const Node &cand, const Box
 // Candidate groups and the tests shared by the pair loops
 // ---------------------------------------------------------------------------
 // A wave holds the G home particles of one leaf, LPP = 64 / G lanes each when
-// it evaluates pair terms.  To find the pairs it turns round: a lane holds a
-// candidate, the home particle is the same for all lanes.
+// it evaluates pair terms.  Candidate leaves come in groups of at most 64, one
+// per lane, which set up a table in LDS (first particle, particle count,
+// periodic shift).
 //
-// Candidate leaves come in groups of at most 64, one per lane, which set up a
-// table in LDS (first particle, particle count, periodic shift) and measure,
-// for every home particle, the distance to the leaf's box: a 64-bit ballot
-// per home particle says which leaves of the group can hold neighbours of it.
-// The candidates are then loaded into registers, kRows rows of 64 slots at a
-// time (slot s = particle s % G of leaf s / G), and tested against each home
-// particle in turn, skipping rows none of whose leaves passed.  A test is a
-// handful of instructions for 64 candidates, its result a ballot in scalar
-// registers, and the hits' ranks are bit counts of that ballot: no hit masks
-// in LDS, no bit-by-bit walk over them, every lane at work.
+// The pairs are found by the matrix cores.  In coordinates from the home
+// leaf's centre, in units of the reach,
+//   r_ij^2 - T_i^2 = (x_j, y_j, z_j, |x_j|^2) . (-2x_i, -2y_i, -2z_i, 1) + |x_i|^2 - T_i^2,
+// a product of inner length 4: with one candidate per lane as four halves, a
+// 16x16x16 product takes 16 candidates against 16 home particles (its other
+// three groups of four inner indices hold the candidates of the other lanes,
+// which zeros in the second operand leave out, so a row of 64 candidates needs
+// no data movement at all), and the sign bit of each result is a hit.  A lane's
+// bits are those of one home particle; they go to LDS as that particle's list
+// of candidate slots.  The thresholds are widened by the rounding of the
+// halves, so the lists hold every pair within reach and about 1 % more; the
+// lists' readers form r^2 exactly and decide.
 //
-// What bounds it: instruction issue.  Testing (particle, leaf) combinations
-// dealt out over the lanes from LDS, with hit masks by LDS atomics and a flush
-// that popped mask bits, spent about 16,600 vector instructions per home leaf
-// on C1-like sets (2.1M particles, G = 16, 92 candidate leaves per home leaf).
+// Measured on 2.1M particles (C1, FP64, G = 16: 92 candidate leaves and 1,370
+// listed pairs per home leaf): testing each candidate against each home
+// particle near its leaf with vector instructions took about 60 % of both
+// loops' time, 4,000 vector and 4,500 scalar instructions per home leaf; this
+// takes about 1,700 vector instructions and 92 matrix instructions.
 constexpr int kGroup = kWave;       // candidate leaves per group
-constexpr int kRows = 4;            // rows of 64 candidates held in registers
 
 // How the separations of a group see the periodic box: no shift at all, one
 // shift per leaf, or the minimum image pair by pair (boxes so small that a
 // leaf's shift is ambiguous).  A pair closer than the reach has the same
-// image under the last two.
-enum : int { kImgNone = 0, kImgShift = 1, kImgPair = 2 };
+// image under the last two, and the one nearest to the home leaf's centre,
+// unless the reach and the home leaf span half the box (kImgWide).
+enum : int { kImgNone = 0, kImgShift = 1, kImgPair = 2, kImgWide = 3 };
 
 // Home particles as the tests read them (one broadcast read each): position
 // and the threshold on r^2 (< 0: takes no part); FP32-pair tests read the
@@ -569,34 +586,77 @@ struct HomeTab {
     HomeRowF f[PREC == SPH_FP32_PAIR ? G : 1];
 };
 
-// Per leaf of the group: first particle and particle count (jm), the shift
-// added to x_i - x_j (FP64), or the distance of the leaf centres with the
-// shift (FP32-pair).  lm: per home particle, the leaves near enough to hold a
-// pair.
-template <int G, int PREC>
-struct LeafTab {
-    using T = std::conditional_t<PREC == SPH_FP64, double, float>;
-    uint2 jm[kGroup];
-    T ox[kGroup], oy[kGroup], oz[kGroup];
-    uint64_t lm[G];
-};
-
-// The relative slack of the box test: it must accept every combination whose
-// candidates the record test can accept (rounding of the two differently
-// formed distances; FP32-pair separations carry single-precision error).  The
-// leaf's half extents grow by this part of the reach.
+// Per leaf of the group: first particle (j0), particle count (low 8 bits of
+// meta) and, in FP64, the shift added to x_i - x_j (two bits per axis from bit 8
+// on: 1 a box length, 2 minus that); FP32-pair: the distance of the leaf centres
+// with the shift.
 template <int PREC>
-__device__ constexpr double box_slack() { return PREC == SPH_FP64 ? 1e-6 : 1e-4; }
+struct LeafTab {
+    uint2 jm[kGroup];
+    float o[3][PREC == SPH_FP32_PAIR ? kGroup : 1];
+};
+__device__ inline double shift_of(uint32_t meta, int axis, const Box &bx)
+{
+    const uint32_t code = (meta >> (8 + 2 * axis)) & 3u;
+    return code == 0 ? 0.0 : (code == 1 ? bx.len[axis] : -bx.len[axis]);
+}
+
+__device__ inline double readlane_d(double v, int l)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// Number of set bits of a ballot below this lane.
+__device__ inline uint32_t rank_of(uint64_t m)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// Above this many candidate leaves (an ordinary home leaf has 60-110) the home
+// leaf's box is wide against its particles' reaches, and each candidate leaf is
+// also tested against every home particle.
+constexpr int kManyLeaves = 160;
+
+// Whether a leaf's box is near enough to some home particle to hold a pair of
+// it: the leaf's largest gather reach squared counts too (reach2 >= 0, forces).
+// The relative slack covers the rounding of the differently formed distances
+// (FP32-pair separations carry single-precision error).
+template <int G, int PREC>
+__device__ inline bool leaf_in_reach(const HomeTab<G, PREC> &H, const Node &nd, const Box &bx, double reach2)
+{
+    constexpr double slack = PREC == SPH_FP64 ? 1.0 + 1e-6 : 1.0 + 1e-4;
+    bool any = false;
+    // (not unrolled: the home table would be held in registers)
+#pragma unroll 1
+    for (int p = 0; p < G; p++) {
+        const HomeRow h = H.d[p];
+        const double c[3] = {h.x, h.y, h.z};
+        double d2 = 0.0;
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            double d = fabs(c[a] - nd.c[a]);
+            if (bx.periodic) d = fmin(d, fabs(bx.len[a] - d));
+            const double g = fmax(d - nd.e[a], 0.0);
+            d2 += g * g;
+        }
+        any = any || (h.thr >= 0.0 && d2 <= fmax(h.thr, reach2) * slack);
+    }
+    return any;
+}
 
 // The next group of at most `depth` candidate leaves of a walk's result
-// (0: none left): a slice of the list, or after a truncated walk the passing
-// ones of the next 64 leaves under the listed nodes (written to wb.tmp).
-template <class Test>
+// (0: none left): a slice of the list, or, where the walk was truncated or
+// (FILTER) the list is long, the leaves (under the listed nodes) that pass
+// test(node) and near(node), up to 64 of them collected in wb.tmp.
+template <bool FILTER, class Test, class Near>
 __device__ inline int next_group(const TreeInfo &T, const Node *nodes, const WalkResult &wr,
-                                 Test test, WalkBuf &wb, int depth, int64_t &pos,
+                                 Test test, Near near, WalkBuf &wb, int depth, int64_t &pos,
                                  const uint32_t *&leaves)
 {
-    if (wr.lev == 0) {
+    if (wr.lev == 0 && (!FILTER || wr.n <= kManyLeaves)) {
         const int left = wr.n - (int)pos;
         if (left <= 0) return 0;
         leaves = wr.list + pos;
@@ -607,111 +667,111 @@ __device__ inline int next_group(const TreeInfo &T, const Node *nodes, const Wal
     const int lane = threadIdx.x & (kWave - 1);
     const int sh = 3 * wr.lev;
     const int64_t L = T.cnt[0], total = (int64_t)wr.n << sh;
+    int have = 0;
+    wave_lds_sync();   // the last group's readers of wb.tmp
     while (pos < total) {
         const int64_t t = pos + lane;
         const int64_t c = t < total ? ((int64_t)wr.list[t >> sh] << sh) + (t & ((1ll << sh) - 1)) : L;
-        const bool pass = c < L && test(load_global(nodes + c));
-        const uint64_t mask = __ballot(pass);
-        pos += kWave;
-        if (mask) {
-            wave_lds_sync();   // the last group's readers of wb.tmp
-            if (pass) wb.tmp[__popcll(mask & __lanemask_lt())] = (uint32_t)c;
-            wave_lds_sync();
-            leaves = wb.tmp;
-            return (int)__popcll(mask);
+        bool pass = false;
+        if (c < L) {
+            const Node nd = load_global(nodes + c);
+            pass = (wr.lev == 0 || test(nd)) && (!FILTER || near(nd));
         }
+        const uint64_t mask = __ballot(pass);
+        const int n = (int)__popcll(mask);
+        if (have + n > kGroup) break;   // the next group starts with these
+        if (pass) wb.tmp[have + rank_of(mask)] = (uint32_t)c;
+        have += n;
+        pos += kWave;
     }
-    return 0;
+    wave_lds_sync();
+    leaves = wb.tmp;
+    return have;
 }
 
-// Leaves per group of a list of n: groups of equal size (whole rows), at most
-// `most`.
+// Rows of 64 candidates whose bits a word holds, candidate slots per word, and
+// the places of a home particle's list (at least a word's slots).
+template <int G>
+struct Words {
+    static constexpr int rows = G == 32 ? 1 : 2;
+    static constexpr int slots = rows * kWave;
+    static constexpr int cap = G == 32 ? 64 : 128;
+    static constexpr int tiles = (G + 15) / 16;   // of 16 home particles
+    static_assert(cap >= slots, "a list takes a word's hits");
+};
+
+// Leaves per group of a list of n: groups of equal size (whole words, so the
+// words hold the same candidates whatever the size), at most `most`.
 template <int G>
 __device__ inline int group_depth(int n, int most)
 {
-    constexpr int LPR = kWave / G;
+    constexpr int LPW = Words<G>::slots / G;
     const int groups = (n + most - 1) / most;
     const int d = groups > 0 ? (n + groups - 1) / groups : most;
-    const int r = (d + LPR - 1) / LPR * LPR;
+    const int r = (d + LPW - 1) / LPW * LPW;
     return r < most ? r : most;
 }
 
-// Set up a group (lane l: leaf leaves[l]): the table, and in `lmask` (lane p
-// for home particle p) the leaves whose box is near enough to home particle p
-// to hold a pair.  hcov < 0: symmetric force criterion (reach R max(h) over
-// both leaves).  Returns how separations see the box.
+// Set up a group (lane l: leaf leaves[l]).  hcov < 0: symmetric force criterion
+// (reach R max(h) over both leaves).  Returns how separations see the box.
+// near (when not null): per home particle that takes part (a bit of takes_part),
+// the leaves whose box is within its reach.
 template <int G, int PREC, int K>
 __device__ inline int open_group(const uint32_t *leaves, int count, const uint32_t *__restrict__ lstart,
                                  const Node *__restrict__ nodes, const Node &home, const Box &bx,
-                                 double hcov, const HomeTab<G, PREC> &H, uint64_t takes_part,
-                                 LeafTab<G, PREC> &tab, uint64_t &lmask)
+                                 double hcov, LeafTab<PREC> &tab, const HomeTab<G, PREC> &H,
+                                 uint64_t takes_part, uint64_t *near)
 {
     constexpr double RK = Kern<K>::R;
     const int lane = threadIdx.x & (kWave - 1);
-    // (a missing leaf is far away)
-    double cx = 1e150, cy = 0.0, cz = 0.0, ex = 0.0, ey = 0.0, ez = 0.0, reach2 = -1.0;
-    bool per_pair = false, shifted = false;
+    bool per_pair = false, shifted = false, spans = false;
     uint2 jm{0u, 0u};
-    if (lane < G) tab.lm[lane] = 0;
+    // the leaf's box as the home particles see it (a missing one is far away,
+    // one with pair-by-pair images is near to all)
+    double c[3] = {1e150, 0.0, 0.0}, e[3] = {0.0, 0.0, 0.0};
     if (lane < count) {
-        const uint32_t c = leaves[lane];
-        const uint32_t j0 = as_global(lstart)[c];
+        const uint32_t leaf = leaves[lane];
+        const uint32_t j0 = as_global(lstart)[leaf];
         jm.x = j0;
-        jm.y = as_global(lstart)[c + 1] - j0;
-        const Node cand = load_global(nodes + c);
+        jm.y = as_global(lstart)[leaf + 1] - j0;
+        const Node cand = load_global(nodes + leaf);
         const double reach = RK * (hcov < 0.0 ? fmax(home.hmax, cand.hmax) : hcov);
         const Shift sh = leaf_shift(home, cand, bx, reach);
         per_pair = sh.per_pair;
-        shifted = sh.s[0] != 0.0 || sh.s[1] != 0.0 || sh.s[2] != 0.0;
-        // the box as the home particles see it; a leaf with pair-by-pair
-        // images is near to all of them
-        cx = cand.c[0] - sh.s[0];
-        cy = cand.c[1] - sh.s[1];
-        cz = cand.c[2] - sh.s[2];
-        const double slack = per_pair ? INFINITY : box_slack<PREC>() * reach;
-        ex = cand.e[0] + slack;
-        ey = cand.e[1] + slack;
-        ez = cand.e[2] + slack;
-        if (hcov < 0.0) {
-            const double hk = RK * cand.hmax;
-            reach2 = hk * hk;
-        }
-        if constexpr (PREC == SPH_FP64) {
-            tab.ox[lane] = sh.s[0];
-            tab.oy[lane] = sh.s[1];
-            tab.oz[lane] = sh.s[2];
-        } else {
-            tab.ox[lane] = (float)((home.c[0] - cand.c[0]) + (per_pair ? 0.0 : sh.s[0]));
-            tab.oy[lane] = (float)((home.c[1] - cand.c[1]) + (per_pair ? 0.0 : sh.s[1]));
-            tab.oz[lane] = (float)((home.c[2] - cand.c[2]) + (per_pair ? 0.0 : sh.s[2]));
+#pragma unroll
+        for (int a = 0; a < 3; a++) {
+            shifted = shifted || sh.s[a] != 0.0;
+            if (per_pair) spans = spans || !(reach + home.e[a] < 0.49 * bx.len[a]);
+            if constexpr (PREC == SPH_FP64)
+                jm.y |= (sh.s[a] > 0.0 ? 1u : (sh.s[a] < 0.0 ? 2u : 0u)) << (8 + 2 * a);
+            else
+                tab.o[a][lane] = (float)((home.c[a] - cand.c[a]) + (per_pair ? 0.0 : sh.s[a]));
+            c[a] = cand.c[a] - sh.s[a];
+            // (the slack is far above the rounding of the distances)
+            e[a] = per_pair ? INFINITY : cand.e[a] + 1e-6 * reach;
         }
     }
     tab.jm[lane] = jm;
-    const int img = __ballot(per_pair) ? kImgPair : (__ballot(shifted) ? kImgShift : kImgNone);
+    const int img = __ballot(spans) ? kImgWide
+                    : __ballot(per_pair) ? kImgPair
+                                         : (__ballot(shifted) ? kImgShift : kImgNone);
+    if (near) {
 #pragma unroll
-    for (int p = 0; p < G; p++) {
-        if (!((takes_part >> p) & 1)) continue;
-        const HomeRow h = H.d[p];
-        const double dx = fmax(fabs(h.x - cx) - ex, 0.0);
-        const double dy = fmax(fabs(h.y - cy) - ey, 0.0);
-        const double dz = fmax(fabs(h.z - cz) - ez, 0.0);
-        const double d2 = (dx * dx + dy * dy) + dz * dz;
-        // (every lane stores the same value)
-        tab.lm[p] = __ballot(d2 <= fmax(h.thr, reach2));
+        for (int p = 0; p < G; p++) {
+            uint64_t m = 0;
+            if ((takes_part >> p) & 1) {
+                const HomeRow h = H.d[p];
+                const double dx = fmax(fabs(h.x - c[0]) - e[0], 0.0);
+                const double dy = fmax(fabs(h.y - c[1]) - e[1], 0.0);
+                const double dz = fmax(fabs(h.z - c[2]) - e[2], 0.0);
+                m = __ballot((dx * dx + dy * dy) + dz * dz <= h.thr);
+            }
+            near[p] = m;   // (every lane stores the same value)
+        }
     }
     wave_lds_sync();
-    lmask = tab.lm[lane < G ? lane : 0];
-    if (lane >= G) lmask = 0;
     return img;
 }
-
-// One row of candidates in this lane's registers.
-template <int PREC>
-struct Cand {
-    using T = std::conditional_t<PREC == SPH_FP64, double, float>;
-    T x, y, z;      // position, or the offset from its leaf's centre
-    T ox, oy, oz;   // shift (FP64, kImgShift) or leaf-centre distance (FP32-pair)
-};
 
 // x_i - x_j and r^2 of one home particle and one candidate: the expression
 // every test and evaluation uses, so all see the same bits (r^2 in FP64 as
@@ -747,119 +807,110 @@ __device__ inline T separation(const Box &bx, T hx, T hy, T hz, T x, T y, T z, T
     }
 }
 
-// Candidate of this lane in row `row` of the open group; an empty slot's is far
-// away (its tests fail).  Returns its index (a valid one in any case).
-template <int G, int PREC, int IMG>
-__device__ inline uint32_t load_cand(const LeafTab<G, PREC> &tab, int row, const Pos4 *__restrict__ pos,
-                                     const Off4 *__restrict__ off, Cand<PREC> &c)
+// r^2 of home particle (hx, hy, hz) and candidate j of leaf k of the open
+// group, and the separation; w: what the candidate's position record carries
+// besides.
+template <int PREC, class T>
+__device__ inline T group_separation(const LeafTab<PREC> &tab, int img, const Box &bx, T hx, T hy, T hz,
+                                     int k, uint2 jm, uint32_t j, const Pos4 *__restrict__ pos,
+                                     const Off4 *__restrict__ off, T &dx, T &dy, T &dz, T &w)
 {
-    using T = typename Cand<PREC>::T;
-    const int s = row * kWave + (int)(threadIdx.x & (kWave - 1));
-    const int k = s / G, slot = s % G;
-    const uint2 jm = tab.jm[k];
-    const bool ok = slot < (int)jm.y;
-    const uint32_t j = jm.x + (ok ? slot : 0);   // (a missing leaf's entry is particle 0)
     if constexpr (PREC == SPH_FP64) {
-        const auto *q = as_global((const double *)(pos + j));
-        c.x = q[0];
-        c.y = q[1];
-        c.z = q[2];
+        const auto *o = as_global((const double *)(pos + j));
+        const double x = o[0], y = o[1], z = o[2];
+        w = o[3];
+        if (img == kImgNone)
+            return separation<PREC, kImgNone, T>(bx, hx, hy, hz, x, y, z, 0.0, 0.0, 0.0, dx, dy, dz);
+        if (img == kImgShift)
+            return separation<PREC, kImgShift, T>(bx, hx, hy, hz, x, y, z, shift_of(jm.y, 0, bx),
+                                                  shift_of(jm.y, 1, bx), shift_of(jm.y, 2, bx), dx, dy, dz);
+        return separation<PREC, kImgPair, T>(bx, hx, hy, hz, x, y, z, 0.0, 0.0, 0.0, dx, dy, dz);
     } else {
-        const auto *q = as_global((const float *)(off + j));
-        c.x = q[0];
-        c.y = q[1];
-        c.z = q[2];
+        const auto *o = as_global((const float *)(off + j));
+        const float x = o[0], y = o[1], z = o[2];
+        w = o[3];
+        if (img < kImgPair)
+            return separation<PREC, kImgNone, T>(bx, hx, hy, hz, x, y, z, tab.o[0][k], tab.o[1][k], tab.o[2][k],
+                                                 dx, dy, dz);
+        return separation<PREC, kImgPair, T>(bx, hx, hy, hz, x, y, z, tab.o[0][k], tab.o[1][k], tab.o[2][k], dx,
+                                             dy, dz);
     }
-    if constexpr (PREC != SPH_FP64 || IMG == kImgShift) {
-        c.ox = tab.ox[k];
-        c.oy = tab.oy[k];
-        c.oz = tab.oz[k];
-    }
-    c.x = ok ? c.x : (PREC == SPH_FP64 ? (T)1e150 : (T)1e18f);
-    return j;
 }
 
-__device__ inline uint64_t readlane64(uint64_t v, int l)
-{
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
-    return ((uint64_t)hi << 32) | lo;
-}
-__device__ inline double readlane_d(double v, int l)
-{
-    return __builtin_bit_cast(double, readlane64(__builtin_bit_cast(uint64_t, v), l));
-}
-
-// Number of set bits of a ballot below this lane.
-__device__ inline uint32_t rank_of(uint64_t m)
-{
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-
-// The open group's candidates against the home particles.  hit(r2, thr, w) is
-// the ballot of a row's test (w: the value load(j) gave for the candidate), and
-// put(at, rank, slot, r2, w) takes a hit at place at + rank of the lists (`cap`
-// >= 64 places for each home particle, one after the other).  cnt (lane p)
-// counts the hits held.  Returns the home
-// particle whose hit list is full: the caller empties that list (or all of
-// them), sets cnt to match and calls again to go on (lmask then holds what is
-// left of the group); -1 when the group is done.  Which hits a list holds when
-// it is full depends on the particle and the rows alone.
-template <int G, int PREC, int IMG, int NR, class Load, class Hit, class Put>
-__device__ inline int test_rows(const LeafTab<G, PREC> &tab, const HomeTab<G, PREC> &H, int count,
-                                const Box &bx, const Pos4 *__restrict__ pos,
-                                const Off4 *__restrict__ off, uint64_t &lmask, int &cnt, int cap,
-                                bool diag, int &tested, Load load, Hit hit, Put put)
+// The density loop in FP64 tests candidates lane by lane: a lane holds a
+// candidate of each of kRows rows of 64 slots (slot s = particle s % G of leaf
+// s / G), the home particle is the same for all lanes, a test is ten
+// instructions for 64 candidates and its result a ballot, whose bits rank the
+// hits; r^2 of a hit goes straight to the home particle's list.  Rows none of
+// whose leaves are near the home particle are skipped.  Measured against the
+// products below (which find the pairs faster, but whose readers then have to
+// fetch each candidate again): 2.1M particles, M4 2.26 against 2.30 ms, 262,144
+// with the quintic kernel 0.97 against 1.39 ms.
+//
+// near (lane p): what is left of home particle p's near leaves in the open
+// group; cnt (lane p): the hits its list holds, at most `cap`.  Returns the home
+// particle whose list is full: the caller empties it, sets cnt to match and
+// calls again to go on; -1 when the group is done.  What a list holds when it
+// is full depends on the particle and the rows alone.
+constexpr int kRows = 4;
+template <int G, int IMG, int NR, class Mass, class Put>
+__device__ inline int test_rows(const LeafTab<SPH_FP64> &tab, const HomeTab<G, SPH_FP64> &H, int count,
+                                const Box &bx, const Pos4 *__restrict__ pos, uint64_t &near, int &cnt,
+                                int cap, Mass mass, Put put)
 {
     constexpr int LPR = kWave / G;                      // leaves per row
     constexpr uint32_t RM = (1u << LPR) - 1;            // one row's leaves
     constexpr uint32_t BM = NR * LPR >= 32 ? ~0u : (1u << (NR * LPR)) - 1;
     static_assert(NR * LPR <= 32, "a block's leaves fit 32 bits");
-    using T = typename Cand<PREC>::T;
     const int lane = threadIdx.x & (kWave - 1);
     const int nrows = (count + LPR - 1) / LPR;
     for (int r0 = 0; r0 < nrows; r0 += NR) {
         // home particles with a near leaf among these rows
-        const uint32_t near = (uint32_t)(lmask >> (r0 * LPR)) & BM;
-        uint64_t todo = __ballot(near != 0);
+        const uint32_t here = (uint32_t)(near >> (r0 * LPR)) & BM;
+        uint64_t todo = __ballot(here != 0);
         if (todo == 0) continue;
-        if (diag)
-            for (int r = 0; r < NR; r++)
-                tested += (int)__popcll(__ballot(((near >> (r * LPR)) & RM) != 0));
-        Cand<PREC> c[NR];
-        decltype(load(0u)) w[NR];
+        double x[NR], y[NR], z[NR], ox[NR], oy[NR], oz[NR];
+        double w[NR];
         __builtin_amdgcn_s_setprio(2);
 #pragma unroll
-        for (int r = 0; r < NR; r++) w[r] = load(load_cand<G, PREC, IMG>(tab, r0 + r, pos, off, c[r]));
+        for (int r = 0; r < NR; r++) {
+            const int s = (r0 + r) * kWave + lane;
+            const int slot = s % G;
+            const uint2 jm = tab.jm[s / G];
+            const bool ok = slot < (int)(jm.y & 255u);
+            const uint32_t j = jm.x + (ok ? slot : 0);   // (a missing leaf's entry is particle 0)
+            const auto *q = as_global((const double *)(pos + j));
+            x[r] = ok ? q[0] : 1e150;         // an empty slot is far away
+            y[r] = q[1];
+            z[r] = q[2];
+            w[r] = mass(j);
+            if constexpr (IMG == kImgShift) {
+                ox[r] = shift_of(jm.y, 0, bx);
+                oy[r] = shift_of(jm.y, 1, bx);
+                oz[r] = shift_of(jm.y, 2, bx);
+            }
+        }
         __builtin_amdgcn_s_setprio(0);
         do {
             const int p = (int)__builtin_ctzll(todo);
             todo &= todo - 1;
-            T hx, hy, hz, thr;
-            if constexpr (PREC == SPH_FP64) {
-                const HomeRow h = H.d[p];
-                hx = h.x; hy = h.y; hz = h.z; thr = h.thr;
-            } else {
-                const HomeRowF h = H.f[p];
-                hx = h.x; hy = h.y; hz = h.z; thr = h.thr;
-            }
-            const uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)near, p);
+            const HomeRow h = H.d[p];
+            const uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)here, p);
             int have = __builtin_amdgcn_readlane(cnt, p);
             int full = -1;
 #pragma unroll
             for (int r = 0; r < NR; r++) {
                 if (!((bits >> (r * LPR)) & RM)) continue;
-                T dx, dy, dz;
-                const T r2 = separation<PREC, IMG>(bx, hx, hy, hz, c[r].x, c[r].y, c[r].z, c[r].ox,
-                                                   c[r].oy, c[r].oz, dx, dy, dz);
-                const uint64_t m = hit(r2, thr, w[r]);
+                double dx, dy, dz;
+                const double r2 = separation<SPH_FP64, IMG>(bx, h.x, h.y, h.z, x[r], y[r], z[r], ox[r], oy[r],
+                                                            oz[r], dx, dy, dz);
+                const uint64_t m = __ballot(r2 < h.thr);
                 const int to = have + (int)__popcll(m);
                 if (to > cap) {
                     full = r;
                     goto filled;
                 }
-                if (__builtin_amdgcn_inverse_ballot_w64(m))
-                    put((uint32_t)(p * cap + have), rank_of(m), (r0 + r) * kWave + lane, r2, w[r]);
+                if (__builtin_amdgcn_inverse_ballot_w64(m)) put((uint32_t)(p * cap + have) + rank_of(m), r2, w[r]);
                 have = to;
             }
         filled:
@@ -868,14 +919,279 @@ __device__ inline int test_rows(const LeafTab<G, PREC> &tab, const HomeTab<G, PR
                 // what is done leaves the masks: these rows of the particles
                 // before p, and of p the rows before the full one
                 const uint32_t mine = lane < p ? BM : (lane == p ? (1u << (full * LPR)) - 1u : 0u);
-                lmask &= ~((uint64_t)mine << (r0 * LPR));
+                near &= ~((uint64_t)mine << (r0 * LPR));
                 return p;
             }
         } while (todo);
         // these rows are done for every home particle
-        lmask &= ~((uint64_t)BM << (r0 * LPR));
+        near &= ~((uint64_t)BM << (r0 * LPR));
     }
     return -1;
+}
+
+using Half2 = _Float16 __attribute__((ext_vector_type(2)));
+using Half4 = _Float16 __attribute__((ext_vector_type(4)));
+using Float4 = float __attribute__((ext_vector_type(4)));
+
+// Rounded towards zero.
+__device__ inline Half2 to_halves(float a, float b)
+{
+    return __builtin_bit_cast(Half2, __builtin_amdgcn_cvt_pkrtz(a, b));
+}
+
+// What the halves leave open.  A coordinate X rounds by at most 2^-10 |X| (or
+// 2^-14 where it has no normal half), so two points at distance r <= T of each
+// other and |X_i| <= H of the home centre come out at most 2^-10 (2 H + T) +
+// 2^-13 further apart; |x_j|^2 rounds downwards, which only adds hits; the sums
+// are single precision.  kHalfRel and kHalfAbs hold these with room to spare.
+// Beyond kHalfFar reaches nothing is tested: every candidate is listed.
+constexpr float kHalfRel = 1.1e-3f, kHalfAbs = 4e-4f, kHalfFar = 150.f, kHalfTop = 65504.f;
+
+// The home leaf as the product's second operand, per home particle: (-2 x_i, 1)
+// as halves and the constants |x_i|^2 - T_i^2 and |x_i|^2 (1e30: takes no part).
+// It stays in LDS: held in registers it displaced what the pair terms need.
+struct alignas(16) HomeCol {
+    Half4 b;
+    float c, n;
+};
+template <int G>
+struct HomeOp {
+    HomeCol col[16 * Words<G>::tiles];
+};
+template <>
+struct HomeOp<0> {};   // (not used)
+
+// Units of the product's coordinates: 1 / unit length, the largest |x_i| (in
+// units), and whether every candidate is listed.
+struct HomeUnits {
+    float scale, extent;
+    bool wide;
+};
+
+// thr: the home particles' squared reaches in H (< 0: takes no part), unit: the
+// unit length (about the reach over R).
+template <int G, int PREC>
+__device__ inline HomeUnits home_operand(const HomeTab<G, PREC> &H, const Node &home, double unit, HomeOp<G> &O)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const double s = 1.0 / unit;
+    HomeUnits U;
+    U.scale = (float)s;
+    U.extent = (float)(sqrt((home.e[0] * home.e[0] + home.e[1] * home.e[1]) + home.e[2] * home.e[2]) * s);
+    bool far = false;
+    if (lane < 16 * Words<G>::tiles) {
+        const bool in = lane < G;
+        const HomeRow h = H.d[in ? lane : 0];
+        const bool part = in && h.thr >= 0.0;
+        float X, Y, Z;
+        if constexpr (PREC == SPH_FP64) {
+            X = (float)(h.x - home.c[0]) * U.scale;
+            Y = (float)(h.y - home.c[1]) * U.scale;
+            Z = (float)(h.z - home.c[2]) * U.scale;
+        } else {
+            const HomeRowF f = H.f[in ? lane : 0];
+            X = f.x * U.scale;
+            Y = f.y * U.scale;
+            Z = f.z * U.scale;
+        }
+        const Half2 xy = to_halves(X, Y), z0 = to_halves(Z, 0.f);
+        const float n = __builtin_amdgcn_fdot2(xy, xy, __builtin_amdgcn_fdot2(z0, z0, 0.f, false), false);
+        const float T = __builtin_amdgcn_sqrtf((float)h.thr) * U.scale;
+        const float Tw = T * (1.f + kHalfRel) + 2.f * kHalfRel * U.extent + kHalfAbs;
+        far = part && !(U.extent + T <= kHalfFar);
+        HomeCol c;
+        c.b = Half4{(_Float16)-2 * xy.x, (_Float16)-2 * xy.y, (_Float16)-2 * z0.x, (_Float16)1};
+        c.c = part ? n - Tw * Tw : 1e30f;
+        c.n = part ? n : 1e30f;
+        O.col[lane] = c;
+    }
+    U.wide = __ballot(far) != 0ull;
+    wave_lds_sync();
+    return U;
+}
+
+// Sum over the four lanes l % 16, l % 16 + 16, + 32, + 48 of a lane and of
+// those before it.
+__device__ inline void column_scan(uint32_t v, uint32_t &before, uint32_t &total)
+{
+    const int row = (int)(threadIdx.x & (kWave - 1)) / 16;
+    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);   // rows 0 0 2 2, rows 1 1 3 3
+    const uint32_t pair = a[0] + a[1];
+    const auto b = __builtin_amdgcn_permlane32_swap(pair, pair, false, false);
+    before = ((row & 1) ? a[0] : 0u) + ((row & 2) ? b[0] : 0u);
+    total = b[0] + b[1];
+}
+
+// The open group's pairs.  Every candidate within reach of a home particle
+// (FORCE: or the home particle within its reach, which the position records
+// carry squared) is listed for it: ids holds Words<G>::cap slots of the group
+// per home particle, and use(n) is called with this lane's home particle's
+// number n (particle lane / LPP) whenever a list might overflow and at the
+// group's end.  A list's order depends on the particle and the candidates alone.
+template <int G, int PREC, bool FORCE, class Use>
+__device__ inline void group_pairs(const LeafTab<PREC> &tab, const Node &home, const Box &bx, int count, int img,
+                                   const HomeOp<G> &op, const HomeUnits &U, const Pos4 *__restrict__ pos,
+                                   const Off4 *__restrict__ off, uint16_t *ids, Use use)
+{
+    using W = Words<G>;
+    constexpr bool F64 = PREC == SPH_FP64;
+    using T = std::conditional_t<F64, double, float>;
+    constexpr int NT = W::tiles;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int words = (count * G + W::slots - 1) / W::slots;
+    // the slot of this lane's candidate in row r of a word, so that a result's
+    // bits, in the order t, v within a row, are consecutive slots
+    const int sub = ((lane >> 2) & 3) * (16 * W::rows) + (lane >> 4) * 4 + (lane & 3);
+    const bool wide = U.wide || img == kImgWide;
+    struct Raw {
+        T x, y, z, w;
+        uint32_t meta;
+        int k;
+        bool ok;
+    };
+    auto load = [&](int word, Raw (&c)[W::rows]) {
+#pragma unroll
+        for (int r = 0; r < W::rows; r++) {
+            const int s = word * W::slots + r * 16 + sub;
+            c[r].k = s / G;
+            const uint2 jm = tab.jm[c[r].k];
+            const int slot = s % G;
+            c[r].ok = slot < (int)(jm.y & 255u);
+            c[r].meta = jm.y;
+            const uint32_t j = jm.x + (c[r].ok ? slot : 0);   // (a missing leaf's entry is particle 0)
+            const auto *q = as_global(F64 ? (const T *)(pos + j) : (const T *)(off + j));
+            c[r].x = q[0];
+            c[r].y = q[1];
+            c[r].z = q[2];
+            if constexpr (FORCE) c[r].w = q[3];
+        }
+    };
+    uint32_t held[NT] = {};
+    __builtin_amdgcn_s_setprio(2);
+    for (int word = 0;; word++) {
+        uint32_t bits[NT] = {}, before[NT] = {}, total[NT] = {};
+        bool over = false;
+        if (word < words) {
+            Raw raw[W::rows];
+            load(word, raw);
+            HomeCol col[NT];
+#pragma unroll
+            for (int u = 0; u < NT; u++) col[u] = op.col[lane % 16 + 16 * u];
+#pragma unroll
+            for (int r = 0; r < W::rows; r++) {
+                float X, Y, Z;
+                if constexpr (F64) {
+                    double cx = home.c[0], cy = home.c[1], cz = home.c[2];
+                    if (img == kImgShift) {
+                        cx += shift_of(raw[r].meta, 0, bx);
+                        cy += shift_of(raw[r].meta, 1, bx);
+                        cz += shift_of(raw[r].meta, 2, bx);
+                    }
+                    X = (float)(raw[r].x - cx);
+                    Y = (float)(raw[r].y - cy);
+                    Z = (float)(raw[r].z - cz);
+                } else {
+                    X = raw[r].x - tab.o[0][raw[r].k];
+                    Y = raw[r].y - tab.o[1][raw[r].k];
+                    Z = raw[r].z - tab.o[2][raw[r].k];
+                }
+                if (img == kImgPair) {
+                    X = min_image_f(X, (float)bx.len[0], (float)bx.half[0]);
+                    Y = min_image_f(Y, (float)bx.len[1], (float)bx.half[1]);
+                    Z = min_image_f(Z, (float)bx.len[2], (float)bx.half[2]);
+                }
+                X *= U.scale;
+                Y *= U.scale;
+                Z *= U.scale;
+                Half2 xy = to_halves(X, Y);
+                const Half2 z0 = to_halves(Z, 0.f);
+                float n = __builtin_amdgcn_fdot2(xy, xy, __builtin_amdgcn_fdot2(z0, z0, 0.f, false), false);
+                // an empty slot, or a candidate out of reach by far, hits nothing
+                float z = Z, nf = 0.f;
+                bool ok = raw[r].ok;
+                if (!wide) ok = ok && n <= 4e4f;
+                if constexpr (FORCE) {
+                    // |x_j|^2 - T_j^2, rounded downwards; a reach beyond the halves'
+                    // range takes everything
+                    const float Tj = __builtin_amdgcn_sqrtf((float)raw[r].w) * U.scale;
+                    const float Tw = Tj * (1.f + 2.f * kHalfRel) + 2.f * kHalfRel * U.extent + kHalfAbs;
+                    const bool big = raw[r].ok && !(U.extent + Tw <= kHalfFar);
+                    nf = n - Tw * Tw * (1.f + kHalfRel);
+                    nf = ok ? nf : kHalfTop;
+                    nf = big ? -kHalfTop : nf;
+                    ok = ok && !big;
+                }
+                if (wide) {
+                    n = 0.f;
+                    nf = 0.f;
+                    z = 0.f;
+                    ok = raw[r].ok;
+                    xy = Half2{0, 0};
+                    if (!ok) nf = kHalfTop;
+                }
+                if (!ok) {
+                    xy = Half2{0, 0};
+                    z = 0.f;
+                    n = kHalfTop;
+                }
+                const Half2 zn = to_halves(z, n);
+                const Half4 a{xy.x, xy.y, zn.x, zn.y};
+                Half4 af = a;
+                if constexpr (FORCE) af.w = to_halves(nf, 0.f).x;
+#pragma unroll
+                for (int u = 0; u < NT; u++) {
+                    const float c = wide ? (col[u].c < 1e29f ? -1.f : 1e30f) : col[u].c;
+                    const float cn = wide ? c : col[u].n;
+                    const Float4 C{c, c, c, c}, CN{cn, cn, cn, cn};
+                    const Half4 zero{0, 0, 0, 0};
+#pragma unroll
+                    for (int t = 0; t < 4; t++) {
+                        const Half4 b = lane / 16 == t ? col[u].b : zero;
+                        const Float4 D = __builtin_amdgcn_mfma_f32_16x16x16f16(a, b, C, 0, 0, 0);
+                        Float4 E = D;
+                        if constexpr (FORCE) E = __builtin_amdgcn_mfma_f32_16x16x16f16(af, b, CN, 0, 0, 0);
+#pragma unroll
+                        for (int v = 0; v < 4; v++) {
+                            const float d = D[v], e = E[v];
+                            const uint32_t sign = __builtin_bit_cast(uint32_t, d) | __builtin_bit_cast(uint32_t, e);
+                            bits[u] = __builtin_amdgcn_alignbit(bits[u], sign, 31);
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < NT; u++) {
+                column_scan((uint32_t)__popc(bits[u]), before[u], total[u]);
+                over = over || held[u] + total[u] > (uint32_t)W::cap;
+            }
+        }
+        if (word == words || __ballot(over) != 0ull) {
+            __builtin_amdgcn_s_setprio(0);
+            wave_lds_sync();
+            constexpr int LPP = kWave / G;
+            const int p = lane / LPP;
+            int n = __shfl((int)held[0], p % 16);
+            if constexpr (NT == 2) {
+                const int n1 = __shfl((int)held[1], p % 16);
+                n = p < 16 ? n : n1;
+            }
+            use(n);
+            wave_lds_sync();
+#pragma unroll
+            for (int u = 0; u < NT; u++) held[u] = 0;
+            if (word == words) break;
+            __builtin_amdgcn_s_setprio(2);
+        }
+        // this lane's hits to its home particle's list
+#pragma unroll
+        for (int u = 0; u < NT; u++) {
+            const int i = lane % 16 + 16 * u;
+            uint16_t *to = ids + (i < G ? i : 0) * W::cap + held[u] + before[u];
+            const int last = word * W::slots + (lane >> 4) * (16 * W::rows) + 16 * W::rows - 1;
+            for (uint32_t m = bits[u]; m; m &= m - 1) *to++ = (uint16_t)(last - __builtin_ctz(m));
+            held[u] += total[u];
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -936,11 +1252,17 @@ __device__ inline int find_req(const uint32_t *pre, int nreq, int64_t g)
 // polynomial in x.
 template <int K>
 struct Sums {
-    double d0 = 0.0, d1 = 0.0, d2 = 0.0;
+    double d0 = 0.0, d1 = 0.0, d2 = 0.0;   // (FP32-pair: sum m f, sum m q f')
     double wn = 0.0;                       // D3 of unequal masses, quintic's D3
     double edge = 1e300;                   // smallest |q - knot| met
     int n = 0, n1 = 0;                     // entries inside R h, inside h
     static constexpr int N = K == SPH_KERNEL_QUINTIC ? 5 : 3;
+};
+
+// Sums of a particle whose list filled up and was started afresh.
+struct PartSums {
+    double d0, d1, d2, wn;
+    int n, n1;
 };
 
 template <int K, bool EQ>
@@ -1025,11 +1347,15 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
     static_assert(KP % CHUNK == 0, "lists hold whole steps");
     __shared__ WalkBuf wb;
     __shared__ TreeInfo T;
+    __shared__ LeafTab<PREC> tab;
     __shared__ union {
-        LeafTab<G, PREC> tab;
-        uint32_t walk_spare[kFront];   // lent to walks, which run between sweeps
+        uint16_t id[F64 ? 1 : G * Words<G>::cap];   // FP32-pair: pairs of each home particle
+        uint32_t walk_spare[kFront];                // lent to walks, which run between sweeps
     } S;
     __shared__ HomeTab<G, PREC> H;
+    __shared__ HomeOp<F64 ? 0 : G> op;
+    __shared__ uint64_t near_of[G];
+    __shared__ PartSums part[G];
     __shared__ uint32_t pre[kMaxBatch + 1];
     batch_prefix(B, pre);
     const int lane = threadIdx.x;
@@ -1128,102 +1454,61 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
         for (;;) {
             const double hinv = 1.0 / h;
             const double h2x4 = (RK * h) * (RK * h);
-            Sums<K> sm;
-            double s0 = 0.0, s2 = 0.0;   // FP32-pair sums
-            const float h2x4f = (float)h2x4, hinvf = (float)hinv;
+            uint64_t emptied = 0;   // bit p: home particle p's list was, in this sweep
+            // the pair terms of one entry (eq: all masses are equal, m not used)
+            auto add = [&](Sums<K> &sm, auto eq, ListR2 r2, double m, double hinv, double h2x4) {
+                constexpr bool EQ = decltype(eq)::value;
+                if constexpr (F64) {
+                    add_entry<K, EQ>(sm, r2, m, hinv, h2x4);
+                } else {
+                    // branch-free: an entry outside R h adds 0 * f
+                    const bool in = r2 < (float)h2x4;
+                    const double mj = in ? (EQ ? mu : m) : 0.0;
+                    float f, df;
+                    const float qq = sqrtf(r2) * (float)hinv;
+                    kern<K>(qq, f, df);
+                    sm.d0 += mj * (double)f;
+                    sm.d1 += mj * (double)(qq * df);
+                    sm.n += in ? 1 : 0;
+                }
+            };
             // the pair terms of this particle's list entries [0, n), its lanes
             // sharing them four at a time; entries past n up to a whole step
             // are far away and add nothing
-            auto eval_list = [&](int n) {
-                const ListR2 *l = cr2 + p * KP;
-                const double *lm = cm + p * KP;
-                if constexpr (F64) {
-                    using D2 = double __attribute__((ext_vector_type(2)));
-                    auto sums = [&](auto eq) {
-                        constexpr bool EQ = decltype(eq)::value;
+            auto eval_list = [&](Sums<K> &sm, int n) {
+                const auto *l = as_global(cr2 + p * KP);
+                const auto *lm = as_global(cm + p * KP);
+                auto sums = [&](auto eq) {
+                    constexpr bool EQ = decltype(eq)::value;
+                    if constexpr (F64) {
+                        using D2 = double __attribute__((ext_vector_type(2)));
+                        using P2 = const __attribute__((address_space(1))) D2 *;
                         for (int e = 2 * q; e < n; e += CHUNK) {
-                            const D2 u = *(const __attribute__((address_space(1))) D2 *)(l + e);
-                            const D2 v = *(const __attribute__((address_space(1))) D2 *)(l + e + 2 * LPP);
+                            const D2 u = *(P2)(l + e), v = *(P2)(l + e + 2 * LPP);
                             D2 mu2{}, mv2{};
                             if constexpr (!EQ) {
-                                mu2 = *(const __attribute__((address_space(1))) D2 *)(lm + e);
-                                mv2 = *(const __attribute__((address_space(1))) D2 *)(lm + e + 2 * LPP);
+                                mu2 = *(P2)(lm + e);
+                                mv2 = *(P2)(lm + e + 2 * LPP);
                             }
-                            add_entry<K, EQ>(sm, u.x, mu2.x, hinv, h2x4);
-                            add_entry<K, EQ>(sm, u.y, mu2.y, hinv, h2x4);
-                            add_entry<K, EQ>(sm, v.x, mv2.x, hinv, h2x4);
-                            add_entry<K, EQ>(sm, v.y, mv2.y, hinv, h2x4);
+                            add(sm, eq, u.x, mu2.x, hinv, h2x4);
+                            add(sm, eq, u.y, mu2.y, hinv, h2x4);
+                            add(sm, eq, v.x, mv2.x, hinv, h2x4);
+                            add(sm, eq, v.y, mv2.y, hinv, h2x4);
                         }
-                    };
-                    if (equal_m) sums(std::true_type{});
-                    else sums(std::false_type{});
-                } else {
-                    using F4 = float __attribute__((ext_vector_type(4)));
-                    using D4 = double __attribute__((ext_vector_type(4)));
-                    for (int e = 4 * q; e < n; e += CHUNK) {
-                        const F4 u = *(const __attribute__((address_space(1))) F4 *)(l + e);
-                        D4 mw{mu, mu, mu, mu};
-                        if (!equal_m) mw = *(const __attribute__((address_space(1))) D4 *)(lm + e);
-#pragma unroll
-                        for (int k = 0; k < 4; k++) {
-                            // branch-free: an entry outside R h adds 0 * f
-                            const bool in = u[k] < h2x4f;
-                            const double mj = in ? mw[k] : 0.0;
-                            float f, df;
-                            const float qq = sqrtf(u[k]) * hinvf;
-                            kern<K>(qq, f, df);
-                            s0 += mj * (double)f;
-                            s2 += mj * (double)(qq * df);
-                            sm.n += in ? 1 : 0;
-                        }
-                    }
-                }
-            };
-            // the n entries of home particle pp's list, which is full, added to
-            // its sums (on its first lane) by the whole wave; the list starts
-            // afresh.  n and the order depend on the particle and the rows
-            // alone
-            auto empty_list = [&](int pp, int n) {
-                Sums<K> t;
-                double t0 = 0.0, t2 = 0.0;
-                const double hv = readlane_d(hinv, pp * LPP), hh = readlane_d(h2x4, pp * LPP);
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-                for (int e = lane; e < n; e += kWave) {
-                    const ListR2 r2 = as_global(cr2)[pp * KP + e];
-                    const double mw = equal_m ? mu : as_global(cm)[pp * KP + e];
-                    if constexpr (F64) {
-                        if (equal_m) add_entry<K, true>(t, r2, mw, hv, hh);
-                        else add_entry<K, false>(t, r2, mw, hv, hh);
                     } else {
-                        const bool in = r2 < (float)hh;
-                        const double mj = in ? mw : 0.0;
-                        float f, df;
-                        const float qq = sqrtf(r2) * (float)hv;
-                        kern<K>(qq, f, df);
-                        t0 += mj * (double)f;
-                        t2 += mj * (double)(qq * df);
-                        t.n += in ? 1 : 0;
+                        using F4 = float __attribute__((ext_vector_type(4)));
+                        using D4 = double __attribute__((ext_vector_type(4)));
+                        for (int e = 4 * q; e < n; e += CHUNK) {
+                            const F4 u = *(const __attribute__((address_space(1))) F4 *)(l + e);
+                            D4 mw{};
+                            if constexpr (!EQ) mw = *(const __attribute__((address_space(1))) D4 *)(lm + e);
+#pragma unroll
+                            for (int k = 0; k < 4; k++) add(sm, eq, u[k], mw[k], hinv, h2x4);
+                        }
                     }
-                }
-                const int n0 = (int)wave_sum_int(t.n), n1 = (int)wave_sum_int(t.n1);
-                const bool own = lane == pp * LPP;
-                sm.n += own ? n0 : 0;
-                if constexpr (F64) {
-                    sm.n1 += own ? n1 : 0;
-                    const double d0 = wave_sum(t.d0), d1 = wave_sum(t.d1), d2 = wave_sum(t.d2);
-                    const double wn = wave_sum(t.wn);
-                    sm.d0 += own ? d0 : 0.0;
-                    sm.d1 += own ? d1 : 0.0;
-                    sm.d2 += own ? d2 : 0.0;
-                    sm.wn += own ? wn : 0.0;
-                } else {
-                    t0 = wave_sum(t0);
-                    t2 = wave_sum(t2);
-                    s0 += own ? t0 : 0.0;
-                    s2 += own ? t2 : 0.0;
-                }
+                };
+                if (equal_m) sums(std::true_type{});
+                else sums(std::false_type{});
             };
             // entries [n, whole step) of this particle's list: far away
             auto pad_list = [&](int n) {
@@ -1232,92 +1517,168 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                     cr2[p * KP + e] = F64 ? (ListR2)1e300 : (ListR2)1e30f;
                     if (!equal_m) cm[p * KP + e] = 0.0;
                 }
-                // the lanes read what other lanes of the wave stored
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                wave_mem_sync();
+            };
+            // the n entries of home particle pp's list, which is full, added to its
+            // sums by the whole wave; the list starts afresh
+            auto empty_list = [&](int pp, int n) {
+                Sums<K> t;
+                const double hv = readlane_d(hinv, pp * LPP), hh = readlane_d(h2x4, pp * LPP);
+                wave_mem_sync();
+                for (int e = lane; e < n; e += kWave) {
+                    const ListR2 r2 = as_global(cr2)[pp * KP + e];
+                    if (equal_m) add(t, std::true_type{}, r2, 0.0, hv, hh);
+                    else add(t, std::false_type{}, r2, as_global(cm)[pp * KP + e], hv, hh);
+                }
+                const bool first_time = !((emptied >> pp) & 1);
+                count_up(kCntDensListOverflows, first_time ? 1 : 0);
+                emptied |= 1ull << pp;
+                const double d0 = wave_sum(t.d0), d1 = wave_sum(t.d1), d2 = wave_sum(t.d2), wn = wave_sum(t.wn);
+                const int n0 = (int)wave_sum_int(t.n), n1 = (int)wave_sum_int(t.n1);
+                const PartSums c = first_time ? PartSums{} : part[pp];
+                wave_lds_sync();
+                if (lane == 0) part[pp] = PartSums{c.d0 + d0, c.d1 + d1, c.d2 + d2, c.wn + wn, c.n + n0, c.n1 + n1};
+                wave_lds_sync();
             };
             if (__ballot(!conv && !cached) != 0ull) {
                 // sweep: every particle still iterating rebuilds its list
                 // around its current h.  A list that fills up is added to the
-                // sums and started afresh; it cannot serve later steps then
+                // particle's sums and started afresh; it cannot serve later
+                // steps then
                 double rc2 = -1.0;
                 if (!conv) {
                     Rc = fmin(kCacheGrow * h, hcov);
-                    rc2 = (RK * Rc) * (RK * Rc) * (1.0 + 1e-6);   // far above rounding
+                    rc2 = (RK * Rc) * (RK * Rc);
                 }
                 wave_lds_sync();
-                if (q == 0) {
-                    H.d[p].thr = rc2;
-                    if constexpr (!F64) H.f[p].thr = (float)rc2;
-                }
+                if (q == 0) H.d[p].thr = rc2;
                 wave_lds_sync();
-                const uint64_t lanes_in = __ballot(!conv);
-                uint64_t takes_part = 0;   // bit p: home particle p
-#pragma unroll
-                for (int k = 0; k < G; k++)
-                    takes_part |= ((lanes_in >> (k * LPP)) & 1ull) << k;
-                const int depth = group_depth<G>(wr.n, B.stage > 0 ? B.stage * G / 2 : kGroup);
-                uint64_t emptied = 0;      // bit p: the list of home particle p is not complete
-                int held = 0;              // lane p: entries in the list of home particle p
-                int64_t at = 0;
-                const uint32_t *leaves = nullptr;
                 const auto &Q = *reload(Ap);
                 const Node home = load_const(reload(A.nodes) + leaf);
                 const Box bx = load_const(&reload(B.req[r])->box);
-                auto test = near_home(home, bx);
-                for (;;) {
-                    const int ng = next_group(T, Q.nodes, wr, test, wb, depth, at, leaves);
-                    if (ng == 0) break;
-                    uint64_t lmask;
-                    const int img = open_group<G, PREC, K>(leaves, ng, Q.lstart, Q.nodes, home, bx, hcov,
-                                                           H, takes_part, S.tab, lmask);
-                    count_up(kCntDensVisits, ng);
-                    int tested = 0;
-                    const bool diag = Q.count_tests != 0;
-                    auto load = [&](uint32_t j) { return equal_m ? mu : as_global(Q.m)[j]; };
-                    auto hit = [&](auto r2, auto thr, double) { return __ballot(r2 < thr); };
-                    auto put = [&](uint32_t at, uint32_t rank, int, auto r2, double mw) {
-                        // (fixed uniform base, 32-bit lane offset)
-                        auto *to = (__attribute__((address_space(1))) char *)cr2;
-                        *(__attribute__((address_space(1))) ListR2 *)(to + (at + rank) * (uint32_t)sizeof(ListR2)) = r2;
-                        if (!equal_m) {
-                            auto *tm = (__attribute__((address_space(1))) char *)cm;
-                            *(__attribute__((address_space(1))) double *)(tm + (at + rank) * 8u) = mw;
-                        }
-                    };
-                    for (;;) {
-                        int full;
-                        if (img == kImgNone || (img == kImgShift && !F64))
-                            full = test_rows<G, PREC, kImgNone, kRows>(S.tab, H, ng, bx, Q.pos, Q.off, lmask,
-                                                                       held, KP, diag, tested, load, hit, put);
-                        else if (img == kImgShift)
-                            full = test_rows<G, PREC, F64 ? kImgShift : kImgNone, kRows / 2>(
-                                S.tab, H, ng, bx, Q.pos, Q.off, lmask, held, KP, diag, tested, load, hit, put);
-                        else
-                            full = test_rows<G, PREC, kImgPair, kRows / 2>(
-                                S.tab, H, ng, bx, Q.pos, Q.off, lmask, held, KP, diag, tested, load, hit, put);
-                        if (full < 0) break;
-                        empty_list(full, __builtin_amdgcn_readlane(held, full));
-                        held = lane == full ? 0 : held;
-                        count_up(kCntDensListOverflows, (emptied >> full) & 1 ? 0 : 1);
-                        emptied |= 1ull << full;
-                    }
-                    if (diag) {
-                        count_up(kCntDensBoxes, ng * (int)__popcll(takes_part));
-                        count_up(kCntDensTests, tested * kWave);
-                    }
-                    wave_lds_sync();   // the next group rewrites the table
+                HomeUnits units{};
+                if constexpr (!F64) units = home_operand<G, PREC>(H, home, hcov, op);
+                uint64_t takes_part = 0;   // bit p: home particle p
+                {
+                    const uint64_t lanes_in = __ballot(!conv);
+#pragma unroll
+                    for (int k = 0; k < G; k++) takes_part |= ((lanes_in >> (k * LPP)) & 1ull) << k;
                 }
-                const int mine = __shfl(held, p);   // every lane takes part
-                count = conv ? 0 : mine;
+                const int depth = group_depth<G>(wr.n, B.stage > 0 ? B.stage * G / 2 : kGroup);
+                count = 0;
+                int held = 0;              // FP64: entries of home particle `lane`'s list
+                int64_t at = 0;
+                const uint32_t *leaves = nullptr;
+                auto test = near_home(home, bx);
+                auto reached = [&](const Node &nd) { return leaf_in_reach<G, PREC>(H, nd, bx, -1.0); };
+                for (;;) {
+                    const int ng = next_group<!F64>(T, Q.nodes, wr, test, reached, wb, depth, at, leaves);
+                    if (ng == 0) break;
+                    const int img = open_group<G, PREC, K>(leaves, ng, Q.lstart, Q.nodes, home, bx, hcov, tab, H,
+                                                           takes_part, F64 ? near_of : nullptr);
+                    count_up(kCntDensVisits, ng);
+                    if (Q.count_tests) {
+                        count_up(kCntDensBoxes, ng * (int)__popcll(takes_part));
+                        count_up(kCntDensTests, ng * G * (int)__popcll(takes_part));
+                    }
+                    if constexpr (F64) {
+                        uint64_t near = near_of[lane < G ? lane : 0];
+                        if (lane >= G) near = 0;
+                        auto mass = [&](uint32_t j) { return equal_m ? mu : as_global(Q.m)[j]; };
+                        auto put = [&](uint32_t to, double r2, double m) {
+                            // (fixed uniform base, 32-bit lane offset)
+                            auto *list = (__attribute__((address_space(1))) char *)cr2;
+                            *(__attribute__((address_space(1))) double *)(list + to * 8u) = r2;
+                            if (!equal_m) {
+                                auto *lm = (__attribute__((address_space(1))) char *)cm;
+                                *(__attribute__((address_space(1))) double *)(lm + to * 8u) = m;
+                            }
+                        };
+                        for (;;) {
+                            int full;
+                            if (img == kImgNone)
+                                full = test_rows<G, kImgNone, kRows>(tab, H, ng, bx, Q.pos, near, held, KP, mass, put);
+                            else if (img == kImgShift)
+                                full = test_rows<G, kImgShift, kRows / 2>(tab, H, ng, bx, Q.pos, near, held, KP,
+                                                                          mass, put);
+                            else
+                                full = test_rows<G, kImgPair, kRows / 2>(tab, H, ng, bx, Q.pos, near, held, KP,
+                                                                         mass, put);
+                            if (full < 0) break;
+                            empty_list(full, __builtin_amdgcn_readlane(held, full));
+                            held = lane == full ? 0 : held;
+                        }
+                        wave_lds_sync();   // the next group rewrites the table
+                    } else {
+                        // r^2 of the pairs to the particle's list, its lanes taking
+                        // them in turn, two at a time (both positions requested
+                        // before either is used)
+                        auto use = [&](int n) {
+                            const HomeRow hd = H.d[p];
+                            ListR2 hx = hd.x, hy = hd.y, hz = hd.z;
+                            if constexpr (!F64) {
+                                hx = H.f[p].x;
+                                hy = H.f[p].y;
+                                hz = H.f[p].z;
+                            }
+                            const uint16_t *id = S.id + p * Words<G>::cap;
+                            int done = 0;
+                            for (;;) {
+                                const int m = n - done < KP - count ? n - done : KP - count;
+                                auto *to = as_global_out(cr2 + p * KP + count);
+                                auto *tm = as_global_out(cm + p * KP + count);
+                                for (int e = q; e < m; e += 2 * LPP) {
+                                    const bool two = e + LPP < m;
+                                    const int sa = id[done + e], sb = id[done + (two ? e + LPP : e)];
+                                    const uint2 ma = tab.jm[sa / G], mb = tab.jm[sb / G];
+                                    const uint32_t ja = ma.x + (uint32_t)(sa % G), jb = mb.x + (uint32_t)(sb % G);
+                                    ListR2 dx, dy, dz, w;
+                                    const ListR2 ra = group_separation<PREC, ListR2>(
+                                        tab, img, bx, hx, hy, hz, sa / G, ma, ja, Q.pos, Q.off, dx, dy, dz, w);
+                                    const ListR2 rb = group_separation<PREC, ListR2>(
+                                        tab, img, bx, hx, hy, hz, sb / G, mb, jb, Q.pos, Q.off, dx, dy, dz, w);
+                                    to[e] = ra;
+                                    if (two) to[e + LPP] = rb;
+                                    if (!equal_m) {
+                                        tm[e] = as_global(Q.m)[ja];
+                                        if (two) tm[e + LPP] = as_global(Q.m)[jb];
+                                    }
+                                }
+                                count += m;
+                                done += m;
+                                const bool full = done < n;
+                                if (__ballot(full) == 0ull) break;
+                                // full lists (KP entries, whatever the groups)
+                                for (uint64_t f = __ballot(full && q == 0); f; f &= f - 1)
+                                    empty_list((int)__builtin_ctzll(f) / LPP, KP);
+                                if (full) count = 0;
+                            }
+                        };
+                        group_pairs<G, PREC, false>(tab, home, bx, ng, img, op, units, Q.pos, Q.off, S.id, use);
+                    }
+                }
+                if constexpr (F64) {
+                    const int mine = __shfl(held, p);   // every lane takes part
+                    count = conv ? 0 : mine;
+                }
                 cached = !conv && !((emptied >> p) & 1);
                 pad_list(count);
             }
-            eval_list(conv ? 0 : count);
+            Sums<K> sm;
+            eval_list(sm, conv ? 0 : count);
+            if (((emptied >> p) & 1) && q == 0) {
+                const PartSums &t = part[p];
+                sm.d0 += t.d0;
+                sm.d1 += t.d1;
+                sm.d2 += t.d2;
+                sm.wn += t.wn;
+                sm.n += t.n;
+                sm.n1 += t.n1;
+            }
             // one evaluation for every particle still iterating (uniform)
             count_up(kCntNrTotal, (int)__popcll(__ballot(!conv && q == 0)));
             const int cnt = group_sum<LPP>(sm.n) - 1;   // without the particle itself
+            double s0, s2;
             // x: relative change of h to the root (the polynomial's, where it
             // could be solved), b1: the polynomial's derivative there
             double x = 0.0, b1 = 0.0, edge = 0.0;
@@ -1358,8 +1719,8 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                     b1 = (3.0 * D3 * x + 2.0 * D2) * x + D1;
                 }
             } else {
-                s0 = group_sum<LPP>(s0);
-                s2 = group_sum<LPP>(s2);
+                s0 = group_sum<LPP>(sm.d0);
+                s2 = group_sum<LPP>(sm.d1);
             }
             if (!conv && q == 0) evals_leaf += cnt;
             if (!conv) {
@@ -1459,12 +1820,6 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
 // Force loop
 // ---------------------------------------------------------------------------
 
-// Hits held per home particle between two flushes (16-bit ids, 4 KB of LDS:
-// with the walk buffer and the tables a wave stays within 10 KB up to G = 16).
-// At least the 64 hits that one row can give.
-template <int G>
-constexpr int force_list() { return 2048 / G; }
-
 // AC: the launch carries artificial conductivity (some set of the batch has
 // alpha_AC > 0; a set with alpha_AC = 0 then adds exact zeros).
 // SW: the launch carries per-particle alpha or the velocity divergence and
@@ -1474,16 +1829,16 @@ template <int G, int PREC, bool AC, bool SW, int K>
 __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(Batch<ForceArgs> B)
 {
     constexpr int LPP = kWave / G;
-    constexpr int CAP = force_list<G>();
     constexpr bool F64 = PREC == SPH_FP64;
     __shared__ WalkBuf wb;
     __shared__ TreeInfo T;
-    __shared__ LeafTab<G, PREC> tab;
+    __shared__ LeafTab<PREC> tab;
     __shared__ union {
-        uint16_t id[G * CAP];          // hits of each home particle: slots of the open group
-        uint32_t walk_spare[kFront];   // lent to walks, which run between groups
+        uint16_t id[G * Words<G>::cap];   // pairs of each home particle: slots of the open group
+        uint32_t walk_spare[kFront];      // lent to walks, which run between groups
     } S;
     __shared__ HomeTab<G, PREC> H;
+    __shared__ HomeOp<G> op;
     __shared__ uint32_t pre[kMaxBatch + 1];
     batch_prefix(B, pre);
     const int lane = threadIdx.x;
@@ -1545,12 +1900,8 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
         const Node home = load_const(F.nodes + leaf);
         if (q == 0) {
             H.d[p] = HomeRow{hx, hy, hz, active ? hi2x4 : -1.0};
-            if constexpr (!F64) H.f[p] = HomeRowF{hfx, hfy, hfz, active ? (float)hi2x4 : -1.f};
+            if constexpr (!F64) H.f[p] = HomeRowF{hfx, hfy, hfz, 0.f};
         }
-        const uint64_t lanes_in = __ballot(active);
-        uint64_t takes_part = 0;   // bit p: home particle p
-#pragma unroll
-        for (int k = 0; k < G; k++) takes_part |= ((lanes_in >> (k * LPP)) & 1ull) << k;
         // symmetric criterion: a node can hold force neighbours of the home leaf
         // if its box is closer than 2 max(h over home, h over node)
         auto test = [&bx, &home](const Node &nd) {
@@ -1565,7 +1916,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
 
         double axi = 0.0, ayi = 0.0, azi = 0.0, dui = 0.0, vs_max = -INFINITY;
         double dvs = 0.0, cxs = 0.0, cys = 0.0, czs = 0.0;   // div v, curl v sums (SW)
-        int cnt = 0, selfs = 0;
+        int cnt = 0;
         int lmx_l = 0;                                       // block time-steps
         const int lev_i = F.lev ? as_global(F.lev)[ii] : 0;
         // FP32-pair: the neighbours' single-precision records (32 bytes)
@@ -1688,100 +2039,55 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
             lmx_l = lj > lmx_l ? lj : lmx_l;
             if (lj < lev_i - F.lim && as_global(F.active)[j] == 0) atomicMax(&F.mark[j], lev_i);
         };
-        // the hits this particle holds, its lanes sharing them round-robin.
-        // The particle itself is among the hits of its own leaf: it takes no
-        // pair terms and is not counted
-        auto flush = [&](int n, int img) {
-            const uint32_t self = (uint32_t)i;
-            for (int e = q; e < n; e += LPP) {
-                const int s = S.id[p * CAP + e];
-                const int k = s / G;
-                const uint32_t j = tab.jm[k].x + (uint32_t)(s % G);
-                Real dx, dy, dz, r2;
-                JData d;
-                if constexpr (F64) {
-                    d = load_global(F.rec + j);
-                    const auto *o = as_global((const double *)(F.pos + j));
-                    const double x = o[0], y = o[1], z = o[2];
-                    if (img == kImgNone)
-                        r2 = separation<PREC, kImgNone, double>(bx, hx, hy, hz, x, y, z, 0.0, 0.0, 0.0,
-                                                                dx, dy, dz);
-                    else if (img == kImgShift)
-                        r2 = separation<PREC, kImgShift, double>(bx, hx, hy, hz, x, y, z, tab.ox[k],
-                                                                 tab.oy[k], tab.oz[k], dx, dy, dz);
-                    else
-                        r2 = separation<PREC, kImgPair, double>(bx, hx, hy, hz, x, y, z, 0.0, 0.0, 0.0,
-                                                                dx, dy, dz);
-                } else {
-                    d = load_global(F.rec32 + j);
-                    const auto *o = as_global((const float *)(F.off + j));
-                    const float x = o[0], y = o[1], z = o[2];
-                    if (img != kImgPair)
-                        r2 = separation<PREC, kImgNone, float>(bx, hfx, hfy, hfz, x, y, z, tab.ox[k],
-                                                               tab.oy[k], tab.oz[k], dx, dy, dz);
-                    else
-                        r2 = separation<PREC, kImgPair, float>(bx, hfx, hfy, hfz, x, y, z, tab.ox[k],
-                                                               tab.oy[k], tab.oz[k], dx, dy, dz);
-                }
-                if (j != self) {
-                    limiter(j);
-                    pair_terms(j, d, dx, dy, dz, r2);
-                } else {
-                    selfs++;
-                }
-            }
+        const HomeUnits units = home_operand<G, PREC>(H, home, home.hmax, op);
+        const Real reach2 = (Real)hi2x4;
+        auto reached = [&](const Node &nd) {
+            const double hk = RK * nd.hmax;
+            return leaf_in_reach<G, PREC>(H, nd, bx, hk * hk);
         };
         const int depth = group_depth<G>(wr.n, B.stage > 0 ? B.stage * G / 2 : kGroup);
         int64_t at = 0;
         const uint32_t *leaves = nullptr;
         for (;;) {
-            const int ng = next_group(T, F.nodes, wr, test, wb, depth, at, leaves);
+            const int ng = next_group<true>(T, F.nodes, wr, test, reached, wb, depth, at, leaves);
             if (ng == 0) break;
-            uint64_t lmask;
-            const int img = open_group<G, PREC, K>(leaves, ng, F.lstart, F.nodes, home, bx, -1.0, H,
-                                                   takes_part, tab, lmask);
-            int tested = 0;
-            const bool diag = F.count_tests != 0;
-            // a candidate's own squared gather reach (R h)^2
-            auto load = [&](uint32_t j) {
-                const double hj = as_global(F.h)[j];
-                return (Real)((RK * hj) * (RK * hj));
+            const int img = open_group<G, PREC, K>(leaves, ng, F.lstart, F.nodes, home, bx, -1.0, tab, H, 0, nullptr);
+            if (F.count_tests) {
+                count_up(kCntForceBoxes, ng);
+                count_up(kCntForceTests, ng * G * (int)__popcll(__ballot(active && q == 0)));
+            }
+            // the pairs this particle's list holds, its lanes sharing them
+            // round-robin: those within its own or the neighbour's reach, except
+            // the particle itself
+            auto use = [&](int n) {
+                const uint32_t self = (uint32_t)i;
+                const uint16_t *id = S.id + p * Words<G>::cap;
+                for (int e = q; e < n; e += LPP) {
+                    const int s = id[e];
+                    const uint2 jm = tab.jm[s / G];
+                    const uint32_t j = jm.x + (uint32_t)(s % G);
+                    Real dx, dy, dz, w;
+                    JData d;
+                    if constexpr (F64) d = load_global(F.rec + j);
+                    else d = load_global(F.rec32 + j);
+                    const Real r2 = group_separation<PREC, Real>(
+                        tab, img, bx, F64 ? (Real)hx : (Real)hfx, F64 ? (Real)hy : (Real)hfy,
+                        F64 ? (Real)hz : (Real)hfz, s / G, jm, j, F.pos, F.off, dx, dy, dz, w);
+                    if ((r2 < reach2 || r2 < w) && j != self) {
+                        cnt++;
+                        limiter(j);
+                        pair_terms(j, d, dx, dy, dz, r2);
+                    }
+                }
             };
-            // the particle itself passes too; the flush drops it
-            auto hit = [&](Real r2, Real thr, Real w) { return __ballot(r2 < thr) | __ballot(r2 < w); };
-            auto put = [&](uint32_t at, uint32_t rank, int s, Real, Real) { S.id[at + rank] = (uint16_t)s; };
-            int held = 0;              // lane p: hits held of home particle p
-            for (;;) {
-                int full;
-                if (img == kImgNone || (img == kImgShift && !F64))
-                    full = test_rows<G, PREC, kImgNone, kRows>(tab, H, ng, bx, F.pos, F.off, lmask, held, CAP,
-                                                               diag, tested, load, hit, put);
-                else if (img == kImgShift)
-                    full = test_rows<G, PREC, F64 ? kImgShift : kImgNone, kRows / 2>(
-                        tab, H, ng, bx, F.pos, F.off, lmask, held, CAP, diag, tested, load, hit, put);
-                else
-                    full = test_rows<G, PREC, kImgPair, kRows / 2>(tab, H, ng, bx, F.pos, F.off, lmask, held,
-                                                                   CAP, diag, tested, load, hit, put);
-                wave_lds_sync();
-                const int n = __shfl(held, p);
-                cnt += n;
-                flush(n, img);
-                held = 0;
-                wave_lds_sync();
-                if (full < 0) break;
-            }
-            if (diag) {
-                count_up(kCntForceBoxes, ng * (int)__popcll(takes_part));
-                count_up(kCntForceTests, tested * kWave);
-            }
+            group_pairs<G, PREC, true>(tab, home, bx, ng, img, op, units, F.pos, F.off, S.id, use);
         }
         axi = group_sum<LPP>(axi);
         ayi = group_sum<LPP>(ayi);
         azi = group_sum<LPP>(azi);
         dui = group_sum<LPP>(dui);
         vs_max = group_max<LPP>(vs_max);
-        selfs = group_sum<LPP>(selfs);
-        cnt -= selfs;
+        cnt = group_sum<LPP>(cnt);
         if (F.lev) lmx_l = group_max_int<LPP>(lmx_l);
         if constexpr (SW) {
             dvs = group_sum<LPP>(dvs);

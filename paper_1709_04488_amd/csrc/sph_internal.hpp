@@ -195,12 +195,13 @@ struct alignas(32) ForceRec32 {
 
 // A particle's position as the pair loops' candidate loads read it: FP64, or
 // in FP32-pair mode the single-precision offset from the centre of its leaf.
-// One record per particle: a row of 64 candidates takes two or one wide loads.
+// One record per particle, which also carries the squared gather reach (R h)^2
+// once the force records are written.
 struct alignas(32) Pos4 {
-    double x, y, z, pad;
+    double x, y, z, reach2;
 };
 struct alignas(16) Off4 {
-    float x, y, z, pad;
+    float x, y, z, reach2;
 };
 static_assert(sizeof(Pos4) == sizeof(ForceRec32), "they share memory");
 
