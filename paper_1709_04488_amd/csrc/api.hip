@@ -304,7 +304,7 @@ sph_status build_from(sph_ctx *c, const sph_particles *ps, bool with_m)
     const int64_t n = ps->n;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     timer_begin(c, 2, &e0, &e1);
-    TRY(build_order(c, n, ps->x, ps->y, ps->z));
+    TRY(build_order(c, n, ps->x, ps->y, ps->z, false));
     GatherList g{};
     const void *src[] = {ps->x, ps->y, ps->z, ps->h, ps->m};
     void *dst[] = {c->s.x, c->s.y, c->s.z, c->s.h, c->s.m};
@@ -377,7 +377,7 @@ sph_status forces_pre(sph_ctx *c, const sph_particles *ps)
     if (n == 0) return SPH_OK;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (!reuse) {
-        TRY(build_order(c, n, ps->x, ps->y, ps->z));
+        TRY(build_order(c, n, ps->x, ps->y, ps->z, false));
         c->built = true;
         c->built_x = ps->x;
         c->built_n = n;
@@ -430,7 +430,7 @@ sph_status step_pre(sph_ctx *c, double dt)
     TRY(kick_drift(c, n, dt));
     hipEvent_t e0 = nullptr, e1 = nullptr;
     timer_begin(c, 2, &e0, &e1);
-    TRY(build_order(c, n, c->s.x, c->s.y, c->s.z));
+    TRY(build_order(c, n, c->s.x, c->s.y, c->s.z, true));
     GatherList g{};
     Sorted &S = c->s, &T = c->t;
     double **sa[] = {&S.x, &S.y, &S.z, &S.vx, &S.vy, &S.vz, &S.m, &S.u, &S.h,
@@ -549,7 +549,7 @@ sph_status evaluate_pre(sph_ctx *c, const sph_particles *ps, bool laid_out = fal
     // device from the density loop to the force loop
     hipEvent_t e0 = nullptr, e1 = nullptr;
     timer_begin(c, 2, &e0, &e1);
-    TRY(build_order(c, n, ps->x, ps->y, ps->z));
+    TRY(build_order(c, n, ps->x, ps->y, ps->z, false));
     GatherList g{};
     const void *src[] = {ps->x, ps->y, ps->z, ps->h, ps->m, ps->u, ps->vx, ps->vy, ps->vz,
                          ps->alpha};
@@ -986,7 +986,7 @@ sph_status sph_upload_state(sph_ctx *c, const sph_particles *ps)
     c->n = n;
     if (n == 0) return fail(c, SPH_EINVAL, "resident state needs n > 0");
     drop_graph(c);
-    TRY(build_order(c, n, ps->x, ps->y, ps->z));
+    TRY(build_order(c, n, ps->x, ps->y, ps->z, true));
     GatherList g{};
     const void *src[] = {ps->x, ps->y, ps->z, ps->vx, ps->vy, ps->vz, ps->m, ps->u, ps->h,
                          ps->alpha};
@@ -1047,7 +1047,7 @@ static sph_status substep_pre(sph_ctx *c)
     // re-sort: everything that persists per particle moves with it
     hipEvent_t e0 = nullptr, e1 = nullptr;
     timer_begin(c, 2, &e0, &e1);
-    TRY(build_order(c, n, S.x, S.y, S.z));
+    TRY(build_order(c, n, S.x, S.y, S.z, true));
     GatherList g{};
     double **sa[] = {&S.x, &S.y, &S.z, &S.vx, &S.vy, &S.vz, &S.m, &S.u, &S.h, &S.vhx, &S.vhy,
                      &S.vhz, &S.uh, &S.ax, &S.ay, &S.az, &S.du, &S.rho, &S.omega, &S.dt, &S.vsig};
@@ -1369,7 +1369,7 @@ sph_status sph_mfv_gradients(sph_ctx *c, sph_mfv_set *s)
     double *gs[12] = {S.vpx, S.vpy, S.vpz, S.up, S.al, S.alp, S.adot, S.dprev, S.curlv,
                       T.x, T.y, T.z};
     double *conds = S.divv;
-    TRY(build_order(c, n, s->x, s->y, s->z));
+    TRY(build_order(c, n, s->x, s->y, s->z, false));
     GatherList g{};
     const void *src[] = {s->x, s->y, s->z, s->h};
     void *dst[] = {S.x, S.y, S.z, S.h};

@@ -105,7 +105,10 @@ __device__ inline uint64_t spread3(uint64_t v)
 // particles in FP64: 6.10 -> 5.16 ms per evaluation, keys 21.5 -> 24 us.
 // FP32-pair keeps the Morton order: its separations are differences of offsets
 // rounded against the leaf centres, so other leaves would change results in
-// their seventh digit.
+// their seventh digit.  So do resident states: the neighbour counts of
+// particles that a sub-step leaves inactive stay at their place in the order
+// when it changes, so another order would hand them to other particles, and a
+// full sub-step gives the bits of a global step.
 struct HilbertTable {
     uint8_t v[24 * 8];
 };
@@ -753,7 +756,8 @@ static inline unsigned grid_for(int64_t n, int threads)
     return (unsigned)((n + threads - 1) / threads);
 }
 
-sph_status build_order(sph_ctx *c, int64_t n, const double *x, const double *y, const double *z)
+sph_status build_order(sph_ctx *c, int64_t n, const double *x, const double *y, const double *z,
+                       bool state)
 {
     if (n == 0) return SPH_OK;
     const sph_params &p = c->p;
@@ -769,8 +773,9 @@ sph_status build_order(sph_ctx *c, int64_t n, const double *x, const double *y, 
         hipLaunchKernelGGL(k_box_final, dim3(1), dim3(64), 0, c->stream, nb, c->d_part, c->d_box);
     }
     const int bits = key_bits(n);
+    const int hilbert = p.precision == SPH_FP64 && !state ? 1 : 0;
     hipLaunchKernelGGL(k_keys, dim3(grid_for(n, 256)), dim3(256), 0, c->stream, n, x, y, z,
-                       c->d_box, fb, bits, c->p.precision == SPH_FP64 ? 1 : 0, c->keys[0], c->vals[0]);
+                       c->d_box, fb, bits, hilbert, c->keys[0], c->vals[0]);
     // small sets: tiles of 1024 keys (more, shorter blocks); up to
     // kRsRawTiles tiles the scatter blocks form the digit offsets from the raw
     // counts themselves (one launch fewer per pass).  A stable sort's result

@@ -615,24 +615,26 @@ __device__ inline uint32_t rank_of(uint64_t m)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// Above this many candidate leaves (an ordinary home leaf has 60-110) the home
-// leaf's box is wide against its particles' reaches, and each candidate leaf is
-// also tested against every home particle.
+// Above this many candidate leaves (an ordinary home leaf has 50-110) the home
+// leaf's box is wide against its particles' reaches -- the outermost leaves of a
+// condensed set see every leaf of it -- and the walk is repeated with a test of
+// each node against every home particle.  Plummer sphere of 100,003 particles:
+// 1 % of the home leaves had 2,000 to 6,400 candidate leaves, and the launch
+// lasted as long as they did.
 constexpr int kManyLeaves = 160;
 
-// Whether a leaf's box is near enough to some home particle to hold a pair of
-// it: the leaf's largest gather reach squared counts too (reach2 >= 0, forces).
-// The relative slack covers the rounding of the differently formed distances
+// Whether a node's box is within reach of some home particle that takes part (a
+// bit of `part`): its own squared reach in H or lim2, whichever is larger.  The
+// relative slack covers the rounding of the differently formed distances
 // (FP32-pair separations carry single-precision error).
 template <int G, int PREC>
-__device__ inline bool leaf_in_reach(const HomeTab<G, PREC> &H, const Node &nd, const Box &bx, double reach2)
+__device__ inline bool node_in_reach(const HomeTab<G, PREC> &H, uint64_t part, const Node &nd, const Box &bx,
+                                     double lim2)
 {
     constexpr double slack = PREC == SPH_FP64 ? 1.0 + 1e-6 : 1.0 + 1e-4;
     bool any = false;
-    // (not unrolled: the home table would be held in registers)
-#pragma unroll 1
-    for (int p = 0; p < G; p++) {
-        const HomeRow h = H.d[p];
+    for (; part; part &= part - 1) {
+        const HomeRow h = H.d[__builtin_ctzll(part)];
         const double c[3] = {h.x, h.y, h.z};
         double d2 = 0.0;
 #pragma unroll
@@ -642,21 +644,33 @@ __device__ inline bool leaf_in_reach(const HomeTab<G, PREC> &H, const Node &nd, 
             const double g = fmax(d - nd.e[a], 0.0);
             d2 += g * g;
         }
-        any = any || (h.thr >= 0.0 && d2 <= fmax(h.thr, reach2) * slack);
+        any = any || d2 <= fmax(h.thr, lim2) * slack;
     }
     return any;
 }
 
+// The lanes' flags (the same on all lanes of a particle) as a bit per particle.
+template <int G>
+__device__ inline uint64_t particle_bits(bool flag)
+{
+    constexpr int LPP = kWave / G;
+    const uint64_t lanes = __ballot(flag);
+    uint64_t bits = 0;
+#pragma unroll
+    for (int k = 0; k < G; k++) bits |= ((lanes >> (k * LPP)) & 1ull) << k;
+    return bits;
+}
+
 // The next group of at most `depth` candidate leaves of a walk's result
-// (0: none left): a slice of the list, or, where the walk was truncated or
-// (FILTER) the list is long, the leaves (under the listed nodes) that pass
-// test(node) and near(node), up to 64 of them collected in wb.tmp.
-template <bool FILTER, class Test, class Near>
+// (0: none left): a slice of the list, or, where the walk was truncated, the
+// leaves under the listed nodes that pass the test, up to 64 of them collected
+// in wb.tmp.
+template <class Test>
 __device__ inline int next_group(const TreeInfo &T, const Node *nodes, const WalkResult &wr,
-                                 Test test, Near near, WalkBuf &wb, int depth, int64_t &pos,
+                                 Test test, WalkBuf &wb, int depth, int64_t &pos,
                                  const uint32_t *&leaves)
 {
-    if (wr.lev == 0 && (!FILTER || wr.n <= kManyLeaves)) {
+    if (wr.lev == 0) {
         const int left = wr.n - (int)pos;
         if (left <= 0) return 0;
         leaves = wr.list + pos;
@@ -672,11 +686,7 @@ __device__ inline int next_group(const TreeInfo &T, const Node *nodes, const Wal
     while (pos < total) {
         const int64_t t = pos + lane;
         const int64_t c = t < total ? ((int64_t)wr.list[t >> sh] << sh) + (t & ((1ll << sh) - 1)) : L;
-        bool pass = false;
-        if (c < L) {
-            const Node nd = load_global(nodes + c);
-            pass = (wr.lev == 0 || test(nd)) && (!FILTER || near(nd));
-        }
+        const bool pass = c < L && test(load_global(nodes + c));
         const uint64_t mask = __ballot(pass);
         const int n = (int)__popcll(mask);
         if (have + n > kGroup) break;   // the next group starts with these
@@ -860,7 +870,7 @@ __device__ inline int test_rows(const LeafTab<SPH_FP64> &tab, const HomeTab<G, S
 {
     constexpr int LPR = kWave / G;                      // leaves per row
     constexpr uint32_t RM = (1u << LPR) - 1;            // one row's leaves
-    constexpr uint32_t BM = NR * LPR >= 32 ? ~0u : (1u << (NR * LPR)) - 1;
+    constexpr uint32_t BM = (uint32_t)((1ull << (NR * LPR)) - 1);
     static_assert(NR * LPR <= 32, "a block's leaves fit 32 bits");
     const int lane = threadIdx.x & (kWave - 1);
     const int nrows = (count + LPR - 1) / LPR;
@@ -1424,26 +1434,21 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
         }
 
         double hcov = A.walk_margin * wave_max(active ? h : 0.0);
-        auto near_home = [&](const Node &home, const Box &bx) {
+        // A node can hold neighbours if its box is within R hcov of the home leaf's
+        // box, and (`close`) within R hw of some home particle, hw the walk's
+        // margin over its h
+        bool close = false;
+        double hw = hcov;
+        auto near_home = [&](const Node &home, const Box &bx, uint64_t part) {
             const double R = RK * hcov * (1.0 + 1e-10);
             const double R2 = R * R;
-            return [&bx, &home, R2](const Node &nd) { return box_gap2(home, nd, bx) < R2; };
+            const bool cl = close;
+            return [&bx, &home, R2, part, cl](const Node &nd) {
+                return box_gap2(home, nd, bx) < R2 && (!cl || node_in_reach<G, PREC>(H, part, nd, bx, -1.0));
+            };
         };
-        auto walk_home = [&]() {
-            const Node home = load_const(reload(A.nodes) + leaf);
-            const Box bx = load_const(&reload(B.req[r])->box);
-            const WalkResult w = walk(T, A.nodes, near_home(home, bx), wb, S.walk_spare);
-            count_up(kCntDensWalks, 1);
-            if (w.lev) count_up(kCntDensOverflows, 1);
-            return w;
-        };
-        // the walk and the candidate loads are chains of dependent loads: the
-        // wave issues them at raised priority, ahead of waves in their
-        // arithmetic (measured: the force loop 1 % faster, the density loop
-        // unchanged)
-        __builtin_amdgcn_s_setprio(2);
-        WalkResult wr = walk_home();
-        __builtin_amdgcn_s_setprio(0);
+        WalkResult wr{0, 0, nullptr};
+        bool walked = false;
         int iter = 0;
         int evals_leaf = 0;   // this lane's density pairs evaluated for this leaf
         // list state of this particle: `cached` = the list holds every
@@ -1452,6 +1457,30 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
         double Rc = 0.0;
         int count = 0;
         for (;;) {
+            if (!walked) {
+                // the walk and the candidate loads are chains of dependent loads:
+                // the wave issues them at raised priority, ahead of waves in their
+                // arithmetic (measured: the force loop 1 % faster, the density
+                // loop unchanged)
+                __builtin_amdgcn_s_setprio(2);
+                const Node home = load_const(reload(A.nodes) + leaf);
+                const Box bx = load_const(&reload(B.req[r])->box);
+                const uint64_t part = particle_bits<G>(!conv);
+                close = false;
+                hw = hcov;
+                for (;;) {
+                    wr = walk(T, A.nodes, near_home(home, bx, part), wb, S.walk_spare);
+                    count_up(kCntDensWalks, close ? 0 : 1);
+                    if (!close && wr.lev) count_up(kCntDensOverflows, 1);
+                    if (close || (wr.lev == 0 && wr.n <= kManyLeaves)) break;
+                    close = true;
+                    hw = A.walk_margin * h;
+                    if (q == 0) H.d[p].thr = (RK * hw) * (RK * hw);
+                    wave_lds_sync();
+                }
+                __builtin_amdgcn_s_setprio(0);
+                walked = true;
+            }
             const double hinv = 1.0 / h;
             const double h2x4 = (RK * h) * (RK * h);
             uint64_t emptied = 0;   // bit p: home particle p's list was, in this sweep
@@ -1547,7 +1576,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                 // steps then
                 double rc2 = -1.0;
                 if (!conv) {
-                    Rc = fmin(kCacheGrow * h, hcov);
+                    Rc = fmin(kCacheGrow * h, hw);
                     rc2 = (RK * Rc) * (RK * Rc);
                 }
                 wave_lds_sync();
@@ -1558,21 +1587,15 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                 const Box bx = load_const(&reload(B.req[r])->box);
                 HomeUnits units{};
                 if constexpr (!F64) units = home_operand<G, PREC>(H, home, hcov, op);
-                uint64_t takes_part = 0;   // bit p: home particle p
-                {
-                    const uint64_t lanes_in = __ballot(!conv);
-#pragma unroll
-                    for (int k = 0; k < G; k++) takes_part |= ((lanes_in >> (k * LPP)) & 1ull) << k;
-                }
+                const uint64_t takes_part = particle_bits<G>(!conv);
                 const int depth = group_depth<G>(wr.n, B.stage > 0 ? B.stage * G / 2 : kGroup);
                 count = 0;
                 int held = 0;              // FP64: entries of home particle `lane`'s list
                 int64_t at = 0;
                 const uint32_t *leaves = nullptr;
-                auto test = near_home(home, bx);
-                auto reached = [&](const Node &nd) { return leaf_in_reach<G, PREC>(H, nd, bx, -1.0); };
+                auto test = near_home(home, bx, takes_part);
                 for (;;) {
-                    const int ng = next_group<!F64>(T, Q.nodes, wr, test, reached, wb, depth, at, leaves);
+                    const int ng = next_group(T, Q.nodes, wr, test, wb, depth, at, leaves);
                     if (ng == 0) break;
                     const int img = open_group<G, PREC, K>(leaves, ng, Q.lstart, Q.nodes, home, bx, hcov, tab, H,
                                                            takes_part, F64 ? near_of : nullptr);
@@ -1784,12 +1807,9 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
             if (cached && !(h <= Rc)) cached = false;
             iter++;
             if (__ballot(!conv) == 0ull || iter >= A.max_iter) break;
-            const double hmx = wave_max(conv ? 0.0 : h);
-            if (hmx > hcov) {
-                hcov = A.walk_margin * hmx;
-                __builtin_amdgcn_s_setprio(2);
-                wr = walk_home();
-                __builtin_amdgcn_s_setprio(0);
+            if (__ballot(!conv && h > hw) != 0ull) {
+                hcov = A.walk_margin * wave_max(conv ? 0.0 : h);
+                walked = false;
             }
         }
         bool bad = false, slow = false, wide = false;
@@ -1903,16 +1923,26 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
             if constexpr (!F64) H.f[p] = HomeRowF{hfx, hfy, hfz, 0.f};
         }
         // symmetric criterion: a node can hold force neighbours of the home leaf
-        // if its box is closer than 2 max(h over home, h over node)
-        auto test = [&bx, &home](const Node &nd) {
+        // if its box is closer than R max(h over home, h over node), and (`close`)
+        // of some home particle if it is closer than R max(h, h over node)
+        const uint64_t part = particle_bits<G>(active);
+        bool close = false;
+        auto test = [&](const Node &nd) {
             const double R = RK * fmax(home.hmax, nd.hmax) * (1.0 + 1e-10);
-            return box_gap2(home, nd, bx) < R * R;
+            const double hk = RK * nd.hmax;
+            return box_gap2(home, nd, bx) < R * R &&
+                   (!close || node_in_reach<G, PREC>(H, part, nd, bx, hk * hk));
         };
         // walk and candidate loads at raised priority, as in the density loop
         __builtin_amdgcn_s_setprio(2);
-        const WalkResult wr = walk(T, F.nodes, test, wb, S.walk_spare);
+        WalkResult wr;
+        for (;;) {
+            wr = walk(T, F.nodes, test, wb, S.walk_spare);
+            if (!close && wr.lev) count_up(kCntForceOverflows, 1);
+            if (close || (wr.lev == 0 && wr.n <= kManyLeaves)) break;
+            close = true;
+        }
         __builtin_amdgcn_s_setprio(0);
-        if (wr.lev) count_up(kCntForceOverflows, 1);
 
         double axi = 0.0, ayi = 0.0, azi = 0.0, dui = 0.0, vs_max = -INFINITY;
         double dvs = 0.0, cxs = 0.0, cys = 0.0, czs = 0.0;   // div v, curl v sums (SW)
@@ -2041,15 +2071,11 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
         };
         const HomeUnits units = home_operand<G, PREC>(H, home, home.hmax, op);
         const Real reach2 = (Real)hi2x4;
-        auto reached = [&](const Node &nd) {
-            const double hk = RK * nd.hmax;
-            return leaf_in_reach<G, PREC>(H, nd, bx, hk * hk);
-        };
         const int depth = group_depth<G>(wr.n, B.stage > 0 ? B.stage * G / 2 : kGroup);
         int64_t at = 0;
         const uint32_t *leaves = nullptr;
         for (;;) {
-            const int ng = next_group<true>(T, F.nodes, wr, test, reached, wb, depth, at, leaves);
+            const int ng = next_group(T, F.nodes, wr, test, wb, depth, at, leaves);
             if (ng == 0) break;
             const int img = open_group<G, PREC, K>(leaves, ng, F.lstart, F.nodes, home, bx, -1.0, tab, H, 0, nullptr);
             if (F.count_tests) {

@@ -362,8 +362,9 @@ sph_status ensure_capacity(sph_ctx *c, int64_t n);
 
 // ---- build.hip ---------------------------------------------------------------
 // Bounding box, keys, sort: fills c->perm (sorted -> source) for n positions.
+// `state`: the positions of a resident state (they keep the Morton order).
 sph_status build_order(sph_ctx *c, int64_t n, const double *x, const double *y,
-                       const double *z);
+                       const double *z, bool state);
 // Gather `count` arrays through c->perm: dst[k] = src[perm[k]].
 struct GatherList {
     int32_t count;
