@@ -778,17 +778,17 @@ sph_status sph_create(sph_ctx **out, const sph_params *p, void *hip_stream, size
     init_static_scratch(c);
     bool ok = hipMalloc((void **)&c->d_status, sizeof(int32_t) * kStatusWords) == hipSuccess &&
               hipMalloc((void **)&c->d_scal, sizeof(double) * 16) == hipSuccess &&
-              hipMalloc((void **)&c->d_counts, sizeof(int64_t) * kCountWords) == hipSuccess &&
+              hipMalloc((void **)&c->d_counts, sizeof(int64_t) * kCountRows * kCountWords) == hipSuccess &&
               hipMalloc((void **)&c->d_box, sizeof(double) * 8) == hipSuccess &&
               hipMalloc((void **)&c->d_part, sizeof(double) * 1024 * 8) == hipSuccess &&
               hipMalloc((void **)&c->d_tree, sizeof(TreeInfo)) == hipSuccess &&
-              hipMalloc((void **)&c->d_work, sizeof(uint32_t) * 64) == hipSuccess &&
+              hipMalloc((void **)&c->d_work, sizeof(uint32_t) * kXcds * kWorkStride) == hipSuccess &&
               hipMalloc(&c->d_dargs, kArgBytes) == hipSuccess &&
               hipMalloc(&c->d_fargs, kArgBytes) == hipSuccess &&
               hipMalloc((void **)&c->d_clock, sizeof(BlockClock)) == hipSuccess &&
               hipHostMalloc((void **)&c->h_status, sizeof(int32_t) * kStatusWords) == hipSuccess &&
               hipHostMalloc((void **)&c->h_scal, sizeof(double) * 16) == hipSuccess &&
-              hipHostMalloc((void **)&c->h_counts, sizeof(int64_t) * kCountWords) == hipSuccess &&
+              hipHostMalloc((void **)&c->h_counts, sizeof(int64_t) * kCountRows * kCountWords) == hipSuccess &&
               hipHostMalloc((void **)&c->h_clock, sizeof(BlockClock)) == hipSuccess;
     if (!ok) {
         (void)hipGetLastError();
@@ -801,7 +801,7 @@ sph_status sph_create(sph_ctx **out, const sph_params *p, void *hip_stream, size
     // middle of the first calls' work
     ok = hipMemsetAsync(c->d_status, 0, sizeof(int32_t) * kStatusWords, c->stream) == hipSuccess &&
          hipMemsetAsync(c->d_scal, 0, sizeof(double) * 16, c->stream) == hipSuccess &&
-         hipMemsetAsync(c->d_counts, 0, sizeof(int64_t) * kCountWords, c->stream) == hipSuccess &&
+         hipMemsetAsync(c->d_counts, 0, sizeof(int64_t) * kCountRows * kCountWords, c->stream) == hipSuccess &&
          hipMemsetAsync(c->d_clock, 0, sizeof(BlockClock), c->stream) == hipSuccess &&
          hipStreamSynchronize(c->stream) == hipSuccess;
     if (!ok) { sph_destroy(c); return SPH_EDEVICE; }
@@ -1262,13 +1262,18 @@ sph_status sph_state_info(sph_ctx *c, sph_state_stats *info)
     const bool block = c->p.block_lmax > 0 && c->resident;
     TRY(hip_check(c, hipMemcpyAsync(c->h_scal, c->d_scal, sizeof(double) * 8,
                                     hipMemcpyDeviceToHost, c->stream), "copy scalars"));
-    TRY(hip_check(c, hipMemcpyAsync(c->h_counts, c->d_counts, sizeof(int64_t) * kCountWords,
+    TRY(hip_check(c, hipMemcpyAsync(c->h_counts, c->d_counts, sizeof(int64_t) * kCountRows * kCountWords,
                                     hipMemcpyDeviceToHost, c->stream), "copy counts"));
     if (block)
         TRY(hip_check(c, hipMemcpyAsync(c->h_clock, c->d_clock, sizeof(BlockClock),
                                         hipMemcpyDeviceToHost, c->stream), "copy block clock"));
     TRY(hip_check(c, hipStreamSynchronize(c->stream), "hipStreamSynchronize"));
-    const int64_t *counts = c->h_counts;
+    int64_t counts[kCountWords] = {};
+    for (int r = 0; r < kCountRows; r++)
+        for (int k = 0; k < kCountWords; k++) {
+            const int64_t v = c->h_counts[r * kCountWords + k];
+            counts[k] = k == kCntNrMax ? std::max(counts[k], v) : counts[k] + v;
+        }
     std::memset(info, 0, sizeof(*info));
     info->dt_next = c->h_scal[0];
     info->dt_last = c->h_scal[1];

@@ -59,14 +59,14 @@ __global__ void k_prologue(Args a, Args *dst, int64_t *__restrict__ counts, int 
 {
     const int t = threadIdx.x;
     if (t == 0) *dst = a;
-    if (t < nwords) counts[first + t] = 0;
-    if (t < nwords2) counts[first2 + t] = 0;
-    if (t < kXcds) work[t] = 0u;
+    for (int k = 0; k < nwords; k++) counts[t * kCountWords + first + k] = 0;
+    for (int k = 0; k < nwords2; k++) counts[t * kCountWords + first2 + k] = 0;
+    if (t < kXcds) work[t * kWorkStride] = 0u;
 }
 
 static_assert(sizeof(DensArgs) <= kArgBytes, "density argument block too large");
 static_assert(sizeof(ForceArgs) <= kArgBytes, "force argument block too large");
-static_assert(kCntDensWords <= 64 && kCntForceWords <= 64, "prologue zeroes one word per lane");
+static_assert(kCountRows == 64, "the prologue zeroes a row per lane");
 
 } // namespace
 

@@ -228,6 +228,9 @@ __device__ inline void for_each_home_leaf(int64_t L, uint32_t *__restrict__ work
     const int x0 = (int)(blockIdx.x % kXcds);
     const uint32_t rank = blockIdx.x / kXcds;          // among the blocks of eighth x0
     const uint32_t nstatic = gridDim.x / kXcds;        // static first claims per eighth
+    // small sets: the first claims take everything, and no block asks the
+    // counters (1,000 particles as 1,008 waves: 54 -> 36 us of the force loop)
+    const bool all_static = (int64_t)nstatic * claim >= per;
     for (int r = 0; r < kXcds; r++) {
         const int x = (x0 + r) % kXcds;
         const int64_t beg = x * per;
@@ -237,7 +240,8 @@ __device__ inline void for_each_home_leaf(int64_t L, uint32_t *__restrict__ work
         for (int k = 0;; k++) {
             uint32_t c = rank;
             if (r > 0 || k > 0 || rank >= nstatic) {   // (a grid not a multiple of 8)
-                if (lane == 0) c = nstatic + atomicAdd(&work[x], 1u);
+                if (all_static) return;
+                if (lane == 0) c = nstatic + atomicAdd(&work[x * kWorkStride], 1u);
                 // wave-uniform from here on (scalar registers): the leaf's
                 // argument block, node and particle range are then loaded once
                 // per wave
@@ -1388,7 +1392,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
     // flushed when the wave moves to another request
     auto flush_counts = [&]() {
         if (cur >= 0 && tally != 0) {
-            unsigned long long *to = (unsigned long long *)&Ap->counts[lane];
+            unsigned long long *to = (unsigned long long *)&Ap->counts[blockIdx.x % kCountRows * kCountWords + lane];
             if (lane == kCntNrMax) atomicMax(to, (unsigned long long)tally);
             else atomicAdd(to, (unsigned long long)tally);
         }
@@ -1870,7 +1874,8 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
     const __attribute__((address_space(4))) ForceArgs *Fp = nullptr;
     auto flush_counts = [&]() {
         if (cur >= 0 && tally != 0)
-            atomicAdd((unsigned long long *)&Fp->counts[lane], (unsigned long long)tally);
+            atomicAdd((unsigned long long *)&Fp->counts[blockIdx.x % kCountRows * kCountWords + lane],
+                      (unsigned long long)tally);
         tally = 0;
     };
     for_each_home_leaf(pre[B.nreq], B.work, B.claim, [&](int64_t gleaf) {

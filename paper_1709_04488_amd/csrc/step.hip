@@ -940,7 +940,7 @@ sph_status reduce_dt(sph_ctx *c, int64_t n)
 
 __global__ void k_zero_work(uint32_t *__restrict__ w)
 {
-    if (threadIdx.x < kXcds) w[threadIdx.x] = 0u;
+    if (threadIdx.x < kXcds) w[threadIdx.x * kWorkStride] = 0u;
 }
 
 sph_status zero_work(sph_ctx *c)
