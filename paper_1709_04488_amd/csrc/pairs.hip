@@ -168,22 +168,26 @@ sph_status density_launch(sph_ctx *const *cs, int count, int64_t nmax)
     B.claim = c->p.claim_leaves > 0 ? c->p.claim_leaves : 1;
     B.stage = c->p.stage_leaves;
     B.work = c->d_work;
-    int64_t leaves_bound = 0;
+    int64_t leaves_bound = 0, items_bound = 0;
     for (int r = 0; r < count; r++) {
         B.req[r] = (const DensArgs *)cs[r]->d_dargs;
+        const bool splits = splits_density(cs[r]->p.precision, cs[r]->p.periodic);
+        const int k = slice_split(cs[r]->n, c->p.leaf_size, splits);
+        B.split = r == 0 || k < B.split ? k : B.split;
         leaves_bound += cs[r]->n;
+        items_bound += cs[r]->n << (splits ? split_of(cs[r]->n, c->p.leaf_size) : 0);
     }
     if (leaves_bound > (int64_t)0xFFFFFFFFll)
         return fail(c, SPH_EINVAL, "a batch holds more than 2^32 - 1 particles");
     (void)nmax;
-    unsigned grid = pair_grid(leaves_bound);
+    unsigned grid = pair_grid(items_bound);
     // the candidate lists of the set whose scratch serves the most blocks at
     // this leaf size; the grid never exceeds it
     const sph_ctx *owner = nullptr;
     for (int r = 0; r < count; r++)
         if (cs[r]->cache && (!owner || cs[r]->cache_size > owner->cache_size)) owner = cs[r];
     const int64_t blocks =
-        owner ? owner->cache_size / cache_bytes(c->p.leaf_size, c->p.kernel, 1) : 0;
+        owner ? (owner->cache_size << B.split) / cache_bytes(c->p.leaf_size, c->p.kernel, 1) : 0;
     if (blocks < kXcds) return fail(c, SPH_ESTATE, "density: no candidate-list scratch");
     B.cache = owner->cache;
     if ((int64_t)grid > blocks) grid = (unsigned)(blocks / kXcds * kXcds);
@@ -207,15 +211,16 @@ sph_status forces_launch(sph_ctx *const *cs, int count, int64_t nmax)
     B.claim = c->p.claim_leaves > 0 ? c->p.claim_leaves : 1;
     B.stage = c->p.stage_leaves;
     B.work = c->d_work;
-    int64_t leaves_bound = 0;
+    int64_t leaves_bound = 0, items_bound = 0;
     for (int r = 0; r < count; r++) {
         B.req[r] = (const ForceArgs *)cs[r]->d_fargs;
         leaves_bound += cs[r]->n;
+        items_bound += cs[r]->n << split_of(cs[r]->n, c->p.leaf_size);
     }
     if (leaves_bound > (int64_t)0xFFFFFFFFll)
         return fail(c, SPH_EINVAL, "a batch holds more than 2^32 - 1 particles");
     (void)nmax;
-    const unsigned grid = pair_grid(leaves_bound);
+    const unsigned grid = pair_grid(items_bound);
     bool ac = false, sw = false;
     for (int r = 0; r < count; r++) {
         ac = ac || cs[r]->p.alpha_ac != 0.0;

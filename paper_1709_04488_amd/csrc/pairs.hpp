@@ -143,6 +143,23 @@ __device__ inline double group_max(double v)
     return v;
 }
 
+// Reductions over groups of `lanes` lanes (a power of two of at least K,
+// wave-uniform).
+template <int K, class T>
+__device__ inline T lanes_sum(T v, int lanes)
+{
+    v = group_sum<K>(v);
+    for (int o = K; o < lanes; o <<= 1) v += __shfl_xor(v, o);
+    return v;
+}
+template <int K>
+__device__ inline double lanes_max(double v, int lanes)
+{
+    v = group_max<K>(v);
+    for (int o = K; o < lanes; o <<= 1) v = fmax(v, __shfl_xor(v, o));
+    return v;
+}
+
 // Wave-wide maxima: each 16-lane row by DPP, then the four rows' values read
 // into scalar registers (wave-uniform result).
 __device__ inline double wave_max(double v)
@@ -164,6 +181,17 @@ __device__ inline int group_max_int(int v)
     if constexpr (K >= 4) { const int w = xlane<2>(v); v = w > v ? w : v; }
     if constexpr (K >= 8) { const int w = xlane<4>(v); v = w > v ? w : v; }
     if constexpr (K >= 16) { const int w = xlane<8>(v); v = w > v ? w : v; }
+    return v;
+}
+
+template <int K>
+__device__ inline int lanes_max_int(int v, int lanes)
+{
+    v = group_max_int<K>(v);
+    for (int o = K; o < lanes; o <<= 1) {
+        const int w = __shfl_xor(v, o);
+        v = w > v ? w : v;
+    }
     return v;
 }
 
@@ -653,16 +681,13 @@ __device__ inline bool node_in_reach(const HomeTab<G, PREC> &H, uint64_t part, c
     return any;
 }
 
-// The lanes' flags (the same on all lanes of a particle) as a bit per particle.
-template <int G>
-__device__ inline uint64_t particle_bits(bool flag)
+// The lanes' flags (the same on all of a particle's `lpp` lanes) as a bit per
+// particle.
+__device__ inline uint64_t particle_bits(bool flag, int lpp)
 {
-    constexpr int LPP = kWave / G;
-    const uint64_t lanes = __ballot(flag);
-    uint64_t bits = 0;
-#pragma unroll
-    for (int k = 0; k < G; k++) bits |= ((lanes >> (k * LPP)) & 1ull) << k;
-    return bits;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int src = lane * lpp;
+    return __ballot(__shfl(flag ? 1 : 0, src & (kWave - 1)) != 0 && src < kWave);
 }
 
 // The next group of at most `depth` candidate leaves of a walk's result
@@ -1014,7 +1039,8 @@ __device__ inline HomeUnits home_operand(const HomeTab<G, PREC> &H, const Node &
         const float Tw = T * (1.f + kHalfRel) + 2.f * kHalfRel * U.extent + kHalfAbs;
         far = part && !(U.extent + T <= kHalfFar);
         HomeCol c;
-        c.b = Half4{(_Float16)-2 * xy.x, (_Float16)-2 * xy.y, (_Float16)-2 * z0.x, (_Float16)1};
+        c.b = part ? Half4{(_Float16)-2 * xy.x, (_Float16)-2 * xy.y, (_Float16)-2 * z0.x, (_Float16)1}
+                   : Half4{0, 0, 0, 0};
         c.c = part ? n - Tw * Tw : 1e30f;
         c.n = part ? n : 1e30f;
         O.col[lane] = c;
@@ -1040,10 +1066,10 @@ __device__ inline void column_scan(uint32_t v, uint32_t &before, uint32_t &total
 // (FORCE: or the home particle within its reach, which the position records
 // carry squared) is listed for it: ids holds Words<G>::cap slots of the group
 // per home particle, and use(n) is called with this lane's home particle's
-// number n (particle lane / LPP) whenever a list might overflow and at the
+// number n (p: that particle) whenever a list might overflow and at the
 // group's end.  A list's order depends on the particle and the candidates alone.
 template <int G, int PREC, bool FORCE, class Use>
-__device__ inline void group_pairs(const LeafTab<PREC> &tab, const Node &home, const Box &bx, int count, int img,
+__device__ inline void group_pairs(int p, const LeafTab<PREC> &tab, const Node &home, const Box &bx, int count, int img,
                                    const HomeOp<G> &op, const HomeUnits &U, const Pos4 *__restrict__ pos,
                                    const Off4 *__restrict__ off, uint16_t *ids, Use use)
 {
@@ -1182,8 +1208,6 @@ __device__ inline void group_pairs(const LeafTab<PREC> &tab, const Node &home, c
         if (word == words || __ballot(over) != 0ull) {
             __builtin_amdgcn_s_setprio(0);
             wave_lds_sync();
-            constexpr int LPP = kWave / G;
-            const int p = lane / LPP;
             int n = __shfl((int)held[0], p % 16);
             if constexpr (NT == 2) {
                 const int n1 = __shfl((int)held[1], p % 16);
@@ -1224,16 +1248,31 @@ template <int PREC>
 constexpr int pair_waves_per_simd() { return 4; }
 
 
+constexpr int log2_of(int v) { return v > 1 ? 1 + log2_of(v / 2) : 0; }
+
+// Home leaves of a request, and log2 of the waves that share one.
 template <class Args>
-__device__ inline void batch_prefix(const Batch<Args> &B, uint32_t *pre)
+__device__ inline uint32_t home_leaves(const Args &A)
+{
+    return A.leaf_count ? *A.leaf_count : (uint32_t)A.tree->cnt[0];
+}
+template <int G, class Args>
+__device__ inline int home_split(const Args &A, bool splits)
+{
+    if (!splits) return 0;
+    const int all = split_of(A.n, G), some = split_of((int64_t)home_leaves(A) * G, G);
+    return all > some ? all : some;
+}
+
+template <int G, class Args, class Splits>
+__device__ inline void batch_prefix(const Batch<Args> &B, uint32_t *pre, Splits splits)
 {
     // the host keeps the total leaf count (<= total particles) below 2^32
     if (threadIdx.x == 0) {
         uint32_t acc = 0;
         pre[0] = 0;
         for (int r = 0; r < B.nreq; r++) {
-            const uint32_t *lc = B.req[r]->leaf_count;
-            acc += lc ? *lc : (uint32_t)B.req[r]->tree->cnt[0];
+            acc += home_leaves(*B.req[r]) << home_split<G>(*B.req[r], splits(*B.req[r]));
             pre[r + 1] = acc;
         }
     }
@@ -1333,16 +1372,6 @@ __device__ inline void add_entry(Sums<K> &s, double r2, double m, double hinv, d
     }
 }
 
-template <int KK>
-__device__ inline double group_min(double v)
-{
-    if constexpr (KK >= 2) v = fmin(v, xlane<1>(v));
-    if constexpr (KK >= 4) v = fmin(v, xlane<2>(v));
-    if constexpr (KK >= 8) v = fmin(v, xlane<4>(v));
-    if constexpr (KK >= 16) v = fmin(v, xlane<8>(v));
-    return v;
-}
-
 // A tight tolerance: the result then does not depend on how the root was
 // approached, and the polynomial above may stand in for a pass.  With a loose
 // one (the paper's 1 %) the solve stops at whatever h meets it, so it keeps to
@@ -1352,13 +1381,10 @@ constexpr double kTightTol = 1e-9;
 template <int G, int PREC, int K>
 __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(Batch<DensArgs> B)
 {
-    constexpr int LPP = kWave / G;   // lanes per home particle
-    constexpr int KP = Kern<K>::list;
+    constexpr int L0 = kWave / G;   // lanes per home particle of a whole leaf
     constexpr double RK = Kern<K>::R, SIG = Kern<K>::sigma;
     constexpr bool F64 = PREC == SPH_FP64;
-    // list entries that the lanes of a particle read per step: 4 each
-    constexpr int CHUNK = 4 * LPP;
-    static_assert(KP % CHUNK == 0, "lists hold whole steps");
+    static_assert(Kern<K>::list % (4 * L0) == 0, "lists hold whole steps of four entries per lane");
     __shared__ WalkBuf wb;
     __shared__ TreeInfo T;
     __shared__ LeafTab<PREC> tab;
@@ -1370,10 +1396,11 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
     __shared__ HomeOp<F64 ? 0 : G> op;
     __shared__ uint64_t near_of[G];
     __shared__ PartSums part[G];
+    __shared__ double part_edge[F64 ? G : 1];
     __shared__ uint32_t pre[kMaxBatch + 1];
-    batch_prefix(B, pre);
+    auto splits = [](const DensArgs &A) { return splits_density(PREC, A.box.periodic); };
+    batch_prefix<G>(B, pre, splits);
     const int lane = threadIdx.x;
-    const int p = lane / LPP, q = lane % LPP;
     // Candidate lists of this block: for every home particle up to KP entries
     // (r^2, and m unless all masses are equal) of the candidates within R Rc
     // of it, in the order a sweep meets them, one particle after the other.
@@ -1381,13 +1408,14 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
     // as floats (half the bytes, the same values); FP64 lists hold doubles.
     // A particle's lanes read 64 consecutive bytes of its list per load.
     using ListR2 = std::conditional_t<F64, double, float>;
-    double *const cslice = B.cache + (size_t)blockIdx.x * (2 * KP * G);
+    const int slice = (Kern<K>::list * G) >> B.split;
+    double *const cslice = B.cache + (size_t)blockIdx.x * (2 * slice);
     ListR2 *const cr2 = reinterpret_cast<ListR2 *>(cslice);
-    double *const cm = cslice + KP * G;
+    double *const cm = cslice + slice;
     // the request's counters, lane k for counts[k] (no scalar registers)
     int64_t tally = 0;
     auto count_up = [&](int k, int v) { tally += lane == k ? v : 0; };
-    int cur = -1;
+    int cur = -1, split = 0;
     const __attribute__((address_space(4))) DensArgs *Ap = nullptr;
     // flushed when the wave moves to another request
     auto flush_counts = [&]() {
@@ -1406,15 +1434,23 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
             cur = r;
             Ap = as_const(B.req[r]);
             load_tree(Ap->tree, T);
+            split = __builtin_amdgcn_readfirstlane(home_split<G>(*B.req[r], splits(*B.req[r])));
         }
         const auto &A = *Ap;
-        const int64_t li = gleaf - (int64_t)__builtin_amdgcn_readfirstlane(pre[r]);
+        const int64_t item = gleaf - (int64_t)__builtin_amdgcn_readfirstlane(pre[r]);
+        const int64_t li = item >> split;
         const int64_t leaf = A.leaf_list ? (int64_t)as_const(A.leaf_list)[li] : li;
         if (A.leaf_act && as_const(A.leaf_act)[leaf] == 0) return;   // no active particle
-        const int64_t first = as_const(A.lstart)[leaf];
-        const int nhome = (int)(as_const(A.lstart)[leaf + 1] - first);
+        // this wave's share of the leaf, and the lanes of each of its particles
+        const int share = G >> split, LPP = L0 << split;
+        const int p = lane >> (log2_of(L0) + split), q = lane & (LPP - 1);
+        const int64_t first = (int64_t)as_const(A.lstart)[leaf] + (item & ((1 << split) - 1)) * share;
+        const int nhome = (int)((int64_t)as_const(A.lstart)[leaf + 1] - first);
         const int64_t i = first + p;
         const bool active = p < nhome && (!A.active || as_global(A.active)[i] != 0);
+        if (__ballot(active) == 0ull) return;
+        // entries that a step of a particle's lanes reads, and a list's (whole steps)
+        const int CHUNK = 4 * LPP, KP = (Kern<K>::list << (split - slice_split(A.n, G, splits(*B.req[r])))) & -CHUNK;
         const int64_t ii = active ? i : first;
         const double mi = as_global(A.m)[ii];
         const double mu = as_const(A.mrange)[0];
@@ -1425,6 +1461,8 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
         bool conv = !active;
         double h_out = h, rho_out = 0.0, om_out = 1.0;
         int n_out = 0;
+        if (split > 0 && lane < G) H.d[lane].thr = -1.0;
+        wave_lds_sync();
         if (q == 0) {
             H.d[p].x = as_global(A.x)[ii];
             H.d[p].y = as_global(A.y)[ii];
@@ -1469,7 +1507,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                 __builtin_amdgcn_s_setprio(2);
                 const Node home = load_const(reload(A.nodes) + leaf);
                 const Box bx = load_const(&reload(B.req[r])->box);
-                const uint64_t part = particle_bits<G>(!conv);
+                const uint64_t part = particle_bits(!conv, LPP);
                 close = false;
                 hw = hcov;
                 for (;;) {
@@ -1545,7 +1583,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
             };
             // entries [n, whole step) of this particle's list: far away
             auto pad_list = [&](int n) {
-                const int end = (n + CHUNK - 1) / CHUNK * CHUNK;
+                const int end = (n + CHUNK - 1) & -CHUNK;
                 for (int e = n + q; e < end; e += LPP) {
                     cr2[p * KP + e] = F64 ? (ListR2)1e300 : (ListR2)1e30f;
                     if (!equal_m) cm[p * KP + e] = 0.0;
@@ -1570,7 +1608,11 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                 const int n0 = (int)wave_sum_int(t.n), n1 = (int)wave_sum_int(t.n1);
                 const PartSums c = first_time ? PartSums{} : part[pp];
                 wave_lds_sync();
-                if (lane == 0) part[pp] = PartSums{c.d0 + d0, c.d1 + d1, c.d2 + d2, c.wn + wn, c.n + n0, c.n1 + n1};
+                const double edge = F64 ? -wave_max(-t.edge) : 0.0;
+                if (lane == 0) {
+                    part[pp] = PartSums{c.d0 + d0, c.d1 + d1, c.d2 + d2, c.wn + wn, c.n + n0, c.n1 + n1};
+                    if constexpr (F64) part_edge[pp] = first_time ? edge : fmin(part_edge[pp], edge);
+                }
                 wave_lds_sync();
             };
             if (__ballot(!conv && !cached) != 0ull) {
@@ -1591,7 +1633,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                 const Box bx = load_const(&reload(B.req[r])->box);
                 HomeUnits units{};
                 if constexpr (!F64) units = home_operand<G, PREC>(H, home, hcov, op);
-                const uint64_t takes_part = particle_bits<G>(!conv);
+                const uint64_t takes_part = particle_bits(!conv, LPP);
                 const int depth = group_depth<G>(wr.n, B.stage > 0 ? B.stage * G / 2 : kGroup);
                 count = 0;
                 int held = 0;              // FP64: entries of home particle `lane`'s list
@@ -1677,11 +1719,11 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                                 if (__ballot(full) == 0ull) break;
                                 // full lists (KP entries, whatever the groups)
                                 for (uint64_t f = __ballot(full && q == 0); f; f &= f - 1)
-                                    empty_list((int)__builtin_ctzll(f) / LPP, KP);
+                                    empty_list((int)__builtin_ctzll(f) >> (log2_of(L0) + split), KP);
                                 if (full) count = 0;
                             }
                         };
-                        group_pairs<G, PREC, false>(tab, home, bx, ng, img, op, units, Q.pos, Q.off, S.id, use);
+                        group_pairs<G, PREC, false>(p, tab, home, bx, ng, img, op, units, Q.pos, Q.off, S.id, use);
                     }
                 }
                 if constexpr (F64) {
@@ -1699,12 +1741,13 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                 sm.d1 += t.d1;
                 sm.d2 += t.d2;
                 sm.wn += t.wn;
+                if constexpr (F64) sm.edge = fmin(sm.edge, part_edge[p]);
                 sm.n += t.n;
                 sm.n1 += t.n1;
             }
             // one evaluation for every particle still iterating (uniform)
             count_up(kCntNrTotal, (int)__popcll(__ballot(!conv && q == 0)));
-            const int cnt = group_sum<LPP>(sm.n) - 1;   // without the particle itself
+            const int cnt = lanes_sum<L0>(sm.n, LPP) - 1;   // without the particle itself
             double s0, s2;
             // x: relative change of h to the root (the polynomial's, where it
             // could be solved), b1: the polynomial's derivative there
@@ -1713,16 +1756,16 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
             if constexpr (F64) {
                 const double sc = equal_m ? mu : 1.0;
                 const double f3 = K == SPH_KERNEL_QUINTIC ? 1.0 : 3.0;
-                const double D0 = sc * group_sum<LPP>(sm.d0);
-                const double D1 = sc * (f3 * group_sum<LPP>(sm.d1));
-                const double D2 = sc * (f3 * group_sum<LPP>(sm.d2));
-                double D3 = group_sum<LPP>(sm.wn);
+                const double D0 = sc * lanes_sum<L0>(sm.d0, LPP);
+                const double D1 = sc * (f3 * lanes_sum<L0>(sm.d1, LPP));
+                const double D2 = sc * (f3 * lanes_sum<L0>(sm.d2, LPP));
+                double D3 = lanes_sum<L0>(sm.wn, LPP);
                 if constexpr (K != SPH_KERNEL_QUINTIC) {
-                    const int n1 = group_sum<LPP>(sm.n1);
+                    const int n1 = lanes_sum<L0>(sm.n1, LPP);
                     if (equal_m) D3 = (double)(2 * (cnt + 1) - n1);
                 }
                 D3 *= sc;
-                edge = group_min<LPP>(sm.edge);
+                edge = -lanes_max<L0>(-sm.edge, LPP);
                 constexpr double N = Sums<K>::N;
                 s0 = D0;
                 s2 = N * D0 - D1;
@@ -1746,8 +1789,8 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                     b1 = (3.0 * D3 * x + 2.0 * D2) * x + D1;
                 }
             } else {
-                s0 = group_sum<LPP>(sm.d0);
-                s2 = group_sum<LPP>(sm.d1);
+                s0 = lanes_sum<L0>(sm.d0, LPP);
+                s2 = lanes_sum<L0>(sm.d1, LPP);
             }
             if (!conv && q == 0) evals_leaf += cnt;
             if (!conv) {
@@ -1788,9 +1831,9 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                     if (!inside) hn = hi_b < INFINITY ? 0.5 * (lo_b + hi_b) : 2.0 * h;
                     // the polynomial is the kernel sum at hn itself if no
                     // neighbour crosses a knot on the way (the 1e-13 covers the
-                    // rounding of q) and the list holds every neighbour there:
-                    // the solve is done without another pass
-                    const bool exact = poly && inside && cached && hn <= Rc &&
+                    // rounding of q) and the pass has seen every neighbour there:
+                    // the solve is done without another one
+                    const bool exact = poly && inside && hn <= Rc &&
                                        edge > RK * fabs(x) * (1.0 + 1e-9) + 1e-13 &&
                                        (K != SPH_KERNEL_QUINTIC || fabs(x) <= 1e-5);
                     if (!(hn == hn)) {
@@ -1852,7 +1895,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
 template <int G, int PREC, bool AC, bool SW, int K>
 __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(Batch<ForceArgs> B)
 {
-    constexpr int LPP = kWave / G;
+    constexpr int L0 = kWave / G;   // lanes per home particle of a whole leaf
     constexpr bool F64 = PREC == SPH_FP64;
     __shared__ WalkBuf wb;
     __shared__ TreeInfo T;
@@ -1864,13 +1907,12 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
     __shared__ HomeTab<G, PREC> H;
     __shared__ HomeOp<G> op;
     __shared__ uint32_t pre[kMaxBatch + 1];
-    batch_prefix(B, pre);
+    batch_prefix<G>(B, pre, [](const ForceArgs &) { return true; });
     const int lane = threadIdx.x;
-    const int p = lane / LPP, q = lane % LPP;
     // the request's counters, lane k for counts[k] (no scalar registers)
     int64_t tally = 0;
     auto count_up = [&](int k, int v) { tally += lane == k ? v : 0; };
-    int cur = -1;
+    int cur = -1, split = 0;
     const __attribute__((address_space(4))) ForceArgs *Fp = nullptr;
     auto flush_counts = [&]() {
         if (cur >= 0 && tally != 0)
@@ -1885,9 +1927,11 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
             cur = r;
             Fp = as_const(B.req[r]);
             load_tree(Fp->tree, T);
+            split = __builtin_amdgcn_readfirstlane(home_split<G>(*B.req[r], true));
         }
         const auto &F = *Fp;
-        const int64_t li = gleaf - (int64_t)__builtin_amdgcn_readfirstlane(pre[r]);
+        const int64_t item = gleaf - (int64_t)__builtin_amdgcn_readfirstlane(pre[r]);
+        const int64_t li = item >> split;
         const int64_t leaf = F.leaf_list ? (int64_t)as_const(F.leaf_list)[li] : li;
         if (F.leaf_act && as_const(F.leaf_act)[leaf] == 0) return;   // no active particle
         const Box bx = load_const(&B.req[r]->box);
@@ -1896,10 +1940,14 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
         const double alpha_ac = AC ? F.alpha_ac : 0.0, u_per_c2 = AC ? F.u_per_c2 : 0.0;
         const double inv_gamma = AC ? F.inv_gamma : 0.0;
         const bool ac_price = AC && F.ac_price != 0;
-        const int64_t first = as_const(F.lstart)[leaf];
-        const int nhome = (int)(as_const(F.lstart)[leaf + 1] - first);
+        // this wave's share of the leaf, and the lanes of each of its particles
+        const int share = G >> split, LPP = L0 << split;
+        const int p = lane >> (log2_of(L0) + split), q = lane & (LPP - 1);
+        const int64_t first = (int64_t)as_const(F.lstart)[leaf] + (item & ((1 << split) - 1)) * share;
+        const int nhome = (int)((int64_t)as_const(F.lstart)[leaf + 1] - first);
         const int64_t i = first + p;
         const bool active = p < nhome && (!F.active || as_global(F.active)[i] != 0);
+        if (__ballot(active) == 0ull) return;
         const int64_t ii = p < nhome ? i : first;
         const double hx = as_global(F.x)[ii], hy = as_global(F.y)[ii], hz = as_global(F.z)[ii];
         float hfx = 0.f, hfy = 0.f, hfz = 0.f;
@@ -1923,6 +1971,8 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
         const float vxif = (float)vxi, vyif = (float)vyi, vzif = (float)vzi;
         const float Aif = (float)Ai, cif = (float)ci, rhoif = (float)rhoi;
         const Node home = load_const(F.nodes + leaf);
+        if (split > 0 && lane < G) H.d[lane].thr = -1.0;
+        wave_lds_sync();
         if (q == 0) {
             H.d[p] = HomeRow{hx, hy, hz, active ? hi2x4 : -1.0};
             if constexpr (!F64) H.f[p] = HomeRowF{hfx, hfy, hfz, 0.f};
@@ -1930,7 +1980,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
         // symmetric criterion: a node can hold force neighbours of the home leaf
         // if its box is closer than R max(h over home, h over node), and (`close`)
         // of some home particle if it is closer than R max(h, h over node)
-        const uint64_t part = particle_bits<G>(active);
+        const uint64_t part = particle_bits(active, LPP);
         bool close = false;
         auto test = [&](const Node &nd) {
             const double R = RK * fmax(home.hmax, nd.hmax) * (1.0 + 1e-10);
@@ -2111,20 +2161,20 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
                     }
                 }
             };
-            group_pairs<G, PREC, true>(tab, home, bx, ng, img, op, units, F.pos, F.off, S.id, use);
+            group_pairs<G, PREC, true>(p, tab, home, bx, ng, img, op, units, F.pos, F.off, S.id, use);
         }
-        axi = group_sum<LPP>(axi);
-        ayi = group_sum<LPP>(ayi);
-        azi = group_sum<LPP>(azi);
-        dui = group_sum<LPP>(dui);
-        vs_max = group_max<LPP>(vs_max);
-        cnt = group_sum<LPP>(cnt);
-        if (F.lev) lmx_l = group_max_int<LPP>(lmx_l);
+        axi = lanes_sum<L0>(axi, LPP);
+        ayi = lanes_sum<L0>(ayi, LPP);
+        azi = lanes_sum<L0>(azi, LPP);
+        dui = lanes_sum<L0>(dui, LPP);
+        vs_max = lanes_max<L0>(vs_max, LPP);
+        cnt = lanes_sum<L0>(cnt, LPP);
+        if (F.lev) lmx_l = lanes_max_int<L0>(lmx_l, LPP);
         if constexpr (SW) {
-            dvs = group_sum<LPP>(dvs);
-            cxs = group_sum<LPP>(cxs);
-            cys = group_sum<LPP>(cys);
-            czs = group_sum<LPP>(czs);
+            dvs = lanes_sum<L0>(dvs, LPP);
+            cxs = lanes_sum<L0>(cxs, LPP);
+            cys = lanes_sum<L0>(cys, LPP);
+            czs = lanes_sum<L0>(czs, LPP);
         }
         bool bad = false;
         if (active && q == 0) {

@@ -88,6 +88,44 @@ inline unsigned pair_grid(int64_t n)
     return (unsigned)blocks;
 }
 
+// log2 of the waves that share a home leaf of a set of n particles.  A wave is
+// latency-bound, and a small set has fewer leaves than the chip has SIMDs (1,024),
+// so up to some 4,500 waves, four per SIMD, share the leaves of a set: with a
+// quarter of the home particles a wave has a quarter of the tests and of the
+// Newton steps' sums per lane, but its own walk and its own staging of the same
+// candidate leaves.  Whole leaves against this rule (density + forces, us):
+// 1,000 particles FP64 85 + 37 / 39 + 29 (16 waves per leaf); 8,000 quintic FP64
+// 765 + 218 / 276 + 107; a Plummer sphere of 12,000 FP64 4,650 + 170 / 1,640 +
+// 101; 24,389 FP32-pair, forces 99 / 78.  The line: at twice as many, 46,656
+// particles gain a third, but 32,768 on a lattice take 81 + 74 instead of 58 + 44,
+// and a batch, which fills the chip anyway and whose sets are split as each is
+// alone, loses 20 %.
+constexpr int64_t kSplitParticles = 49152;
+__host__ __device__ inline int split_of(int64_t n, int G)
+{
+    int k = 0;
+    while ((2 << k) <= G && (n << (k + 1)) <= kSplitParticles) k++;
+    return k;
+}
+
+// Density loop: FP32-pair in a periodic box keeps whole leaves.  Where a
+// candidate leaf's shift is ambiguous its pairs' separations take another
+// rounding, and whether it is depends on the largest h of the home particles
+// that the wave holds, so shares would change results in their eighth digit.
+__host__ __device__ inline bool splits_density(int precision, int periodic)
+{
+    return precision == SPH_FP64 || !periodic;
+}
+
+// log2 of the blocks that share the density lists of a whole leaf: half as many
+// as share the leaf, so that a list holds whole steps of 4 entries per lane (a
+// particle of its own wave has all 64).
+__host__ __device__ inline int slice_split(int64_t n, int G, bool splits)
+{
+    const int k = splits ? split_of(n, G) : 0;
+    return k > 0 ? k - 1 : 0;
+}
+
 // Density-loop candidate lists: up to Kern<K>::list entries per home
 // particle (160 for the M4, whose sphere of radius 2 Rc holds ~90 neighbours
 // at eta = 1.2; 480 for the quintic's ~300 within 3 Rc), each an FP64 r^2 and
