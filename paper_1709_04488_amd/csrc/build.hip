@@ -199,20 +199,34 @@ __global__ __launch_bounds__(256) void k_keys(int64_t n, const double *__restric
 
 // ---- LSD radix sort, 8-bit digits ------------------------------------------
 
-// inclusive block-wide sum scan, 256 threads, one value each; sh[255] holds
-// the total on return
-__device__ inline uint32_t block_scan_256(uint32_t v, uint32_t *sh)
+// Block-wide exclusive scan (sum or max, of values that are 0 or above) of one
+// value per thread, WAVES waves; total: over all threads.  Shuffles inside the
+// waves and one exchange of their totals: with a barrier pair for each doubling
+// of the distance instead, the two scans of a radix scatter block took longer
+// than the rest of it.  sh: WAVES words.
+template <bool MAX, int WAVES>
+__device__ inline uint32_t block_scan(uint32_t v, uint32_t *sh, uint32_t &total)
 {
-    const int t = threadIdx.x;
-    sh[t] = v;
-    __syncthreads();
-    for (int d = 1; d < 256; d <<= 1) {
-        const uint32_t o = t >= d ? sh[t - d] : 0u;
-        __syncthreads();
-        sh[t] += o;
-        __syncthreads();
+    auto op = [](uint32_t a, uint32_t b) { return MAX ? (a > b ? a : b) : a + b; };
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    uint32_t s = v;
+    for (int d = 1; d < kWave; d <<= 1) {
+        const uint32_t o = __shfl_up(s, d);
+        if (lane >= d) s = op(s, o);
     }
-    return sh[t];
+    if (lane == kWave - 1) sh[w] = s;
+    __syncthreads();
+    uint32_t before = 0;
+    total = 0;
+#pragma unroll
+    for (int k = 0; k < WAVES; k++) {
+        const uint32_t o = sh[k];
+        before = k < w ? op(before, o) : before;
+        total = op(total, o);
+    }
+    __syncthreads();   // sh is free again
+    const uint32_t prev = __shfl_up(s, 1);
+    return lane > 0 ? op(before, prev) : before;
 }
 
 template <int ITEMS>
@@ -240,16 +254,16 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_hist(int64_t n, const uint64_
 __global__ __launch_bounds__(256) void k_rs_digit_scan(uint32_t *__restrict__ hist, int64_t ntiles,
                                                        uint32_t *__restrict__ totals)
 {
-    __shared__ uint32_t sh[256];
+    __shared__ uint32_t sh[4];
     uint32_t *a = hist + (int64_t)blockIdx.x * ntiles;
     uint32_t run = 0;
     for (int64_t b0 = 0; b0 < ntiles; b0 += 256) {
         const int64_t k = b0 + threadIdx.x;
         const uint32_t v = k < ntiles ? a[k] : 0u;
-        const uint32_t incl = block_scan_256(v, sh);
-        if (k < ntiles) a[k] = run + incl - v;
-        run += sh[255];
-        __syncthreads();
+        uint32_t sum;
+        const uint32_t before = block_scan<false, 4>(v, sh, sum);
+        if (k < ntiles) a[k] = run + before;
+        run += sum;
     }
     if (threadIdx.x == 0) totals[blockIdx.x] = run;
 }
@@ -274,6 +288,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(int64_t n, const uint
 {
     __shared__ uint32_t wcnt[kRsThreads / kWave][256];
     __shared__ uint32_t dbase[256];
+    __shared__ uint32_t sums[kRsThreads / kWave];
     __shared__ uint32_t tbase[256];            // first slot of each digit in the tile
     constexpr int TILE = kRsThreads * ITEMS;
     __shared__ uint64_t skey[TILE];            // the tile in digit order
@@ -299,12 +314,8 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(int64_t n, const uint
         digit_total = totals[threadIdx.x];
     }
     // first position of each digit: exclusive scan of the digit totals
-    {
-        const uint32_t v = digit_total;
-        const uint32_t incl = block_scan_256(v, dbase);
-        __syncthreads();
-        dbase[threadIdx.x] = incl - v;
-    }
+    uint32_t all;
+    dbase[threadIdx.x] = block_scan<false, kRsThreads / kWave>(digit_total, sums, all);
     __syncthreads();
     const uint64_t lt = __lanemask_lt();
     const int64_t base = blockIdx.x * (int64_t)TILE + w * (ITEMS * kWave);
@@ -339,11 +350,7 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(int64_t n, const uint
         wcnt[ww][threadIdx.x] = run;
         run += v;
     }
-    {
-        const uint32_t incl = block_scan_256(run, tbase);
-        __syncthreads();
-        tbase[threadIdx.x] = incl - run;
-    }
+    tbase[threadIdx.x] = block_scan<false, kRsThreads / kWave>(run, sums, all);
     __syncthreads();
     // stage the tile in digit order (stable: wave, then item, then lane)
     for (int r = 0; r < ITEMS; r++) {
@@ -414,24 +421,6 @@ __device__ inline bool seg_break(int64_t k, const uint64_t *__restrict__ keys,
     return (keys[k - 1] >> sh) != (keys[k] >> sh);
 }
 
-// block-wide inclusive scan of one value per thread (max or sum)
-template <bool MAX>
-__device__ inline uint32_t block_scan(uint32_t v, uint32_t *sh)
-{
-    const int t = threadIdx.x;
-    sh[t] = v;
-    __syncthreads();
-    for (int d = 1; d < kScanThreads; d <<= 1) {
-        uint32_t o = t >= d ? sh[t - d] : 0u;
-        __syncthreads();
-        sh[t] = MAX ? (sh[t] > o ? sh[t] : o) : sh[t] + o;
-        __syncthreads();
-    }
-    uint32_t r = sh[t];
-    __syncthreads();
-    return r;
-}
-
 // per tile: break flags and the largest segment start inside the tile
 __global__ __launch_bounds__(kScanThreads) void k_seg_tiles(int64_t n, const uint64_t *__restrict__ keys,
                                                             const double *__restrict__ h,
@@ -439,7 +428,7 @@ __global__ __launch_bounds__(kScanThreads) void k_seg_tiles(int64_t n, const uin
                                                             int bits, uint32_t *__restrict__ flag,
                                                             uint32_t *__restrict__ tmax)
 {
-    __shared__ uint32_t sh[kScanThreads];
+    __shared__ uint32_t sh[kScanThreads / kWave];
     const double ext = fmax(fmax(box[3] - box[0], box[4] - box[1]), box[5] - box[2]);
     const int64_t base = blockIdx.x * (int64_t)kScanTile + threadIdx.x * 4;
     uint32_t mx = 0;
@@ -451,8 +440,9 @@ __global__ __launch_bounds__(kScanThreads) void k_seg_tiles(int64_t n, const uin
             if (b) mx = (uint32_t)k;
         }
     }
-    uint32_t r = block_scan<true>(mx, sh);
-    if (threadIdx.x == kScanThreads - 1) tmax[blockIdx.x] = r;
+    uint32_t top;
+    block_scan<true, kScanThreads / kWave>(mx, sh, top);
+    if (threadIdx.x == 0) tmax[blockIdx.x] = top;
 }
 
 // exclusive scan over the tile values, one block (max or sum); copy (when not
@@ -461,21 +451,14 @@ template <bool MAX>
 __global__ __launch_bounds__(1024) void k_scan_tiles(uint32_t *__restrict__ a, int64_t ntile,
                                                      uint32_t *__restrict__ copy)
 {
-    __shared__ uint32_t sums[1024];
+    __shared__ uint32_t sums[16];
     const int t = threadIdx.x;
     const int64_t chunk = (ntile + 1023) / 1024;
     const int64_t s0 = t * chunk, s1 = s0 + chunk < ntile ? s0 + chunk : ntile;
     uint32_t s = 0;
     for (int64_t k = s0; k < s1; k++) s = MAX ? (a[k] > s ? a[k] : s) : s + a[k];
-    sums[t] = s;
-    __syncthreads();
-    for (int d = 1; d < 1024; d <<= 1) {
-        uint32_t v = t >= d ? sums[t - d] : 0u;
-        __syncthreads();
-        sums[t] = MAX ? (sums[t] > v ? sums[t] : v) : sums[t] + v;
-        __syncthreads();
-    }
-    uint32_t run = t > 0 ? sums[t - 1] : 0u;
+    uint32_t all;
+    uint32_t run = block_scan<MAX, 16>(s, sums, all);
     for (int64_t k = s0; k < s1; k++) {
         uint32_t v = a[k];
         if (copy) copy[k] = v;
@@ -490,7 +473,7 @@ __global__ __launch_bounds__(kScanThreads) void k_seg_apply(int64_t n, int G,
                                                             const uint32_t *__restrict__ tmax,
                                                             uint32_t *__restrict__ tcnt)
 {
-    __shared__ uint32_t sh[kScanThreads];
+    __shared__ uint32_t sh[kScanThreads / kWave];
     const int64_t base = blockIdx.x * (int64_t)kScanTile + threadIdx.x * 4;
     uint32_t loc[4];
     uint32_t mx = 0;
@@ -499,14 +482,8 @@ __global__ __launch_bounds__(kScanThreads) void k_seg_apply(int64_t n, int G,
         loc[e] = (k < n && flag[k]) ? (uint32_t)k : 0u;
         mx = loc[e] > mx ? loc[e] : mx;
     }
-    uint32_t incl = block_scan<true>(mx, sh);
-    uint32_t prev = threadIdx.x > 0 ? sh[threadIdx.x - 1] : 0u;
-    // sh was overwritten by the scan's final value per thread before return;
-    // recompute the exclusive prefix from the inclusive values
-    __syncthreads();
-    sh[threadIdx.x] = incl;
-    __syncthreads();
-    prev = threadIdx.x > 0 ? sh[threadIdx.x - 1] : 0u;
+    uint32_t all;
+    const uint32_t prev = block_scan<true, kScanThreads / kWave>(mx, sh, all);
     uint32_t seg = prev > tmax[blockIdx.x] ? prev : tmax[blockIdx.x];
     uint32_t count = 0;
     for (int e = 0; e < 4; e++) {
@@ -517,9 +494,8 @@ __global__ __launch_bounds__(kScanThreads) void k_seg_apply(int64_t n, int G,
         flag[k] = ls;
         count += ls;
     }
-    __syncthreads();
-    uint32_t tot = block_scan<false>(count, sh);
-    if (threadIdx.x == kScanThreads - 1) tcnt[blockIdx.x] = tot;
+    block_scan<false, kScanThreads / kWave>(count, sh, all);
+    if (threadIdx.x == 0) tcnt[blockIdx.x] = all;
 }
 
 // per tile: the first particle of every leaf
@@ -527,15 +503,16 @@ __global__ __launch_bounds__(kScanThreads) void k_leaf_starts(int64_t n, const u
                                                            const uint32_t *__restrict__ toff,
                                                            uint32_t *__restrict__ lstart)
 {
-    __shared__ uint32_t sh[kScanThreads];
+    __shared__ uint32_t sh[kScanThreads / kWave];
     const int64_t base = blockIdx.x * (int64_t)kScanTile + threadIdx.x * 4;
     uint32_t cnt = 0;
     for (int e = 0; e < 4; e++) {
         int64_t k = base + e;
         if (k < n) cnt += flag[k];
     }
-    uint32_t incl = block_scan<false>(cnt, sh);
-    uint32_t run = toff[blockIdx.x] + incl - cnt;   // leaf starts before this thread's items
+    uint32_t all;
+    // leaf starts before this thread's items
+    uint32_t run = toff[blockIdx.x] + block_scan<false, kScanThreads / kWave>(cnt, sh, all);
     for (int e = 0; e < 4; e++) {
         int64_t k = base + e;
         if (k >= n) break;
@@ -776,35 +753,39 @@ sph_status build_order(sph_ctx *c, int64_t n, const double *x, const double *y, 
     const int hilbert = p.precision == SPH_FP64 && !state ? 1 : 0;
     hipLaunchKernelGGL(k_keys, dim3(grid_for(n, 256)), dim3(256), 0, c->stream, n, x, y, z,
                        c->d_box, fb, bits, hilbert, c->keys[0], c->vals[0]);
-    // small sets: tiles of 1024 keys (more, shorter blocks); up to
-    // kRsRawTiles tiles the scatter blocks form the digit offsets from the raw
-    // counts themselves (one launch fewer per pass).  A stable sort's result
-    // does not depend on the tiling.
-    const bool small = rs_use_small(n);
+    // (a stable sort's result does not depend on the tiling)
+    const bool small = n <= kRsSmallMax;
     const int64_t ntiles = small ? rs_small_tiles(n) : ceil_div(n, kRsTile);
-    if (256 * ntiles + 256 > c->hist_cap) return fail(c, SPH_ENOMEM, "radix count capacity");
+    // more counts than c->hist holds: the gather's destination, idle until the sort ends
+    uint32_t *hist = c->hist;
+    int64_t room = c->hist_cap;
+    if (256 * ntiles + 256 > room) {
+        hist = (uint32_t *)c->t.x;
+        room = 2 * c->ncap;
+    }
+    if (!hist || 256 * ntiles + 256 > room) return fail(c, SPH_ENOMEM, "radix count capacity");
     const int passes = (3 * bits + 7) / 8;
-    const int raw = ntiles <= kRsRawTiles ? 1 : 0;
+    const int raw = ntiles <= kRsRawMax ? 1 : 0;
     int cur = 0;
     for (int ps = 0; ps < passes; ps++) {
         int shift = 8 * ps;
         if (small)
             hipLaunchKernelGGL(k_rs_hist<kRsItemsSmall>, dim3((unsigned)ntiles), dim3(kRsThreads), 0,
-                               c->stream, n, c->keys[cur], shift, c->hist, ntiles);
+                               c->stream, n, c->keys[cur], shift, hist, ntiles);
         else
             hipLaunchKernelGGL(k_rs_hist<kRsItems>, dim3((unsigned)ntiles), dim3(kRsThreads), 0,
-                               c->stream, n, c->keys[cur], shift, c->hist, ntiles);
+                               c->stream, n, c->keys[cur], shift, hist, ntiles);
         if (!raw)
-            hipLaunchKernelGGL(k_rs_digit_scan, dim3(256), dim3(256), 0, c->stream, c->hist, ntiles,
-                               c->hist + 256 * ntiles);
+            hipLaunchKernelGGL(k_rs_digit_scan, dim3(256), dim3(256), 0, c->stream, hist, ntiles,
+                               hist + 256 * ntiles);
         if (small)
             hipLaunchKernelGGL(k_rs_scatter<kRsItemsSmall>, dim3((unsigned)ntiles), dim3(kRsThreads),
                                0, c->stream, n, c->keys[cur], c->vals[cur], c->keys[cur ^ 1],
-                               c->vals[cur ^ 1], shift, c->hist, ntiles, c->hist + 256 * ntiles, raw);
+                               c->vals[cur ^ 1], shift, hist, ntiles, hist + 256 * ntiles, raw);
         else
             hipLaunchKernelGGL(k_rs_scatter<kRsItems>, dim3((unsigned)ntiles), dim3(kRsThreads), 0,
                                c->stream, n, c->keys[cur], c->vals[cur], c->keys[cur ^ 1],
-                               c->vals[cur ^ 1], shift, c->hist, ntiles, c->hist + 256 * ntiles, raw);
+                               c->vals[cur ^ 1], shift, hist, ntiles, hist + 256 * ntiles, raw);
         cur ^= 1;
     }
     c->perm = c->vals[cur];

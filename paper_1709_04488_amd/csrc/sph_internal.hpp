@@ -55,21 +55,27 @@ constexpr int64_t kMaxPairBlocks = 256 * 16;
 
 // Active-leaf compaction of block time-steps: leaves per block, and the
 // per-block counts (one more than the blocks, for the bound of n leaves)
-// Radix sort tiles: 4096 keys (256 threads x 16) per block; sets of at most
-// kRsRawTiles small tiles of 1024 keys (256 x 4) sort with those instead (four
-// times the blocks and a quarter of each block's chain), and up to kRsRawTiles
-// tiles the scatter forms the digit offsets from the raw counts.  The counts
-// take 256 words per tile plus 256 digit totals.
+// Radix sort tiles: 1024 keys (256 threads x 4) per block up to kRsSmallMax
+// particles, 4096 (256 x 16) above.  A pass over a few hundred thousand keys is
+// latency, not bandwidth: tiles of 4096 left 195,112 keys in 48 blocks on 256 CUs,
+// 22.6 us per scatter (build of the order and tree: 209 -> 136 us with small
+// tiles; 512,000: 233 -> 188; 1.7M: 390 -> 413, where the blocks suffice and the
+// larger tiles write longer runs).  Up to kRsRawMax tiles the scatter blocks form
+// the digit offsets from the raw counts themselves, one launch fewer per pass; each
+// block reads all tiles' counts then, which at 63 tiles cost 64,000 particles 170
+// against 120 us, and at 12 gained 12,167 as many as 12 us.  The counts take 256
+// words per tile plus 256 digit totals; where that is more than hist_words, they
+// stand in memory that the sort's successor fills (the budgets do not change).
 constexpr int kRsItems = 16, kRsItemsSmall = 4;
 constexpr int64_t kRsTile = 256 * kRsItems, kRsTileSmall = 256 * kRsItemsSmall;
-constexpr int64_t kRsRawTiles = 64;
+constexpr int64_t kRsSmallMax = 1 << 20, kRsRawMax = 24;
+constexpr int64_t kRsHistTiles = 64;   // small tiles that hist_words has room for
 constexpr int64_t rs_small_tiles(int64_t n) { return (n + kRsTileSmall - 1) / kRsTileSmall; }
-constexpr bool rs_use_small(int64_t n) { return rs_small_tiles(n) <= kRsRawTiles; }
 constexpr int64_t hist_words(int64_t cap)
 {
     // the larger of the two tilings any n <= cap can use
     const int64_t big = (cap + kRsTile - 1) / kRsTile;
-    const int64_t small = rs_small_tiles(cap) < kRsRawTiles ? rs_small_tiles(cap) : kRsRawTiles;
+    const int64_t small = rs_small_tiles(cap) < kRsHistTiles ? rs_small_tiles(cap) : kRsHistTiles;
     return 256 * (big > small ? big : small) + 256;
 }
 
