@@ -395,7 +395,7 @@ sph_status forces_pre(sph_ctx *c, const sph_particles *ps)
     c->f_div = ps->divv || ps->curlv;
     TRY(build_tree(c, n));
     timer_end(c, 2, e0, e1);
-    TRY(force_prep(c, n, c->s.u, c->s.vx, c->s.vy, c->s.vz));
+    TRY(force_prep(c, n, c->s.u, c->s.vx, c->s.vy, c->s.vz, false));
     return forces_prepare(c, n);
 }
 
@@ -417,8 +417,7 @@ sph_status forces_post(sph_ctx *c, const sph_particles *ps)
         sl.count++;
     }
     TRY(scatter(c, n, sl, c->perm));
-    TRY(reduce_dt(c, n));
-    return reduce_diag(c, n);
+    return reduce_diag(c, n, true);
 }
 
 // resident state, first half of a step: kicks, drift, re-sort, tree, density arguments
@@ -466,8 +465,7 @@ sph_status step_mid(sph_ctx *c)
     const int64_t n = c->n;
     resident_force_inputs(c);
     // the force walk needs the boxes' largest h after the h solve
-    TRY(refresh_hmax(c, n));
-    TRY(force_prep(c, n, c->s.up, c->s.vpx, c->s.vpy, c->s.vpz));
+    TRY(force_prep(c, n, c->s.up, c->s.vpx, c->s.vpy, c->s.vpz, true));
     return forces_prepare(c, n);
 }
 
@@ -479,8 +477,7 @@ sph_status step_post(sph_ctx *c, double dt, double *dt_used)
     TRY(av_rate(c, n, c->s.alp));
     TRY(av_cd10(c, n, false));
     TRY(closing_kick(c, n, dt));
-    TRY(reduce_dt(c, n));
-    TRY(reduce_diag(c, n));
+    TRY(reduce_diag(c, n, true));
     c->steps++;
     c->dt_used_out = dt_used;
     return SPH_OK;
@@ -573,8 +570,7 @@ sph_status evaluate_mid(sph_ctx *c)
     const int64_t n = c->n;
     if (n == 0) return SPH_OK;
     // the force walk needs the boxes' largest h after the h solve
-    TRY(refresh_hmax(c, n));
-    TRY(force_prep(c, n, c->s.u, c->s.vx, c->s.vy, c->s.vz));
+    TRY(force_prep(c, n, c->s.u, c->s.vx, c->s.vy, c->s.vz, true));
     return forces_prepare(c, n);
 }
 
@@ -598,8 +594,7 @@ sph_status evaluate_post(sph_ctx *c, const sph_particles *ps)
         sl.count++;
     }
     TRY(scatter_eos(c, n, sl, c->perm, c->s.u, ps->pressure, ps->cs));
-    TRY(reduce_dt(c, n));
-    return reduce_diag(c, n);
+    return reduce_diag(c, n, true);
 }
 
 
@@ -1001,8 +996,7 @@ sph_status sph_upload_state(sph_ctx *c, const sph_particles *ps)
                                     hipMemcpyDeviceToDevice, c->stream), "copy ids"));
     TRY(build_tree(c, n));
     TRY(run_density(c, n));
-    TRY(refresh_hmax(c, n));
-    TRY(force_prep(c, n, c->s.u, c->s.vx, c->s.vy, c->s.vz));
+    TRY(force_prep(c, n, c->s.u, c->s.vx, c->s.vy, c->s.vz, true));
     // the initial forces see the uploaded alpha
     c->f_alpha = c->res_alpha ? c->s.al : nullptr;
     c->f_div = c->p.av_switch != SPH_AV_NONE;
@@ -1011,9 +1005,8 @@ sph_status sph_upload_state(sph_ctx *c, const sph_particles *ps)
     TRY(av_cd10(c, n, true));
     // block time-steps: first levels, steps and opening kicks
     if (c->p.block_lmax > 0) TRY(block_finish(c, n, true));
-    TRY(reduce_dt(c, n));
     TRY(hip_check(c, hipMemsetAsync(c->d_scal + 1, 0, sizeof(double) * 2, c->stream), "reset time"));
-    TRY(reduce_diag(c, n));
+    TRY(reduce_diag(c, n, true));
     c->built = false;
     c->resident = true;
     c->steps = 0;
@@ -1105,8 +1098,7 @@ static sph_status substep_mid(sph_ctx *c)
 {
     const int64_t n = c->n;
     Sorted &S = c->s;
-    sph_status st = refresh_hmax(c, n);
-    if (st == SPH_OK) st = force_prep(c, n, S.up, S.vpx, S.vpy, S.vpz);
+    sph_status st = force_prep(c, n, S.up, S.vpx, S.vpy, S.vpz, true);
     if (st == SPH_OK) st = forces_prepare(c, n);
     clear_block_flags(c);
     return st;
@@ -1119,7 +1111,7 @@ static sph_status substep_post(sph_ctx *c)
     const int64_t n = c->n;
     TRY(block_av(c, n));
     TRY(block_finish(c, n, false));
-    TRY(reduce_diag(c, n));
+    TRY(reduce_diag(c, n, false));
     c->steps++;
     return SPH_OK;
 }

@@ -162,6 +162,33 @@ struct FixedBox {
     double lo[3], hi[3];
 };
 
+// The box's corners, from either place.
+__device__ inline void key_box(const double *box, const FixedBox &fb, double b[6])
+{
+    for (int a = 0; a < 3; a++) {
+        b[a] = fb.fixed ? fb.lo[a] : box[a];
+        b[3 + a] = fb.fixed ? fb.hi[a] : box[3 + a];
+    }
+}
+
+__device__ inline uint64_t position_key(const double b[6], double x, double y, double z, int bits, int hilbert,
+                                        const uint8_t *tab)
+{
+    double ext = fmax(fmax(b[3] - b[0], b[4] - b[1]), b[5] - b[2]);
+    double cells = (double)(1u << bits);
+    double scale = ext > 0.0 ? cells / ext : 0.0;
+    double top = cells - 1.0;
+    double q[3] = {(x - b[0]) * scale, (y - b[1]) * scale, (z - b[2]) * scale};
+    uint64_t key = 0;
+    for (int a = 0; a < 3; a++) {
+        double c = floor(q[a]);
+        c = c < 0.0 ? 0.0 : (c > top ? top : c);
+        if (c != c) c = 0.0;   // NaN position: any key; flagged by the density loop
+        key |= spread3((uint64_t)c) << a;
+    }
+    return hilbert ? hilbert_key(key, bits, tab) : key;
+}
+
 __global__ __launch_bounds__(256) void k_keys(int64_t n, const double *__restrict__ x,
                                               const double *__restrict__ y,
                                               const double *__restrict__ z, double *box,
@@ -175,25 +202,10 @@ __global__ __launch_bounds__(256) void k_keys(int64_t n, const double *__restric
     int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (k >= n) return;
     double b[6];
-    for (int a = 0; a < 3; a++) {
-        b[a] = fb.fixed ? fb.lo[a] : box[a];
-        b[3 + a] = fb.fixed ? fb.hi[a] : box[3 + a];
-    }
+    key_box(box, fb, b);
     if (fb.fixed && k == 0)
         for (int a = 0; a < 6; a++) box[a] = b[a];
-    double ext = fmax(fmax(b[3] - b[0], b[4] - b[1]), b[5] - b[2]);
-    double cells = (double)(1u << bits);
-    double scale = ext > 0.0 ? cells / ext : 0.0;
-    double top = cells - 1.0;
-    double q[3] = {(x[k] - b[0]) * scale, (y[k] - b[1]) * scale, (z[k] - b[2]) * scale};
-    uint64_t key = 0;
-    for (int a = 0; a < 3; a++) {
-        double c = floor(q[a]);
-        c = c < 0.0 ? 0.0 : (c > top ? top : c);
-        if (c != c) c = 0.0;   // NaN position: any key; flagged by the density loop
-        key |= spread3((uint64_t)c) << a;
-    }
-    keys[k] = hilbert ? hilbert_key(key, bits, tab) : key;
+    keys[k] = position_key(b, x[k], y[k], z[k], bits, hilbert, tab);
     vals[k] = (uint32_t)k;
 }
 
@@ -378,6 +390,105 @@ __global__ __launch_bounds__(kRsThreads) void k_rs_scatter(int64_t n, const uint
     }
 }
 
+// Up to kSmallSet particles: keys and all passes of the sort in one block of 16
+// waves, the keys in LDS.  Wave w holds `rounds` x 64 consecutive keys; ranks as in
+// k_rs_scatter, so the sort is stable and its order the same.  What this saves is
+// launches: 4,096 keys took nine of them, 47 us, and this takes 28 us (1,000: 43 and
+// 11 us).
+constexpr int kSmallSet = 4096;
+
+__global__ __launch_bounds__(1024) void k_sort_small(int n, const double *__restrict__ x,
+                                                     const double *__restrict__ y,
+                                                     const double *__restrict__ z, double *box, FixedBox fb,
+                                                     int bits, int hilbert, uint64_t *__restrict__ keys,
+                                                     uint32_t *__restrict__ vals)
+{
+    constexpr int W = 16, R = kSmallSet / (W * kWave);
+    __shared__ uint64_t skey[kSmallSet];
+    __shared__ uint16_t sval[kSmallSet];
+    __shared__ uint16_t wcnt[W][256];
+    __shared__ uint16_t dbase[256];
+    __shared__ uint32_t sums[W];
+    __shared__ uint8_t tab[sizeof(HilbertTable)];
+    const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
+    if (t < (int)sizeof(HilbertTable)) tab[t] = kHilbert.v[t];
+    __syncthreads();
+    double b[6];
+    key_box(box, fb, b);
+    if (fb.fixed && t == 0)
+        for (int a = 0; a < 6; a++) box[a] = b[a];
+    const int rounds = (n + W * kWave - 1) / (W * kWave);
+    const int base = w * rounds * kWave + lane;
+    const uint64_t lt = __lanemask_lt();
+    uint64_t key[R];
+    uint32_t val[R], rank[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int k = base + r * kWave;
+        // past the end: the largest key, which stays behind all others
+        key[r] = ~0ull;
+        val[r] = 0u;
+        if (r < rounds && k < n) {
+            key[r] = position_key(b, x[k], y[k], z[k], bits, hilbert, tab);
+            val[r] = (uint32_t)k;
+        }
+    }
+    for (int shift = 0; shift < 3 * bits; shift += 8) {
+        for (int k = t; k < W * 256; k += 1024) (&wcnt[0][0])[k] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            if (r >= rounds) break;
+            const uint32_t d = (uint32_t)(key[r] >> shift) & 255u;
+            uint64_t mask = ~0ull;
+            for (int k = 0; k < 8; k++) {
+                const uint64_t bb = __ballot((d >> k) & 1u);
+                mask &= ((d >> k) & 1u) ? bb : ~bb;
+            }
+            const uint32_t before = wcnt[w][d], prior = (uint32_t)__popcll(mask & lt);
+            rank[r] = before + prior;
+            wave_lds_sync();
+            if (prior == 0) wcnt[w][d] = (uint16_t)(before + (uint32_t)__popcll(mask));
+            wave_lds_sync();
+        }
+        __syncthreads();
+        // per digit (one thread each): the waves' offsets, then the digit's first slot
+        uint32_t run = 0, all;
+        if (t < 256)
+            for (int k = 0; k < W; k++) {
+                const uint32_t v = wcnt[k][t];
+                wcnt[k][t] = (uint16_t)run;
+                run += v;
+            }
+        const uint32_t first = block_scan<false, W>(run, sums, all);
+        if (t < 256) dbase[t] = (uint16_t)first;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            if (r >= rounds) break;
+            const uint32_t d = (uint32_t)(key[r] >> shift) & 255u;
+            const uint32_t to = dbase[d] + wcnt[w][d] + rank[r];
+            skey[to] = key[r];
+            sval[to] = (uint16_t)val[r];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            if (r >= rounds) break;
+            key[r] = skey[base + r * kWave];
+            val[r] = sval[base + r * kWave];
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int k = base + r * kWave;
+        if (r < rounds && k < n) {
+            keys[k] = key[r];
+            vals[k] = val[r];
+        }
+    }
+}
+
 // ---- gathers ------------------------------------------------------------------
 
 __global__ __launch_bounds__(256) void k_gather(int64_t n, const uint32_t *__restrict__ perm,
@@ -525,12 +636,8 @@ __global__ __launch_bounds__(kScanThreads) void k_leaf_starts(int64_t n, const u
 }
 
 // tree levels from the leaf count (one thread)
-__global__ void k_tree_info(int64_t n, int G, const uint32_t *__restrict__ toff,
-                            const uint32_t *__restrict__ tcnt, int64_t ntile,
-                            TreeInfo *__restrict__ T)
+__device__ inline void tree_levels(int64_t n, int G, int64_t L, TreeInfo *__restrict__ T)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    int64_t L = (int64_t)toff[ntile - 1] + tcnt[ntile - 1];
     T->leaf_size = G;
     T->n = n;
     int64_t cnt = L, off = 0;
@@ -544,6 +651,47 @@ __global__ void k_tree_info(int64_t n, int G, const uint32_t *__restrict__ toff,
     }
     T->nlev = lev;
     for (int l = lev; l < kMaxLevels; l++) { T->off[l] = off; T->cnt[l] = 0; }
+}
+
+__global__ void k_tree_info(int64_t n, int G, const uint32_t *__restrict__ toff,
+                            const uint32_t *__restrict__ tcnt, int64_t ntile,
+                            TreeInfo *__restrict__ T)
+{
+    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+    tree_levels(n, G, (int64_t)toff[ntile - 1] + tcnt[ntile - 1], T);
+}
+
+// Up to kSmallSet particles: segments, leaf starts and tree levels in one block
+// (the six launches above took 22 us for 1,000 particles; this takes 6 us, and 9 us
+// for 4,096).
+__global__ __launch_bounds__(1024) void k_leaves_small(int n, int G, const uint64_t *__restrict__ keys,
+                                                       const double *__restrict__ h,
+                                                       const double *__restrict__ box, int bits,
+                                                       uint32_t *__restrict__ lstart, TreeInfo *__restrict__ T)
+{
+    constexpr int E = kSmallSet / 1024;   // consecutive particles per thread
+    __shared__ uint32_t sh[16];
+    const double ext = fmax(fmax(box[3] - box[0], box[4] - box[1]), box[5] - box[2]);
+    const int base = threadIdx.x * E;
+    bool brk[E];
+    uint32_t mx = 0, all;
+    for (int e = 0; e < E; e++) {
+        brk[e] = base + e < n && seg_break(base + e, keys, h, ext, bits);
+        if (brk[e]) mx = (uint32_t)(base + e);
+    }
+    uint32_t seg = block_scan<true, 16>(mx, sh, all);
+    uint32_t starts = 0;   // bit e: a leaf starts at item e
+    for (int e = 0; e < E; e++) {
+        if (brk[e]) seg = (uint32_t)(base + e);
+        if (base + e < n && ((uint32_t)(base + e) - seg) % (uint32_t)G == 0u) starts |= 1u << e;
+    }
+    uint32_t run = block_scan<false, 16>((uint32_t)__popc(starts), sh, all);
+    for (int e = 0; e < E; e++)
+        if ((starts >> e) & 1u) lstart[run++] = (uint32_t)(base + e);
+    if (threadIdx.x == 0) {
+        lstart[all] = (uint32_t)n;
+        tree_levels(n, G, all, T);
+    }
 }
 
 __device__ inline Node merge_children(const Node *__restrict__ child, int64_t c0, int64_t c1)
@@ -615,10 +763,9 @@ __global__ __launch_bounds__(256) void k_leaves(const TreeInfo *__restrict__ T,
 
 // largest h of every leaf after the h solve changed h (boxes are unchanged),
 // one thread per leaf over its consecutive particles
-__global__ __launch_bounds__(256) void k_leaf_hmax(const TreeInfo *__restrict__ T,
-                                                   const uint32_t *__restrict__ lstart,
-                                                   const double *__restrict__ h,
-                                                   Node *__restrict__ nodes)
+// The leaves' largest h, by the grid's 16-lane groups.
+__device__ inline void leaf_hmax(const TreeInfo *__restrict__ T, const uint32_t *__restrict__ lstart,
+                                 const double *__restrict__ h, Node *__restrict__ nodes)
 {
     const int64_t L = T->cnt[0];
     const int q = threadIdx.x % kLeafLanes;
@@ -631,7 +778,15 @@ __global__ __launch_bounds__(256) void k_leaf_hmax(const TreeInfo *__restrict__ 
     }
 }
 
-constexpr int64_t kSmallLevel = 2048;   // children per level handled by one block
+__global__ __launch_bounds__(256) void k_leaf_hmax(const TreeInfo *__restrict__ T,
+                                                   const uint32_t *__restrict__ lstart,
+                                                   const double *__restrict__ h,
+                                                   Node *__restrict__ nodes)
+{
+    leaf_hmax(T, lstart, h, nodes);
+}
+
+constexpr int64_t kSmallLevel = 4096;   // children per level handled by one block
 constexpr int kBigLevels = 4;           // levels built grid-wide at most
 
 // level `lev` from level lev-1, grid-wide, when the child level is large
@@ -669,7 +824,8 @@ __global__ __launch_bounds__(1024) void k_tree_level_small(const TreeInfo *__res
 
 // Force record of particle k: A_k = P_k / (Omega_k rho_k^2),
 // c_k = sqrt(gamma P_k / rho_k), 1/h_k, v_k, m_k, rho_k with
-// P_k = (gamma - 1) rho_k u_k.  Also (R h_k)^2 into the position records.
+// P_k = (gamma - 1) rho_k u_k.  Also (R h_k)^2 into the position records and,
+// with a tree, its leaves' largest h (the same h, one launch fewer).
 __global__ __launch_bounds__(256) void k_force_prep(int64_t n, double gamma,
                                                     const double *__restrict__ rho,
                                                     const double *__restrict__ omega,
@@ -681,8 +837,12 @@ __global__ __launch_bounds__(256) void k_force_prep(int64_t n, double gamma,
                                                     const double *__restrict__ vz,
                                                     ForceRec *__restrict__ rec,
                                                     ForceRec32 *__restrict__ rec32, double support,
-                                                    Pos4 *__restrict__ pos, Off4 *__restrict__ off)
+                                                    Pos4 *__restrict__ pos, Off4 *__restrict__ off,
+                                                    const TreeInfo *__restrict__ T,
+                                                    const uint32_t *__restrict__ lstart,
+                                                    Node *__restrict__ nodes)
 {
+    if (T) leaf_hmax(T, lstart, h, nodes);
     int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (k >= n) return;
     const double r = rho[k];
@@ -751,6 +911,15 @@ sph_status build_order(sph_ctx *c, int64_t n, const double *x, const double *y, 
     }
     const int bits = key_bits(n);
     const int hilbert = p.precision == SPH_FP64 && !state ? 1 : 0;
+    if (n <= kSmallSet) {
+        hipLaunchKernelGGL(k_sort_small, dim3(1), dim3(1024), 0, c->stream, (int)n, x, y, z, c->d_box, fb, bits,
+                           hilbert, c->keys[0], c->vals[0]);
+        c->perm = c->vals[0];
+        c->skeys = c->keys[0];
+        c->scratch_u32 = (uint32_t *)c->keys[1];
+        c->tree_n = -1;
+        return hip_check(c, hipGetLastError(), "build_order");
+    }
     hipLaunchKernelGGL(k_keys, dim3(grid_for(n, 256)), dim3(256), 0, c->stream, n, x, y, z,
                        c->d_box, fb, bits, hilbert, c->keys[0], c->vals[0]);
     // (a stable sort's result does not depend on the tiling)
@@ -834,20 +1003,25 @@ sph_status build_tree(sph_ctx *c, int64_t n)
     if (c->node_cap < node_count_bound(n)) return fail(c, SPH_ENOMEM, "node capacity");
     uint32_t *tmax = c->hist, *tcnt = c->hist + ntile;
     uint32_t *flag = c->scratch_u32;
-    hipLaunchKernelGGL(k_seg_tiles, dim3((unsigned)ntile), dim3(kScanThreads), 0, c->stream, n,
-                       c->skeys, c->s.h, c->d_box, key_bits(n), flag, tmax);
-    hipLaunchKernelGGL((k_scan_tiles<true>), dim3(1), dim3(1024), 0, c->stream, tmax, ntile,
-                       (uint32_t *)nullptr);
-    hipLaunchKernelGGL(k_seg_apply, dim3((unsigned)ntile), dim3(kScanThreads), 0, c->stream, n, G,
-                       flag, tmax, tcnt);
-    // tcnt -> exclusive offsets in place; the counts themselves go to tmax
-    // for the total
-    hipLaunchKernelGGL((k_scan_tiles<false>), dim3(1), dim3(1024), 0, c->stream, tcnt, ntile,
-                       tmax);
-    hipLaunchKernelGGL(k_tree_info, dim3(1), dim3(64), 0, c->stream, n, G, tcnt, tmax, ntile,
-                       c->d_tree);
-    hipLaunchKernelGGL(k_leaf_starts, dim3((unsigned)ntile), dim3(kScanThreads), 0, c->stream, n,
-                       flag, tcnt, c->lstart);
+    if (n <= kSmallSet) {
+        hipLaunchKernelGGL(k_leaves_small, dim3(1), dim3(1024), 0, c->stream, (int)n, G, c->skeys, c->s.h,
+                           c->d_box, key_bits(n), c->lstart, c->d_tree);
+    } else {
+        hipLaunchKernelGGL(k_seg_tiles, dim3((unsigned)ntile), dim3(kScanThreads), 0, c->stream, n,
+                           c->skeys, c->s.h, c->d_box, key_bits(n), flag, tmax);
+        hipLaunchKernelGGL((k_scan_tiles<true>), dim3(1), dim3(1024), 0, c->stream, tmax, ntile,
+                           (uint32_t *)nullptr);
+        hipLaunchKernelGGL(k_seg_apply, dim3((unsigned)ntile), dim3(kScanThreads), 0, c->stream, n, G,
+                           flag, tmax, tcnt);
+        // tcnt -> exclusive offsets in place; the counts themselves go to tmax
+        // for the total
+        hipLaunchKernelGGL((k_scan_tiles<false>), dim3(1), dim3(1024), 0, c->stream, tcnt, ntile,
+                           tmax);
+        hipLaunchKernelGGL(k_tree_info, dim3(1), dim3(64), 0, c->stream, n, G, tcnt, tmax, ntile,
+                           c->d_tree);
+        hipLaunchKernelGGL(k_leaf_starts, dim3((unsigned)ntile), dim3(kScanThreads), 0, c->stream, n,
+                           flag, tcnt, c->lstart);
+    }
     hipLaunchKernelGGL(k_leaves, dim3(grid_for(n, 256)), dim3(256), 0, c->stream, c->d_tree,
                        c->lstart, c->s.x, c->s.y, c->s.z, c->s.h, c->nodes,
                        f32 ? nullptr : c->s.pos(), f32 ? c->s.off : nullptr);
@@ -868,14 +1042,17 @@ sph_status refresh_hmax(sph_ctx *c, int64_t n)
 }
 
 sph_status force_prep(sph_ctx *c, int64_t n, const double *u_sorted, const double *vx,
-                      const double *vy, const double *vz)
+                      const double *vy, const double *vz, bool hmax)
 {
     if (n == 0) return SPH_OK;
+    if (hmax && c->tree_n != n) return fail(c, SPH_ESTATE, "force_prep: tree not built");
     const bool f32 = c->p.precision == SPH_FP32_PAIR;
     hipLaunchKernelGGL(k_force_prep, dim3(grid_for(n, 256)), dim3(256), 0, c->stream, n,
                        c->p.gamma, c->s.rho, c->s.omega, u_sorted, c->s.h, c->s.m, vx, vy, vz,
                        c->s.frec, f32 ? c->s.frec32 : nullptr, kern_support(c->p.kernel),
-                       f32 ? nullptr : c->s.pos(), f32 ? c->s.off : nullptr);
+                       f32 ? nullptr : c->s.pos(), f32 ? c->s.off : nullptr,
+                       hmax ? c->d_tree : nullptr, c->lstart, c->nodes);
+    if (hmax) upper_levels(c, n);
     return hip_check(c, hipGetLastError(), "force_prep");
 }
 

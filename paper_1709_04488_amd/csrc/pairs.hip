@@ -50,14 +50,31 @@ inline void fill_common(sph_ctx *c, int64_t n, Args &a)
 namespace {
 
 // A set's pair-loop prologue in one launch: its argument block, its counters
-// of that loop and its claim counters zeroed.  Stream order puts it after the
+// of that loop and its claim counters zeroed, and with mrange the smallest and
+// largest mass from the blocks' partial results.  Stream order puts it after the
 // set's previous pair loop and before the next launch that reads them (a
 // batched launch claims through its first set's counters).
 template <class Args>
 __global__ void k_prologue(Args a, Args *dst, int64_t *__restrict__ counts, int first, int nwords,
-                           int first2, int nwords2, uint32_t *__restrict__ work)
+                           int first2, int nwords2, uint32_t *__restrict__ work,
+                           const double *__restrict__ mparts, int nparts, double *__restrict__ mrange)
 {
     const int t = threadIdx.x;
+    if (mrange) {
+        double lo = INFINITY, hi = -INFINITY;
+        for (int b = t; b < nparts; b += 64) {
+            lo = fmin(lo, mparts[2 * b]);
+            hi = fmax(hi, mparts[2 * b + 1]);
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            lo = fmin(lo, __shfl_xor(lo, o));
+            hi = fmax(hi, __shfl_xor(hi, o));
+        }
+        if (t == 0) {
+            mrange[0] = lo;
+            mrange[1] = hi;
+        }
+    }
     if (t == 0) *dst = a;
     for (int k = 0; k < nwords; k++) counts[t * kCountWords + first + k] = 0;
     for (int k = 0; k < nwords2; k++) counts[t * kCountWords + first2 + k] = 0;
@@ -99,10 +116,11 @@ sph_status density_prepare(sph_ctx *c, int64_t n)
         if (!q) return fail(c, SPH_EINVAL, "density: internal buffer not allocated");
     if (!a.pos || !a.off) return fail(c, SPH_EINVAL, "density: positions not allocated");
     if (c->tree_n != n || n <= 0) return fail(c, SPH_ESTATE, "density: tree not built");
-    TRY_(reduce_mass_range(c, n));
+    int nparts = 0;
+    TRY_(reduce_mass_range(c, n, &nparts));
     hipLaunchKernelGGL(k_prologue<DensArgs>, dim3(1), dim3(64), 0, c->stream, a,
                        (DensArgs *)c->d_dargs, c->d_counts, (int)kCntDensFirst, (int)kCntDensWords,
-                       (int)kCntDensListOverflows, 1, c->d_work);
+                       (int)kCntDensListOverflows, 1, c->d_work, c->d_part, nparts, c->d_scal + 8);
     return hip_check(c, hipGetLastError(), "density arguments");
 }
 
@@ -151,7 +169,8 @@ sph_status forces_prepare(sph_ctx *c, int64_t n)
     if (c->tree_n != n || n <= 0) return fail(c, SPH_ESTATE, "forces: tree not built");
     hipLaunchKernelGGL(k_prologue<ForceArgs>, dim3(1), dim3(64), 0, c->stream, a,
                        (ForceArgs *)c->d_fargs, c->d_counts, (int)kCntForceFirst,
-                       (int)kCntForceWords, 0, 0, c->d_work);
+                       (int)kCntForceWords, 0, 0, c->d_work, (const double *)nullptr, 0,
+                       (double *)nullptr);
     return hip_check(c, hipGetLastError(), "force arguments");
 }
 

@@ -433,7 +433,7 @@ sph_status build_tree(sph_ctx *c, int64_t n);
 sph_status refresh_hmax(sph_ctx *c, int64_t n);
 // Force records from rho, omega, h, m and the given sorted u and velocities.
 sph_status force_prep(sph_ctx *c, int64_t n, const double *u_sorted, const double *vx,
-                      const double *vy, const double *vz);
+                      const double *vy, const double *vz, bool hmax);
 sph_status iota(sph_ctx *c, int64_t n, uint32_t *v);
 int64_t node_count_bound(int64_t n);
 
@@ -510,10 +510,10 @@ sph_status block_next(sph_ctx *c, int64_t n);           // Tn = min te; drift ev
 sph_status block_predict(sph_ctx *c, int64_t n);        // predictors, active set, leaf counts
 sph_status block_finish(sph_ctx *c, int64_t n, bool init);  // close, levels, limiter, open, clock
 sph_status block_av(sph_ctx *c, int64_t n);             // switches of the active particles
-sph_status reduce_dt(sph_ctx *c, int64_t n);
-// smallest and largest sorted mass -> d_scal[8], d_scal[9]
-sph_status reduce_mass_range(sph_ctx *c, int64_t n);
-sph_status reduce_diag(sph_ctx *c, int64_t n);
+// smallest and largest sorted mass per block -> d_part[2b], d_part[2b + 1]
+sph_status reduce_mass_range(sph_ctx *c, int64_t n, int *blocks);
+// conserved quantities and neighbour counts; with_dt: and min dt -> d_scal[0]
+sph_status reduce_diag(sph_ctx *c, int64_t n, bool with_dt);
 // zero d_counts[first..first+count) with a kernel (capture-safe, no memset)
 sph_status zero_counts(sph_ctx *c, int first, int count);
 // zero the per-XCD claim counters of the persistent pair kernels

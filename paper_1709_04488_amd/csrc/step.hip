@@ -185,41 +185,8 @@ __global__ __launch_bounds__(256) void k_av_cd10(int64_t n, double amin, double 
     dprev[k] = d;
 }
 
-// min over dt_i -> scal[0]
-__global__ __launch_bounds__(kRedThreads) void k_min_partial(int64_t n, const double *__restrict__ v,
-                                                             double *__restrict__ part)
-{
-    double mn = INFINITY;
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n;
-         k += (int64_t)gridDim.x * blockDim.x)
-        mn = fmin(mn, v[k]);
-    __shared__ double sh[kRedThreads];
-    sh[threadIdx.x] = mn;
-    __syncthreads();
-    for (int s = kRedThreads / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] = fmin(sh[threadIdx.x], sh[threadIdx.x + s]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
-}
-
-__global__ __launch_bounds__(kRedThreads) void k_min_final(int nb, const double *__restrict__ part,
-                                                           double *__restrict__ out)
-{
-    __shared__ double sh[kRedThreads];
-    double mn = INFINITY;
-    for (int b = threadIdx.x; b < nb; b += kRedThreads) mn = fmin(mn, part[b]);
-    sh[threadIdx.x] = mn;
-    __syncthreads();
-    for (int s = kRedThreads / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) sh[threadIdx.x] = fmin(sh[threadIdx.x], sh[threadIdx.x + s]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[0] = sh[0];
-}
-
-// smallest and largest mass -> out[0], out[1] (equal masses let the density
-// loop keep only r^2 in its candidate lists)
+// smallest and largest mass of each block's particles (the density loop's prologue
+// finishes; equal masses let the loop keep only r^2 in its candidate lists)
 __global__ __launch_bounds__(kRedThreads) void k_mrange_partial(int64_t n, const double *__restrict__ m,
                                                                 double *__restrict__ part)
 {
@@ -246,34 +213,17 @@ __global__ __launch_bounds__(kRedThreads) void k_mrange_partial(int64_t n, const
     }
 }
 
-__global__ __launch_bounds__(kRedThreads) void k_mrange_final(int nb, const double *__restrict__ part,
-                                                              double *__restrict__ out)
+static_assert(kRedVals == 8, "seven sums and a minimum");
+__device__ inline void diag_merge(double (*sh)[kRedThreads], int to, int from)
 {
-    __shared__ double sl[kRedThreads], sh[kRedThreads];
-    double lo = INFINITY, hi = -INFINITY;
-    for (int b = threadIdx.x; b < nb; b += kRedThreads) {
-        lo = fmin(lo, part[2 * b]);
-        hi = fmax(hi, part[2 * b + 1]);
-    }
-    sl[threadIdx.x] = lo;
-    sh[threadIdx.x] = hi;
-    __syncthreads();
-    for (int s = kRedThreads / 2; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) {
-            sl[threadIdx.x] = fmin(sl[threadIdx.x], sl[threadIdx.x + s]);
-            sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + s]);
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        out[0] = sl[0];
-        out[1] = sh[0];
-    }
+    for (int a = 0; a < 7; a++) sh[a][to] += sh[a][from];
+    sh[7][to] = fmin(sh[7][to], sh[7][from]);
 }
 
 // Sums in a fixed order (grid-stride per thread, fixed tree per block, fixed
 // order over blocks), so they are reproducible bit for bit.
-//   [0] 1/2 m v^2  [1] m u  [2..4] m v  [5] sum nngb  [6] sum nforce
+//   [0] 1/2 m v^2  [1] m u  [2..4] m v  [5] sum nngb  [6] sum nforce  [7] min dt
+// (dt null: left out)
 __global__ __launch_bounds__(kRedThreads) void k_diag_partial(int64_t n, const double *__restrict__ m,
                                                               const double *__restrict__ vx,
                                                               const double *__restrict__ vy,
@@ -281,9 +231,10 @@ __global__ __launch_bounds__(kRedThreads) void k_diag_partial(int64_t n, const d
                                                               const double *__restrict__ u,
                                                               const int32_t *__restrict__ nngb,
                                                               const int32_t *__restrict__ nforce,
+                                                              const double *__restrict__ dt,
                                                               double *__restrict__ part)
 {
-    double acc[kRedVals] = {0, 0, 0, 0, 0, 0, 0, 0};
+    double acc[kRedVals] = {0, 0, 0, 0, 0, 0, 0, INFINITY};
     for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n;
          k += (int64_t)gridDim.x * blockDim.x) {
         double mk = m[k];
@@ -294,13 +245,14 @@ __global__ __launch_bounds__(kRedThreads) void k_diag_partial(int64_t n, const d
         acc[4] += mk * vz[k];
         acc[5] += (double)nngb[k];
         acc[6] += (double)nforce[k];
+        if (dt) acc[7] = fmin(acc[7], dt[k]);
     }
     __shared__ double sh[kRedVals][kRedThreads];
     for (int a = 0; a < kRedVals; a++) sh[a][threadIdx.x] = acc[a];
     __syncthreads();
     for (int s = kRedThreads / 2; s > 0; s >>= 1) {
         if ((int)threadIdx.x < s)
-            for (int a = 0; a < kRedVals; a++) sh[a][threadIdx.x] += sh[a][threadIdx.x + s];
+            diag_merge(sh, threadIdx.x, threadIdx.x + s);
         __syncthreads();
     }
     if (threadIdx.x < kRedVals) part[blockIdx.x * kRedVals + threadIdx.x] = sh[threadIdx.x][0];
@@ -310,22 +262,25 @@ __global__ __launch_bounds__(kRedThreads) void k_diag_partial(int64_t n, const d
 // fixed tree over the 256 threads
 __global__ __launch_bounds__(kRedThreads) void k_diag_final(int nb, const double *__restrict__ part,
                                                             double *__restrict__ scal,
-                                                            int64_t *__restrict__ counts)
+                                                            int64_t *__restrict__ counts, int with_dt)
 {
     __shared__ double sh[kRedVals][kRedThreads];
     double acc[kRedVals];
-    for (int v = 0; v < kRedVals; v++) acc[v] = 0.0;
-    for (int b = threadIdx.x; b < nb; b += kRedThreads)
-        for (int v = 0; v < kRedVals; v++) acc[v] += part[b * kRedVals + v];
+    for (int v = 0; v < kRedVals; v++) acc[v] = v == 7 ? INFINITY : 0.0;
+    for (int b = threadIdx.x; b < nb; b += kRedThreads) {
+        for (int v = 0; v < 7; v++) acc[v] += part[b * kRedVals + v];
+        acc[7] = fmin(acc[7], part[b * kRedVals + 7]);
+    }
     for (int v = 0; v < kRedVals; v++) sh[v][threadIdx.x] = acc[v];
     __syncthreads();
     for (int st = kRedThreads / 2; st > 0; st >>= 1) {
         if ((int)threadIdx.x < st)
-            for (int v = 0; v < kRedVals; v++) sh[v][threadIdx.x] += sh[v][threadIdx.x + st];
+            diag_merge(sh, threadIdx.x, threadIdx.x + st);
         __syncthreads();
     }
     if (threadIdx.x < 5) scal[3 + threadIdx.x] = sh[threadIdx.x][0];
     else if (threadIdx.x < 7) counts[threadIdx.x - 5] = (int64_t)sh[threadIdx.x][0];
+    else if (threadIdx.x == 7 && with_dt) scal[0] = sh[7][0];
 }
 
 __global__ __launch_bounds__(1024) void k_scan_offsets(int64_t n, int64_t *__restrict__ a)
@@ -916,26 +871,13 @@ sph_status closing_kick(sph_ctx *c, int64_t n, double dt_host)
     return hip_check(c, hipGetLastError(), "closing_kick");
 }
 
-sph_status reduce_mass_range(sph_ctx *c, int64_t n)
+sph_status reduce_mass_range(sph_ctx *c, int64_t n, int *blocks)
 {
     if (n == 0) return SPH_OK;
-    const int nb = (int)std::min<int64_t>(kRedBlocks / 2, (n + kRedThreads - 1) / kRedThreads);
-    hipLaunchKernelGGL(k_mrange_partial, dim3(nb), dim3(kRedThreads), 0, c->stream, n, c->s.m,
+    *blocks = (int)std::min<int64_t>(kRedBlocks / 2, (n + kRedThreads - 1) / kRedThreads);
+    hipLaunchKernelGGL(k_mrange_partial, dim3(*blocks), dim3(kRedThreads), 0, c->stream, n, c->s.m,
                        c->d_part);
-    hipLaunchKernelGGL(k_mrange_final, dim3(1), dim3(kRedThreads), 0, c->stream, nb, c->d_part,
-                       c->d_scal + 8);
     return hip_check(c, hipGetLastError(), "reduce_mass_range");
-}
-
-sph_status reduce_dt(sph_ctx *c, int64_t n)
-{
-    if (n == 0) return SPH_OK;
-    int nb = (int)std::min<int64_t>(kRedBlocks, (n + kRedThreads - 1) / kRedThreads);
-    hipLaunchKernelGGL(k_min_partial, dim3(nb), dim3(kRedThreads), 0, c->stream, n, c->s.dt,
-                       c->d_part);
-    hipLaunchKernelGGL(k_min_final, dim3(1), dim3(kRedThreads), 0, c->stream, nb, c->d_part,
-                       c->d_scal);
-    return hip_check(c, hipGetLastError(), "reduce_dt");
 }
 
 __global__ void k_zero_work(uint32_t *__restrict__ w)
@@ -961,14 +903,15 @@ sph_status scan_offsets(sph_ctx *c, int64_t n, int64_t *a)
     return hip_check(c, hipGetLastError(), "scan_offsets");
 }
 
-sph_status reduce_diag(sph_ctx *c, int64_t n)
+sph_status reduce_diag(sph_ctx *c, int64_t n, bool with_dt)
 {
     if (n == 0) return SPH_OK;
     int nb = (int)std::min<int64_t>(kRedBlocks, (n + kRedThreads - 1) / kRedThreads);
     hipLaunchKernelGGL(k_diag_partial, dim3(nb), dim3(kRedThreads), 0, c->stream, n, c->s.m,
-                       c->s.vx, c->s.vy, c->s.vz, c->s.u, c->s.nngb, c->s.nforce, c->d_part);
+                       c->s.vx, c->s.vy, c->s.vz, c->s.u, c->s.nngb, c->s.nforce,
+                       with_dt ? c->s.dt : nullptr, c->d_part);
     hipLaunchKernelGGL(k_diag_final, dim3(1), dim3(kRedThreads), 0, c->stream, nb, c->d_part,
-                       c->d_scal, c->d_counts);
+                       c->d_scal, c->d_counts, with_dt ? 1 : 0);
     return hip_check(c, hipGetLastError(), "reduce_diag");
 }
 
