@@ -1449,13 +1449,18 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
         const int64_t i = first + p;
         const bool active = p < nhome && (!A.active || as_global(A.active)[i] != 0);
         if (__ballot(active) == 0ull) return;
-        // entries that a step of a particle's lanes reads, and a list's (whole steps)
-        const int CHUNK = 4 * LPP, KP = (Kern<K>::list << (split - slice_split(A.n, G, splits(*B.req[r])))) & -CHUNK;
         const int64_t ii = active ? i : first;
         const double mi = as_global(A.m)[ii];
         const double mu = as_const(A.mrange)[0];
         const bool equal_m = mu == as_const(A.mrange)[1];
         const bool tight = F64 && A.h_rtol <= kTightTol;
+        // entries that a step of a particle's lanes reads, and a list's (whole
+        // steps): the scratch holds an r^2 and a mass per entry as doubles, so equal
+        // masses leave room for twice as many, four times with single-precision r^2
+        // (a list that fills up is summed up in every pass instead of once: 12,167
+        // particles FP32-pair 160 -> 104 us)
+        const int more = (split - slice_split(A.n, G, splits(*B.req[r]))) + (equal_m ? (F64 ? 1 : 2) : 0);
+        const int CHUNK = 4 * LPP, KP = (Kern<K>::list << more) & -CHUNK;
         double h = as_global((const double *)A.h)[ii];
         double lo_b = 0.0, hi_b = INFINITY;
         bool conv = !active;

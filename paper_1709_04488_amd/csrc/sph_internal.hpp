@@ -137,7 +137,8 @@ __host__ __device__ inline int slice_split(int64_t n, int G, bool splits)
 // at eta = 1.2; 480 for the quintic's ~300 within 3 Rc), each an FP64 r^2 and
 // an FP64 mass, for the candidates within R Rc, Rc = kCacheGrow h (capped by
 // the walk radius), so that Newton steps within that bound reuse them.  A
-// block holds the lists of one leaf's G particles.
+// block holds the lists of one leaf's G particles; with equal masses the masses'
+// places hold r^2 too.
 constexpr double kCacheGrow = 1.15;
 inline int64_t cache_bytes(int G, int kernel, int64_t blocks)
 {
