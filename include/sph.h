@@ -5,7 +5,7 @@
  * SPH main loop described in the GANDALF paper (Hubber, Rosotti & Booth 2017,
  * arXiv:1709.04488, sections 2.1 and 5.1):
  *
- *   neighbour search  -- a Morton-key radix sort and a leaf/box tree over the
+ *   neighbour search  -- a radix sort along a space-filling curve and a leaf/box tree over the
  *                        sorted particles (the paper's KD-tree with N_LEAF
  *                        particles per leaf and smoothing-sphere extent boxes,
  *                        section 4.2, rebuilt for the GPU)
@@ -170,8 +170,8 @@ typedef struct {
     int32_t kernel;     /* SPH_KERNEL_M4 (default, R = 2) or SPH_KERNEL_QUINTIC (R = 3) */
     /* Launch shape of the density and force loops (the autotuner's knobs
      * besides leaf_size; neither changes what is computed):
-     *   stage_leaves: candidate leaves staged in LDS per step of a sweep,
-     *     1..128/leaf_size (0: all 128/leaf_size the LDS tile holds).  The
+     *   stage_leaves: how many candidate leaves a sweep handles at a time,
+     *     1..128/leaf_size (0: the most, 64 leaves; k: k leaf_size / 2 of them).  The
      *     density results do not depend on it; the force sums may change in
      *     their last bits (the split of a particle's terms over its lanes).
      *   claim_leaves: home leaves a wavefront claims per atomic claim of the
@@ -286,7 +286,7 @@ sph_status sph_set_stream(sph_ctx *ctx, void *hip_stream);
 sph_status sph_set_params(sph_ctx *ctx, const sph_params *p);
 
 /*
- * Neighbour-search structure for ps (reads x, y, z, h): bounding box, Morton
+ * Neighbour-search structure for ps (reads x, y, z, h): bounding box, curve
  * keys, device radix sort, sorted copies of the particle data, leaves of
  * leaf_size consecutive particles with their bounding boxes and largest h, and
  * the tree of boxes above them.  sph_density builds it itself; this entry

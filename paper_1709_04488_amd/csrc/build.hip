@@ -1,10 +1,10 @@
-// Neighbour-search structure: bounding box, Morton keys, LSD radix sort,
+// Neighbour-search structure: bounding box, Hilbert or Morton keys, LSD radix sort,
 // gathers into sorted order, leaf boxes and the 8-ary box tree above them.
 //
 // The paper builds a balanced KD-tree by median splits with N_LEAF particles
 // per leaf and propagates each cell's smoothing-sphere extent box upwards
-// (section 4.2).  On the GPU the same role is played by a Morton-order sort
-// (one radix sort instead of a recursive median selection, which the paper
+// (section 4.2).  On the GPU the same role is played by a sort along a
+// space-filling curve (one radix sort instead of a recursive median selection, which the paper
 // names as its tree-build scaling bottleneck, section 5.2.1) followed by
 // leaves of leaf_size consecutive sorted particles; every leaf and node keeps
 // the bounding box of its particles and their largest h.
@@ -18,7 +18,7 @@ namespace {
 
 constexpr int kBoxThreads = 256;
 constexpr int kRsThreads = 256;
-// Bits per axis of the Morton key, by set size: at least 64 cells per mean
+// Bits per axis of the key, by set size: at least 64 cells per mean
 // particle spacing along an axis (particles sharing a cell keep their input
 // order: the sort is stable), rounded up to what a number of 8-bit passes
 // holds: 10 bits (4 passes) up to 2^12 particles, 13 (5 passes) up to 2^21,
@@ -509,11 +509,11 @@ __global__ void k_iota(int64_t n, uint32_t *__restrict__ v)
 // ---- leaves and tree -------------------------------------------------------------
 //
 // Leaves are runs of at most G consecutive sorted particles that never cross
-// the boundary of a Morton cell about 4 h wide: a new segment starts between
+// the boundary of a cell of the curve about 4 h wide: a new segment starts between
 // sorted particles k-1 and k when their keys differ above the level whose
 // cell edge is the largest power-of-two fraction of the box not below
 // 4 max(h_k-1, h_k).  Without this rule a run of G particles can straddle a
-// jump of the Morton curve and get a box as large as the domain.
+// jump of the curve and get a box as large as the domain.
 
 constexpr int kScanTile = 1024;     // particles per block in the leaf scans
 constexpr int kScanThreads = 256;   // 4 particles per thread

@@ -4,21 +4,23 @@
 // Work decomposition (the GPU analogue of the paper's per-leaf-cell neighbour
 // gathering, section 4.2, with a leaf as the unit of work as in its OpenMP
 // loop, section 5.2.1): one wavefront per home leaf of at most G sorted
-// particles, 64/G lanes per particle.  The wave walks the box tree to collect
-// the leaves that can hold neighbours of its particles into an LDS list.
-// Candidate leaves are then handled 128/G at a time (128 candidate slots):
-//   stage  -- one coalesced load per field brings their positions into LDS;
-//   test   -- each (home particle, staged leaf) combination is first judged
-//             by the distance from the particle to the leaf's box; the
-//             passing ones are dealt out over the 64 lanes, which test their
-//             candidates and set hit bits in a per-particle 128-bit mask
-//             (no pair arithmetic yet);
-//   flush  -- each particle's lanes evaluate the pair terms of its hits.
-// The test is cheap and runs for every candidate of a passing combination;
-// the expensive pair terms run only for hits, with the lanes compacted (a
-// wave-wide branch on "any lane hit" would otherwise execute them for almost
-// every candidate).  Each output is accumulated by its own lanes in a fixed
-// order, so results are deterministic and need no atomics.
+// particles, or per share of one in small sets, its lanes divided among the home
+// particles.  The wave walks the box tree to collect the leaves that can hold
+// neighbours of its particles into an LDS list.  Candidate leaves are then handled
+// in groups of up to 64, one per lane:
+//   open  -- each lane's leaf, its particle count and its periodic shift go to a
+//            table in LDS;
+//   find  -- FP64 density: each home particle in turn against a candidate per
+//            lane, ballots rank the hits and their r^2 goes to the particle's list
+//            in global scratch; forces and FP32-pair density: matrix products
+//            of candidates and home particles, whose signs are the hits, as a list
+//            of candidate slots per home particle in LDS;
+//   use   -- each particle's lanes share its list: pair terms, or r^2 to the
+//            density loop's scratch lists, which every Newton step then reads.
+// The expensive pair terms run only for hits, with the lanes compacted.  Each
+// output is accumulated by its own lanes in a fixed order, so results are
+// deterministic and need no atomics.  The neighbour export and the MFV geometry
+// still stage candidates in LDS and test them lane by lane (for_each_leaf_group).
 //
 // This header holds the kernels, templated on the smoothing kernel; it is
 // compiled by pairs_m4.hip and pairs_quintic.hip only.

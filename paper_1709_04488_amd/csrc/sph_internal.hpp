@@ -260,7 +260,7 @@ struct alignas(16) Off4 {
 };
 static_assert(sizeof(Pos4) == sizeof(ForceRec32), "they share memory");
 
-// Arrays in sorted (Morton) order.
+// Arrays in sorted order (along the Hilbert or Morton curve).
 struct Sorted {
     double *x = nullptr, *y = nullptr, *z = nullptr;
     double *vx = nullptr, *vy = nullptr, *vz = nullptr;

@@ -6,10 +6,9 @@ Three separate choices of how the density and force loops map onto the GPU
 * leaf size G (8, 16 or 32 particles) -- the cell size.  One wavefront per
   leaf of G home particles with 64/G lanes each; smaller leaves give tighter
   candidate sets but more tree walks per particle.
-* LDS stage depth (stage_leaves) -- candidate leaves staged in LDS per step
-  of a sweep: the whole tile (128/G leaves) or half of it.  A shallower stage
-  runs more, smaller test-and-flush rounds with denser hit masks; a deeper
-  one fewer rounds.
+* stage depth (stage_leaves) -- candidate leaves that a sweep handles at a
+  time: 64 (stage_leaves = 128/G) or half as many.  A shallower stage runs more,
+  smaller rounds of setting up and testing; a deeper one fewer rounds.
 * claim size (claim_leaves) -- home leaves a wavefront takes per atomic claim
   of the persistent loop (1 or 4): the wavefront-to-cell mapping.  Larger
   claims give a wave a run of neighbouring leaves (shared candidates in L2,
