@@ -777,7 +777,7 @@ sph_status sph_create(sph_ctx **out, const sph_params *p, void *hip_stream, size
               hipMalloc((void **)&c->d_box, sizeof(double) * 8) == hipSuccess &&
               hipMalloc((void **)&c->d_part, sizeof(double) * 1024 * 8) == hipSuccess &&
               hipMalloc((void **)&c->d_tree, sizeof(TreeInfo)) == hipSuccess &&
-              hipMalloc((void **)&c->d_work, sizeof(uint32_t) * kXcds * kWorkStride) == hipSuccess &&
+              hipMalloc((void **)&c->d_work, sizeof(uint32_t) * kWorkWords) == hipSuccess &&
               hipMalloc(&c->d_dargs, kArgBytes) == hipSuccess &&
               hipMalloc(&c->d_fargs, kArgBytes) == hipSuccess &&
               hipMalloc((void **)&c->d_clock, sizeof(BlockClock)) == hipSuccess &&

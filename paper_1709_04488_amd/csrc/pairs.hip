@@ -55,6 +55,12 @@ namespace {
 // set's previous pair loop and before the next launch that reads them (a
 // batched launch claims through its first set's counters).
 template <class Args>
+__host__ __device__ inline Args *heavy_args(Args *a)
+{
+    return (Args *)((char *)a + kArgBytes / 2);
+}
+
+template <class Args>
 __global__ void k_prologue(Args a, Args *dst, int64_t *__restrict__ counts, int first, int nwords,
                            int first2, int nwords2, uint32_t *__restrict__ work,
                            const double *__restrict__ mparts, int nparts, double *__restrict__ mrange)
@@ -75,14 +81,23 @@ __global__ void k_prologue(Args a, Args *dst, int64_t *__restrict__ counts, int 
             mrange[1] = hi;
         }
     }
-    if (t == 0) *dst = a;
+    if (t == 0) {
+        *dst = a;
+        // the second launch: the heavy leaves
+        Args b = a;
+        b.leaf_list = a.heavy;
+        b.leaf_count = a.heavy_count;
+        b.heavy = nullptr;
+        *heavy_args(dst) = b;
+        *a.heavy_count = 0u;
+    }
     for (int k = 0; k < nwords; k++) counts[t * kCountWords + first + k] = 0;
     for (int k = 0; k < nwords2; k++) counts[t * kCountWords + first2 + k] = 0;
-    if (t < kXcds) work[t * kWorkStride] = 0u;
+    if (t < 2 * kXcds) work[t * kWorkStride] = 0u;
 }
 
-static_assert(sizeof(DensArgs) <= kArgBytes, "density argument block too large");
-static_assert(sizeof(ForceArgs) <= kArgBytes, "force argument block too large");
+static_assert(sizeof(DensArgs) <= kArgBytes / 2, "density argument block too large");
+static_assert(sizeof(ForceArgs) <= kArgBytes / 2, "force argument block too large");
 static_assert(kCountRows == 64, "the prologue zeroes a row per lane");
 
 } // namespace
@@ -110,6 +125,8 @@ sph_status density_prepare(sph_ctx *c, int64_t n)
     a.leaf_act = c->f_act ? c->leaf_act : nullptr;
     a.leaf_list = c->f_act ? c->act_list : nullptr;
     a.leaf_count = c->f_act ? c->act_cnt : nullptr;
+    a.heavy = second_launch(n, c->p.leaf_size, c->p.periodic) ? c->scratch_u32 : nullptr;
+    a.heavy_count = c->d_work + (2 * kXcds + 0) * kWorkStride;
     const void *req[] = {a.nodes, a.x, a.y, a.z, a.m, a.h, a.rho, a.omega, a.nngb, a.status,
                          a.counts, a.tree, a.lstart, a.work, c->d_dargs};
     for (const void *q : req)
@@ -149,6 +166,8 @@ sph_status forces_prepare(sph_ctx *c, int64_t n)
     a.leaf_act = c->f_act ? c->leaf_act : nullptr;
     a.leaf_list = c->f_act ? c->act_list : nullptr;
     a.leaf_count = c->f_act ? c->act_cnt : nullptr;
+    a.heavy = second_launch(n, c->p.leaf_size, c->p.periodic) ? c->scratch_u32 : nullptr;
+    a.heavy_count = c->d_work + (2 * kXcds + 1) * kWorkStride;
     if (c->f_block) {
         a.lev = c->s.lev;
         a.lmx = c->s.lmx;
@@ -187,9 +206,14 @@ sph_status density_launch(sph_ctx *const *cs, int count, int64_t nmax)
     B.claim = c->p.claim_leaves > 0 ? c->p.claim_leaves : 1;
     B.stage = c->p.stage_leaves;
     B.work = c->d_work;
+    Batch<DensArgs> B2 = B;   // of the heavy leaves
+    B2.work = c->d_work + kXcds * kWorkStride;
+    bool twice = false;
     int64_t leaves_bound = 0, items_bound = 0;
     for (int r = 0; r < count; r++) {
         B.req[r] = (const DensArgs *)cs[r]->d_dargs;
+        B2.req[r] = heavy_args((DensArgs *)cs[r]->d_dargs);
+        twice = twice || second_launch(cs[r]->n, c->p.leaf_size, cs[r]->p.periodic);
         const bool splits = splits_density(cs[r]->p.precision, cs[r]->p.periodic);
         const int k = slice_split(cs[r]->n, c->p.leaf_size, splits);
         B.split = r == 0 || k < B.split ? k : B.split;
@@ -208,14 +232,19 @@ sph_status density_launch(sph_ctx *const *cs, int count, int64_t nmax)
     const int64_t blocks =
         owner ? (owner->cache_size << B.split) / cache_bytes(c->p.leaf_size, c->p.kernel, 1) : 0;
     if (blocks < kXcds) return fail(c, SPH_ESTATE, "density: no candidate-list scratch");
-    B.cache = owner->cache;
+    B.cache = B2.cache = owner->cache;
+    B2.split = B.split;
     if ((int64_t)grid > blocks) grid = (unsigned)(blocks / kXcds * kXcds);
     hipEvent_t e0 = nullptr, e1 = nullptr;
     timer_begin(c, 0, &e0, &e1);
-    if (c->p.kernel == SPH_KERNEL_QUINTIC)
-        launch_density<SPH_KERNEL_QUINTIC>(c->stream, c->p.leaf_size, c->p.precision, grid, B);
-    else
-        launch_density<SPH_KERNEL_M4>(c->stream, c->p.leaf_size, c->p.precision, grid, B);
+    auto blocks_of = [&](const Batch<DensArgs> &b) { return &b == &B2 ? std::min(grid, kHeavyBlocks) : grid; };
+    for (const Batch<DensArgs> *b : {&B, &B2}) {
+        if (b == &B2 && !twice) break;
+        if (c->p.kernel == SPH_KERNEL_QUINTIC)
+            launch_density<SPH_KERNEL_QUINTIC>(c->stream, c->p.leaf_size, c->p.precision, blocks_of(*b), *b);
+        else
+            launch_density<SPH_KERNEL_M4>(c->stream, c->p.leaf_size, c->p.precision, blocks_of(*b), *b);
+    }
     timer_end(c, 0, e0, e1);
     return hip_check(c, hipGetLastError(), "density kernel");
 }
@@ -230,9 +259,14 @@ sph_status forces_launch(sph_ctx *const *cs, int count, int64_t nmax)
     B.claim = c->p.claim_leaves > 0 ? c->p.claim_leaves : 1;
     B.stage = c->p.stage_leaves;
     B.work = c->d_work;
+    Batch<ForceArgs> B2 = B;   // of the heavy leaves
+    B2.work = c->d_work + kXcds * kWorkStride;
+    bool twice = false;
     int64_t leaves_bound = 0, items_bound = 0;
     for (int r = 0; r < count; r++) {
         B.req[r] = (const ForceArgs *)cs[r]->d_fargs;
+        B2.req[r] = heavy_args((ForceArgs *)cs[r]->d_fargs);
+        twice = twice || second_launch(cs[r]->n, c->p.leaf_size, cs[r]->p.periodic);
         leaves_bound += cs[r]->n;
         items_bound += cs[r]->n << split_of(cs[r]->n, c->p.leaf_size);
     }
@@ -247,10 +281,14 @@ sph_status forces_launch(sph_ctx *const *cs, int count, int64_t nmax)
     }
     hipEvent_t e0 = nullptr, e1 = nullptr;
     timer_begin(c, 1, &e0, &e1);
-    if (c->p.kernel == SPH_KERNEL_QUINTIC)
-        launch_forces<SPH_KERNEL_QUINTIC>(c->stream, c->p.leaf_size, c->p.precision, ac, sw, grid, B);
-    else
-        launch_forces<SPH_KERNEL_M4>(c->stream, c->p.leaf_size, c->p.precision, ac, sw, grid, B);
+    auto blocks_of = [&](const Batch<ForceArgs> &b) { return &b == &B2 ? std::min(grid, kHeavyBlocks) : grid; };
+    for (const Batch<ForceArgs> *b : {&B, &B2}) {
+        if (b == &B2 && !twice) break;
+        if (c->p.kernel == SPH_KERNEL_QUINTIC)
+            launch_forces<SPH_KERNEL_QUINTIC>(c->stream, c->p.leaf_size, c->p.precision, ac, sw, blocks_of(*b), *b);
+        else
+            launch_forces<SPH_KERNEL_M4>(c->stream, c->p.leaf_size, c->p.precision, ac, sw, blocks_of(*b), *b);
+    }
     timer_end(c, 1, e0, e1);
     return hip_check(c, hipGetLastError(), "force kernel");
 }

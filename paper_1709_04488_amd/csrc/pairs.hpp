@@ -657,6 +657,24 @@ __device__ inline uint32_t rank_of(uint64_t m)
 // lasted as long as they did.
 constexpr int kManyLeaves = 160;
 
+// A home leaf with more candidate leaves than this after the second walk is left to
+// the launch after this one, where a wave has one of its particles: each of them has
+// thousands of neighbours, and one wave with all 16 lasted as long as everything
+// else.  Plummer spheres: 78,446 particles FP32-pair with the quintic kernel 25.7 ->
+// 9.0 ms, 30,000 FP64 1.78 -> 1.10 ms; the launch without such a leaf costs each
+// loop 3-5 us.  From 256 leaves on the force loop of the first took 2.6 instead of
+// 1.3 ms (too many leaves for that many waves each), from 768 the density loops 3
+// and 15 % more.
+constexpr int kHeavyLeaves = 384;
+template <class Args>
+__device__ inline bool left_over(const Args &A, int split, const WalkResult &wr, int64_t leaf)
+{
+    if (!A.heavy || split > 0 || (wr.lev == 0 && wr.n <= kHeavyLeaves)) return false;
+    if ((threadIdx.x & (kWave - 1)) == 0) A.heavy[atomicAdd(A.heavy_count, 1u)] = (uint32_t)leaf;
+    wave_lds_sync();   // the home table is rewritten for the next leaf
+    return true;
+}
+
 // Whether a node's box is within reach of some home particle that takes part (a
 // bit of `part`): its own squared reach in H or lim2, whichever is larger.  The
 // relative slack covers the rounding of the differently formed distances
@@ -1528,6 +1546,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                     wave_lds_sync();
                 }
                 __builtin_amdgcn_s_setprio(0);
+                if (iter == 0 && close && left_over(A, split, wr, leaf)) return;
                 walked = true;
             }
             const double hinv = 1.0 / h;
@@ -2005,6 +2024,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_forces(B
             close = true;
         }
         __builtin_amdgcn_s_setprio(0);
+        if (close && left_over(F, split, wr, leaf)) return;
 
         double axi = 0.0, ayi = 0.0, azi = 0.0, dui = 0.0, vs_max = -INFINITY;
         double dvs = 0.0, cxs = 0.0, cys = 0.0, czs = 0.0;   // div v, curl v sums (SW)

@@ -46,6 +46,9 @@ struct DensArgs {
     // then leaf_list[0 .. *leaf_count) (nullptr: every leaf)
     const int32_t *active, *leaf_act;
     const uint32_t *leaf_list, *leaf_count;
+    // where a launch leaves its heavy home leaves to the next one (nullptr: it
+    // keeps them), and their count
+    uint32_t *heavy, *heavy_count;
 };
 
 struct ForceArgs {
@@ -81,6 +84,9 @@ struct ForceArgs {
     // wake-up marks of inactive neighbours (atomic max), level spread lim
     const int32_t *active, *leaf_act;
     const uint32_t *leaf_list, *leaf_count;
+    // where a launch leaves its heavy home leaves to the next one (nullptr: it
+    // keeps them), and their count
+    uint32_t *heavy, *heavy_count;
     const int32_t *lev;
     int32_t *lmx, *mark;
     int32_t lim;

@@ -86,6 +86,9 @@ constexpr int64_t act_tiles(int64_t cap) { return (cap + kActTile - 1) / kActTil
 // (195,112 particles FP64, 12,200 claims a loop: forces 290 -> 178 us, density
 // 264 -> 215 us; 2.1M: forces 1.87 -> 1.76 ms).
 constexpr int kWorkStride = 64;
+// d_work: the claim counters of a loop's two launches, then the heavy leaves' counts
+// of the density and the force loop.
+constexpr int kWorkWords = (2 * kXcds + 2) * kWorkStride;
 inline unsigned pair_grid(int64_t n)
 {
     int64_t blocks = (n + 7) / 8;
@@ -121,6 +124,16 @@ __host__ __device__ inline int split_of(int64_t n, int G)
 __host__ __device__ inline bool splits_density(int precision, int periodic)
 {
     return precision == SPH_FP64 || !periodic;
+}
+
+// Whether a loop leaves its heavy home leaves (kHeavyLeaves) to a second launch
+// with a wave for each of their particles: isolated sets of whole leaves, whose
+// outermost particles' supports can hold thousands of others.  In a periodic box
+// they cannot outgrow the mean density, and the launch would cost each loop 3-5 us.
+constexpr unsigned kHeavyBlocks = 1024;   // one per SIMD: most sets have no heavy leaf
+inline bool second_launch(int64_t n, int G, int periodic)
+{
+    return !periodic && split_of(n, G) == 0;
 }
 
 // log2 of the blocks that share the density lists of a whole leaf: half as many

@@ -8,7 +8,8 @@ above them whole leaves); scatter blocks that form digit offsets themselves (24
 tiles of 1,024) and one tile more; small and large sort tiles (2^20).  Isolated
 FP32-pair sets share leaves in both loops, periodic ones in the force loop alone.
 Equal masses have the longer lists.  Far particles around a cluster overflow the
-walk, repeat it with a test per home particle and fill their lists.
+walk, repeat it with a test per home particle and fill their lists; in the larger
+set (whole leaves) they go to the second launch.
 
 Tolerances: FP64 1e-10 relative (a, du/dt of the per-particle scale) and exact
 counts; FP32-pair 1e-5, Omega 5e-5, a and du/dt 1e-4 of the scale -- the ones of
@@ -94,12 +95,13 @@ def test_larger_sets_match_oracle_samples(sph, orc, n, leaf, precision):
     _compare(out, ref, precision)
 
 
-@pytest.mark.parametrize("leaf,precision", [(8, 0), (16, 0), (32, 0), (16, 1)])
-def test_far_particles_of_a_shared_set_match_oracle(sph, orc, leaf, precision):
-    w = cluster_with_outliers(n_cluster=7000, seed=67)
+@pytest.mark.parametrize("n,leaf,precision", [(7000, 8, 0), (7000, 16, 0), (7000, 32, 0), (7000, 16, 1),
+                                              (25000, 8, 0), (25000, 16, 0), (25000, 32, 1)])
+def test_far_particles_match_oracle(sph, orc, n, leaf, precision):
+    w = cluster_with_outliers(n_cluster=n, seed=67)
     print(f"case: {w.name} leaf={leaf} precision={precision}", flush=True)
     a = w.arrays
     ref = orc.evaluate(orc.Params(**w.setup), a["x"], a["y"], a["z"], a["vx"], a["vy"], a["vz"], a["m"], a["u"],
                        a["h"])
-    assert np.all(ref["nngb"][-5:] >= 6900)
+    assert np.all(ref["nngb"][-5:] >= 0.9 * n)   # (the case is what it is meant to be)
     _compare(_evaluate(sph, w, precision, leaf, 0), ref, precision)
