@@ -1,0 +1,74 @@
+"""Sets at the edges of what the entry points take: any unit of length, values
+that are not finite, leaves that are wide against their particles' reaches.
+
+A set in another unit of length is the same set: with a power of two between the
+units every FP64 operation rounds alike, so the results have to scale to the bit
+(h with the unit, rho with its cube, Omega, counts and the signal speed not at all,
+the accelerations with its inverse).
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from paper_1709_04488_amd import workloads as W  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def sph():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1709_04488_amd import sph as s
+    s.load()
+    return s
+
+
+def _set(n, periodic, equal_m=True, seed=3):
+    rng = np.random.default_rng(seed)
+    if periodic:
+        a = {k: rng.uniform(0, 1, n) for k in "xyz"}
+        a["h"] = 1.2 * n ** (-1.0 / 3.0) * rng.uniform(0.8, 1.2, n)
+    else:
+        w = W.plummer(n, seed)
+        a = {k: w.arrays[k].copy() for k in ("x", "y", "z", "h")}
+    a.update({k: rng.normal(0, 0.3, n) for k in ("vx", "vy", "vz")})
+    a["m"] = np.full(n, 1.0 / n) if equal_m else rng.uniform(0.5, 1.5, n) / n
+    a["u"] = rng.uniform(0.3, 2.0, n)
+    return a, W.default_setup(periodic=periodic)
+
+
+def _in_unit(a, setup, unit):
+    """The set with lengths in units of 1 / unit."""
+    a = {k: v * unit if k in ("x", "y", "z", "h") else v for k, v in a.items()}
+    return a, dict(setup, lo=tuple(unit * v for v in setup["lo"]), hi=tuple(unit * v for v in setup["hi"]))
+
+
+def _run(sph, a, setup, forces=True, **kw):
+    """(outputs, status) of one evaluation, or of the density alone."""
+    with sph.Context(sph.Params.from_setup(setup, **kw)) as ctx:
+        p = sph.Particles.from_host(a)
+        ctx.evaluate(p) if forces else ctx.density(p)
+        status = ctx.sync_status()
+        return p.host(), status
+
+
+# powers of the unit in each output
+UNIT = {"h": 1, "rho": -3, "omega": 0, "vsig": 0, "dt": 1, "ax": -1, "ay": -1, "az": -1, "dudt": -1}
+
+
+@pytest.mark.parametrize("kernel", [0, 1])
+@pytest.mark.parametrize("periodic,leaf", [(True, 16), (False, 8), (False, 32)])
+@pytest.mark.parametrize("log2_unit", [-110, -66, 64, 83])
+def test_fp64_in_any_unit(sph, log2_unit, periodic, leaf, kernel):
+    a, setup = _set(3000, periodic)
+    print(f"case: unit 2^{log2_unit} periodic={periodic} leaf={leaf} kernel={kernel}", flush=True)
+    ref, ok = _run(sph, a, setup, leaf_size=leaf, kernel=kernel)
+    unit = 2.0 ** log2_unit
+    out, status = _run(sph, *_in_unit(a, setup, unit), leaf_size=leaf, kernel=kernel)
+    assert status == ok
+    for k in ("nngb", "nforce"):
+        assert np.array_equal(out[k], ref[k]), k
+    for k, power in UNIT.items():
+        assert np.array_equal(out[k], ref[k] * unit ** power), k
