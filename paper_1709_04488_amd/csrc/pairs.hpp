@@ -1570,11 +1570,12 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                 if constexpr (F64) {
                     add_entry<K, EQ>(sm, r2, m, hinv, h2x4);
                 } else {
-                    // branch-free: an entry outside R h adds 0 * f
+                    // branch-free: an entry outside R h adds 0 * f(0), whatever it
+                    // holds (padding, a position that is not finite)
                     const bool in = r2 < (float)h2x4;
                     const double mj = in ? (EQ ? mu : m) : 0.0;
                     float f, df;
-                    const float qq = sqrtf(r2) * (float)hinv;
+                    const float qq = in ? sqrtf(r2) * (float)hinv : 0.f;
                     kern<K>(qq, f, df);
                     sm.d0 += mj * (double)f;
                     sm.d1 += mj * (double)(qq * df);
@@ -1623,7 +1624,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
             auto pad_list = [&](int n) {
                 const int end = (n + CHUNK - 1) & -CHUNK;
                 for (int e = n + q; e < end; e += LPP) {
-                    cr2[p * KP + e] = F64 ? (ListR2)1e300 : (ListR2)1e30f;
+                    cr2[p * KP + e] = F64 ? (ListR2)1e300 : (ListR2)INFINITY;
                     if (!equal_m) cm[p * KP + e] = 0.0;
                 }
                 wave_mem_sync();

@@ -72,3 +72,55 @@ def test_fp64_in_any_unit(sph, log2_unit, periodic, leaf, kernel):
         assert np.array_equal(out[k], ref[k]), k
     for k, power in UNIT.items():
         assert np.array_equal(out[k], ref[k] * unit ** power), k
+
+
+@pytest.mark.parametrize("equal_m", [True, False])
+@pytest.mark.parametrize("periodic,kernel", [(True, 0), (False, 1)])
+@pytest.mark.parametrize("log2_unit", [-50, 55, 60])
+def test_fp32_density_in_any_unit(sph, log2_unit, periodic, kernel, equal_m):
+    """Up to where squares of lengths leave the single-precision range (the force
+    loop's h^-4 leaves it earlier)."""
+    a, setup = _set(3000, periodic, equal_m)
+    print(f"case: fp32 unit 2^{log2_unit} periodic={periodic} kernel={kernel} equal_m={equal_m}", flush=True)
+    ref, ok = _run(sph, a, setup, forces=False, kernel=kernel, precision=1)
+    unit = 2.0 ** log2_unit
+    out, status = _run(sph, *_in_unit(a, setup, unit), forces=False, kernel=kernel, precision=1)
+    assert status == ok
+    assert np.array_equal(out["nngb"], ref["nngb"])
+    for k in ("h", "rho", "omega"):
+        assert np.array_equal(out[k], ref[k] * unit ** UNIT[k]), k
+
+
+def _without(a, i):
+    return {k: np.delete(v, i) for k, v in a.items()}
+
+
+def _same_but(out, ref, i, precision):
+    """The other particles' results as in the set without particle i, to the
+    tolerances of the small-set tests (another leaf structure)."""
+    tol = 1e-10 if precision == 0 else 1e-4
+    for k in ("nngb", "nforce"):
+        d = np.delete(out[k], i) != ref[k]
+        # (single precision: a pair at the kernel's edge may fall to either side)
+        assert np.count_nonzero(d) <= (0 if precision == 0 else 5), k
+    for k in ("h", "rho", "omega", "vsig", "dt", "ax", "ay", "az", "dudt"):
+        o = np.delete(out[k], i)
+        scale = np.abs(ref[k]) if k in ("h", "rho", "omega", "vsig", "dt") else np.abs(ref[k]).max()
+        assert np.max(np.abs(o - ref[k]) / scale) < tol, k
+
+
+@pytest.mark.parametrize("precision", [1])
+@pytest.mark.parametrize("periodic,kernel,n", [(True, 0, 700), (True, 1, 2000), (False, 0, 2000)])
+def test_nan_position_stays_alone(sph, precision, periodic, kernel, n):
+    """A particle whose position is not a number is flagged and is nobody's
+    neighbour (the small periodic sets list every candidate: their leaves see the
+    box's images ambiguously)."""
+    a, setup = _set(n, periodic)
+    i = 555
+    a["x"][i] = np.nan
+    print(f"case: nan position precision={precision} periodic={periodic} kernel={kernel} n={n}", flush=True)
+    out, status = _run(sph, a, setup, kernel=kernel, precision=precision)
+    assert status == sph.SPH_ENONFINITE
+    ref, status = _run(sph, _without(a, i), setup, kernel=kernel, precision=precision)
+    assert status == sph.SPH_OK
+    _same_but(out, ref, i, precision)
