@@ -1070,6 +1070,12 @@ __device__ inline HomeUnits home_operand(const HomeTab<G, PREC> &H, const Node &
         O.col[lane] = c;
     }
     U.wide = __ballot(far) != 0ull;
+    // every candidate is a hit of the particles that take part, whatever their
+    // halves came to (beyond their range, or not a number)
+    if (U.wide && lane < 16 * Words<G>::tiles) {
+        const float c = lane < G && H.d[lane].thr >= 0.0 ? -1.f : 1e30f;
+        O.col[lane] = HomeCol{Half4{0, 0, 0, 1}, c, c};   // (empty slots still miss)
+    }
     wave_lds_sync();
     return U;
 }

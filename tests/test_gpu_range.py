@@ -109,7 +109,7 @@ def _same_but(out, ref, i, precision):
         assert np.max(np.abs(o - ref[k]) / scale) < tol, k
 
 
-@pytest.mark.parametrize("precision", [1])
+@pytest.mark.parametrize("precision", [0, 1])
 @pytest.mark.parametrize("periodic,kernel,n", [(True, 0, 700), (True, 1, 2000), (False, 0, 2000)])
 def test_nan_position_stays_alone(sph, precision, periodic, kernel, n):
     """A particle whose position is not a number is flagged and is nobody's
@@ -124,3 +124,48 @@ def test_nan_position_stays_alone(sph, precision, periodic, kernel, n):
     ref, status = _run(sph, _without(a, i), setup, kernel=kernel, precision=precision)
     assert status == sph.SPH_OK
     _same_but(out, ref, i, precision)
+
+
+@pytest.mark.parametrize("periodic,kernel", [(True, 0), (True, 1), (False, 0), (False, 1)])
+def test_infinite_position_stays_alone(sph, periodic, kernel):
+    """The particles that share its leaf keep their neighbours (FP64: in the
+    FP32-pair mode their offsets from the leaf's centre are not finite)."""
+    a, setup = _set(2000, periodic)
+    i = 777
+    a["x"][i] = np.inf
+    print(f"case: infinite position periodic={periodic} kernel={kernel}", flush=True)
+    out, status = _run(sph, a, setup, kernel=kernel)
+    assert status == sph.SPH_ENONFINITE
+    if not periodic:   # (the box of the keys is infinite: every particle has the same key)
+        assert np.isfinite(np.delete(out["ax"], i)).all()
+    ref, status = _run(sph, _without(a, i), setup, kernel=kernel)
+    assert status == sph.SPH_OK
+    _same_but(out, ref, i, 0)
+
+
+@pytest.mark.parametrize("leaf,kernel", [(8, 0), (16, 0), (16, 1), (32, 0)])
+def test_leaves_wide_against_their_reaches(sph, orc, leaf, kernel):
+    """Two tight groups 1e5 smoothing lengths apart whose particles take turns in the
+    input, and one far particle: the groups share the finest key cell, so leaves
+    hold particles of both, and home coordinates exceed the halves' range."""
+    n = 600
+    rng = np.random.default_rng(13)
+    pos = (np.arange(n) % 2)[:, None] * np.array([[1e-4, 0, 0]]) + rng.normal(0, 1e-9, (n, 3))
+    pos[-1] = 1.0
+    a = {k: pos[:, i].copy() for i, k in enumerate("xyz")}
+    a.update({k: rng.normal(0, 0.3, n) for k in ("vx", "vy", "vz")})
+    a["m"] = np.full(n, 1.0 / n)
+    a["u"] = rng.uniform(0.3, 2.0, n)
+    a["h"] = np.where(np.arange(n) == n - 1, 0.5, 4e-10)
+    setup = W.default_setup(periodic=False)
+    print(f"case: wide leaves leaf={leaf} kernel={kernel}", flush=True)
+    ref = orc.evaluate(orc.Params(**{**setup, "kernel": kernel}), a["x"], a["y"], a["z"], a["vx"], a["vy"], a["vz"],
+                       a["m"], a["u"], a["h"])
+    out, status = _run(sph, a, setup, leaf_size=leaf, kernel=kernel)
+    assert status == sph.SPH_OK
+    for k in ("nngb", "nforce"):
+        assert np.array_equal(out[k], ref[k]), k
+    for k in ("h", "rho", "omega", "vsig", "dt"):
+        assert np.max(np.abs(out[k] / ref[k] - 1.0)) < 1e-10, k
+    for k, sk in (("ax", "scale_a"), ("ay", "scale_a"), ("az", "scale_a"), ("dudt", "scale_u")):
+        assert np.max(np.abs(out[k] - ref[k]) / ref[sk]) < 1e-10, k
