@@ -1365,6 +1365,7 @@ __device__ inline void add_entry(Sums<K> &s, double r2, double m, double hinv, d
     const double q = (r2 * rsqrt_nr1(r2 + 1e-300)) * hinv;
     const bool in = r2 < h2;
     s.n += in ? 1 : 0;
+    if constexpr (!EQ) m = in ? m : 0.0;   // (infinity * 0 outside R h)
     if constexpr (K == SPH_KERNEL_QUINTIC) {
         const double t3 = 3.0 - q;
         const double a = fmax(t3, 0.0), b = fmax(2.0 - q, 0.0), c = fmax(1.0 - q, 0.0);

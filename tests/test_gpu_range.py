@@ -169,3 +169,30 @@ def test_leaves_wide_against_their_reaches(sph, orc, leaf, kernel):
         assert np.max(np.abs(out[k] / ref[k] - 1.0)) < 1e-10, k
     for k, sk in (("ax", "scale_a"), ("ay", "scale_a"), ("az", "scale_a"), ("dudt", "scale_u")):
         assert np.max(np.abs(out[k] - ref[k]) / ref[sk]) < 1e-10, k
+
+
+@pytest.mark.parametrize("precision,kernel", [(0, 0), (0, 1), (1, 0)])
+@pytest.mark.parametrize("mass", [np.inf, np.nan])
+def test_mass_that_is_not_finite_stays_within_reach(sph, mass, precision, kernel):
+    """It spoils the particles that have it within R h, and no other's density."""
+    a, setup = _set(2000, True, equal_m=False)
+    i = 777
+    ref, status = _run(sph, a, setup, forces=False, kernel=kernel, precision=precision)
+    assert status == sph.SPH_OK
+    reach = (2.0, 3.0)[kernel] * ref["h"]
+    d = np.stack([a[k] - a[k][i] for k in "xyz"])
+    r = np.sqrt(((d - np.round(d)) ** 2).sum(0))
+    a["m"][i] = mass
+    # guesses beyond the root, so that lists hold the particle for many whose
+    # root does not reach it
+    a["h"] = 1.1 * ref["h"]
+    print(f"case: mass {mass} precision={precision} kernel={kernel}", flush=True)
+    out, status = _run(sph, a, setup, forces=False, kernel=kernel, precision=precision)
+    assert status == sph.SPH_ENONFINITE
+    # (a guess that reaches it gives no Newton step to go by)
+    far = r > 1.1 * reach * (1.0 + 1e-6)
+    assert np.count_nonzero(far & (r < 1.15 * 1.1 * reach)) > 5   # (the case is what it is meant to be)
+    for k in ("h", "rho", "omega"):
+        assert np.max(np.abs(out[k][far] / ref[k][far] - 1.0)) < (1e-10 if precision == 0 else 1e-5), k
+    if precision == 0:
+        assert np.array_equal(out["nngb"][far], ref["nngb"][far])
