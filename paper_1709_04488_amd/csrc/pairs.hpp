@@ -1340,10 +1340,13 @@ __device__ inline int find_req(const uint32_t *pre, int nreq, int64_t g)
 //   sum m f(q') = (1 + x)^-N (D0 + x D1 + x^2 D2 + x^3 D3 ...),
 // N = 3 (M4: exact with D0..D3) or 5 (quintic: D4 and D5 left out, an error of
 // order x^4), and the h-rho relation sum m f = eta^3 m_i / sigma is a
-// polynomial in x.
+// polynomial in x.  Of D1 the sum of q f' is kept (D1 = N D0 - it): Omega is that
+// sum over D0, and where the particle itself is nearly all of D0 it would be lost
+// in the difference.
 template <int K>
 struct Sums {
-    double d0 = 0.0, d1 = 0.0, d2 = 0.0;   // (FP32-pair: sum m f, sum m q f')
+    double d0 = 0.0, s2 = 0.0;             // sum m f, sum m q f' (M4, FP64: a third of it)
+    double d2 = 0.0;
     double wn = 0.0;                       // D3 of unequal masses, quintic's D3
     double edge = 1e300;                   // smallest |q - knot| met
     int n = 0, n1 = 0;                     // entries inside R h, inside h
@@ -1352,7 +1355,7 @@ struct Sums {
 
 // Sums of a particle whose list filled up and was started afresh.
 struct PartSums {
-    double d0, d1, d2, wn;
+    double d0, s2, d2, wn;
     int n, n1;
 };
 
@@ -1374,17 +1377,17 @@ __device__ inline void add_entry(Sums<K> &s, double r2, double m, double hinv, d
         const double a3 = a2 * a, b3 = b2 * b, c3 = c2 * c;
         const double a4 = a2 * a2, b4 = b2 * b2, c4 = c2 * c2;
         const double e0 = a4 * a - 6.0 * (b4 * b) + 15.0 * (c4 * c);
-        const double e1 = 15.0 * a4 - 60.0 * b4 + 75.0 * c4;
+        const double t = 30.0 * b4 - 5.0 * a4 - 75.0 * c4;
         const double e2 = 90.0 * a3 - 240.0 * b3 + 150.0 * c3;
         const double e3 = 270.0 * a2 - 480.0 * b2 + 150.0 * c2;
         if constexpr (EQ) {
             s.d0 += e0;
-            s.d1 += e1;
+            s.s2 = fma(q, t, s.s2);
             s.d2 += e2;
             s.wn += e3;
         } else {
             s.d0 += m * e0;
-            s.d1 += m * e1;
+            s.s2 = fma(m * q, t, s.s2);
             s.d2 += m * e2;
             s.wn += m * e3;
         }
@@ -1394,17 +1397,17 @@ __device__ inline void add_entry(Sums<K> &s, double r2, double m, double hinv, d
         s.edge = fmin(fmin(s.edge, fabs(t2)), fabs(t1));
         const double a2 = a * a, b2 = b * b;
         const double e0 = (0.25 * a2) * a - b2 * b;
-        const double e1 = 0.5 * a2 - b2;     // x 3
+        const double t = b2 - 0.25 * a2;     // x 3
         const double e2 = a - b;             // x 3
         const bool in1 = t1 > 0.0;
         if constexpr (EQ) {
             s.d0 += e0;
-            s.d1 += e1;
+            s.s2 = fma(q, t, s.s2);
             s.d2 += e2;
             s.n1 += in1 ? 1 : 0;
         } else {
             s.d0 += m * e0;
-            s.d1 += m * e1;
+            s.s2 = fma(m * q, t, s.s2);
             s.d2 += m * e2;
             s.wn += m * ((in ? 2.0 : 0.0) - (in1 ? 1.0 : 0.0));
         }
@@ -1585,7 +1588,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                     const float qq = in ? sqrtf(r2) * (float)hinv : 0.f;
                     kern<K>(qq, f, df);
                     sm.d0 += mj * (double)f;
-                    sm.d1 += mj * (double)(qq * df);
+                    sm.s2 += mj * (double)(qq * df);
                     sm.n += in ? 1 : 0;
                 }
             };
@@ -1650,13 +1653,13 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                 const bool first_time = !((emptied >> pp) & 1);
                 count_up(kCntDensListOverflows, first_time ? 1 : 0);
                 emptied |= 1ull << pp;
-                const double d0 = wave_sum(t.d0), d1 = wave_sum(t.d1), d2 = wave_sum(t.d2), wn = wave_sum(t.wn);
+                const double d0 = wave_sum(t.d0), s2 = wave_sum(t.s2), d2 = wave_sum(t.d2), wn = wave_sum(t.wn);
                 const int n0 = (int)wave_sum_int(t.n), n1 = (int)wave_sum_int(t.n1);
                 const PartSums c = first_time ? PartSums{} : part[pp];
                 wave_lds_sync();
                 const double edge = F64 ? -wave_max(-t.edge) : 0.0;
                 if (lane == 0) {
-                    part[pp] = PartSums{c.d0 + d0, c.d1 + d1, c.d2 + d2, c.wn + wn, c.n + n0, c.n1 + n1};
+                    part[pp] = PartSums{c.d0 + d0, c.s2 + s2, c.d2 + d2, c.wn + wn, c.n + n0, c.n1 + n1};
                     if constexpr (F64) part_edge[pp] = first_time ? edge : fmin(part_edge[pp], edge);
                 }
                 wave_lds_sync();
@@ -1784,7 +1787,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
             if (((emptied >> p) & 1) && q == 0) {
                 const PartSums &t = part[p];
                 sm.d0 += t.d0;
-                sm.d1 += t.d1;
+                sm.s2 += t.s2;
                 sm.d2 += t.d2;
                 sm.wn += t.wn;
                 if constexpr (F64) sm.edge = fmin(sm.edge, part_edge[p]);
@@ -1802,8 +1805,10 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
             if constexpr (F64) {
                 const double sc = equal_m ? mu : 1.0;
                 const double f3 = K == SPH_KERNEL_QUINTIC ? 1.0 : 3.0;
+                constexpr double N = Sums<K>::N;
                 const double D0 = sc * lanes_sum<L0>(sm.d0, LPP);
-                const double D1 = sc * (f3 * lanes_sum<L0>(sm.d1, LPP));
+                s2 = sc * (f3 * lanes_sum<L0>(sm.s2, LPP));
+                const double D1 = N * D0 - s2;
                 const double D2 = sc * (f3 * lanes_sum<L0>(sm.d2, LPP));
                 double D3 = lanes_sum<L0>(sm.wn, LPP);
                 if constexpr (K != SPH_KERNEL_QUINTIC) {
@@ -1812,9 +1817,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                 }
                 D3 *= sc;
                 edge = -lanes_max<L0>(-sm.edge, LPP);
-                constexpr double N = Sums<K>::N;
                 s0 = D0;
-                s2 = N * D0 - D1;
                 if (tight) {
                     // (1 + x)^N eta^3 m / sigma against D0 + x D1 + ..., through x^3
                     const double kt = A.eta3 * mi / SIG;
@@ -1836,7 +1839,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                 }
             } else {
                 s0 = lanes_sum<L0>(sm.d0, LPP);
-                s2 = lanes_sum<L0>(sm.d1, LPP);
+                s2 = lanes_sum<L0>(sm.s2, LPP);
             }
             if (!conv && q == 0) evals_leaf += cnt;
             if (!conv) {

@@ -196,3 +196,36 @@ def test_mass_that_is_not_finite_stays_within_reach(sph, mass, precision, kernel
         assert np.max(np.abs(out[k][far] / ref[k][far] - 1.0)) < (1e-10 if precision == 0 else 1e-5), k
     if precision == 0:
         assert np.array_equal(out["nngb"][far], ref["nngb"][far])
+
+
+@pytest.mark.parametrize("precision,kernel,passes", [(0, 0, 50), (0, 0, 12), (0, 1, 50), (0, 1, 12), (1, 0, 8)])
+@pytest.mark.parametrize("n", [2, 3, 4])
+def test_no_root_keeps_omega(sph, n, kernel, precision, passes):
+    """So few particles have no h that solves the h-rho relation: h grows until the
+    passes end, Omega falls with (r / h)^2 towards zero, and the solve is reported as
+    not converged, with finite results."""
+    rng = np.random.default_rng(n)
+    a = {k: rng.uniform(0, 1, n) for k in "xyz"}
+    a.update({k: rng.normal(0, 0.3, n) for k in ("vx", "vy", "vz")})
+    a["m"] = np.full(n, 1.0 / n)
+    a["u"] = np.ones(n)
+    a["h"] = np.full(n, 1.0)
+    print(f"case: no root n={n} kernel={kernel} precision={precision} passes={passes}", flush=True)
+    out, status = _run(sph, a, W.default_setup(periodic=False), kernel=kernel, precision=precision,
+                       h_max_iter=passes)
+    assert status == sph.SPH_ENOTCONVERGED
+    for k in ("h", "rho", "omega", "ax", "ay", "az", "dudt", "vsig", "dt"):
+        assert np.isfinite(out[k]).all(), k
+    assert np.array_equal(out["nngb"], np.full(n, n - 1))
+    pos = np.stack([a[k] for k in "xyz"])
+    q = np.sqrt(((pos[:, :, None] - pos[:, None, :]) ** 2).sum(0)) / out["h"][:, None]
+    if kernel:   # q f' and f, exact to (q^4) where q is small: expanded about q = 0
+        f = 66.0 - 60.0 * q ** 2 + 30.0 * q ** 4
+        qdf = -120.0 * q ** 2 + 120.0 * q ** 4
+    else:
+        f = 1.0 - 1.5 * q ** 2 + 0.75 * q ** 3
+        qdf = -3.0 * q ** 2 + 2.25 * q ** 3
+    omega = -qdf.sum(1) / (3.0 * f.sum(1))
+    if passes < 50:   # (f' in its B-spline form rounds to some 4e-16 / q of itself: q is 1e-3 here, 1e-15 after 50)
+        assert q.max() < 0.02
+        assert np.max(np.abs(out["omega"] / omega - 1.0)) < (1e-3 if kernel or precision else 1e-9)
