@@ -1834,7 +1834,9 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                         if (__ballot(!conv && fabs(st) > 1e-16 + 1e-15 * fabs(x) && fabs(x) < 1.0) == 0ull)
                             break;
                     }
-                    poly = fabs(x) < 0.5 && fabs(st) <= 1e-15 + 1e-12 * fabs(x);
+                    // (a massless particle's relation has no root in h: plain Newton
+                    // halves h until the particle is alone)
+                    poly = kt > 0.0 && fabs(x) < 0.5 && fabs(st) <= 1e-15 + 1e-12 * fabs(x);
                     b1 = (3.0 * D3 * x + 2.0 * D2) * x + D1;
                 }
             } else {

@@ -229,3 +229,21 @@ def test_no_root_keeps_omega(sph, n, kernel, precision, passes):
     if passes < 50:   # (f' in its B-spline form rounds to some 4e-16 / q of itself: q is 1e-3 here, 1e-15 after 50)
         assert q.max() < 0.02
         assert np.max(np.abs(out["omega"] / omega - 1.0)) < (1e-3 if kernel or precision else 1e-9)
+
+
+@pytest.mark.parametrize("precision,kernel", [(0, 0), (0, 1), (1, 0)])
+def test_massless_particle(sph, precision, kernel):
+    """h^3 rho = 0 holds for every h that reaches no other particle: h is halved from
+    its guess until it does."""
+    a, setup = _set(2000, True, equal_m=False)
+    a["m"][[5, 900]] = 0.0
+    print(f"case: massless precision={precision} kernel={kernel}", flush=True)
+    out, status = _run(sph, a, setup, kernel=kernel, precision=precision)
+    support = (2.0, 3.0)[kernel]
+    for i in (5, 900):
+        d = np.stack([a[k] - a[k][i] for k in "xyz"])
+        r = np.sort(np.sqrt(((d - np.round(d)) ** 2).sum(0)))[1]
+        h = a["h"][i]
+        while support * h > r:
+            h *= 0.5
+        assert out["h"][i] == h and out["nngb"][i] == 0
