@@ -1420,6 +1420,17 @@ __device__ inline void add_entry(Sums<K> &s, double r2, double m, double hinv, d
 // the plain Newton path.
 constexpr double kTightTol = 1e-9;
 
+// The polynomial stands for the kernel sum near h: further away neighbours cross
+// the kernel's knots, and the quintic's lacks its last two terms, while Newton on
+// F(h) is exact where the density is uniform.  Up to a change of h of a half, cold
+// quintic solves took up to 15 passes instead of Newton's 9 (cluster in a void, mean
+// 3.42; with a tenth at most 8, mean 3.22, density of 80,000 particles 10.9 -> 6.4
+// ms, with a fifth 10.9 again).  M4: guesses three times too large 5.70 passes, with
+// a fifth 3.98 and a tenth 4.01 (80,000: 2.57 and 1.90 ms); 2,097,152 particles with
+// the benchmark's guesses 2.31 ms up to a half or a fifth, 2.37 with a tenth.
+template <int K>
+constexpr double kPolyStep = K == SPH_KERNEL_QUINTIC ? 0.1 : 0.2;
+
 template <int G, int PREC, int K>
 __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(Batch<DensArgs> B)
 {
@@ -1836,7 +1847,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                     }
                     // (a massless particle's relation has no root in h: plain Newton
                     // halves h until the particle is alone)
-                    poly = kt > 0.0 && fabs(x) < 0.5 && fabs(st) <= 1e-15 + 1e-12 * fabs(x);
+                    poly = kt > 0.0 && fabs(x) < kPolyStep<K> && fabs(st) <= 1e-15 + 1e-12 * fabs(x);
                     b1 = (3.0 * D3 * x + 2.0 * D2) * x + D1;
                 }
             } else {

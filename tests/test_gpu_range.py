@@ -247,3 +247,21 @@ def test_massless_particle(sph, precision, kernel):
         while support * h > r:
             h *= 0.5
         assert out["h"][i] == h and out["nngb"][i] == 0
+
+
+@pytest.mark.parametrize("kernel", [0, 1])
+def test_cold_solve_takes_few_passes(sph, kernel):
+    """A cluster in a void, guesses off by up to 2: plain Newton needs up to 9 passes
+    with the quintic kernel and 10 with M4, and a caller may allow no more."""
+    n = 5000
+    k = n * 3 // 4
+    rng = np.random.default_rng(5)
+    pos = np.concatenate([np.mod(rng.normal(0.5, 0.03, (k, 3)), 1), rng.uniform(0, 1, (n - k, 3))])
+    a = {c: pos[:, i].copy() for i, c in enumerate("xyz")}
+    a.update({c: rng.normal(0, 0.3, n) for c in ("vx", "vy", "vz")})
+    a["m"] = np.full(n, 1.0 / n)
+    a["u"] = rng.uniform(0.3, 2, n)
+    a["h"] = np.where(np.arange(n) < k, 0.12 * k ** (-1 / 3), 1.2 * (n - k) ** (-1 / 3)) * rng.uniform(0.8, 1.2, n)
+    print(f"case: passes of a cold solve kernel={kernel}", flush=True)
+    out, status = _run(sph, a, W.default_setup(), kernel=kernel, h_max_iter=9 if kernel else 10)
+    assert status == sph.SPH_OK
