@@ -939,7 +939,7 @@ __device__ inline int test_rows(const LeafTab<SPH_FP64> &tab, const HomeTab<G, S
             const bool ok = slot < (int)(jm.y & 255u);
             const uint32_t j = jm.x + (ok ? slot : 0);   // (a missing leaf's entry is particle 0)
             const auto *q = as_global((const double *)(pos + j));
-            x[r] = ok ? q[0] : 1e150;         // an empty slot is far away
+            x[r] = ok ? q[0] : INFINITY;      // an empty slot is far away
             y[r] = q[1];
             z[r] = q[2];
             w[r] = mass(j);
@@ -1420,6 +1420,9 @@ __device__ inline void add_entry(Sums<K> &s, double r2, double m, double hinv, d
 // the plain Newton path.
 constexpr double kTightTol = 1e-9;
 
+// r^2 of the places that fill an FP64 list up to a whole step.
+constexpr double kPadding = 1e300;
+
 // The polynomial stands for the kernel sum near h: further away neighbours cross
 // the kernel's knots, and the quintic's lacks its last two terms, while Newton on
 // F(h) is exact where the density is uniform.  Up to a change of h of a half, cold
@@ -1583,7 +1586,8 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                 walked = true;
             }
             const double hinv = 1.0 / h;
-            const double h2x4 = (RK * h) * (RK * h);
+            // (an infinite guess reaches every particle, but not the lists' padding)
+            const double h2x4 = fmin((RK * h) * (RK * h), kPadding);
             uint64_t emptied = 0;   // bit p: home particle p's list was, in this sweep
             // the pair terms of one entry (eq: all masses are equal, m not used)
             auto add = [&](Sums<K> &sm, auto eq, ListR2 r2, double m, double hinv, double h2x4) {
@@ -1645,7 +1649,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
             auto pad_list = [&](int n) {
                 const int end = (n + CHUNK - 1) & -CHUNK;
                 for (int e = n + q; e < end; e += LPP) {
-                    cr2[p * KP + e] = F64 ? (ListR2)1e300 : (ListR2)INFINITY;
+                    cr2[p * KP + e] = F64 ? (ListR2)kPadding : (ListR2)INFINITY;
                     if (!equal_m) cm[p * KP + e] = 0.0;
                 }
                 wave_mem_sync();

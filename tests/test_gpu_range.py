@@ -265,3 +265,15 @@ def test_cold_solve_takes_few_passes(sph, kernel):
     print(f"case: passes of a cold solve kernel={kernel}", flush=True)
     out, status = _run(sph, a, W.default_setup(), kernel=kernel, h_max_iter=9 if kernel else 10)
     assert status == sph.SPH_OK
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("periodic,kernel,equal_m", [(True, 0, True), (False, 1, False)])
+def test_infinite_guess_reaches_each_particle_once(sph, precision, periodic, kernel, equal_m):
+    a, setup = _set(2000, periodic, equal_m)
+    i = 777
+    a["h"][i] = np.inf
+    print(f"case: infinite guess precision={precision} periodic={periodic} kernel={kernel}", flush=True)
+    out, status = _run(sph, a, setup, precision=precision, kernel=kernel)
+    assert status == sph.SPH_ENONFINITE
+    assert out["nngb"][i] == a["x"].size - 1 and out["nforce"][i] == a["x"].size - 1
