@@ -1595,15 +1595,16 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                 if constexpr (F64) {
                     add_entry<K, EQ>(sm, r2, m, hinv, h2x4);
                 } else {
-                    // branch-free: an entry outside R h adds 0 * f(0), whatever it
-                    // holds (padding, a position that is not finite)
+                    // branch-free: an entry outside R h adds 0 * f, whatever it holds
+                    // (padding, a position that is not finite: f and f' are zero, q
+                    // f' is not a number)
                     const bool in = r2 < (float)h2x4;
                     const double mj = in ? (EQ ? mu : m) : 0.0;
                     float f, df;
-                    const float qq = in ? sqrtf(r2) * (float)hinv : 0.f;
+                    const float qq = sqrtf(r2) * (float)hinv;
                     kern<K>(qq, f, df);
                     sm.d0 += mj * (double)f;
-                    sm.s2 += mj * (double)(qq * df);
+                    sm.s2 += mj * (double)(in ? qq * df : 0.f);
                     sm.n += in ? 1 : 0;
                 }
             };
