@@ -121,6 +121,7 @@ sph_status density_prepare(sph_ctx *c, int64_t n)
     a.h_rtol = c->p.precision == SPH_FP32_PAIR ? std::max(c->p.h_rtol, 2e-6) : c->p.h_rtol;
     a.walk_margin = 1.1;
     a.max_iter = c->p.h_max_iter;
+    a.lanewise = lanewise_density(n, c->p.precision, c->p.periodic) ? 1 : 0;
     a.active = c->f_act;
     a.leaf_act = c->f_act ? c->leaf_act : nullptr;
     a.leaf_list = c->f_act ? c->act_list : nullptr;
@@ -208,12 +209,13 @@ sph_status density_launch(sph_ctx *const *cs, int count, int64_t nmax)
     B.work = c->d_work;
     Batch<DensArgs> B2 = B;   // of the heavy leaves
     B2.work = c->d_work + kXcds * kWorkStride;
-    bool twice = false;
+    bool twice = false, lanewise = false;
     int64_t leaves_bound = 0, items_bound = 0;
     for (int r = 0; r < count; r++) {
         B.req[r] = (const DensArgs *)cs[r]->d_dargs;
         B2.req[r] = heavy_args((DensArgs *)cs[r]->d_dargs);
         twice = twice || second_launch(cs[r]->n, c->p.leaf_size, cs[r]->p.periodic);
+        lanewise = lanewise || lanewise_density(cs[r]->n, cs[r]->p.precision, cs[r]->p.periodic);
         const bool splits = splits_density(cs[r]->p.precision, cs[r]->p.periodic);
         const int k = slice_split(cs[r]->n, c->p.leaf_size, splits);
         B.split = r == 0 || k < B.split ? k : B.split;
@@ -241,9 +243,9 @@ sph_status density_launch(sph_ctx *const *cs, int count, int64_t nmax)
     for (const Batch<DensArgs> *b : {&B, &B2}) {
         if (b == &B2 && !twice) break;
         if (c->p.kernel == SPH_KERNEL_QUINTIC)
-            launch_density<SPH_KERNEL_QUINTIC>(c->stream, c->p.leaf_size, c->p.precision, blocks_of(*b), *b);
+            launch_density<SPH_KERNEL_QUINTIC>(c->stream, c->p.leaf_size, c->p.precision, lanewise, blocks_of(*b), *b);
         else
-            launch_density<SPH_KERNEL_M4>(c->stream, c->p.leaf_size, c->p.precision, blocks_of(*b), *b);
+            launch_density<SPH_KERNEL_M4>(c->stream, c->p.leaf_size, c->p.precision, lanewise, blocks_of(*b), *b);
     }
     timer_end(c, 0, e0, e1);
     return hip_check(c, hipGetLastError(), "density kernel");

@@ -896,7 +896,8 @@ __device__ inline T group_separation(const LeafTab<PREC> &tab, int img, const Bo
     }
 }
 
-// The density loop in FP64 tests candidates lane by lane: a lane holds a
+// The density loop in FP64 tests candidates lane by lane (in FP32-pair mode some
+// groups, lanewise_density): a lane holds a
 // candidate of each of kRows rows of 64 slots (slot s = particle s % G of leaf
 // s / G), the home particle is the same for all lanes, a test is ten
 // instructions for 64 candidates and its result a ballot, whose bits rank the
@@ -912,11 +913,13 @@ __device__ inline T group_separation(const LeafTab<PREC> &tab, int img, const Bo
 // calls again to go on; -1 when the group is done.  What a list holds when it
 // is full depends on the particle and the rows alone.
 constexpr int kRows = 4;
-template <int G, int IMG, int NR, class Mass, class Put>
-__device__ inline int test_rows(const LeafTab<SPH_FP64> &tab, const HomeTab<G, SPH_FP64> &H, int count,
-                                const Box &bx, const Pos4 *__restrict__ pos, uint64_t &near, int &cnt,
-                                int cap, Mass mass, Put put)
+template <int G, int PREC, int IMG, int NR, class Mass, class Put>
+__device__ inline int test_rows(const LeafTab<PREC> &tab, const HomeTab<G, PREC> &H, int count,
+                                const Box &bx, const Pos4 *__restrict__ pos, const Off4 *__restrict__ off,
+                                uint64_t &near, int &cnt, int cap, Mass mass, Put put)
 {
+    constexpr bool F64 = PREC == SPH_FP64;
+    using T = std::conditional_t<F64, double, float>;
     constexpr int LPR = kWave / G;                      // leaves per row
     constexpr uint32_t RM = (1u << LPR) - 1;            // one row's leaves
     constexpr uint32_t BM = (uint32_t)((1ull << (NR * LPR)) - 1);
@@ -928,7 +931,7 @@ __device__ inline int test_rows(const LeafTab<SPH_FP64> &tab, const HomeTab<G, S
         const uint32_t here = (uint32_t)(near >> (r0 * LPR)) & BM;
         uint64_t todo = __ballot(here != 0);
         if (todo == 0) continue;
-        double x[NR], y[NR], z[NR], ox[NR], oy[NR], oz[NR];
+        T x[NR], y[NR], z[NR], ox[NR], oy[NR], oz[NR];
         double w[NR];
         __builtin_amdgcn_s_setprio(2);
 #pragma unroll
@@ -938,12 +941,16 @@ __device__ inline int test_rows(const LeafTab<SPH_FP64> &tab, const HomeTab<G, S
             const uint2 jm = tab.jm[s / G];
             const bool ok = slot < (int)(jm.y & 255u);
             const uint32_t j = jm.x + (ok ? slot : 0);   // (a missing leaf's entry is particle 0)
-            const auto *q = as_global((const double *)(pos + j));
-            x[r] = ok ? q[0] : INFINITY;      // an empty slot is far away
+            const auto *q = as_global(F64 ? (const T *)(pos + j) : (const T *)(off + j));
+            x[r] = ok ? q[0] : (T)INFINITY;   // an empty slot is far away
             y[r] = q[1];
             z[r] = q[2];
             w[r] = mass(j);
-            if constexpr (IMG == kImgShift) {
+            if constexpr (!F64) {
+                ox[r] = tab.o[0][s / G];
+                oy[r] = tab.o[1][s / G];
+                oz[r] = tab.o[2][s / G];
+            } else if constexpr (IMG == kImgShift) {
                 ox[r] = shift_of(jm.y, 0, bx);
                 oy[r] = shift_of(jm.y, 1, bx);
                 oz[r] = shift_of(jm.y, 2, bx);
@@ -953,17 +960,30 @@ __device__ inline int test_rows(const LeafTab<SPH_FP64> &tab, const HomeTab<G, S
         do {
             const int p = (int)__builtin_ctzll(todo);
             todo &= todo - 1;
-            const HomeRow h = H.d[p];
+            T hx, hy, hz, thr;
+            if constexpr (F64) {
+                const HomeRow h = H.d[p];
+                hx = h.x;
+                hy = h.y;
+                hz = h.z;
+                thr = h.thr;
+            } else {
+                const HomeRowF h = H.f[p];
+                hx = h.x;
+                hy = h.y;
+                hz = h.z;
+                thr = (float)H.d[p].thr;
+            }
             const uint32_t bits = (uint32_t)__builtin_amdgcn_readlane((int)here, p);
             int have = __builtin_amdgcn_readlane(cnt, p);
             int full = -1;
 #pragma unroll
             for (int r = 0; r < NR; r++) {
                 if (!((bits >> (r * LPR)) & RM)) continue;
-                double dx, dy, dz;
-                const double r2 = separation<SPH_FP64, IMG>(bx, h.x, h.y, h.z, x[r], y[r], z[r], ox[r], oy[r],
-                                                            oz[r], dx, dy, dz);
-                const uint64_t m = __ballot(r2 < h.thr);
+                T dx, dy, dz;
+                const T r2 = separation<PREC, IMG, T>(bx, hx, hy, hz, x[r], y[r], z[r], ox[r], oy[r], oz[r], dx, dy,
+                                                      dz);
+                const uint64_t m = __ballot(r2 < thr);
                 const int to = have + (int)__popcll(m);
                 if (to > cap) {
                     full = r;
@@ -1434,7 +1454,9 @@ constexpr double kPadding = 1e300;
 template <int K>
 constexpr double kPolyStep = K == SPH_KERNEL_QUINTIC ? 0.1 : 0.2;
 
-template <int G, int PREC, int K>
+// LW: the launch holds FP32-pair sets whose wide groups are tested lane by lane
+// (DensArgs::lanewise).
+template <int G, int PREC, int K, bool LW>
 __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(Batch<DensArgs> B)
 {
     constexpr int L0 = kWave / G;   // lanes per home particle of a whole leaf
@@ -1715,46 +1737,58 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                         count_up(kCntDensBoxes, ng * (int)__popcll(takes_part));
                         count_up(kCntDensTests, ng * G * (int)__popcll(takes_part));
                     }
-                    if constexpr (F64) {
+                    // FP32-pair groups whose every candidate the products would list
+                    // are tested lane by lane too
+                    if (F64 || (LW && (units.wide || img == kImgWide) && Q.lanewise)) {
                         uint64_t near = near_of[lane < G ? lane : 0];
-                        if (lane >= G) near = 0;
+                        if constexpr (!F64) {
+                            near = ~0ull;
+                            held = __shfl(count, (lane * LPP) & (kWave - 1));
+                        }
+                        if (lane >= G || !((takes_part >> lane) & 1)) near = 0;
                         auto mass = [&](uint32_t j) { return equal_m ? mu : as_global(Q.m)[j]; };
-                        auto put = [&](uint32_t to, double r2, double m) {
+                        auto put = [&](uint32_t to, ListR2 r2, double m) {
                             // (fixed uniform base, 32-bit lane offset)
                             auto *list = (__attribute__((address_space(1))) char *)cr2;
-                            *(__attribute__((address_space(1))) double *)(list + to * 8u) = r2;
+                            *(__attribute__((address_space(1))) ListR2 *)(list + to * (uint32_t)sizeof(ListR2)) = r2;
                             if (!equal_m) {
                                 auto *lm = (__attribute__((address_space(1))) char *)cm;
                                 *(__attribute__((address_space(1))) double *)(lm + to * 8u) = m;
                             }
                         };
+                        auto rows = [&](auto im, auto nr) {
+                            constexpr int IM = decltype(im)::value, NR = decltype(nr)::value;
+                            return test_rows<G, PREC, IM, NR>(tab, H, ng, bx, Q.pos, Q.off, near, held, KP, mass, put);
+                        };
+                        using None = std::integral_constant<int, kImgNone>;
+                        using Shift = std::integral_constant<int, kImgShift>;
+                        using Pair = std::integral_constant<int, kImgPair>;
+                        using Full = std::integral_constant<int, kRows>;
+                        using Half = std::integral_constant<int, kRows / 2>;
+                        using One = std::integral_constant<int, 1>;
                         for (;;) {
                             int full;
-                            if (img == kImgNone)
-                                full = test_rows<G, kImgNone, kRows>(tab, H, ng, bx, Q.pos, near, held, KP, mass, put);
-                            else if (img == kImgShift)
-                                full = test_rows<G, kImgShift, kRows / 2>(tab, H, ng, bx, Q.pos, near, held, KP,
-                                                                          mass, put);
-                            else
-                                full = test_rows<G, kImgPair, kRows / 2>(tab, H, ng, bx, Q.pos, near, held, KP,
-                                                                         mass, put);
+                            if constexpr (F64) {
+                                if (img == kImgNone) full = rows(None{}, Full{});
+                                else if (img == kImgShift) full = rows(Shift{}, Half{});
+                                else full = rows(Pair{}, Half{});
+                            } else {
+                                if (img < kImgPair) full = rows(None{}, One{});
+                                else full = rows(Pair{}, One{});
+                            }
                             if (full < 0) break;
                             empty_list(full, __builtin_amdgcn_readlane(held, full));
                             held = lane == full ? 0 : held;
                         }
+                        if constexpr (!F64) count = __shfl(held, p);
                         wave_lds_sync();   // the next group rewrites the table
-                    } else {
+                    } else if constexpr (!F64) {
                         // r^2 of the pairs to the particle's list, its lanes taking
                         // them in turn, two at a time (both positions requested
                         // before either is used)
                         auto use = [&](int n) {
-                            const HomeRow hd = H.d[p];
-                            ListR2 hx = hd.x, hy = hd.y, hz = hd.z;
-                            if constexpr (!F64) {
-                                hx = H.f[p].x;
-                                hy = H.f[p].y;
-                                hz = H.f[p].z;
-                            }
+                            const HomeRowF hd = H.f[p];
+                            const float hx = hd.x, hy = hd.y, hz = hd.z;
                             const uint16_t *id = S.id + p * Words<G>::cap;
                             int done = 0;
                             for (;;) {
@@ -2581,14 +2615,16 @@ __global__ __launch_bounds__(kWave, 4) void k_mfv(MfvArgs M)
 // pairs_quintic.hip)
 // ---------------------------------------------------------------------------
 template <int K>
-void launch_density(hipStream_t st, int G, int prec, unsigned grid, const Batch<DensArgs> &B)
+void launch_density(hipStream_t st, int G, int prec, bool lanewise, unsigned grid, const Batch<DensArgs> &B)
 {
     auto go = [&](auto g) {
         constexpr int GG = decltype(g)::value;
-        if (prec == SPH_FP32_PAIR)
-            hipLaunchKernelGGL((k_density<GG, SPH_FP32_PAIR, K>), dim3(grid), dim3(kWave), 0, st, B);
+        if (prec == SPH_FP32_PAIR && lanewise)
+            hipLaunchKernelGGL((k_density<GG, SPH_FP32_PAIR, K, true>), dim3(grid), dim3(kWave), 0, st, B);
+        else if (prec == SPH_FP32_PAIR)
+            hipLaunchKernelGGL((k_density<GG, SPH_FP32_PAIR, K, false>), dim3(grid), dim3(kWave), 0, st, B);
         else
-            hipLaunchKernelGGL((k_density<GG, SPH_FP64, K>), dim3(grid), dim3(kWave), 0, st, B);
+            hipLaunchKernelGGL((k_density<GG, SPH_FP64, K, false>), dim3(grid), dim3(kWave), 0, st, B);
     };
     switch (G) {
     case 8: go(std::integral_constant<int, 8>{}); break;

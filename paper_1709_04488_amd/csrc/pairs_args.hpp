@@ -41,6 +41,7 @@ struct DensArgs {
     double h_rtol;
     double walk_margin;
     int32_t max_iter;
+    int32_t lanewise;       // FP32-pair: test wide groups lane by lane (lanewise_density)
     // block time-steps: particles that take part (nullptr: all) and their
     // count per leaf (leaves without any are skipped); the home leaves are
     // then leaf_list[0 .. *leaf_count) (nullptr: every leaf)
@@ -128,10 +129,11 @@ struct MfvArgs {
 
 // One launch of a pair kernel instantiated for smoothing kernel K
 // (SPH_KERNEL_M4 or SPH_KERNEL_QUINTIC) at leaf size G (8, 16 or 32) and
-// precision prec, on stream st.  ac / sw select the force variant carrying
+// precision prec, on stream st.  lanewise selects the FP32-pair density variant for
+// small periodic sets, ac / sw select the force variant carrying
 // artificial conductivity / per-particle alpha and div v, curl v.
 template <int K>
-void launch_density(hipStream_t st, int G, int prec, unsigned grid, const Batch<DensArgs> &B);
+void launch_density(hipStream_t st, int G, int prec, bool lanewise, unsigned grid, const Batch<DensArgs> &B);
 template <int K>
 void launch_forces(hipStream_t st, int G, int prec, bool ac, bool sw, unsigned grid,
                    const Batch<ForceArgs> &B);

@@ -3,7 +3,7 @@
 
 namespace sph {
 
-template void launch_density<SPH_KERNEL_QUINTIC>(hipStream_t, int, int, unsigned, const Batch<DensArgs> &);
+template void launch_density<SPH_KERNEL_QUINTIC>(hipStream_t, int, int, bool, unsigned, const Batch<DensArgs> &);
 template void launch_forces<SPH_KERNEL_QUINTIC>(hipStream_t, int, int, bool, bool, unsigned,
                                   const Batch<ForceArgs> &);
 template void launch_neighbours<SPH_KERNEL_QUINTIC>(hipStream_t, int, unsigned, const NgbArgs &, int);

@@ -126,6 +126,20 @@ __host__ __device__ inline bool splits_density(int precision, int periodic)
     return precision == SPH_FP64 || !periodic;
 }
 
+// FP32-pair density: where a reach and a leaf span half the box, the image of a pair
+// is not that of its leaf, the products of the search cannot be formed and list every
+// candidate.  Such groups are tested lane by lane as in FP64; lists of all candidates
+// overflowed, and every Newton step swept again (2,500 particles at random 1,285 us,
+// lane by lane 290; 2,197 on a lattice with the quintic kernel 887 and 226).  The
+// line: guesses of h three times too large make 10,000 particles such a set (6,970 and
+// 1,740 us) and 40,000 not; the variant's registers cost 4,194,304 particles 2.5 %, and
+// 12,167 nothing.
+constexpr int64_t kLanewiseParticles = 32768;
+inline bool lanewise_density(int64_t n, int precision, int periodic)
+{
+    return precision == SPH_FP32_PAIR && periodic && n <= kLanewiseParticles;
+}
+
 // Whether a loop leaves its heavy home leaves (kHeavyLeaves) to a second launch
 // with a wave for each of their particles: isolated sets of whole leaves, whose
 // outermost particles' supports can hold thousands of others.  In a periodic box

@@ -277,3 +277,61 @@ def test_infinite_guess_reaches_each_particle_once(sph, precision, periodic, ker
     out, status = _run(sph, a, setup, precision=precision, kernel=kernel)
     assert status == sph.SPH_ENONFINITE
     assert out["nngb"][i] == a["x"].size - 1 and out["nforce"][i] == a["x"].size - 1
+
+
+def _uniform(n, guess=1.0, equal_m=True, seed=5):
+    rng = np.random.default_rng(seed)
+    a = {k: rng.uniform(0, 1, n) for k in "xyz"}
+    a.update({k: rng.normal(0, 0.3, n) for k in ("vx", "vy", "vz")})
+    a["m"] = np.full(n, 1.0 / n) if equal_m else rng.uniform(0.5, 1.5, n) / n
+    a["u"] = rng.uniform(0.3, 2.0, n)
+    a["h"] = guess * 1.2 * n ** (-1.0 / 3.0) * rng.uniform(0.9, 1.1, n)
+    return a
+
+
+@pytest.mark.parametrize("n,kernel,leaf", [(700, 0, 8), (700, 0, 16), (700, 0, 32), (1300, 1, 16), (2500, 0, 16)])
+def test_fp32_lists_of_small_boxes(sph, orc, n, kernel, leaf):
+    """Reaches that span much of the box: the images are ambiguous, and the lists
+    still hold what is within reach (with equal masses up to 640 and 1,920 of them)."""
+    a, setup = _uniform(n), W.default_setup()
+    print(f"case: fp32 small box n={n} kernel={kernel} leaf={leaf}", flush=True)
+    with sph.Context(sph.Params.from_setup(setup, precision=1, kernel=kernel, leaf_size=leaf)) as ctx:
+        p = sph.Particles.from_host(a)
+        ctx.evaluate(p)
+        ctx.sync()
+        assert ctx.state_info()["dens_list_overflows"] == 0
+        out = p.host()
+    ref = orc.evaluate(orc.Params(**{**setup, "kernel": kernel}), a["x"], a["y"], a["z"], a["vx"], a["vy"], a["vz"],
+                       a["m"], a["u"], a["h"])
+    for k in ("h", "rho", "omega", "vsig", "dt"):
+        assert np.max(np.abs(out[k] / ref[k] - 1.0)) < (5e-5 if k == "omega" else 1e-5), k
+    for k, sk in (("ax", "scale_a"), ("ay", "scale_a"), ("az", "scale_a"), ("dudt", "scale_u")):
+        assert np.max(np.abs(out[k] - ref[k]) / ref[sk]) < 1e-4, k
+
+
+@pytest.mark.parametrize("kernel,equal_m", [(0, True), (0, False), (1, True)])
+def test_fp32_small_and_large_boxes_in_one_batch(sph, kernel, equal_m):
+    """A set above the line of the lane-by-lane tests, with guesses that make its
+    images ambiguous, gives the same bits alone and beside sets below it."""
+    sets = [_uniform(700, 1.0, equal_m), _uniform(33000, 6.0, equal_m), _uniform(5000, 2.0, equal_m)]
+    print(f"case: fp32 boxes in one batch kernel={kernel} equal_m={equal_m}", flush=True)
+    params = sph.Params.from_setup(W.default_setup(), precision=1, kernel=kernel)
+    keys = ("h", "rho", "omega", "nngb", "ax", "ay", "az", "dudt", "vsig", "nforce")
+    alone = []
+    for a in sets:
+        with sph.Context(params) as ctx:
+            p = sph.Particles.from_host(a)
+            ctx.evaluate(p)
+            ctx.sync()
+            alone.append(p.host(*keys))
+    ctxs = [sph.Context(params) for _ in sets]
+    parts = [sph.Particles.from_host(a) for a in sets]
+    sph.batch_evaluate(ctxs, parts)
+    for c in ctxs:
+        c.sync()
+    for p, ref in zip(parts, alone):
+        out = p.host(*keys)
+        for k in keys:
+            assert np.array_equal(out[k], ref[k]), (p.n, k)
+    for c in ctxs:
+        c.close()
