@@ -1609,7 +1609,8 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
             }
             const double hinv = 1.0 / h;
             // (an infinite guess reaches every particle, but not the lists' padding)
-            const double h2x4 = fmin((RK * h) * (RK * h), kPadding);
+            double h2x4 = (RK * h) * (RK * h);
+            h2x4 = h2x4 > kPadding ? kPadding : h2x4;
             uint64_t emptied = 0;   // bit p: home particle p's list was, in this sweep
             // the pair terms of one entry (eq: all masses are equal, m not used)
             auto add = [&](Sums<K> &sm, auto eq, ListR2 r2, double m, double hinv, double h2x4) {

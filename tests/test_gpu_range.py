@@ -335,3 +335,21 @@ def test_fp32_small_and_large_boxes_in_one_batch(sph, kernel, equal_m):
             assert np.array_equal(out[k], ref[k]), (p.n, k)
     for c in ctxs:
         c.close()
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("periodic,kernel", [(True, 0), (False, 1)])
+def test_undefined_guess_reaches_nothing(sph, precision, periodic, kernel):
+    a, setup = _set(2000, periodic)
+    i = 777
+    ref, status = _run(sph, a, setup, forces=False, precision=precision, kernel=kernel)
+    assert status == sph.SPH_OK
+    a["h"][i] = np.nan
+    print(f"case: undefined guess precision={precision} periodic={periodic} kernel={kernel}", flush=True)
+    out, status = _run(sph, a, setup, forces=False, precision=precision, kernel=kernel)
+    assert status == sph.SPH_ENONFINITE
+    assert out["nngb"][i] <= 0 and np.isnan(out["h"][i])
+    others = np.arange(2000) != i
+    assert np.array_equal(out["nngb"][others], ref["nngb"][others])
+    for k in ("h", "rho", "omega"):
+        assert np.max(np.abs(out[k][others] / ref[k][others] - 1.0)) < (1e-10 if precision == 0 else 1e-5), k
