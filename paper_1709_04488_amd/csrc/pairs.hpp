@@ -664,7 +664,12 @@ constexpr int kManyLeaves = 160;
 // 9.0 ms, 30,000 FP64 1.78 -> 1.10 ms; the launch without such a leaf costs each
 // loop 3-5 us.  From 256 leaves on the force loop of the first took 2.6 instead of
 // 1.3 ms (too many leaves for that many waves each), from 768 the density loops 3
-// and 15 % more.
+// and 15 % more.  The h solve leaves a leaf at whichever pass its reaches have grown
+// so far, and the next launch begins it anew; and however many leaves it leaves,
+// their particles have a wave each: guesses of h three times too large make all
+// leaves of 150,000 particles heavy (FP64 70 ms when leaves without end shared the
+// waves of small sets' rule, one particle per wave 15 ms, no second launch 55),
+// guesses of a tenth to five times 60,000 with five far away (FP32-pair 125, 24, 63).
 constexpr int kHeavyLeaves = 384;
 template <class Args>
 __device__ inline bool left_over(const Args &A, int split, const WalkResult &wr, int64_t leaf)
@@ -1318,6 +1323,7 @@ template <int G, class Args>
 __device__ inline int home_split(const Args &A, bool splits)
 {
     if (!splits) return 0;
+    if (A.leaf_count && A.leaf_count == A.heavy_count) return log2_of(G);   // heavy leaves
     const int all = split_of(A.n, G), some = split_of((int64_t)home_leaves(A) * G, G);
     return all > some ? all : some;
 }
@@ -1604,7 +1610,7 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                     wave_lds_sync();
                 }
                 __builtin_amdgcn_s_setprio(0);
-                if (iter == 0 && close && left_over(A, split, wr, leaf)) return;
+                if (close && left_over(A, split, wr, leaf)) return;
                 walked = true;
             }
             const double hinv = 1.0 / h;

@@ -140,11 +140,19 @@ inline bool lanewise_density(int64_t n, int precision, int periodic)
     return precision == SPH_FP32_PAIR && periodic && n <= kLanewiseParticles;
 }
 
-// Whether a loop leaves its heavy home leaves (kHeavyLeaves) to a second launch
-// with a wave for each of their particles: isolated sets of whole leaves, whose
-// outermost particles' supports can hold thousands of others.  In a periodic box
-// they cannot outgrow the mean density, and the launch would cost each loop 3-5 us.
-constexpr unsigned kHeavyBlocks = 1024;   // one per SIMD: most sets have no heavy leaf
+// Whether a loop leaves its heavy home leaves (kHeavyLeaves) to a second launch with
+// a wave for each of their particles: isolated sets of whole leaves, whose outermost
+// particles' supports can hold thousands of others.  Not in a periodic box, where
+// the launch would cost each loop 3-5 us: its sets are mostly near their mean density
+// throughout, and only a void's particles whose supports reach a cluster (25,000
+// particles, sigma 0.02 of the box: 11,900 neighbours) would gain.  Not in sets whose
+// leaves are shared, down to 2 of 16 particles per wave: they keep the tail that is
+// left (12,000 Plummer FP64 1.4 ms against 1.1 ms of 30,000).
+//
+// kHeavyBlocks: two per SIMD.  One, two, four: 150,000 particles with guesses of h
+// three times too large 23, 15, 11.5 ms; the forces of 150,000 quintic ones 1.92, 1.63,
+// 1.53; sets without a heavy leaf 0, 0 and 3 us more per loop.
+constexpr unsigned kHeavyBlocks = 2048;
 inline bool second_launch(int64_t n, int G, int periodic)
 {
     return !periodic && split_of(n, G) == 0;
