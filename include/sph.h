@@ -171,9 +171,10 @@ typedef struct {
     /* Launch shape of the density and force loops (the autotuner's knobs
      * besides leaf_size; neither changes what is computed):
      *   stage_leaves: how many candidate leaves a sweep handles at a time,
-     *     1..128/leaf_size (0: the most, 64 leaves; k: k leaf_size / 2 of them).  The
-     *     density results do not depend on it; the force sums may change in
-     *     their last bits (the split of a particle's terms over its lanes).
+     *     1..128/leaf_size (0: the most, 64 leaves; k: k leaf_size / 2 of them, in the
+     *     density loop rounded up to a multiple of 64 / leaf_size).  The density
+     *     results do not depend on it; the force sums may change in their last bits
+     *     (the split of a particle's terms over its lanes).
      *   claim_leaves: home leaves a wavefront claims per atomic claim of the
      *     persistent loop, 1..64 (0: 1); results do not depend on it. */
     int32_t stage_leaves;

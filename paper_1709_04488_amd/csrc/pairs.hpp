@@ -1728,7 +1728,10 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                 HomeUnits units{};
                 if constexpr (!F64) units = home_operand<G, PREC>(H, home, hcov, op);
                 const uint64_t takes_part = particle_bits(!conv, LPP);
-                const int depth = group_depth<G>(wr.n, B.stage > 0 ? B.stage * G / 2 : kGroup);
+                // (whole rows, so that a list that fills up does so at the same
+                // row whatever the depth)
+                constexpr int LPR = kWave / G;
+                const int depth = group_depth<G>(wr.n, B.stage > 0 ? (B.stage * G / 2 + LPR - 1) / LPR * LPR : kGroup);
                 count = 0;
                 int held = 0;              // FP64: entries of home particle `lane`'s list
                 int64_t at = 0;

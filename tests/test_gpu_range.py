@@ -353,3 +353,24 @@ def test_undefined_guess_reaches_nothing(sph, precision, periodic, kernel):
     assert np.array_equal(out["nngb"][others], ref["nngb"][others])
     for k in ("h", "rho", "omega"):
         assert np.max(np.abs(out[k][others] / ref[k][others] - 1.0)) < (1e-10 if precision == 0 else 1e-5), k
+
+
+@pytest.mark.parametrize("leaf,stages", [(8, (1, 3, 7, 16)), (16, (1, 5, 8)), (32, (1, 3, 4))])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_density_does_not_depend_on_the_stage_depth(sph, leaf, stages, precision):
+    """Also where the lists fill up (guesses of h too large, unequal masses)."""
+    n = 6000
+    a = _uniform(n, 2.5, equal_m=False, seed=23)
+    print(f"case: stage depth leaf={leaf} precision={precision}", flush=True)
+    ref, status = _run(sph, a, W.default_setup(), forces=False, leaf_size=leaf, precision=precision)
+    assert status == sph.SPH_OK
+    for stage in stages:
+        with sph.Context(sph.Params.from_setup(W.default_setup(), leaf_size=leaf, precision=precision,
+                                               stage_leaves=stage)) as ctx:
+            p = sph.Particles.from_host(a)
+            ctx.evaluate(p)   # (density statistics of one evaluation)
+            ctx.sync()
+            assert ctx.state_info()["dens_list_overflows"] > 0
+            out = p.host()
+        for k in ("h", "rho", "omega", "nngb"):
+            assert np.array_equal(out[k], ref[k]), (stage, k)
