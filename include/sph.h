@@ -236,15 +236,23 @@ typedef struct {
     int64_t dens_pair_evals;  /* density pairs evaluated over all Newton-Raphson iterations */
     int64_t force_pair_evals; /* force pairs evaluated */
     int32_t nr_iter_max;  /* Newton-Raphson iterations of the last density pass (max) */
-    int32_t walk_overflows; /* leaves whose neighbour walk overflowed LDS (slow path) */
+    int32_t walk_overflows; /* neighbour walks that overflowed LDS (slow path): one per leaf and
+                               loop, or per wave where several share a leaf (small sets), and
+                               one more per particle of a leaf that the launch for heavy
+                               leaves takes over */
     int64_t dens_leaf_visits; /* candidate leaves swept by the density loop (all iterations) */
-    int64_t dens_walks;   /* tree walks made by the density loop */
+    int64_t dens_walks;   /* tree walks made by the density loop (one that is repeated with a
+                             test per particle counts once) */
     int64_t nr_iter_total;    /* density evaluations summed over particles (mean = / n) */
     /* the next four only while instrumentation bit 1 is set (else 0) */
-    int64_t dens_candidate_tests; /* particle-candidate distance tests, density loop */
-    int64_t dens_box_tests;   /* particle-leaf box tests, density loop */
-    int64_t force_candidate_tests; /* particle-candidate distance tests, force loop */
-    int64_t force_box_tests;  /* particle-leaf box tests, force loop */
+    int64_t dens_candidate_tests; /* particles x slots (leaf_size each) of their candidate leaves,
+                                     density loop: distance tests, counting those of empty
+                                     slots and those that FP64's box tests save */
+    int64_t dens_box_tests;   /* particles x candidate leaves, density loop: FP64's box tests
+                                 (FP32-pair makes none) */
+    int64_t force_candidate_tests; /* particles x slots of their candidate leaves, force loop */
+    int64_t force_box_tests;  /* candidate leaves of the force loop's home leaves (no box tests
+                                 of particles are made) */
     int32_t density_walk_overflows; /* of walk_overflows: those of the density loop */
     int32_t force_walk_overflows;   /* of walk_overflows: those of the force loop */
     int64_t dens_list_overflows;    /* particles whose density candidate list outgrew its
