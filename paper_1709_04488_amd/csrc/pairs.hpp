@@ -1026,10 +1026,11 @@ __device__ inline Half2 to_halves(float a, float b)
 // What the halves leave open.  A coordinate X rounds by at most 2^-10 |X| (or
 // 2^-14 where it has no normal half), so two points at distance r <= T of each
 // other and |X_i| <= H of the home centre come out at most 2^-10 (2 H + T) +
-// 2^-13 further apart; |x_j|^2 rounds downwards, which only adds hits; the sums
-// are single precision.  kHalfRel and kHalfAbs hold these with room to spare.
-// Beyond kHalfFar reaches nothing is tested: every candidate is listed.
-constexpr float kHalfRel = 1.1e-3f, kHalfAbs = 4e-4f, kHalfFar = 150.f, kHalfTop = 65504.f;
+// 2^-12 further apart; |x_j|^2 rounds downwards, which only adds hits; the sums
+// are single precision, each wrong by up to a unit in the last place, which counts
+// where H is a hundred times T.  kHalfRel and kHalfAbs hold these with a third to
+// spare.  Beyond kHalfFar reaches nothing is tested: every candidate is listed.
+constexpr float kHalfRel = 1.4e-3f, kHalfAbs = 4e-4f, kHalfFar = 150.f, kHalfTop = 65504.f;
 
 // The home leaf as the product's second operand, per home particle: (-2 x_i, 1)
 // as halves and the constants |x_i|^2 - T_i^2 and |x_i|^2 (1e30: takes no part).
