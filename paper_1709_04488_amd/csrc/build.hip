@@ -761,9 +761,8 @@ __global__ __launch_bounds__(256) void k_leaves(const TreeInfo *__restrict__ T,
     }
 }
 
-// largest h of every leaf after the h solve changed h (boxes are unchanged),
-// one thread per leaf over its consecutive particles
-// The leaves' largest h, by the grid's 16-lane groups.
+// The leaves' largest h after the h solve changed h (boxes are unchanged), by the
+// grid's 16-lane groups.
 __device__ inline void leaf_hmax(const TreeInfo *__restrict__ T, const uint32_t *__restrict__ lstart,
                                  const double *__restrict__ h, Node *__restrict__ nodes)
 {

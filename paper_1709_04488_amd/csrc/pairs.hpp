@@ -218,22 +218,6 @@ __device__ inline double wave_sum(double v)
     return (row(0) + row(16)) + (row(32) + row(48));
 }
 
-__device__ inline int wave_max_int(int v)
-{
-    int w = xlane<1>(v);
-    v = w > v ? w : v;
-    w = xlane<2>(v);
-    v = w > v ? w : v;
-    w = xlane<4>(v);
-    v = w > v ? w : v;
-    w = xlane<8>(v);
-    v = w > v ? w : v;
-    const int a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 16);
-    const int c = __builtin_amdgcn_readlane(v, 32), d = __builtin_amdgcn_readlane(v, 48);
-    const int ab = a > b ? a : b, cd = c > d ? c : d;
-    return ab > cd ? ab : cd;
-}
-
 // Persistent work loop over the leaves.  Blocks are dispatched round-robin
 // over the 8 XCDs, so block b runs on XCD b % 8; each XCD first claims leaves
 // from its own contiguous eighth of the leaf range (neighbouring leaves then
@@ -514,17 +498,15 @@ __device__ WalkResult walk(const TreeInfo &T, const Node *nodes, Test test, Walk
     return walk_result(wb, cur, ncur, 0);
 }
 
-// Visit the candidate leaves in groups of at most `depth` (<= NL, the LDS
-// tile): fn(leaves, count) with a wave-uniform count.  After a truncated walk
-// the leaves under each returned node are tested 64 at a time and the
-// passing ones grouped.
+// Visit the candidate leaves in groups of at most NL: fn(leaves, count) with a
+// wave-uniform count.  After a truncated walk the leaves under each returned node
+// are tested 64 at a time and the passing ones grouped.
 template <int NL, class Test, class Fn>
 __device__ int64_t for_each_leaf_group(const TreeInfo &T, const Node *nodes, const WalkResult &wr,
-                                       Test test, WalkBuf &wb, Fn fn, int depth = NL)
+                                       Test test, WalkBuf &wb, Fn fn)
 {
-    const int D = depth >= 1 && depth <= NL ? depth : NL;
     if (wr.lev == 0) {
-        for (int t0 = 0; t0 < wr.n; t0 += D) fn(wr.list + t0, wr.n - t0 < D ? wr.n - t0 : D);
+        for (int t0 = 0; t0 < wr.n; t0 += NL) fn(wr.list + t0, wr.n - t0 < NL ? wr.n - t0 : NL);
         return wr.n;
     }
     const int lane = threadIdx.x & (kWave - 1);
@@ -543,7 +525,7 @@ __device__ int64_t for_each_leaf_group(const TreeInfo &T, const Node *nodes, con
             if (pass) wb.tmp[__popcll(mask & lt)] = (uint32_t)c;
             wave_lds_sync();
             const int cnt = (int)__popcll(mask);
-            for (int t0 = 0; t0 < cnt; t0 += D) fn(wb.tmp + t0, cnt - t0 < D ? cnt - t0 : D);
+            for (int t0 = 0; t0 < cnt; t0 += NL) fn(wb.tmp + t0, cnt - t0 < NL ? cnt - t0 : NL);
             wave_lds_sync();
             tested += b1 - b < kWave ? b1 - b : kWave;
         }

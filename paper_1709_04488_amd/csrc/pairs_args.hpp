@@ -14,7 +14,7 @@ template <class Args>
 struct Batch {
     int32_t nreq;
     int32_t claim;   // home leaves per claim of the persistent loop (>= 1)
-    int32_t stage;   // candidate leaves per staged group (1..128/G)
+    int32_t stage;   // k: k G / 2 candidate leaves per group (0: 64)
     int32_t split;   // log2 of the blocks that share the lists of a leaf
     uint32_t *work;
     double *cache;   // density loop: per-block candidate cache (nullptr: none)

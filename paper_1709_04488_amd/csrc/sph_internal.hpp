@@ -53,8 +53,6 @@ constexpr int kArgBytes = 1024;  // device argument block of one pair-kernel lau
 // candidate-list scratch, so the cap also bounds that scratch.
 constexpr int64_t kMaxPairBlocks = 256 * 16;
 
-// Active-leaf compaction of block time-steps: leaves per block, and the
-// per-block counts (one more than the blocks, for the bound of n leaves)
 // Radix sort tiles: 1024 keys (256 threads x 4) per block up to kRsSmallMax
 // particles, 4096 (256 x 16) above.  A pass over a few hundred thousand keys is
 // latency, not bandwidth: tiles of 4096 left 195,112 keys in 48 blocks on 256 CUs,
@@ -79,6 +77,8 @@ constexpr int64_t hist_words(int64_t cap)
     return 256 * (big > small ? big : small) + 256;
 }
 
+// Active-leaf compaction of block time-steps: leaves per block, and the
+// per-block counts (one more than the blocks, for the bound of n leaves)
 constexpr int kActTile = 1024;
 constexpr int64_t act_tiles(int64_t cap) { return (cap + kActTile - 1) / kActTile + 1; }
 // Claim counters of the persistent loops: one per XCD, each in a memory channel
@@ -467,7 +467,8 @@ sph_status gather(sph_ctx *c, int64_t n, const GatherList &g, bool identity_src_
 sph_status build_tree(sph_ctx *c, int64_t n);
 // leaf and node hmax from the current sorted h (after the h solve), boxes kept
 sph_status refresh_hmax(sph_ctx *c, int64_t n);
-// Force records from rho, omega, h, m and the given sorted u and velocities.
+// Force records from rho, omega, h, m and the given sorted u and velocities; hmax:
+// and the leaves' and nodes' largest h from the current h (after the h solve).
 sph_status force_prep(sph_ctx *c, int64_t n, const double *u_sorted, const double *vx,
                       const double *vy, const double *vz, bool hmax);
 sph_status iota(sph_ctx *c, int64_t n, uint32_t *v);
@@ -550,8 +551,6 @@ sph_status block_av(sph_ctx *c, int64_t n);             // switches of the activ
 sph_status reduce_mass_range(sph_ctx *c, int64_t n, int *blocks);
 // conserved quantities and neighbour counts; with_dt: and min dt -> d_scal[0]
 sph_status reduce_diag(sph_ctx *c, int64_t n, bool with_dt);
-// zero d_counts[first..first+count) with a kernel (capture-safe, no memset)
-sph_status zero_counts(sph_ctx *c, int first, int count);
 // zero the per-XCD claim counters of the persistent pair kernels
 sph_status zero_work(sph_ctx *c);
 // exclusive prefix sum in place over a[0..n], treating a[n] as 0 on input

@@ -229,7 +229,7 @@ class Params:
     block_lmax: int = 0
     block_lim: int = 2
     kernel: int = SPH_KERNEL_M4
-    stage_leaves: int = 0       # launch shape: candidate leaves per LDS stage (0: 128/leaf)
+    stage_leaves: int = 0       # launch shape: k leaf_size / 2 candidate leaves per group (0: 64)
     claim_leaves: int = 0       # launch shape: home leaves per claim (0: 1)
 
     @classmethod
