@@ -1873,8 +1873,8 @@ __global__ __launch_bounds__(kWave, pair_waves_per_simd<PREC>()) void k_density(
                         const double g1 = (3.0 * e3 * x + 2.0 * e2) * x + e1;
                         st = f / g1;
                         x -= st;
-                        // (a lane whose solve runs away ends as not solved)
-                        if (__ballot(!conv && fabs(st) > 1e-16 + 1e-15 * fabs(x) && fabs(x) < 1.0) == 0ull)
+                        // (a lane whose solve leaves the range of use ends as not solved)
+                        if (__ballot(!conv && fabs(st) > 1e-16 + 1e-15 * fabs(x) && fabs(x) < 0.5) == 0ull)
                             break;
                     }
                     // (a massless particle's relation has no root in h: plain Newton
