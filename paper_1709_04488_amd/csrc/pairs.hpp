@@ -10,9 +10,10 @@
 // in groups of up to 64, one per lane:
 //   open  -- each lane's leaf, its particle count and its periodic shift go to a
 //            table in LDS;
-//   find  -- FP64 density: each home particle in turn against a candidate per
-//            lane, ballots rank the hits and their r^2 goes to the particle's list
-//            in global scratch; forces and FP32-pair density: matrix products
+//   find  -- FP64 density (and small FP32-pair boxes, where images are ambiguous):
+//            each home particle in turn against a candidate per lane, ballots rank
+//            the hits and their r^2 goes to the particle's list in global scratch;
+//            forces and FP32-pair density: matrix products
 //            of candidates and home particles, whose signs are the hits, as a list
 //            of candidate slots per home particle in LDS;
 //   use   -- each particle's lanes share its list: pair terms, or r^2 to the
